@@ -34,7 +34,6 @@ struct GemmArgs {
     int groups_base;
     int groups_rem;
     int param_shift;      // log2(compute groups per quantisation group)
-    int lds_wave_bytes;   // LDS region of one wave
     int waves;            // working waves per workgroup (the launch has one more in service mode)
     int spin_limit;     // phase mode: bound on polls of a flag
     int probe_delay;    // phase mode: 64-cycle sleeps before the early sample of the flag
@@ -188,6 +187,13 @@ __device__ __forceinline__ void phase_wait_failed(uint32_t* errors, uint32_t* er
 constexpr int kPhaseMaxSplit = 64;          // largest split_k of the phase protocol
 constexpr uint32_t kPhaseOrigins = 1u << 12;  // tile origins n0 / 16 it covers: n <= 65536
 
+// LDS region of one wave: its [m][BN] fp32 tile.  Two strips per wave: whole 16-row tiles whatever m
+// is, which the four-wave epilogue indexes with constants.
+__host__ __device__ constexpr int gemm_lds_wave_bytes(int BN, int m)
+{
+    return BN == 128 ? 16 * 128 * 4 : (m * BN * 4 + 15) & ~15;
+}
+
 // GC: 1 = every wave has exactly one compute group, 2 = at least two, 0 = decided at run time.
 // BITS: width of the packed fields, 4 (the paper's), 2, 3 or 8 (Section 2: the method carries
 // over to other n-bit schemes; qweight is then int32 [k BITS / 32, n] and qzeros int32
@@ -201,6 +207,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
     static_assert(NS == 1 || (NS == 2 && GC == 1), "two strips per wave: one compute group per wave");
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     constexpr int BN = 16 * V * NS;
+    const int lds_wave_bytes = gemm_lds_wave_bytes(BN, p.m);
     constexpr bool kService = MODE == kAtomicPkF16Service;
 
     const int tid = threadIdx.x;
@@ -415,7 +422,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
     }
 
     // ---- sum the waves' tiles through LDS.  acc[j][r] is row 4*(lane/16)+r, column V*(lane%16)+j.
-    float* red = (float*)(lds_tiles + wave * p.lds_wave_bytes);  // [m][BN]
+    float* red = (float*)(lds_tiles + wave * lds_wave_bytes);  // [m][BN]
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int row = 4 * (lane >> 4) + r;
@@ -448,7 +455,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
         MODE == kDirect || MODE == kAtomicPkF16 || MODE == kAtomicPkF16Phase || MODE == kAtomicPkF16Service;
     constexpr uint32_t kOutsideC = 0xFFFFFF00u;
     const int units = m * BN / EPU;
-    const int wave_floats = p.lds_wave_bytes / 4;
+    const int wave_floats = lds_wave_bytes / 4;
     const float* red0 = (const float*)lds_tiles;
     const rsrc_t rs_out = make_rsrc(p.C, (uint32_t)m * (uint32_t)n * 2u);
 
@@ -647,16 +654,20 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
 // to the kernarg segment (about 0.3 us) precedes the loads.  Everything else comes in `rest`
 // and is fetched by one batch of scalar loads while the first vector loads are in flight.
 //   packed = m | param_shift << 5 | waves << 7 | groups_base << 12
-//   tiles_rem = tiles | groups_rem << 20
+//   split_rem = split_k | groups_rem << 16
+// The whole list is 96 bytes: the host's share of a launch is up to 0.7 us longer from 120 bytes on
+// (2.9 us against 3.6 us on a core far from the GPU; 112 bytes and less cost the same as 56).
 struct GemmRest {
-    float* scratch;
-    uint32_t* tickets;
-    uint32_t* flags;
-    uint32_t* counts;
+    union {
+        float* scratch;   // fp32 sums, partial tiles, fixed-point words
+        uint32_t* flags;  // phase protocol
+    };
+    union {
+        uint32_t* tickets;
+        uint32_t* counts;  // phase protocol
+    };
     uint32_t* errors;
     uint32_t* err_host;
-    int split_k;
-    int lds_wave_bytes;
     int spin_limit;
     int probe_delay;
 };
@@ -664,7 +675,7 @@ struct GemmRest {
 template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1>
 __global__ void __launch_bounds__(kWave * (WMAX + (MODE == kAtomicPkF16Service ? 1 : 0)))
 gemm_kernel(const _Float16* A, const uint32_t* qweight, const _Float16* scales, const uint32_t* qzeros, _Float16* C,
-            int packed, int n, int k, int tiles_rem, const GemmRest rest)
+            int packed, int n, int k, int split_rem, const GemmRest rest)
 {
     GemmArgs p;
     p.A = A;
@@ -676,18 +687,17 @@ gemm_kernel(const _Float16* A, const uint32_t* qweight, const _Float16* scales, 
     p.param_shift = (packed >> 5) & 3;
     p.waves = (packed >> 7) & 31;
     p.groups_base = (int)((unsigned)packed >> 12);
-    p.groups_rem = (int)((unsigned)tiles_rem >> 20);
+    p.groups_rem = (int)((unsigned)split_rem >> 16);
     p.n = n;
     p.k = k;
-    p.tiles = tiles_rem & ((1 << 20) - 1);
+    p.tiles = 0;  // only the launch needs it
+    p.split_k = split_rem & 0xFFFF;
     p.scratch = rest.scratch;
     p.tickets = rest.tickets;
     p.flags = rest.flags;
     p.counts = rest.counts;
     p.errors = rest.errors;
     p.err_host = rest.err_host;
-    p.split_k = rest.split_k;
-    p.lds_wave_bytes = rest.lds_wave_bytes;
     p.spin_limit = rest.spin_limit;
     p.probe_delay = rest.probe_delay;
     gemm_body<V, IPG, MODE, WMAX, GC, BITS, NS>(p);
@@ -2113,24 +2123,26 @@ static int launch_bound(const GemmArgs& a, int waves, size_t lds_bytes, hipStrea
     }
     const unsigned threads = (unsigned)(waves + (MODE == kAtomicPkF16Service ? 1 : 0)) * kWave;
     // (the second grid dimension holds at most 65535)
-    if (a.m > 31 || a.param_shift > 3 || a.waves > 31 || a.groups_base >= (1 << 20) || a.tiles >= (1 << 20) ||
-        a.groups_rem >= (1 << 11) || a.split_k < 1 || a.split_k >= (1 << 16))
+    if (a.m > 31 || a.param_shift > 3 || a.waves > 31 || a.groups_base >= (1 << 20) || a.groups_rem >= (1 << 15) ||
+        a.split_k < 1 || a.split_k >= (1 << 16))
         return W4A16_ERR_UNSUPPORTED;
     const int packed = a.m | a.param_shift << 5 | a.waves << 7 | (int)((unsigned)a.groups_base << 12);
-    const int tiles_rem = a.tiles | a.groups_rem << 20;
+    const int split_rem = a.split_k | a.groups_rem << 16;
+    constexpr bool kPhase = MODE == kAtomicPkF16Phase || MODE == kAtomicPkF16Service;
     GemmRest rest;
-    rest.scratch = a.scratch;
-    rest.tickets = a.tickets;
-    rest.flags = a.flags;
-    rest.counts = a.counts;
+    if constexpr (kPhase) {
+        rest.flags = a.flags;
+        rest.counts = a.counts;
+    } else {
+        rest.scratch = a.scratch;
+        rest.tickets = a.tickets;
+    }
     rest.errors = a.errors;
     rest.err_host = a.err_host;
-    rest.split_k = a.split_k;
-    rest.lds_wave_bytes = a.lds_wave_bytes;
     rest.spin_limit = a.spin_limit;
     rest.probe_delay = a.probe_delay;
     hipLaunchKernelGGL(kern, dim3((unsigned)a.tiles, (unsigned)a.split_k), dim3(threads), lds_bytes, stream, a.A,
-                       a.qweight, a.scales, a.qzeros, a.C, packed, a.n, a.k, tiles_rem, rest);
+                       a.qweight, a.scales, a.qzeros, a.C, packed, a.n, a.k, split_rem, rest);
     return W4A16_HIP(hipGetLastError()) ? W4A16_OK : W4A16_ERR_HIP;
 }
 
@@ -2505,9 +2517,7 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
     a.param_shift = param_shift;
     // LDS: 16 bytes for the phase word, then one [m, tile_cols] fp32 tile per wave, for the sum
     // over the workgroup's waves
-    // (two strips per wave: whole 16-row tiles whatever m is, which the four-wave epilogue indexes with constants)
-    a.lds_wave_bytes = two_strips ? 16 * 128 * 4 : (m * plan.tile_cols * 4 + 15) & ~15;
-    const size_t lds_bytes = 16 + (size_t)a.lds_wave_bytes * plan.waves;
+    const size_t lds_bytes = 16 + (size_t)gemm_lds_wave_bytes(plan.tile_cols, m) * plan.waves;
     a.flags = nullptr;
     a.counts = nullptr;
     a.errors = nullptr;
