@@ -1,4 +1,7 @@
-"""Thin ctypes binding of libw4a16.so (see include/w4a16.h): argument marshalling only.
+"""Thin binding of libw4a16.so (see include/w4a16.h): argument marshalling only.
+
+The GEMM calls a program makes per layer go through the extension module `_call` (csrc/py_call.cpp);
+everything else is ctypes.
 
 Every function has the name of the C entry point it calls.  Tensor arguments are torch
 tensors on the GPU (PyTorch is used for device memory and streams only); their data
@@ -109,6 +112,34 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+def _call_module():
+    """The extension module with the GEMM calls; raises if it was never built."""
+    lib()  # torch's HIP runtime first (see there); also the clearer error when nothing is built
+    import importlib
+    try:
+        return importlib.import_module("paper_2402_00025_amd._call")
+    except ImportError as e:
+        raise FileNotFoundError(
+            f"{_HERE / '_call.so'} cannot be loaded ({e}): build it with `python -m paper_2402_00025_amd.build`") from e
+
+
+def _gemm_entries():
+    """The per-layer calls, as the extension's own functions: nothing of Python lies between a call and
+    the library.  On a tree that has not been built yet they are stand-ins that look again when called."""
+    names = ("w4a16_gemm", "w4a16_gemm_static", "w4a16_gemm_dp", "w8a16_gemm", "w8a16_gemm_dp", "w3a16_gemm",
+             "w3a16_gemm_dp", "w2a16_gemm", "w2a16_gemm_dp", "w4a16_gemm_actorder")
+    try:
+        module = _call_module()
+    except FileNotFoundError:
+        def later(name):
+            return lambda *args, **kwargs: getattr(_call_module(), name)(*args, **kwargs)
+        return {name: later(name) for name in names}
+    return {name: getattr(module, name) for name in names}
+
+
+globals().update(_gemm_entries())
+
+
 def _p(t):
     """Device pointer of a torch tensor (or a raw int / None)."""
     if t is None:
@@ -136,57 +167,12 @@ def strerror(code: int) -> str:
     return lib().w4a16_strerror(int(code)).decode()
 
 
-def w4a16_gemm(A, qweight, scales, qzeros, C, m, n, k, group_size, split_k, stream=None) -> None:
-    _check(lib().w4a16_gemm(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size, split_k,
-                            _stream(stream)), "w4a16_gemm")
-
-
-def w4a16_gemm_static(A, qweight, scales, qzeros, C, m, n, k, group_size, split_k, stream=None) -> None:
-    _check(lib().w4a16_gemm_static(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size, split_k,
-                                   _stream(stream)), "w4a16_gemm_static")
-
-
-def w4a16_gemm_dp(A, qweight, scales, qzeros, C, m, n, k, group_size, stream=None) -> None:
-    _check(lib().w4a16_gemm_dp(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size,
-                               _stream(stream)), "w4a16_gemm_dp")
-
-
-def w8a16_gemm(A, qweight, scales, qzeros, C, m, n, k, group_size, split_k=0, stream=None) -> None:
-    _check(lib().w8a16_gemm(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size, split_k,
-                            _stream(stream)), "w8a16_gemm")
-
-
-def w8a16_gemm_dp(A, qweight, scales, qzeros, C, m, n, k, group_size, stream=None) -> None:
-    _check(lib().w8a16_gemm_dp(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size,
-                               _stream(stream)), "w8a16_gemm_dp")
-
-
 def w8a16_algorithmic_bytes(m, n, k, group_size) -> int:
     return int(lib().w8a16_algorithmic_bytes(m, n, k, group_size))
 
 
-def w2a16_gemm(A, qweight, scales, qzeros, C, m, n, k, group_size, split_k=0, stream=None) -> None:
-    _check(lib().w2a16_gemm(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size, split_k,
-                            _stream(stream)), "w2a16_gemm")
-
-
-def w2a16_gemm_dp(A, qweight, scales, qzeros, C, m, n, k, group_size, stream=None) -> None:
-    _check(lib().w2a16_gemm_dp(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size,
-                               _stream(stream)), "w2a16_gemm_dp")
-
-
 def w2a16_algorithmic_bytes(m, n, k, group_size) -> int:
     return int(lib().w2a16_algorithmic_bytes(m, n, k, group_size))
-
-
-def w3a16_gemm(A, qweight, scales, qzeros, C, m, n, k, group_size, split_k=0, stream=None) -> None:
-    _check(lib().w3a16_gemm(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size, split_k,
-                            _stream(stream)), "w3a16_gemm")
-
-
-def w3a16_gemm_dp(A, qweight, scales, qzeros, C, m, n, k, group_size, stream=None) -> None:
-    _check(lib().w3a16_gemm_dp(_p(A), _p(qweight), _p(scales), _p(qzeros), _p(C), m, n, k, group_size,
-                               _stream(stream)), "w3a16_gemm_dp")
 
 
 def w3a16_algorithmic_bytes(m, n, k, group_size) -> int:
@@ -196,12 +182,6 @@ def w3a16_algorithmic_bytes(m, n, k, group_size) -> int:
 def w4a16_actorder_prepare(qweight, g_idx, qweight_sorted, perm, status, n, k, group_size, stream=None) -> None:
     _check(lib().w4a16_actorder_prepare(_p(qweight), _p(g_idx), _p(qweight_sorted), _p(perm), _p(status), n, k,
                                         group_size, _stream(stream)), "w4a16_actorder_prepare")
-
-
-def w4a16_gemm_actorder(A, qweight_sorted, scales, qzeros, perm, A_work, C, m, n, k, group_size, split_k=0,
-                        stream=None) -> None:
-    _check(lib().w4a16_gemm_actorder(_p(A), _p(qweight_sorted), _p(scales), _p(qzeros), _p(perm), _p(A_work), _p(C),
-                                     m, n, k, group_size, split_k, _stream(stream)), "w4a16_gemm_actorder")
 
 
 def w4a16_read_probe(buffer, nbytes, shape=0, stream=None) -> None:

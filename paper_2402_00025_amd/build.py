@@ -1,13 +1,17 @@
 """Compile the HIP sources into paper_2402_00025_amd/libw4a16.so for gfx950 (cross-compiles
-without a GPU).  The library is built in-tree so it travels with the source tree."""
+without a GPU) and the Python calls of its GEMM entry points into paper_2402_00025_amd/_call.so.
+Both are built in-tree so they travel with the source tree."""
 from __future__ import annotations
 
 import pathlib
 import subprocess
+import sysconfig
 
 HERE = pathlib.Path(__file__).resolve().parent
 SRC = HERE / "csrc" / "w4a16.hip"
 LIB = HERE / "libw4a16.so"
+CALL_SRC = HERE / "csrc" / "py_call.cpp"
+CALL_LIB = HERE / "_call.so"
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
@@ -18,11 +22,29 @@ HIPCC_FLAGS = [
 ]
 
 
+def build_call(verbose: bool = False) -> pathlib.Path:
+    """_call.so: host code only, against torch's headers and libw4a16.so (which is found beside it)."""
+    from torch.utils import cpp_extension
+
+    rocm = pathlib.Path(cpp_extension.ROCM_HOME or "/opt/rocm")
+    include = [sysconfig.get_path("include"), *cpp_extension.include_paths(), str(rocm / "include")]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           *(f for i in include for f in ("-isystem", i)), str(CALL_SRC), "-o", str(CALL_LIB),
+           f"-L{HERE}", "-l:libw4a16.so", "-Wl,-rpath,$ORIGIN",
+           *(f"-L{p}" for p in cpp_extension.library_paths()), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           "-Wall"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALL_LIB
+
+
 def build(verbose: bool = False, extra=()) -> pathlib.Path:
     cmd = ["hipcc", *HIPCC_FLAGS, *extra, "-o", str(LIB), str(SRC)]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    build_call(verbose)
     return LIB
 
 
