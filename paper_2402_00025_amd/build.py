@@ -6,15 +6,16 @@ from __future__ import annotations
 import pathlib
 import subprocess
 import sysconfig
+import tempfile
 
 HERE = pathlib.Path(__file__).resolve().parent
-SRC = HERE / "csrc" / "w4a16.hip"
+SOURCES = [HERE / "csrc" / "w4a16.hip", HERE / "csrc" / "w4a16_rows.hip"]
 LIB = HERE / "libw4a16.so"
 CALL_SRC = HERE / "csrc" / "py_call.cpp"
 CALL_LIB = HERE / "_call.so"
 
 HIPCC_FLAGS = [
-    "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
+    "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
     "-munsafe-fp-atomics",                                     # hardware fp32 / packed-fp16 atomic adds
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",  # no v_pk_*_f32
     "-mllvm", "-amdgpu-kernarg-preload-count=14",                # leading kernel arguments arrive in SGPRs
@@ -40,10 +41,23 @@ def build_call(verbose: bool = False) -> pathlib.Path:
 
 
 def build(verbose: bool = False, extra=()) -> pathlib.Path:
-    cmd = ["hipcc", *HIPCC_FLAGS, *extra, "-o", str(LIB), str(SRC)]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    with tempfile.TemporaryDirectory() as tmp:
+        objects, running = [], []
+        for src in SOURCES:  # side by side
+            objects.append(str(pathlib.Path(tmp) / (src.stem + ".o")))
+            cmd = ["hipcc", *HIPCC_FLAGS, *extra, "-c", "-o", objects[-1], str(src)]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            running.append((cmd, subprocess.Popen(cmd)))
+        for cmd, p in running:
+            if p.wait() != 0:
+                for _, other in running:
+                    other.kill()
+                raise subprocess.CalledProcessError(p.returncode, cmd)
+        cmd = ["hipcc", "-shared", "--offload-arch=gfx950", "-o", str(LIB), *objects]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
     build_call(verbose)
     return LIB
 

@@ -6,6 +6,7 @@
 // data-parallel tiling it is compared with; Section 2.1 the atomic reduction.
 #include "w4a16_device.hpp"
 #include "w4a16_stream.hpp"
+#include "w4a16_rows.hpp"
 
 #include <cstdio>
 #include <cstdlib>
@@ -2436,6 +2437,50 @@ static int run_streamk(const void* A, const void* qweight, const void* scales, c
     return W4A16_HIP(hipGetLastError()) ? W4A16_OK : W4A16_ERR_HIP;
 }
 
+// Many rows (see w4a16_rows.hpp), the library's own launch: tile height and split of k.
+// Workgroups are served one after the other by a compute unit (two at a time, at no more throughput), so the
+// time is the largest number of them on one unit times their chunks; a split adds the fill of C and its
+// packed-fp16 adds.  us per chunk of 128 k: 1.75 with 128 rows, 0.95 with 64; adds: 160 pairs per ns.
+static int run_rows(const void* A, const void* qweight, const void* scales, const void* qzeros, void* C, int m, int n,
+                    int k, int group_size, hipStream_t stream)
+{
+    RowsArgs a;
+    a.A = (const _Float16*)A;
+    a.qweight = (const uint32_t*)qweight;
+    a.scales = (const _Float16*)scales;
+    a.qzeros = (const uint32_t*)qzeros;
+    a.C = (_Float16*)C;
+    a.m = m;
+    a.n = n;
+    a.k = k;
+    a.groups = k / kRowsChunkK;
+    a.param_shift = group_size == 256 ? 1 : 0;
+    a.tiles_n = (n + kRowsTileCols - 1) / kRowsTileCols;
+    double best = 0;
+    int row_blocks = 0;
+    for (int mb = 8; mb >= 4; mb -= 4) {
+        const long long tiles = (long long)((m + 16 * mb - 1) / (16 * mb)) * a.tiles_n;
+        for (int s = 1; s <= 8 && s <= a.groups; ++s) {
+            const long long per_cu = (tiles * s + 255) / 256;
+            const double us = (double)per_cu * ((a.groups + s - 1) / s) * (mb == 8 ? 1.75 : 0.95) +
+                              (s > 1 ? 3.0 + (double)s * m * n / 2 / 160e3 : 0.0);
+            if (row_blocks == 0 || us < best) {
+                best = us;
+                row_blocks = mb;
+                a.split_k = s;
+            }
+        }
+    }
+    a.tiles_m = (m + 16 * row_blocks - 1) / (16 * row_blocks);
+    if ((long long)a.tiles_m * a.tiles_n * a.split_k >= 1ll << 31) return W4A16_ERR_UNSUPPORTED;
+    if (a.split_k > 1) {
+        const size_t words = (size_t)m * n / 2;
+        hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, (uint32_t*)C, words);
+        if (!W4A16_HIP(hipGetLastError())) return W4A16_ERR_HIP;
+    }
+    return W4A16_HIP(launch_rows(a, row_blocks, stream)) ? W4A16_OK : W4A16_ERR_HIP;
+}
+
 static void read_tuning_env()
 {
     static bool done = false;
@@ -2472,6 +2517,12 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
     // row tiles of one launch, so the weights stream once per 64 rows; whatever it does not
     // cover (data-parallel kernel, group sizes below 128, the other tile widths and reductions)
     // runs as one launch per 16 rows.
+    // Where the caller leaves every choice to the library, more than 64 rows at group_size 128 or 256 are one
+    // launch of the many-row kernel (its 32-bit offsets span 128 rows of A).
+    if (bits == 4 && m > 16 * kStreamMaxRowTiles && !dp && split_k == 0 && k < (1 << 22) &&
+        stream_rows_ok(group_size, dp, tile_cols, waves, reduce) && tile_cols == 0 && waves == 0 &&
+        reduce == W4A16_REDUCE_AUTO)
+        return run_rows(A, qweight, scales, qzeros, C, m, n, k, group_size, (hipStream_t)stream_v);
     const int rows_per_launch = stream_rows_ok(group_size, dp, tile_cols, waves, reduce) ? 16 * kStreamMaxRowTiles : 16;
     if (m > rows_per_launch) {
         for (int r = 0; r < m; r += rows_per_launch) {

@@ -1,0 +1,363 @@
+// Kernel for many activation rows (prompts, large batches) on gfx950, wave64: the fused GEMM as a
+// tiled matrix product whose weight operand is unpacked in registers.
+//
+// The streaming kernel's row tiles (up to 64 rows a launch) spend one unpack per 64 rows and wait for
+// every chunk's products before they use them; at 64 rows they reach 410 TFLOP/s and every further 64
+// rows stream the weights again.  Here a workgroup owns 128 (or 64) rows x 256 columns.  Each of its four
+// waves owns a 64-column strip for all the rows, so that a weight is unpacked once per workgroup and an
+// unpacked operand serves 8 (4) row blocks.  The activations of a chunk (128 k) come straight from memory
+// into LDS, one chunk ahead, as do the packed weights of each wave's own strip: neither passes through
+// registers, which the sums (128), the unpacked operands (64) and the products in flight fill to the last
+// ones that two waves per SIMD leave.  The scale of a group is applied in fp32 to its products, as in the
+// other kernels.
+//
+// What bounds it: the issue of instructions.  A 16x16x32 MFMA takes 16 cycles of the matrix unit and about
+// 10 of the issue port, every other vector instruction 4; a chunk has 128 and about 340 of them per wave.
+// m = 2048, n = k = 8192: 240 us = 1145 TFLOP/s (664 us with row tiles); the clock is at 1.73 GHz then, where the
+// matrix units' ceiling is 1.8 PFLOP/s.
+#pragma once
+#include "w4a16_device.hpp"
+
+namespace w4a16 {
+
+struct RowsArgs {
+    const _Float16* A;
+    const uint32_t* qweight;
+    const _Float16* scales;
+    const uint32_t* qzeros;
+    _Float16* C;
+    int m, n, k;
+    int tiles_m, tiles_n;
+    int split_k;
+    int groups;  // 128-k chunks along k, the last one possibly short
+    int param_shift;
+};
+
+constexpr int kRowsStrips = 4;
+constexpr int kRowsTileCols = 64 * kRowsStrips;
+constexpr int kRowsChunkK = 128;
+
+// ---- Unpack in the order of k, so that the activations need no reordering on their way into LDS.
+// 4-bit: a byte permute puts two neighbouring fields into the low bits of two halves, where a field v is the
+// fp16 denormal v 2^-24; a packed fma by 2^15 with -z 2^-9 makes (q - z) 2^-9 of it, exactly.  The factor 2^9
+// is put back when a sum is rounded (kNatScale).  The other widths' routines yield q - z itself.
+template <int BITS>
+struct NatZero {
+    uint32_t c[BITS == 2 || BITS == 3 ? 3 : 1];
+};
+template <int BITS>
+constexpr float kNatScale = BITS == 4 ? 512.f : 1.f;
+
+template <int BITS>
+__device__ __forceinline__ NatZero<BITS> nat_zero(uint32_t z)
+{
+    NatZero<BITS> r;
+    const uint32_t zz = z | (z << 16);
+    if constexpr (BITS == 4) {
+        const half2_t f = {(_Float16)-32768.f, (_Float16)-32768.f};
+        r.c[0] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, zz) * f);
+    } else if constexpr (BITS == 8) {
+        r.c[0] = 0xE400E400u | zz;
+    } else if constexpr (BITS == 2) {
+        const ZeroConst2 t = zero_const2(z);
+        r.c[0] = t.c0; r.c[1] = t.c4; r.c[2] = t.c8;
+    } else {
+        const ZeroConst3 t = zero_const3(z);
+        r.c[0] = t.c0; r.c[1] = t.c3; r.c[2] = t.c6;
+    }
+    return r;
+}
+
+template <int BITS>
+__device__ __forceinline__ half8_t nat_unpack(uint32_t w0, uint32_t w1, const LaneMap& lm, const NatZero<BITS>& z, uint32_t magic)
+{
+    if constexpr (BITS == 8) {
+        return unpack_shift8(w0, w1, ZeroConst8{z.c[0]}, magic);
+    } else if constexpr (BITS == 2) {
+        return unpack_shift2(w0, lm.half_shift, ZeroConst2{z.c[0], z.c[1], z.c[2]}, magic);
+    } else if constexpr (BITS == 3) {
+        const half2_t k64 = {(_Float16)0.015625f, (_Float16)0.015625f};
+        const uint32_t x = __builtin_amdgcn_alignbit(w1, w0, (uint32_t)lm.half_shift);
+        const uint32_t xl = x & 0xFFFu, xh = (x >> 12) & 0xFFFu;
+        const uint32_t yl = xl | (xl << 13), yh = xh | (xh << 13);
+        const uint32_t t0 = (yl & 0x00070007u) | magic, t1 = (yl & 0x01C001C0u) | magic;
+        const uint32_t t2 = (yh & 0x00070007u) | magic, t3 = (yh & 0x01C001C0u) | magic;
+        const half2_t c0 = __builtin_bit_cast(half2_t, z.c[0]), c6 = __builtin_bit_cast(half2_t, z.c[2]);
+        const half2_t h0 = __builtin_bit_cast(half2_t, t0) + c0;
+        const half2_t h1 = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, t1), k64, c6);
+        const half2_t h2 = __builtin_bit_cast(half2_t, t2) + c0;
+        const half2_t h3 = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, t3), k64, c6);
+        const u32x4_t packed = {__builtin_bit_cast(uint32_t, h0), __builtin_bit_cast(uint32_t, h1),
+                                __builtin_bit_cast(uint32_t, h2), __builtin_bit_cast(uint32_t, h3)};
+        return __builtin_bit_cast(half8_t, packed);
+    } else {
+        const half2_t f = {(_Float16)32768.f, (_Float16)32768.f};
+        const half2_t c = __builtin_bit_cast(half2_t, z.c[0]);
+        const uint32_t u = w0 & 0x0F0F0F0Fu, v = (w0 >> 4) & 0x0F0F0F0Fu;
+        u32x4_t packed;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t p = __builtin_amdgcn_perm(v, u, 0x0C040C00u + 0x00010001u * i);
+            packed[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(half2_t, p), f, c));
+        }
+        return __builtin_bit_cast(half8_t, packed);
+    }
+}
+
+hipError_t launch_rows(const RowsArgs& a, int row_blocks, hipStream_t stream);
+
+// 16 bytes per lane from memory straight into LDS: lane l's go to lds + 16 l.
+__device__ __forceinline__ void load_to_lds(rsrc_t r, uint32_t voff, uint32_t soff, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(r), "s"(soff), "s"(lds) : "memory");
+}
+
+template <int BITS>
+constexpr int kRowsWordLoads = (BITS == 8 || BITS == 3) ? 2 : 1;  // 16-byte loads per lane and MFMA step
+template <int BITS>
+constexpr int kRowsWaveWeightBytes = 4 * kRowsWordLoads<BITS> * 1024;
+template <int MB, int BITS>
+constexpr int kRowsLdsBytes = 2 * MB * 4096 + kRowsStrips * kRowsWaveWeightBytes<BITS>;
+
+// MB: 16-row blocks per workgroup tile.  IPG: MFMA steps (32 k) per quantisation group in a chunk (4, 2, 1).
+template <int MB, int BITS, int IPG, bool SPLIT>
+__global__ void __launch_bounds__(256, 2) gemm_rows_kernel(RowsArgs p)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    constexpr int PG = 4 / IPG;  // parameter sets per chunk
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int strip = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = p.m, n = p.n, k = p.k;
+    __builtin_assume(m > 0 && n > 0 && k > 0);
+
+    // block -> (slice, tile)
+    const int total = gridDim.x;
+    const int b = blockIdx.x, xcd = b & 7, q8 = total >> 3, r8 = total & 7;
+    int id = xcd * q8 + (xcd < r8 ? xcd : r8) + (b >> 3);
+    const int per_slice = p.tiles_m * p.tiles_n;
+    const int slice = id / per_slice;
+    id -= slice * per_slice;
+    const int tile_n = id / p.tiles_m, tile_m = id - tile_n * p.tiles_m;
+    const int g_base = p.groups / p.split_k, g_rem = p.groups % p.split_k;
+    const int g0 = slice * g_base + (slice < g_rem ? slice : g_rem);
+    const int g_count = g_base + (slice < g_rem ? 1 : 0);
+
+    const int row0 = tile_m * (16 * MB);
+    const int n0 = (tile_n * kRowsStrips + strip) * 64;
+    const LaneMap lm = make_lane_map<4, BITS>(lane, n0, 1, n, k);
+    const int rows = m - row0 < 16 * MB ? m - row0 : 16 * MB;
+    const rsrc_t rs_a = make_rsrc(p.A + (size_t)row0 * k, (uint32_t)rows * (uint32_t)k * 2u);
+    constexpr int kFields = BITS == 3 ? 1 : 32 / BITS;
+    const int gsize = 32 * IPG;
+    Tensors t;
+    const uint32_t qgroups = ((uint32_t)k / gsize) >> p.param_shift;
+    t.qweight = make_rsrc(p.qweight, (uint32_t)(BITS == 3 ? k / 32 * 3 : k / kFields) * (uint32_t)n * 4u);
+    t.scales = make_rsrc(p.scales, qgroups * (uint32_t)n * 2u);
+    t.qzeros = make_rsrc(p.qzeros, qgroups * (uint32_t)(BITS == 3 ? n / 32 * 3 : n / kFields) * 4u);
+    t.n = n;
+    t.k = k;
+    t.param_shift = p.param_shift;
+
+    // A staging
+    const int srow = 4 * strip + (lane >> 4), skc = (lane & 15) ^ srow;
+    const uint32_t a_voff = ((uint32_t)srow * (uint32_t)k + 8u * (uint32_t)skc) * 2u;
+    const uint32_t lds_base = 0;  // dynamic LDS starts at 0
+    const uint32_t lds_w = lds_base + 2 * MB * 4096 + strip * kRowsWaveWeightBytes<BITS>;
+    // Chunk g's activations: MB pieces of 16 rows, a quarter of each per wave.  Rows behind the last one, k behind
+    // the end (a short last chunk) and whole chunks behind the last one (`voff` outside) come as zeros: their
+    // offsets lie outside the buffer.
+    constexpr uint32_t kOutside = 0x80000000u;  // stays outside when the pieces' rows are added
+    auto stage_a = [&](int g, uint32_t voff, int i) {
+        const uint32_t vo = voff + (uint32_t)i * 32u * (uint32_t)k;
+        load_to_lds(rs_a, vo, (uint32_t)g * 256u, lds_base + (g & 1) * (MB * 4096) + strip * 1024 + i * 4096);
+    };
+    auto stage_w = [&](int g, bool real, int it) {
+        const uint32_t step = (uint32_t)g * 4 + it;
+        const uint32_t dst = lds_w + it * kRowsWordLoads<BITS> * 1024;
+        const bool inside = real && (IPG == 4 || step * 32 < (uint32_t)k);
+        const uint32_t off0 = inside ? lm.off_w : kOutside, off1 = inside ? lm.off_w1 : kOutside;
+        if constexpr (BITS == 8) {
+            load_to_lds(t.qweight, off0, step * 32u * (uint32_t)n, dst);
+            load_to_lds(t.qweight, off0, (step * 32u + 4u) * (uint32_t)n, dst + 1024);
+        } else if constexpr (BITS == 2) {
+            load_to_lds(t.qweight, off0, step * 8u * (uint32_t)n, dst);
+        } else if constexpr (BITS == 3) {
+            load_to_lds(t.qweight, off0, step * 12u * (uint32_t)n, dst);
+            load_to_lds(t.qweight, off1, step * 12u * (uint32_t)n, dst + 1024);
+        } else {
+            load_to_lds(t.qweight, off0, step * 16u * (uint32_t)n, dst);
+        }
+    };
+    auto a_offset = [&](int g, bool real) {
+        return real && (IPG == 4 || g * 128 + 8 * skc < k) ? a_voff : kOutside;
+    };
+
+    float4_t acc[MB][4];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+    uint32_t a_off[4];  // of the chunk in use
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+        a_off[it] = (g0 & 1) * (MB * 4096) + ((lane & 15) * 16 + ((4 * it + (lane >> 4)) ^ (lane & 15))) * 16;
+    const uint32_t magic = unpack_magic<BITS>();
+
+    ParamRegs<4, BITS> par[PG];
+    auto load_params = [&](int g) {
+#pragma unroll
+        for (int s = 0; s < PG; ++s) {
+            int gi = g * PG + s;
+            if (gi >= (k >> 5) / IPG) gi = (k >> 5) / IPG - 1;
+            issue_params<4, BITS>(par[s], lm, t, gi);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < MB; ++i) stage_a(g0, a_offset(g0, true), i);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) stage_w(g0, true, it);
+    load_params(g0);
+    for (int c = 0; c < g_count; ++c) {
+        const int g = g0 + c;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const bool more = c + 1 < g_count;
+        const uint32_t a_next = a_offset(g + 1, more);
+        // this chunk's zero points and scales leave the registers that the next chunk's are loaded into
+        NatZero<BITS> zc[PG][4];
+        ScaleBits<4> sc[PG];
+#pragma unroll
+        for (int s = 0; s < PG; ++s) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t z;
+                if constexpr (BITS == 3)
+                    z = (__builtin_amdgcn_alignbit(par[s].zword1, par[s].zword, (uint32_t)lm.zshift) >> (3 * j)) & 7u;
+                else
+                    z = (par[s].zword >> (lm.zshift + BITS * j)) & ((1u << BITS) - 1u);
+                zc[s][j] = nat_zero<BITS>(z);
+            }
+            sc[s] = par[s].s;
+            asm volatile("" : "+v"(sc[s].r[0]), "+v"(sc[s].r[1]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_params(g + 1);
+        __builtin_amdgcn_sched_barrier(0);
+
+        half8_t a[4];
+#pragma unroll
+        for (int it = 0; it < 4; ++it) a[it] = *(const half8_t*)(lds_raw + a_off[it]);
+        // unpack, and the first row block's products as the operands come
+        half8_t bq[4][4];
+        float4_t tile[2][2];  // [pair of column sets][column set]: the products of one quantisation group
+        const float4_t zero4 = float4_t{0.f, 0.f, 0.f, 0.f};
+        auto mfma = [&](int it, int j, bool first) {
+            float4_t& d = tile[j >> 1][j & 1];
+            d = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[it], bq[it][j], first ? zero4 : d, 0, 0, 0);
+        };
+        auto add = [&](int i, int s, int pr, int e) {
+            acc[i][2 * pr + (e >> 2)][e & 3] = __builtin_fmaf(scale_of<4>(sc[s], 2 * pr + (e >> 2)), tile[pr][e >> 2][e & 3],
+                                                              acc[i][2 * pr + (e >> 2)][e & 3]);
+        };
+        u32x4_t raw[2][2];
+        auto read_raw = [&](int it) {
+            const char* src = lds_raw + lds_w + it * kRowsWordLoads<BITS> * 1024 + lane * 16;
+            raw[it & 1][0] = raw[it & 1][1] = *(const u32x4_t*)src;
+            if constexpr (kRowsWordLoads<BITS> == 2) raw[it & 1][1] = *(const u32x4_t*)(src + 1024);
+        };
+        read_raw(0);
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int s = it / IPG;
+            if (it < 3) read_raw(it + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                bq[it][j] = nat_unpack<BITS>(raw[it & 1][0][j], raw[it & 1][1][j], lm, zc[s][j], magic);
+                mfma(it, j, it % IPG == 0);
+                if ((it * 4 + j) % (16 / MB) == 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    stage_a(g + 1, a_next, (it * 4 + j) / (16 / MB));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (PG > 1 && it % IPG == IPG - 1) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) add(0, s, e >> 3, e & 7);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (PG == 1) {
+            // The other row blocks.  Two column sets at a time: while their products run, the previous pair's
+            // go into the sums, and behind the second pair's products the next block's operands are fetched.
+            auto fetch = [&](int i, int it) { a[it] = *(const half8_t*)(lds_raw + a_off[it] + i * 4096); };
+#pragma unroll
+            for (int it = 0; it < 4; ++it) fetch(1, it);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) add(0, 0, 0, e);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 1; i < MB; ++i) {
+#pragma unroll
+                for (int pr = 0; pr < 2; ++pr) {
+                    if (i <= 2) stage_w(g + 1, more, 2 * (i - 1) + pr);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int it = 0; it < 4; ++it) {
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            mfma(it, 2 * pr + h, it == 0);
+                            if (pr == 1 && h == 1 && i + 1 < MB) fetch(i + 1, it);
+                            add(pr == 0 ? i - 1 : i, 0, 1 - pr, 2 * it + h);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) add(MB - 1, 0, 1, e);
+        } else {
+#pragma unroll
+            for (int it = 0; it < 4; ++it) stage_w(g + 1, more, it);
+#pragma unroll
+            for (int i = 1; i < MB; ++i) {
+#pragma unroll
+                for (int it = 0; it < 4; ++it) a[it] = *(const half8_t*)(lds_raw + a_off[it] + i * 4096);
+#pragma unroll
+                for (int s = 0; s < PG; ++s) {
+#pragma unroll
+                    for (int i2 = 0; i2 < IPG; ++i2)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) mfma(s * IPG + i2, j, i2 == 0);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) add(i, s, e >> 3, e & 7);
+                }
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < 4; ++it) a_off[it] ^= MB * 4096;
+    }
+
+    const rsrc_t rs_c = make_rsrc(p.C + (size_t)row0 * n, (uint32_t)rows * (uint32_t)n * 2u);
+    const int col = n0 + 4 * (lane & 15);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * i + 4 * (lane >> 4) + r;
+            const uint32_t off = col < n && row < rows ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : 0xFFFFFF00u;
+            const half2_t lo = {(_Float16)(acc[i][0][r] * kNatScale<BITS>), (_Float16)(acc[i][1][r] * kNatScale<BITS>)};
+            const half2_t hi = {(_Float16)(acc[i][2][r] * kNatScale<BITS>), (_Float16)(acc[i][3][r] * kNatScale<BITS>)};
+            if constexpr (SPLIT) {
+                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(lo, rs_c, off, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(hi, rs_c, off + 4, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)}, rs_c, off, 0, 0);
+            }
+        }
+}
+
+}  // namespace w4a16
