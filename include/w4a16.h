@@ -23,7 +23,12 @@
  * points of every field width with group_size 128 or 256 (and, for w4a16_gemm_ex, tile_cols 0 or
  * 256, waves 0 or 4, reduce AUTO, ATOMIC_PK_F16 or ATOMIC_PK_F16_PHASE) take up to 64 rows per
  * launch as row tiles that share one pass over the weights; everything else, the data-parallel
- * kernel included, runs one launch per 16 rows, each streaming the weights again.  n a multiple of 8;
+ * kernel included, runs one launch per 16 rows, each streaming the weights again.  Where the
+ * SplitK entry points leave every choice to the library (split_k == 0) and more than one such
+ * launch would be needed, it is one launch of a kernel for many rows instead, unless that takes longer: tiles
+ * of 64 or 128 rows x 256 columns, their k ranges shared by persistent workgroups, the sums
+ * added in fp32 in the order of k (bit-reproducible).  w4a16_plan does not describe it: it
+ * reports the launch per 64 or 16 rows.  n a multiple of 8;
  * g (group_size) one of 32, 64, 128, 256; k a multiple of g; k * n < 2^32.  A split_k requested from w4a16_gemm must cut k into equal
  * shares of whole groups (k / split_k a multiple of g), as Algorithm 1 has it.  The library's own
  * choice (split_k == 0) and w4a16_gemm_ex are not bound by that: they deal out k in compute
@@ -39,12 +44,13 @@
  * keep partial sums, arrival counters or per-tile flags in scratch memory that every call leaves
  * as it found it (sums back at zero, counters one call further).  By default that memory is the
  * library's, one set of buffers per device (at most 16 * n 64-bit words, split_k * m * n floats
- * for the workspace flavour, and, for the in-kernel zeroing, 16 KiB * (1 + split_k) per distinct
- * split_k used), allocated by the first call that needs it (hipMalloc + a synchronous clear; use
+ * for the workspace flavour, for the in-kernel zeroing 16 KiB * (1 + split_k) per distinct
+ * split_k used, and 64 MiB for the sums that the many-row kernel's workgroups hand over), allocated by the first call that needs it (hipMalloc + a synchronous clear; use
  * w4a16_reserve_scratch to do that ahead of time) and never moved or freed before
  * w4a16_release_scratch: a buffer that is outgrown stays alive, so a HIP graph captured earlier
  * keeps working.  A call that would have to allocate while its stream is being captured returns
- * W4A16_ERR_STATE instead.  Split-k calls that overlap in time on one device share the library's
+ * W4A16_ERR_STATE instead (the many-row kernel then shares no tile between workgroups and needs
+ * none).  Split-k calls that overlap in time on one device share the library's
  * buffers and must not be issued on different streams; a caller with several streams gives each
  * its own memory with w4a16_set_workspace, and calls on different streams are then independent.
  *
@@ -294,7 +300,8 @@ int w4a16_set_phase_spin_limit(int polls);
  * the caller keeps alive and untouched while bound.  The call clears it on `stream` (a kernel, so
  * it may be captured) and binds it: from then on calls on that stream with n <= n_max use it and
  * are independent of calls on other streams; n > n_max returns W4A16_ERR_LIMIT.  Only the partial
- * tiles of W4A16_REDUCE_WORKSPACE, which have no bound, stay in the library's own buffer.
+ * tiles of W4A16_REDUCE_WORKSPACE, which have no bound, stay in the library's own buffer.  The
+ * many-row kernel shares no tile between workgroups on such a stream.
  * workspace == NULL unbinds the stream.  Up to 64 bindings per process.
  */
 long long w4a16_workspace_bytes(int n_max);
@@ -302,7 +309,7 @@ int w4a16_set_workspace(void* workspace, long long bytes, int n_max, void* strea
 
 /*
  * Allocate, now, everything the library's own scratch can need for calls with up to n_max columns
- * (about 36 MiB at n_max = 16384), so that no later call allocates, e.g. before capturing graphs.
+ * (about 100 MiB at n_max = 16384), so that no later call allocates, e.g. before capturing graphs.
  */
 int w4a16_reserve_scratch(int n_max);
 

@@ -113,12 +113,6 @@ __device__ __forceinline__ void store_through(uint32_t* word, uint32_t value)
     __hip_atomic_store(word, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ uint32_t pack_half2(float lo, float hi)
-{
-    const half2_t h = {(_Float16)lo, (_Float16)hi};  // v_cvt_f16_f32: round to nearest even
-    return __builtin_bit_cast(uint32_t, h);
-}
-
 // Everything this thread has sent to memory (atomics, write-through stores) has been performed
 // before it goes on.  On gfx9-family hardware the vector memory counter also covers stores and
 // atomics without return.  The "memory" clobber keeps the compiler from moving accesses across.
@@ -1364,6 +1358,8 @@ struct DeviceScratch {
     // call with that split_k: flags [kPhaseOrigins], then counts [kPhaseOrigins][split_k]
     Buffer phase_level[kPhaseMaxSplit + 1];
     Buffer phase_err;  // the error count [1]
+    // many-row kernel: a tile's sums per worker (no invariant), and flags, all zero whenever no call is running
+    Buffer rows_partials, rows_flags;
     uint32_t* err_host = nullptr;  // pinned host word that a wait which ran out sets to 1
     void* retired[64] = {};        // outgrown buffers, freed by w4a16_release_scratch
     int retired_count = 0;
@@ -1379,13 +1375,17 @@ struct ScratchView {
     uint32_t* counts = nullptr;
     uint32_t* errors = nullptr;
     uint32_t* err_host = nullptr;
+    float* rows_partials = nullptr;  // null: this call's tiles are not shared between workers
+    uint32_t* rows_flags = nullptr;
 };
 struct ScratchNeed {
     size_t sums_floats = 0, partial_floats = 0, fixed_words = 0, ticket_count = 0;
+    bool rows = false;    // the many-row kernel's partial sums and flags
     int phase_split = 0;  // 0, or the split_k whose flags and counts the call needs
     int n = 0;            // columns of the call (the phase words cover tile origins n0 / 16)
 };
 enum : int { kScratchLibrary = 0, kScratchStatic = 1 };
+constexpr size_t kRowsPartialBytes = (size_t)kRowsMaxWorkers * 128 * kRowsTileCols * sizeof(float);
 // Word offset of the counts inside a level's buffer, and the buffer's size in words.
 static size_t phase_counts_offset() { return kPhaseOrigins; }
 static size_t phase_level_words(int split_k) { return (size_t)kPhaseOrigins * (1 + (size_t)split_k); }
@@ -2090,14 +2090,24 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
     if (rc == W4A16_OK) rc = grow(s, s.partials, need.partial_floats * sizeof(float), 0, stream, &grew);
     if (rc == W4A16_OK) rc = grow(s, s.fixed, fixed_words * sizeof(uint64_t), (size_t)16 * 16384 * sizeof(uint64_t), stream, &grew);
     if (rc == W4A16_OK) rc = grow(s, s.tickets, need.ticket_count * sizeof(uint32_t), 4096 * sizeof(uint32_t), stream, &grew);
-    if (rc == W4A16_OK && need.phase_split) {
-        rc = grow(s, s.phase_level[need.phase_split], phase_level_words(need.phase_split) * sizeof(uint32_t), 0, stream, &grew);
-        if (rc == W4A16_OK) rc = grow(s, s.phase_err, sizeof(uint32_t), 256, stream, &grew);
+    if (rc == W4A16_OK && need.rows && !s.rows_partials.ptr) {
+        // (64 MiB, once; a call under capture that finds none does without)
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (!W4A16_HIP(hipStreamIsCapturing(stream, &capturing))) return W4A16_ERR_HIP;
+        if (capturing == hipStreamCaptureStatusNone) {
+            rc = grow(s, s.rows_flags, kRowsMaxWorkers * sizeof(uint32_t), 0, stream, &grew);
+            if (rc == W4A16_OK) rc = grow(s, s.rows_partials, kRowsPartialBytes, 0, stream, &grew);
+        }
+    }
+    if (rc == W4A16_OK && (need.phase_split || s.rows_partials.ptr) && !(s.phase_err.ptr && s.err_host)) {
+        rc = grow(s, s.phase_err, sizeof(uint32_t), 256, stream, &grew);
         if (rc == W4A16_OK && !s.err_host) {
             if (!W4A16_HIP(hipHostMalloc((void**)&s.err_host, 256, hipHostMallocMapped))) return W4A16_ERR_HIP;
             *s.err_host = 0u;
         }
     }
+    if (rc == W4A16_OK && need.phase_split)
+        rc = grow(s, s.phase_level[need.phase_split], phase_level_words(need.phase_split) * sizeof(uint32_t), 0, stream, &grew);
     if (rc != W4A16_OK) return rc;
     if (grew && !W4A16_HIP(hipDeviceSynchronize())) return W4A16_ERR_HIP;
     out->sums = (float*)s.sums.ptr;
@@ -2110,6 +2120,8 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
     }
     out->errors = (uint32_t*)s.phase_err.ptr;
     out->err_host = s.err_host;
+    out->rows_partials = (float*)s.rows_partials.ptr;
+    out->rows_flags = (uint32_t*)s.rows_flags.ptr;
     return W4A16_OK;
 }
 
@@ -2437,48 +2449,83 @@ static int run_streamk(const void* A, const void* qweight, const void* scales, c
     return W4A16_HIP(hipGetLastError()) ? W4A16_OK : W4A16_ERR_HIP;
 }
 
-// Many rows (see w4a16_rows.hpp), the library's own launch: tile height and split of k.
-// Workgroups are served one after the other by a compute unit (two at a time, at no more throughput), so the
-// time is the largest number of them on one unit times their chunks; a split adds the fill of C and its
-// packed-fp16 adds.  us per chunk of 128 k: 1.75 with 128 rows, 0.95 with 64; adds: 160 pairs per ns.
-static int run_rows(const void* A, const void* qweight, const void* scales, const void* qzeros, void* C, int m, int n,
-                    int k, int group_size, hipStream_t stream)
+// ---- Many rows (see w4a16_rows.hpp): the library's own launch, or none where other launches take less time.
+struct RowsPlan {
+    int row_blocks, workers;
+    bool whole;  // a worker takes whole tiles: nothing is handed over
+};
+
+// us of `n k` fields and m rows on the launches of up to 64 (group_size 128, 256) or 16 rows; fitted to square and
+// decoder-projection shapes from 2048 x 2048 to 28672 x 4096 (within 15 %).
+static double row_tile_us(int m, double mfields, bool fine_groups)
 {
+    if (fine_groups) return ((m + 15) / 16) * (3.8 + 0.125 * mfields);
+    const int full = m / 64, rest = m % 64;
+    return full * (7.5 + 0.215 * mfields) + (rest ? 2.0 + 0.04 * rest + (0.04 + 0.0027 * rest) * mfields : 0.0);
+}
+
+// The launch with the least estimated time, in us: a worker's chunks one after the other, 4 us around them,
+// and for tiles that workers share 3 us and 1 us (64 rows; 128: 2 us) for every part added to another.  A chunk (all units
+// busy) takes 1.9 us with 128 rows and 1.15 us with 64; where two workers share a unit, 3.65 and 2.2 us; fine
+// groups, which fold their products in two or four times as often, 1.5 and 1.25 (64), 1.85 and 1.5 times that.
+static double plan_rows(int m, int n, int k, int ipg, int bits, bool share_ok, RowsPlan* plan)
+{
+    const int chunks = (k + kRowsChunkK - 1) / kRowsChunkK;
+    double best = 1e30;
+    for (int mb = rows_tall_ok(ipg) ? 8 : 4; mb >= 4; mb -= 4) {
+        const long long tiles = (long long)((m + 16 * mb - 1) / (16 * mb)) * ((n + kRowsTileCols - 1) / kRowsTileCols);
+        if (tiles * chunks >= 1ll << 31) continue;
+        const double one = (mb == 8 ? 1.9 : 1.15) * (ipg == 4 ? 1.0 : ipg == 2 ? 1.5 : 1.85);
+        const double two = (mb == 8 ? 3.65 : 2.2) * (ipg == 4 ? 1.0 : ipg == 2 ? 1.25 : 1.5);
+        const bool pairs_ok = mb == 4 || rows_tall_pairs_ok(bits);
+        auto consider = [&](long long workers, bool whole) {
+            if (workers < 1 || workers > kRowsMaxWorkers || (workers > 256 && !pairs_ok)) return;
+            const long long each = whole ? (tiles + workers - 1) / workers * chunks : (tiles * chunks + workers - 1) / workers;
+            double us = 4.0 + (double)each * (workers > 256 ? two : one);
+            if (!whole && (tiles * chunks) % workers + tiles % workers != 0)
+                us += 3.0 + (double)((chunks + each - 1) / each - 1) * (mb == 8 ? 2.0 : 1.0);
+            if (us < best) {
+                best = us;
+                *plan = RowsPlan{mb, (int)workers, whole};
+            }
+        };
+        consider(tiles < 256 ? tiles : 256, true);
+        consider(tiles < 512 ? tiles : 512, true);
+        if (!share_ok) continue;
+        for (int parts = 2; parts <= 8 && parts <= chunks; ++parts) consider(tiles * parts, false);
+        if (tiles * chunks >= 256) consider(256, false);
+        if (tiles * chunks >= 512) consider(512, false);
+    }
+    return best;
+}
+
+static int run_rows(const RowsPlan& plan, const void* A, const void* qweight, const void* scales, const void* qzeros,
+                    void* C, int m, int n, int k, int group_size, int bits, const ScratchView& view, hipStream_t stream)
+{
+    const int ipg = group_size >= 128 ? 4 : group_size / 32;
     RowsArgs a;
     a.A = (const _Float16*)A;
     a.qweight = (const uint32_t*)qweight;
     a.scales = (const _Float16*)scales;
     a.qzeros = (const uint32_t*)qzeros;
     a.C = (_Float16*)C;
+    a.partials = view.rows_partials;
+    a.flags = view.rows_flags;
+    a.errors = view.errors;
+    a.err_host = view.err_host;
     a.m = m;
     a.n = n;
     a.k = k;
-    a.groups = k / kRowsChunkK;
+    a.chunks = (k + kRowsChunkK - 1) / kRowsChunkK;
     a.param_shift = group_size == 256 ? 1 : 0;
-    a.tiles_n = (n + kRowsTileCols - 1) / kRowsTileCols;
-    double best = 0;
-    int row_blocks = 0;
-    for (int mb = 8; mb >= 4; mb -= 4) {
-        const long long tiles = (long long)((m + 16 * mb - 1) / (16 * mb)) * a.tiles_n;
-        for (int s = 1; s <= 8 && s <= a.groups; ++s) {
-            const long long per_cu = (tiles * s + 255) / 256;
-            const double us = (double)per_cu * ((a.groups + s - 1) / s) * (mb == 8 ? 1.75 : 0.95) +
-                              (s > 1 ? 3.0 + (double)s * m * n / 2 / 160e3 : 0.0);
-            if (row_blocks == 0 || us < best) {
-                best = us;
-                row_blocks = mb;
-                a.split_k = s;
-            }
-        }
-    }
-    a.tiles_m = (m + 16 * row_blocks - 1) / (16 * row_blocks);
-    if ((long long)a.tiles_m * a.tiles_n * a.split_k >= 1ll << 31) return W4A16_ERR_UNSUPPORTED;
-    if (a.split_k > 1) {
-        const size_t words = (size_t)m * n / 2;
-        hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, (uint32_t*)C, words);
-        if (!W4A16_HIP(hipGetLastError())) return W4A16_ERR_HIP;
-    }
-    return W4A16_HIP(launch_rows(a, row_blocks, stream)) ? W4A16_OK : W4A16_ERR_HIP;
+    a.spin_limit = g_spin_limit;
+    a.tiles_m = (m + 16 * plan.row_blocks - 1) / (16 * plan.row_blocks);
+    const int tiles = a.tiles_m * ((n + kRowsTileCols - 1) / kRowsTileCols);
+    a.share_unit = plan.whole ? a.chunks : 1;
+    const int units = plan.whole ? tiles : tiles * a.chunks;
+    a.share = units / plan.workers;
+    a.share_rem = units % plan.workers;
+    return W4A16_HIP(launch_rows(a, bits, ipg, plan.row_blocks, plan.workers, stream)) ? W4A16_OK : W4A16_ERR_HIP;
 }
 
 static void read_tuning_env()
@@ -2517,12 +2564,26 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
     // row tiles of one launch, so the weights stream once per 64 rows; whatever it does not
     // cover (data-parallel kernel, group sizes below 128, the other tile widths and reductions)
     // runs as one launch per 16 rows.
-    // Where the caller leaves every choice to the library, more than 64 rows at group_size 128 or 256 are one
-    // launch of the many-row kernel (its 32-bit offsets span 128 rows of A).
-    if (bits == 4 && m > 16 * kStreamMaxRowTiles && !dp && split_k == 0 && k < (1 << 22) &&
-        stream_rows_ok(group_size, dp, tile_cols, waves, reduce) && tile_cols == 0 && waves == 0 &&
-        reduce == W4A16_REDUCE_AUTO)
-        return run_rows(A, qweight, scales, qzeros, C, m, n, k, group_size, (hipStream_t)stream_v);
+    // Where the caller leaves every choice to the library, a call that would take several launches may be one of
+    // the many-row kernel (its 32-bit offsets span 128 rows of A).
+    const bool fine_groups = group_size < 128;
+    if (m > (fine_groups ? 16 : 16 * kStreamMaxRowTiles) && !dp && split_k == 0 && tile_cols == 0 && waves == 0 &&
+        reduce == W4A16_REDUCE_AUTO && scratch_kind == kScratchLibrary && k < (1 << 22)) {
+        const double others_us = row_tile_us(m, (double)n * k * 1e-6, fine_groups);
+        const int ipg = fine_groups ? group_size / 32 : 4;
+        RowsPlan rows_plan{};
+        if (plan_rows(m, n, k, ipg, bits, true, &rows_plan) < others_us) {
+            ScratchNeed need;
+            need.rows = true;
+            need.n = n;
+            ScratchView view;
+            rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);
+            if (rc != W4A16_OK) return rc;
+            if (view.rows_partials || rows_plan.whole || plan_rows(m, n, k, ipg, bits, false, &rows_plan) < others_us)
+                return run_rows(rows_plan, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, view,
+                                (hipStream_t)stream_v);
+        }
+    }
     const int rows_per_launch = stream_rows_ok(group_size, dp, tile_cols, waves, reduce) ? 16 * kStreamMaxRowTiles : 16;
     if (m > rows_per_launch) {
         for (int r = 0; r < m; r += rows_per_launch) {
@@ -3035,6 +3096,7 @@ int w4a16_reserve_scratch(int n_max)
         w4a16::ScratchNeed need;
         need.n = n_max;
         need.fixed_words = (size_t)16 * n_max;
+        need.rows = true;
         need.phase_split = (size_t)n_max <= 16 * (size_t)w4a16::kPhaseOrigins ? split_k : 0;
         w4a16::ScratchView view;
         const int rc = w4a16::resolve_scratch(w4a16::kScratchLibrary, nullptr, need, &view);
@@ -3058,6 +3120,8 @@ int w4a16_release_scratch(void)
     for (w4a16::Buffer& level : s.phase_level)
         if (level.ptr) (void)hipFree(level.ptr);
     if (s.phase_err.ptr) (void)hipFree(s.phase_err.ptr);
+    if (s.rows_partials.ptr) (void)hipFree(s.rows_partials.ptr);
+    if (s.rows_flags.ptr) (void)hipFree(s.rows_flags.ptr);
     for (int i = 0; i < s.retired_count; ++i) (void)hipFree(s.retired[i]);
     if (s.err_host) (void)hipHostFree(s.err_host);
     s = w4a16::DeviceScratch{};

@@ -54,6 +54,12 @@ __device__ __forceinline__ ZeroConst zero_const(uint32_t z)
     return c;
 }
 
+__device__ __forceinline__ uint32_t pack_half2(float lo, float hi)
+{
+    const half2_t h = {(_Float16)lo, (_Float16)hi};  // v_cvt_f16_f32: round to nearest even
+    return __builtin_bit_cast(uint32_t, h);
+}
+
 // Field i of a packed word: bits [4i, 4i+3].
 __device__ __forceinline__ uint32_t field(uint32_t word, int i) { return (word >> (4 * i)) & 0xFu; }
 

@@ -3,18 +3,24 @@
 //
 // The streaming kernel's row tiles (up to 64 rows a launch) spend one unpack per 64 rows and wait for
 // every chunk's products before they use them; at 64 rows they reach 410 TFLOP/s and every further 64
-// rows stream the weights again.  Here a workgroup owns 128 (or 64) rows x 256 columns.  Each of its four
-// waves owns a 64-column strip for all the rows, so that a weight is unpacked once per workgroup and an
-// unpacked operand serves 8 (4) row blocks.  The activations of a chunk (128 k) come straight from memory
-// into LDS, one chunk ahead, as do the packed weights of each wave's own strip: neither passes through
-// registers, which the sums (128), the unpacked operands (64) and the products in flight fill to the last
-// ones that two waves per SIMD leave.  The scale of a group is applied in fp32 to its products, as in the
-// other kernels.
+// rows stream the weights again.  Here a workgroup owns 128 (or 64) rows x 256 columns at a time.  Each
+// of its four waves owns a 64-column strip for all the rows, so that a weight is unpacked once per tile
+// and an unpacked operand serves 8 (4) row blocks.  The activations of a chunk (128 k) come straight
+// from memory into LDS, one chunk ahead, as do the packed weights of each wave's own strip: neither
+// passes through registers, which the sums (128), the unpacked operands (64) and the products in flight
+// fill to the last ones that two waves per SIMD leave.  Their requests are spread over the unpacking: one
+// 16-byte-per-lane request occupies the unit's memory pipe for 20 cycles, and four waves that issue theirs in
+// one burst stand still for it (m = 333, n = 11008, k = 4096 on whole tiles: 76 us with the burst, 59 without).
+// The scale of a group is applied in fp32 to its products, as in the other kernels.
 //
 // What bounds it: the issue of instructions.  A 16x16x32 MFMA takes 16 cycles of the matrix unit and about
 // 10 of the issue port, every other vector instruction 4; a chunk has 128 and about 340 of them per wave.
-// m = 2048, n = k = 8192: 240 us = 1145 TFLOP/s (664 us with row tiles); the clock is at 1.73 GHz then, where the
-// matrix units' ceiling is 1.8 PFLOP/s.
+// m = 2048, n = k = 8192: 238 us = 1155 TFLOP/s (664 us with row tiles); the clock is at 1.73 GHz then,
+// where the matrix units' ceiling is 1.8 PFLOP/s.
+//
+// Persistent workgroups share the chunks of all tiles evenly, whatever the shape (m = 333, n = 11008, k = 4096, 129
+// tiles: 43 us on 256 workers; 59 us with a workgroup per tile).  A tile that several workers have parts of is
+// added up in fp32, in the order of k.
 #pragma once
 #include "w4a16_device.hpp"
 
@@ -26,16 +32,31 @@ struct RowsArgs {
     const _Float16* scales;
     const uint32_t* qzeros;
     _Float16* C;
+    float* partials;     // [workers][16 MB][256]: the sums of a tile's later parts
+    uint32_t* flags;     // [workers]: 1 while a worker's slot of `partials` is full; all zero whenever no call is running
+    uint32_t* errors;    // count of waits that ran out
+    uint32_t* err_host;  // word in pinned host memory set by a wait that ran out (may be null)
     int m, n, k;
-    int tiles_m, tiles_n;
-    int split_k;
-    int groups;  // 128-k chunks along k, the last one possibly short
-    int param_shift;
+    int tiles_m;
+    int chunks;  // of a tile: 128 consecutive k each, the last one possibly shorter
+    // worker w takes the chunks from start(w) to start(w + 1) of all the tiles' in a row,
+    // start(i) = (i share + min(i, share_rem)) share_unit
+    int share, share_rem, share_unit;
+    int param_shift;  // log2(compute groups per quantisation group)
+    int spin_limit;   // bound on polls of a flag
 };
+
+// Launches the kernel of these field width, compute group size (32 ipg) and tile height (16 row_blocks) on `workers` workgroups.
+hipError_t launch_rows(const RowsArgs& a, int bits, int ipg, int row_blocks, int workers, hipStream_t stream);
+constexpr int kRowsMaxWorkers = 512;
+// Are there kernels of 128-row tiles?  (two workgroups a unit only where LDS holds both: 4- and 2-bit fields)
+constexpr bool rows_tall_ok(int ipg) { return ipg == 4; }
+constexpr bool rows_tall_pairs_ok(int bits) { return bits == 4 || bits == 2; }
 
 constexpr int kRowsStrips = 4;
 constexpr int kRowsTileCols = 64 * kRowsStrips;
 constexpr int kRowsChunkK = 128;
+constexpr int kRowsDeviceScope = 16;  // aux bits of a buffer access that other compute dies' accesses meet: sc1
 
 // ---- Unpack in the order of k, so that the activations need no reordering on their way into LDS.
 // 4-bit: a byte permute puts two neighbouring fields into the low bits of two halves, where a field v is the
@@ -104,8 +125,6 @@ __device__ __forceinline__ half8_t nat_unpack(uint32_t w0, uint32_t w1, const La
     }
 }
 
-hipError_t launch_rows(const RowsArgs& a, int row_blocks, hipStream_t stream);
-
 // 16 bytes per lane from memory straight into LDS: lane l's go to lds + 16 l.
 __device__ __forceinline__ void load_to_lds(rsrc_t r, uint32_t voff, uint32_t soff, uint32_t lds)
 {
@@ -120,244 +139,302 @@ template <int MB, int BITS>
 constexpr int kRowsLdsBytes = 2 * MB * 4096 + kRowsStrips * kRowsWaveWeightBytes<BITS>;
 
 // MB: 16-row blocks per workgroup tile.  IPG: MFMA steps (32 k) per quantisation group in a chunk (4, 2, 1).
-template <int MB, int BITS, int IPG, bool SPLIT>
-__global__ void __launch_bounds__(256, 2) gemm_rows_kernel(RowsArgs p)
+template <int MB, int BITS, int IPG>
+__global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const RowsArgs p)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     constexpr int PG = 4 / IPG;  // parameter sets per chunk
-    const int tid = threadIdx.x, lane = tid & 63;
+    constexpr int kPartialFloats = 16 * MB * kRowsTileCols;
+    const int tid = threadIdx.x;
     const int strip = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = p.m, n = p.n, k = p.k;
     __builtin_assume(m > 0 && n > 0 && k > 0);
 
-    // block -> (slice, tile)
-    const int total = gridDim.x;
-    const int b = blockIdx.x, xcd = b & 7, q8 = total >> 3, r8 = total & 7;
-    int id = xcd * q8 + (xcd < r8 ? xcd : r8) + (b >> 3);
-    const int per_slice = p.tiles_m * p.tiles_n;
-    const int slice = id / per_slice;
-    id -= slice * per_slice;
-    const int tile_n = id / p.tiles_m, tile_m = id - tile_n * p.tiles_m;
-    const int g_base = p.groups / p.split_k, g_rem = p.groups % p.split_k;
-    const int g0 = slice * g_base + (slice < g_rem ? slice : g_rem);
-    const int g_count = g_base + (slice < g_rem ? 1 : 0);
-
-    const int row0 = tile_m * (16 * MB);
-    const int n0 = (tile_n * kRowsStrips + strip) * 64;
-    const LaneMap lm = make_lane_map<4, BITS>(lane, n0, 1, n, k);
-    const int rows = m - row0 < 16 * MB ? m - row0 : 16 * MB;
-    const rsrc_t rs_a = make_rsrc(p.A + (size_t)row0 * k, (uint32_t)rows * (uint32_t)k * 2u);
+    // ---- this worker's range of chunks.  Workgroups go to the eight compute dies in turn; a die takes
+    // neighbouring ranges, the later ones first: a worker waits only for ranges behind its own (see below),
+    // which workgroups ahead of it in the die's order have.
+    const int workers = gridDim.x;
+    const int die = blockIdx.x & 7, per_die = workers >> 3, dies_more = workers & 7;
+    const int w = die * per_die + (die < dies_more ? die : dies_more) + per_die + (die < dies_more ? 1 : 0) - 1 -
+                  (int)(blockIdx.x >> 3);
+    const int U = p.chunks;
+    auto range_start = [&](int i) { return (i * p.share + (i < p.share_rem ? i : p.share_rem)) * p.share_unit; };
+    const int u0 = range_start(w), u1 = range_start(w + 1);
     constexpr int kFields = BITS == 3 ? 1 : 32 / BITS;
-    const int gsize = 32 * IPG;
+    const uint32_t cgroups = (uint32_t)k / (32 * IPG), qgroups = cgroups >> p.param_shift;
     Tensors t;
-    const uint32_t qgroups = ((uint32_t)k / gsize) >> p.param_shift;
     t.qweight = make_rsrc(p.qweight, (uint32_t)(BITS == 3 ? k / 32 * 3 : k / kFields) * (uint32_t)n * 4u);
     t.scales = make_rsrc(p.scales, qgroups * (uint32_t)n * 2u);
     t.qzeros = make_rsrc(p.qzeros, qgroups * (uint32_t)(BITS == 3 ? n / 32 * 3 : n / kFields) * 4u);
     t.n = n;
     t.k = k;
     t.param_shift = p.param_shift;
-
-    // A staging
-    const int srow = 4 * strip + (lane >> 4), skc = (lane & 15) ^ srow;
-    const uint32_t a_voff = ((uint32_t)srow * (uint32_t)k + 8u * (uint32_t)skc) * 2u;
-    const uint32_t lds_base = 0;  // dynamic LDS starts at 0
-    const uint32_t lds_w = lds_base + 2 * MB * 4096 + strip * kRowsWaveWeightBytes<BITS>;
-    // Chunk g's activations: MB pieces of 16 rows, a quarter of each per wave.  Rows behind the last one, k behind
-    // the end (a short last chunk) and whole chunks behind the last one (`voff` outside) come as zeros: their
-    // offsets lie outside the buffer.
-    constexpr uint32_t kOutside = 0x80000000u;  // stays outside when the pieces' rows are added
-    auto stage_a = [&](int g, uint32_t voff, int i) {
-        const uint32_t vo = voff + (uint32_t)i * 32u * (uint32_t)k;
-        load_to_lds(rs_a, vo, (uint32_t)g * 256u, lds_base + (g & 1) * (MB * 4096) + strip * 1024 + i * 4096);
-    };
-    auto stage_w = [&](int g, bool real, int it) {
-        const uint32_t step = (uint32_t)g * 4 + it;
-        const uint32_t dst = lds_w + it * kRowsWordLoads<BITS> * 1024;
-        const bool inside = real && (IPG == 4 || step * 32 < (uint32_t)k);
-        const uint32_t off0 = inside ? lm.off_w : kOutside, off1 = inside ? lm.off_w1 : kOutside;
-        if constexpr (BITS == 8) {
-            load_to_lds(t.qweight, off0, step * 32u * (uint32_t)n, dst);
-            load_to_lds(t.qweight, off0, (step * 32u + 4u) * (uint32_t)n, dst + 1024);
-        } else if constexpr (BITS == 2) {
-            load_to_lds(t.qweight, off0, step * 8u * (uint32_t)n, dst);
-        } else if constexpr (BITS == 3) {
-            load_to_lds(t.qweight, off0, step * 12u * (uint32_t)n, dst);
-            load_to_lds(t.qweight, off1, step * 12u * (uint32_t)n, dst + 1024);
-        } else {
-            load_to_lds(t.qweight, off0, step * 16u * (uint32_t)n, dst);
-        }
-    };
-    auto a_offset = [&](int g, bool real) {
-        return real && (IPG == 4 || g * 128 + 8 * skc < k) ? a_voff : kOutside;
+    auto place = [&](int which, int* row0, int* n0) {
+        const int tile_n = __builtin_amdgcn_readfirstlane(which / p.tiles_m);
+        *row0 = (which - tile_n * p.tiles_m) * (16 * MB);
+        *n0 = (tile_n * kRowsStrips + strip) * 64;
+        return m - *row0 < 16 * MB ? m - *row0 : 16 * MB;
     };
 
-    float4_t acc[MB][4];
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int at = u0; at < u1;) {
+        const int tile_index = __builtin_amdgcn_readfirstlane(at / U), g0 = at - tile_index * U;
+        const int g_count = u1 - at < U - g0 ? u1 - at : U - g0;
+        at += g_count;
+        int row0, n0;
+        const int rows = place(tile_index, &row0, &n0);
+        int lane = tid & 63;  // (hidden: nothing that is worked out from it is held in registers from piece to piece)
+        asm volatile("" : "+v"(lane));
+        const int srow = 4 * strip + (lane >> 4), skc = (lane & 15) ^ srow;
+        const uint32_t a_voff = ((uint32_t)srow * (uint32_t)k + 8u * (uint32_t)skc) * 2u;
+        const uint32_t lds_w = 2 * MB * 4096 + strip * kRowsWaveWeightBytes<BITS>;
+        const rsrc_t rs_a = make_rsrc(p.A + (size_t)row0 * k, (uint32_t)rows * (uint32_t)k * 2u);
+        const LaneMap lm = make_lane_map<4, BITS>(lane, n0, 1, n, k);
+        // A chunk's activations: MB pieces of 16 rows, a quarter of each per wave.  Rows behind the last one, k behind
+        // the end (a short last chunk) and whole chunks behind the last one (`voff` outside) come as zeros: their
+        // offsets lie outside the buffer.
+        constexpr uint32_t kOutside = 0x80000000u;  // stays outside when the pieces' rows are added
+        auto stage_a = [&](int g, uint32_t voff, int i) {
+            const uint32_t vo = voff + (uint32_t)i * 32u * (uint32_t)k;
+            load_to_lds(rs_a, vo, (uint32_t)g * 256u, (uint32_t)(g & 1) * (MB * 4096) + strip * 1024 + i * 4096);
+        };
+        auto stage_w = [&](int g, bool real, int it) {
+            const uint32_t step = (uint32_t)g * 4 + it;
+            const uint32_t dst = lds_w + it * kRowsWordLoads<BITS> * 1024;
+            const bool inside = real && (IPG == 4 || step * 32 < (uint32_t)k);
+            const uint32_t off0 = inside ? lm.off_w : kOutside, off1 = inside ? lm.off_w1 : kOutside;
+            if constexpr (BITS == 8) {
+                load_to_lds(t.qweight, off0, step * 32u * (uint32_t)n, dst);
+                load_to_lds(t.qweight, off0, (step * 32u + 4u) * (uint32_t)n, dst + 1024);
+            } else if constexpr (BITS == 2) {
+                load_to_lds(t.qweight, off0, step * 8u * (uint32_t)n, dst);
+            } else if constexpr (BITS == 3) {
+                load_to_lds(t.qweight, off0, step * 12u * (uint32_t)n, dst);
+                load_to_lds(t.qweight, off1, step * 12u * (uint32_t)n, dst + 1024);
+            } else {
+                load_to_lds(t.qweight, off0, step * 16u * (uint32_t)n, dst);
+            }
+        };
+        auto a_offset = [&](int g, bool real) { return real && (IPG == 4 || g * 128 + 8 * skc < k) ? a_voff : kOutside; };
 
-    uint32_t a_off[4];  // of the chunk in use
+        float4_t acc[MB][4];
 #pragma unroll
-    for (int it = 0; it < 4; ++it)
-        a_off[it] = (g0 & 1) * (MB * 4096) + ((lane & 15) * 16 + ((4 * it + (lane >> 4)) ^ (lane & 15))) * 16;
-    const uint32_t magic = unpack_magic<BITS>();
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-    ParamRegs<4, BITS> par[PG];
-    auto load_params = [&](int g) {
+        uint32_t a_off[4];  // of the chunk in use
 #pragma unroll
-        for (int s = 0; s < PG; ++s) {
+        for (int it = 0; it < 4; ++it)
+            a_off[it] = (g0 & 1) * (MB * 4096) + ((lane & 15) * 16 + ((4 * it + (lane >> 4)) ^ (lane & 15))) * 16;
+        const uint32_t magic = unpack_magic<BITS>();
+
+        ParamRegs<4, BITS> par[PG];
+        auto load_params = [&](int g, int s) {
             int gi = g * PG + s;
-            if (gi >= (k >> 5) / IPG) gi = (k >> 5) / IPG - 1;
+            if (gi >= (int)cgroups) gi = (int)cgroups - 1;
             issue_params<4, BITS>(par[s], lm, t, gi);
-        }
-    };
-#pragma unroll
-    for (int i = 0; i < MB; ++i) stage_a(g0, a_offset(g0, true), i);
-#pragma unroll
-    for (int it = 0; it < 4; ++it) stage_w(g0, true, it);
-    load_params(g0);
-    for (int c = 0; c < g_count; ++c) {
-        const int g = g0 + c;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        const bool more = c + 1 < g_count;
-        const uint32_t a_next = a_offset(g + 1, more);
-        // this chunk's zero points and scales leave the registers that the next chunk's are loaded into
-        NatZero<BITS> zc[PG][4];
-        ScaleBits<4> sc[PG];
-#pragma unroll
-        for (int s = 0; s < PG; ++s) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t z;
-                if constexpr (BITS == 3)
-                    z = (__builtin_amdgcn_alignbit(par[s].zword1, par[s].zword, (uint32_t)lm.zshift) >> (3 * j)) & 7u;
-                else
-                    z = (par[s].zword >> (lm.zshift + BITS * j)) & ((1u << BITS) - 1u);
-                zc[s][j] = nat_zero<BITS>(z);
-            }
-            sc[s] = par[s].s;
-            asm volatile("" : "+v"(sc[s].r[0]), "+v"(sc[s].r[1]));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        load_params(g + 1);
-        __builtin_amdgcn_sched_barrier(0);
-
-        half8_t a[4];
-#pragma unroll
-        for (int it = 0; it < 4; ++it) a[it] = *(const half8_t*)(lds_raw + a_off[it]);
-        // unpack, and the first row block's products as the operands come
-        half8_t bq[4][4];
-        float4_t tile[2][2];  // [pair of column sets][column set]: the products of one quantisation group
-        const float4_t zero4 = float4_t{0.f, 0.f, 0.f, 0.f};
-        auto mfma = [&](int it, int j, bool first) {
-            float4_t& d = tile[j >> 1][j & 1];
-            d = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[it], bq[it][j], first ? zero4 : d, 0, 0, 0);
         };
-        auto add = [&](int i, int s, int pr, int e) {
-            acc[i][2 * pr + (e >> 2)][e & 3] = __builtin_fmaf(scale_of<4>(sc[s], 2 * pr + (e >> 2)), tile[pr][e >> 2][e & 3],
-                                                              acc[i][2 * pr + (e >> 2)][e & 3]);
-        };
-        u32x4_t raw[2][2];
-        auto read_raw = [&](int it) {
-            const char* src = lds_raw + lds_w + it * kRowsWordLoads<BITS> * 1024 + lane * 16;
-            raw[it & 1][0] = raw[it & 1][1] = *(const u32x4_t*)src;
-            if constexpr (kRowsWordLoads<BITS> == 2) raw[it & 1][1] = *(const u32x4_t*)(src + 1024);
-        };
-        read_raw(0);
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int s = it / IPG;
-            if (it < 3) read_raw(it + 1);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < MB; ++i) stage_a(g0, a_offset(g0, true), i);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bq[it][j] = nat_unpack<BITS>(raw[it & 1][0][j], raw[it & 1][1][j], lm, zc[s][j], magic);
-                mfma(it, j, it % IPG == 0);
-                if ((it * 4 + j) % (16 / MB) == 0) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    stage_a(g + 1, a_next, (it * 4 + j) / (16 / MB));
-                    __builtin_amdgcn_sched_barrier(0);
+        for (int it = 0; it < 4; ++it) stage_w(g0, true, it);
+#pragma unroll
+        for (int s = 0; s < PG; ++s) load_params(g0, s);
+        for (int c = 0; c < g_count; ++c) {
+            const int g = g0 + c;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            const bool more = c + 1 < g_count;
+            const uint32_t a_next = a_offset(g + 1, more);
+            // a chunk's zero points and scales leave the registers that the next chunk's are loaded into
+            NatZero<BITS> zc[4];
+            ScaleBits<4> sc[PG];
+            auto take_params = [&](int s) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t z;
+                    if constexpr (BITS == 3)
+                        z = (__builtin_amdgcn_alignbit(par[s].zword1, par[s].zword, (uint32_t)lm.zshift) >> (3 * j)) & 7u;
+                    else
+                        z = (par[s].zword >> (lm.zshift + BITS * j)) & ((1u << BITS) - 1u);
+                    zc[j] = nat_zero<BITS>(z);
                 }
+                sc[s] = par[s].s;
+                asm volatile("" : "+v"(sc[s].r[0]), "+v"(sc[s].r[1]));
+                __builtin_amdgcn_sched_barrier(0);
+                load_params(g + 1, s);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+
+            half8_t a[4];
+#pragma unroll
+            for (int it = 0; it < 4; ++it) a[it] = *(const half8_t*)(lds_raw + a_off[it]);
+            // unpack, and the first row block's products as the operands come
+            half8_t bq[4][4];
+            float4_t tile[2][2];  // [pair of column sets][column set]: the products of one quantisation group
+            const float4_t zero4 = float4_t{0.f, 0.f, 0.f, 0.f};
+            auto mfma = [&](int it, int j, bool first) {
+                float4_t& d = tile[j >> 1][j & 1];
+                d = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[it], bq[it][j], first ? zero4 : d, 0, 0, 0);
+            };
+            auto add = [&](int i, int s, int pr, int e) {
+                acc[i][2 * pr + (e >> 2)][e & 3] = __builtin_fmaf(scale_of<4>(sc[s], 2 * pr + (e >> 2)), tile[pr][e >> 2][e & 3],
+                                                                  acc[i][2 * pr + (e >> 2)][e & 3]);
+            };
+            u32x4_t raw[2][2];
+            auto read_raw = [&](int it) {
+                const char* src = lds_raw + lds_w + it * kRowsWordLoads<BITS> * 1024 + lane * 16;
+                raw[it & 1][0] = raw[it & 1][1] = *(const u32x4_t*)src;
+                if constexpr (kRowsWordLoads<BITS> == 2) raw[it & 1][1] = *(const u32x4_t*)(src + 1024);
+            };
+            read_raw(0);
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int s = it / IPG;
+                if (it % IPG == 0) take_params(s);
+                if (it < 3) read_raw(it + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    bq[it][j] = nat_unpack<BITS>(raw[it & 1][0][j], raw[it & 1][1][j], lm, zc[j], magic);
+                    mfma(it, j, it % IPG == 0);
+                    if ((it * 4 + j) % (16 / MB) == 0) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        stage_a(g + 1, a_next, (it * 4 + j) / (16 / MB));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                if (PG > 1 && it % IPG == IPG - 1) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) add(0, s, e >> 3, e & 7);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (PG > 1 && it % IPG == IPG - 1) {
+            // (where two workgroups share a unit, the one that has products to issue goes first)
+            __builtin_amdgcn_s_setprio(2);
+            if constexpr (PG == 1) {
+                // The other row blocks.  Two column sets at a time: while their products run, the previous pair's
+                // go into the sums, and behind the second pair's products the next block's operands are fetched.
+                auto fetch = [&](int i, int it) { a[it] = *(const half8_t*)(lds_raw + a_off[it] + i * 4096); };
 #pragma unroll
-                for (int e = 0; e < 16; ++e) add(0, s, e >> 3, e & 7);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (PG == 1) {
-            // The other row blocks.  Two column sets at a time: while their products run, the previous pair's
-            // go into the sums, and behind the second pair's products the next block's operands are fetched.
-            auto fetch = [&](int i, int it) { a[it] = *(const half8_t*)(lds_raw + a_off[it] + i * 4096); };
+                for (int it = 0; it < 4; ++it) fetch(1, it);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int it = 0; it < 4; ++it) fetch(1, it);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int e = 0; e < 8; ++e) add(0, 0, 0, e);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) add(0, 0, 0, e);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int i = 1; i < MB; ++i) {
 #pragma unroll
-            for (int i = 1; i < MB; ++i) {
+                    for (int pr = 0; pr < 2; ++pr) {
+                        if (i <= 2) stage_w(g + 1, more, 2 * (i - 1) + pr);
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int pr = 0; pr < 2; ++pr) {
-                    if (i <= 2) stage_w(g + 1, more, 2 * (i - 1) + pr);
-                    __builtin_amdgcn_sched_barrier(0);
+                        for (int it = 0; it < 4; ++it) {
 #pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            mfma(it, 2 * pr + h, it == 0);
-                            if (pr == 1 && h == 1 && i + 1 < MB) fetch(i + 1, it);
-                            add(pr == 0 ? i - 1 : i, 0, 1 - pr, 2 * it + h);
-                            __builtin_amdgcn_sched_barrier(0);
+                            for (int h = 0; h < 2; ++h) {
+                                mfma(it, 2 * pr + h, it == 0);
+                                if (pr == 1 && h == 1 && i + 1 < MB) fetch(i + 1, it);
+                                add(pr == 0 ? i - 1 : i, 0, 1 - pr, 2 * it + h);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
                         }
                     }
                 }
-            }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) add(MB - 1, 0, 1, e);
-        } else {
+                for (int e = 0; e < 8; ++e) add(MB - 1, 0, 1, e);
+            } else {
 #pragma unroll
-            for (int it = 0; it < 4; ++it) stage_w(g + 1, more, it);
+                for (int it = 0; it < 4; ++it) stage_w(g + 1, more, it);
 #pragma unroll
-            for (int i = 1; i < MB; ++i) {
+                for (int i = 1; i < MB; ++i) {
 #pragma unroll
-                for (int it = 0; it < 4; ++it) a[it] = *(const half8_t*)(lds_raw + a_off[it] + i * 4096);
+                    for (int it = 0; it < 4; ++it) a[it] = *(const half8_t*)(lds_raw + a_off[it] + i * 4096);
 #pragma unroll
-                for (int s = 0; s < PG; ++s) {
+                    for (int s = 0; s < PG; ++s) {
 #pragma unroll
-                    for (int i2 = 0; i2 < IPG; ++i2)
+                        for (int i2 = 0; i2 < IPG; ++i2)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) mfma(s * IPG + i2, j, i2 == 0);
+                            for (int j = 0; j < 4; ++j) mfma(s * IPG + i2, j, i2 == 0);
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) add(i, s, e >> 3, e & 7);
+                        for (int e = 0; e < 16; ++e) add(i, s, e >> 3, e & 7);
+                    }
                 }
             }
-        }
+            __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-        for (int it = 0; it < 4; ++it) a_off[it] ^= MB * 4096;
-    }
+            for (int it = 0; it < 4; ++it) a_off[it] ^= MB * 4096;
+        }
+        // what was asked for behind the last chunk has landed (zeros): the next piece's requests go to the same places
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
-    const rsrc_t rs_c = make_rsrc(p.C + (size_t)row0 * n, (uint32_t)rows * (uint32_t)n * 2u);
-    const int col = n0 + 4 * (lane & 15);
+        // ---- the end of a tile, or of this worker's part of one.  A tile whose chunks several workers share is
+        // finished by the one that has its beginning, at the end of that one's range; the others hand their sums over
+        // at the beginning of theirs, so that it hardly ever waits.
+        int el = lane, es = strip;  // (hidden: keeps the addresses below from being held in registers through the loop)
+        asm volatile("" : "+v"(el), "+s"(es));
+        const uint32_t part_off = (uint32_t)(es * (MB * 4)) * 1024u + (uint32_t)el * 16u;
+        if (g0 != 0) {
+            const rsrc_t rs = make_rsrc(p.partials + (size_t)w * kPartialFloats, kPartialFloats * 4);
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+            for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * i + 4 * (lane >> 4) + r;
-            const uint32_t off = col < n && row < rows ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : 0xFFFFFF00u;
-            const half2_t lo = {(_Float16)(acc[i][0][r] * kNatScale<BITS>), (_Float16)(acc[i][1][r] * kNatScale<BITS>)};
-            const half2_t hi = {(_Float16)(acc[i][2][r] * kNatScale<BITS>), (_Float16)(acc[i][3][r] * kNatScale<BITS>)};
-            if constexpr (SPLIT) {
-                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(lo, rs_c, off, 0, 0);
-                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(hi, rs_c, off + 4, 0, 0);
-            } else {
-                __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)}, rs_c, off, 0, 0);
+                for (int j = 0; j < 4; ++j)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs,
+                                                           part_off + (uint32_t)(i * 4 + j) * 1024u, 0, kRowsDeviceScope);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            if (tid == 0) __hip_atomic_store(p.flags + w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            for (int o = w + 1; g0 + g_count < U && o < workers && range_start(o) < (tile_index + 1) * U; ++o) {
+                if (range_start(o + 1) == range_start(o)) continue;
+                bool seen = true;
+                if (es == 0) {
+                    int polls = 0;
+                    do {
+                        seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.flags + o, __ATOMIC_RELAXED,
+                                                                                __HIP_MEMORY_SCOPE_AGENT)) != 0u;
+                        if (!seen) __builtin_amdgcn_s_sleep(4);
+                    } while (!seen && ++polls < p.spin_limit);
+                }
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                const rsrc_t rs = make_rsrc(p.partials + (size_t)o * kPartialFloats, kPartialFloats * 4);
+#pragma unroll
+                for (int i = 0; i < MB; ++i) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[i][j] += __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                                      rs, part_off + (uint32_t)(i * 4 + j) * 1024u, 0,
+                                                                      kRowsDeviceScope));
+                    if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (16 loads in flight)
+                }
+                if (!seen) {  // loud: counted, the next call refuses, and the tile's first element is no number
+                    if (el == 0) {
+                        __hip_atomic_fetch_add(p.errors, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (p.err_host) __hip_atomic_store(p.err_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    }
+                    acc[0][0][0] = __builtin_nanf("");
+                }
+                __builtin_amdgcn_s_barrier();  // every wave has its share
+                if (tid == 0) __hip_atomic_store(p.flags + o, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+            const rsrc_t rs_c = make_rsrc(p.C + (size_t)row0 * n, (uint32_t)rows * (uint32_t)n * 2u);
+            const int col = n0 + 4 * (el & 15);
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * i + 4 * (el >> 4) + r;
+                    const uint32_t off = col < n && row < rows ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
+                    const u32x2_t h = {pack_half2(acc[i][0][r] * kNatScale<BITS>, acc[i][1][r] * kNatScale<BITS>),
+                                       pack_half2(acc[i][2][r] * kNatScale<BITS>, acc[i][3][r] * kNatScale<BITS>)};
+                    __builtin_amdgcn_raw_buffer_store_b64(h, rs_c, off, 0, 0);
+                }
         }
+        // (every wave has read its operands before the next piece's are requested)
+        __builtin_amdgcn_s_barrier();
+    }
 }
 
 }  // namespace w4a16

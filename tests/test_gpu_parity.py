@@ -1448,3 +1448,57 @@ def test_cfg5_split_sweep(oracle):
     b.w4a16_gemm_dp(*p.args())
     assert_parity(p.result(), Cref, "cfg5 dp")
     assert b.w4a16_phase_timeouts() == 0
+
+
+# Many rows, the library's own launch: the kernel of 64- and 128-row tiles whose chunks of 128 k persistent
+# workgroups share (each case twice: the flags of a hand-over are reset by the call that used them).
+MANY_ROWS = [
+    # m, n, k, g
+    (200, 520, 2048, 128),    # ragged rows and columns, tiles in several parts
+    (333, 1032, 128, 128),    # one chunk: nothing to share
+    (129, 264, 4096, 256),    # one row in the last 128-row tile; a group of two chunks
+    (1030, 288, 384, 128),    # many row tiles
+    (40, 288, 1056, 32),      # fine groups, k not a multiple of a chunk
+    (100, 40, 2080, 32),      # fewer columns than one strip
+    (97, 520, 1088, 64),      # half a chunk at the end
+    (600, 2048, 2048, 64),
+    (700, 4096, 1152, 128),   # more tiles than workgroups that share them evenly
+]
+
+
+@pytest.mark.parametrize("bits", [4, 8, 3, 2])
+@pytest.mark.parametrize("m,n,k,g", MANY_ROWS)
+def test_many_rows(oracle, bits, m, n, k, g):
+    n = n // 32 * 32 if bits in (2, 3) else n
+    seed = 4000 + m + n
+    A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
+    rows = np.unique(np.concatenate([np.arange(0, m, max(1, m // 24)), [63 % m, 64 % m, 127 % m, 128 % m, m - 1]]))
+    Cref, _ = oracle.gemm_3bit(A[rows], qw, s, qz, g) if bits == 3 else oracle.gemm_bits(A[rows], qw, s, qz, g, bits)
+    p = DeviceProblem(A, qw, s, qz, g)
+    call = {4: b.w4a16_gemm, 8: b.w8a16_gemm, 3: b.w3a16_gemm, 2: b.w2a16_gemm}[bits]
+    for rep in range(2):
+        p.C.fill_(float("nan"))
+        call(*p.args(), 0)
+        got = p.result().copy()
+        assert np.isfinite(got.astype(np.float32)).all()
+        assert_parity(got[rows], Cref, f"bits={bits} m={m} n={n} k={k} g={g} call {rep}")
+    assert b.w4a16_phase_timeouts() == 0
+
+
+def test_many_rows_one_hot_bit_exact():
+    """One non-zero term per row, swept over all k: every operand of the unpacking in the order of k lands where
+    it belongs, at tile and chunk edges too."""
+    m, n, k, g = 320, 264, 1280, 128
+    rng = np.random.default_rng(11)
+    _, qw, s, qz = random_case(1, n, k, g, seed=12)
+    q = ((qw.view(np.uint32)[:, None, :] >> (4 * np.arange(8, dtype=np.uint32))[None, :, None]) & 15).reshape(k, n)
+    z = ((qz.view(np.uint32)[:, :, None] >> (4 * np.arange(8, dtype=np.uint32))[None, None, :]) & 15).reshape(k // g, n)
+    for base in range(0, k, m):
+        A = np.zeros((m, k), np.float16)
+        A[np.arange(m), base + np.arange(m)] = 1.0
+        p = DeviceProblem(A, qw, s, qz, g)
+        b.w4a16_gemm(*p.args(), 0)
+        rows = base + np.arange(m)
+        want = ((q[rows].astype(np.float32) - z[rows // g].astype(np.float32)) * s[rows // g].astype(np.float32)).astype(np.float16)
+        got = p.result()
+        assert np.array_equal(got, want), base   # (zeros may differ in sign)
