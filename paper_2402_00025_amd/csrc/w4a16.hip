@@ -2572,9 +2572,15 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
         const double others_us = row_tile_us(m, (double)n * k * 1e-6, fine_groups);
         const int ipg = fine_groups ? group_size / 32 : 4;
         RowsPlan rows_plan{};
-        if (plan_rows(m, n, k, ipg, bits, true, &rows_plan) < others_us) {
+        // Workgroups share tiles, through the device's scratch, only where the other launches would split k and use
+        // scratch as well: what runs on two streams at once without a split (the widest matrices) goes on doing so.
+        Plan others;
+        rc = make_plan(fine_groups ? 16 : 16 * kStreamMaxRowTiles, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO,
+                       &others, bits);
+        if (rc != W4A16_OK) return rc;
+        if (plan_rows(m, n, k, ipg, bits, others.split_k > 1, &rows_plan) < others_us) {
             ScratchNeed need;
-            need.rows = true;
+            need.rows = !rows_plan.whole;
             need.n = n;
             ScratchView view;
             rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);

@@ -191,16 +191,17 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
         const LaneMap lm = make_lane_map<4, BITS>(lane, n0, 1, n, k);
         // A chunk's activations: MB pieces of 16 rows, a quarter of each per wave.  Rows behind the last one, k behind
         // the end (a short last chunk) and whole chunks behind the last one (`voff` outside) come as zeros: their
-        // offsets lie outside the buffer.
+        // offsets lie outside the buffer.  The scalar offset stays inside it always: the bound of a buffer access is its
+        // size less that offset, which has no meaning below zero.
         constexpr uint32_t kOutside = 0x80000000u;  // stays outside when the pieces' rows are added
-        auto stage_a = [&](int g, uint32_t voff, int i) {
+        auto stage_a = [&](int g, bool real, uint32_t voff, int i) {
             const uint32_t vo = voff + (uint32_t)i * 32u * (uint32_t)k;
-            load_to_lds(rs_a, vo, (uint32_t)g * 256u, (uint32_t)(g & 1) * (MB * 4096) + strip * 1024 + i * 4096);
+            load_to_lds(rs_a, vo, real ? (uint32_t)g * 256u : 0u, (uint32_t)(g & 1) * (MB * 4096) + strip * 1024 + i * 4096);
         };
         auto stage_w = [&](int g, bool real, int it) {
-            const uint32_t step = (uint32_t)g * 4 + it;
             const uint32_t dst = lds_w + it * kRowsWordLoads<BITS> * 1024;
-            const bool inside = real && (IPG == 4 || step * 32 < (uint32_t)k);
+            const bool inside = real && (IPG == 4 || ((uint32_t)g * 4 + it) * 32 < (uint32_t)k);
+            const uint32_t step = inside ? (uint32_t)g * 4 + it : 0u;
             const uint32_t off0 = inside ? lm.off_w : kOutside, off1 = inside ? lm.off_w1 : kOutside;
             if constexpr (BITS == 8) {
                 load_to_lds(t.qweight, off0, step * 32u * (uint32_t)n, dst);
@@ -235,7 +236,7 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
             issue_params<4, BITS>(par[s], lm, t, gi);
         };
 #pragma unroll
-        for (int i = 0; i < MB; ++i) stage_a(g0, a_offset(g0, true), i);
+        for (int i = 0; i < MB; ++i) stage_a(g0, true, a_offset(g0, true), i);
 #pragma unroll
         for (int it = 0; it < 4; ++it) stage_w(g0, true, it);
 #pragma unroll
@@ -301,7 +302,7 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
                     mfma(it, j, it % IPG == 0);
                     if ((it * 4 + j) % (16 / MB) == 0) {
                         __builtin_amdgcn_sched_barrier(0);
-                        stage_a(g + 1, a_next, (it * 4 + j) / (16 / MB));
+                        stage_a(g + 1, more, a_next, (it * 4 + j) / (16 / MB));
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }

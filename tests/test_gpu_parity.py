@@ -1461,6 +1461,7 @@ MANY_ROWS = [
     (40, 288, 1056, 32),      # fine groups, k not a multiple of a chunk
     (100, 40, 2080, 32),      # fewer columns than one strip
     (97, 520, 1088, 64),      # half a chunk at the end
+    (65, 288, 1056, 32),      # one row in the last tile, a quarter of a chunk at the end
     (600, 2048, 2048, 64),
     (700, 4096, 1152, 128),   # more tiles than workgroups that share them evenly
 ]
@@ -1502,3 +1503,28 @@ def test_many_rows_one_hot_bit_exact():
         want = ((q[rows].astype(np.float32) - z[rows // g].astype(np.float32)) * s[rows // g].astype(np.float32)).astype(np.float16)
         got = p.result()
         assert np.array_equal(got, want), base   # (zeros may differ in sign)
+
+
+def test_many_rows_unsplit_on_two_streams(oracle):
+    """Where the plan reports no split of k, calls on two streams at once share no memory but the weights."""
+    import torch
+    m, n, k, g = 80, 51200, 1024, 128
+    assert b.w4a16_plan(m, n, k, g)["split_k"] == 1
+    _, qw, s, qz = random_case(1, n, k, g, seed=31)
+    rng = np.random.default_rng(32)
+    problems = [DeviceProblem(rng.standard_normal((m, k)).astype(np.float16), qw, s, qz, g) for _ in range(2)]
+    want = []
+    for p in problems:
+        b.w4a16_gemm(*p.args(), 0)
+        want.append(p.result().copy())
+    Cref, _ = oracle.gemm(problems[0].A.cpu().numpy()[[0, 79]], qw, s, qz, g)
+    assert_parity(want[0][[0, 79]], Cref, "first stream's problem")
+    streams = [torch.cuda.Stream() for _ in problems]
+    torch.cuda.synchronize()
+    for _ in range(8):
+        for p, stream in zip(problems, streams):
+            b.w4a16_gemm(*p.args(), 0, stream=stream)
+    torch.cuda.synchronize()
+    for p, w in zip(problems, want):
+        assert np.array_equal(p.C.cpu().numpy(), w)
+    assert b.w4a16_phase_timeouts() == 0
