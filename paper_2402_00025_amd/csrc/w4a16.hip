@@ -2091,12 +2091,16 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
     if (rc == W4A16_OK) rc = grow(s, s.fixed, fixed_words * sizeof(uint64_t), (size_t)16 * 16384 * sizeof(uint64_t), stream, &grew);
     if (rc == W4A16_OK) rc = grow(s, s.tickets, need.ticket_count * sizeof(uint32_t), 4096 * sizeof(uint32_t), stream, &grew);
     if (rc == W4A16_OK && need.rows && !s.rows_partials.ptr) {
-        // (64 MiB, once; a call under capture that finds none does without)
+        // (64 MiB, once; a call that finds none under capture, or no memory for it, does without)
         hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
         if (!W4A16_HIP(hipStreamIsCapturing(stream, &capturing))) return W4A16_ERR_HIP;
         if (capturing == hipStreamCaptureStatusNone) {
             rc = grow(s, s.rows_flags, kRowsMaxWorkers * sizeof(uint32_t), 0, stream, &grew);
             if (rc == W4A16_OK) rc = grow(s, s.rows_partials, kRowsPartialBytes, 0, stream, &grew);
+            if (rc != W4A16_OK && !s.rows_partials.ptr) {
+                (void)hipGetLastError();  // not the next launch's
+                rc = W4A16_OK;
+            }
         }
     }
     if (rc == W4A16_OK && (need.phase_split || s.rows_partials.ptr) && !(s.phase_err.ptr && s.err_host)) {
@@ -2575,18 +2579,22 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
         const int ipg = fine_groups ? group_size / 32 : 4;
         RowsPlan rows_plan{};
         // Workgroups share tiles, through the device's scratch, only where the other launches would split k and use
-        // scratch as well: what runs on two streams at once without a split (the widest matrices) goes on doing so.
+        // scratch as well: what runs on two streams at once without it (the widest matrices) goes on doing so, and
+        // is not refused for a stream's bound workspace of fewer columns.
         Plan others;
         rc = make_plan(fine_groups ? 16 : 16 * kStreamMaxRowTiles, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO,
                        &others, bits);
         if (rc != W4A16_OK) return rc;
-        if (plan_rows(m, n, k, ipg, bits, others.split_k > 1, &rows_plan) < others_us) {
-            ScratchNeed need;
-            need.rows = !rows_plan.whole;
-            need.n = n;
+        const bool share_ok = others.split_k > 1 && others.reduce != W4A16_REDUCE_ATOMIC_PK_F16;
+        if (plan_rows(m, n, k, ipg, bits, share_ok, &rows_plan) < others_us) {
             ScratchView view;
-            rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);
-            if (rc != W4A16_OK) return rc;
+            if (share_ok) {
+                ScratchNeed need;
+                need.rows = !rows_plan.whole;
+                need.n = n;
+                rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);
+                if (rc != W4A16_OK) return rc;
+            }
             if (view.rows_partials || rows_plan.whole || plan_rows(m, n, k, ipg, bits, false, &rows_plan) < others_us)
                 return run_rows(rows_plan, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, view,
                                 (hipStream_t)stream_v);

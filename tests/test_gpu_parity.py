@@ -1528,3 +1528,25 @@ def test_many_rows_unsplit_on_two_streams(oracle):
     for p, w in zip(problems, want):
         assert np.array_equal(p.C.cpu().numpy(), w)
     assert b.w4a16_phase_timeouts() == 0
+
+
+def test_many_rows_unsplit_beside_a_narrow_workspace(oracle):
+    """Where the plan reports no split of k a call needs no scratch: a stream bound to a workspace of fewer columns
+    takes it all the same."""
+    import torch
+    m, n, k, g = 80, 51200, 1024, 128
+    assert b.w4a16_plan(m, n, k, g)["split_k"] == 1
+    p = DeviceProblem(*random_case(m, n, k, g, seed=41), g)
+    nbytes = b.w4a16_workspace_bytes(1024)
+    ws = torch.zeros(nbytes // 4 + 1, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    b.w4a16_set_workspace(ws, nbytes, 1024, stream=stream)
+    try:
+        b.w4a16_gemm(*p.args(), 0, stream=stream)
+        torch.cuda.synchronize()
+        got = p.result().copy()
+    finally:
+        b.w4a16_set_workspace(None, 0, 0, stream=stream)
+    b.w4a16_gemm(*p.args(), 0)
+    assert np.array_equal(got, p.result())
