@@ -28,8 +28,8 @@
  * launch would be needed, it is one launch of a kernel for many rows instead, unless that takes longer: tiles
  * of 64 or 128 rows x 256 columns, their k ranges shared by persistent workgroups, the sums
  * added in fp32 in the order of k (bit-reproducible).  Ranges are shared, through scratch memory,
- * only where w4a16_plan reports a split_k above 1 for the call.  w4a16_plan does not describe it: it
- * reports the launch per 64 or 16 rows.  n a multiple of 8;
+ * only where w4a16_plan reports a split_k above 1 for the call.  n is at most 2^23 for it.  w4a16_plan does not describe
+ * it (it reports the launch per 64 or 16 rows); w4a16_plan_many_rows does.  n a multiple of 8;
  * g (group_size) one of 32, 64, 128, 256; k a multiple of g; k * n < 2^32.  A split_k requested from w4a16_gemm must cut k into equal
  * shares of whole groups (k / split_k a multiple of g), as Algorithm 1 has it.  The library's own
  * choice (split_k == 0) and w4a16_gemm_ex are not bound by that: they deal out k in compute
@@ -244,6 +244,14 @@ int w4a16_plan(int m, int n, int k, int group_size, int dp, int* split_k, int* t
  * the values are outputs only, except `split_k` in.  W4A16_ERR_UNSUPPORTED for any other width. */
 int w4a16_plan_bits(int bits, int m, int n, int k, int group_size, int dp, int* split_k, int* tile_cols,
                     int* waves, int* reduce);
+/*
+ * The many-row launch of a SplitK call of this field width with split_k == 0: the rows of a tile (64 or 128; 0 if the
+ * call goes to the launches w4a16_plan reports instead), the workgroups, and whether these share tiles (1) or take
+ * whole ones (0).  may_share == 0: the launch of a call that finds no scratch for shared tiles (a stream with a bound
+ * workspace; under capture before any such call).  Host only; no HIP call; the last three may be NULL.
+ */
+int w4a16_plan_many_rows(int bits, int m, int n, int k, int group_size, int may_share, int* tile_rows,
+                         int* workgroups, int* shared);
 
 /* Argument check alone (host only, no HIP call): what w4a16_gemm would return before launching
  * (equal shares required of a requested split_k). */

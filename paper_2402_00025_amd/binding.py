@@ -31,6 +31,7 @@ EXPORTS = (
     "w2a16_gemm", "w2a16_gemm_dp", "w2a16_algorithmic_bytes", "w3a16_gemm", "w3a16_gemm_dp", "w3a16_algorithmic_bytes", "w4a16_actorder_prepare", "w4a16_gemm_actorder",
     "w4a16_read_probe", "w4a16_gemm_static", "w4a16_set_phase_spin_limit", "w4a16_workspace_bytes",
     "w4a16_set_workspace", "w4a16_reserve_scratch", "w4a16_gemm_streamk_bits",
+    "w4a16_plan_many_rows",
 )
 
 _lib = None
@@ -91,6 +92,7 @@ def lib() -> ctypes.CDLL:
     L.w4a16_gemm_dp_ex.argtypes = [vp] * 5 + [ci] * 6 + [vp]
     L.w4a16_plan.argtypes = [ci] * 5 + [ip] * 4
     L.w4a16_plan_bits.argtypes = [ci] * 6 + [ip] * 4
+    L.w4a16_plan_many_rows.argtypes = [ci] * 6 + [ip] * 3
     L.w4a16_check.argtypes = [ci] * 5
     L.w4a16_unpack.argtypes = [vp] * 4 + [ci] * 3 + [vp]
     L.w4a16_dequant.argtypes = [vp] * 4 + [ci] * 3 + [vp]
@@ -221,6 +223,14 @@ def w4a16_plan_bits(bits, m, n, k, group_size, dp=False, split_k=0) -> dict:
     _check(lib().w4a16_plan_bits(bits, m, n, k, group_size, int(bool(dp)), ctypes.byref(s), ctypes.byref(t),
                                  ctypes.byref(w), ctypes.byref(r)), "w4a16_plan_bits")
     return dict(split_k=s.value, tile_cols=t.value, waves=w.value, reduce=r.value)
+
+
+def w4a16_plan_many_rows(bits, m, n, k, group_size, may_share=True) -> dict | None:
+    """The many-row launch of a SplitK call with split_k = 0, or None where the call goes to other launches."""
+    r, w, s = (ctypes.c_int(0) for _ in range(3))
+    _check(lib().w4a16_plan_many_rows(bits, m, n, k, group_size, int(bool(may_share)), ctypes.byref(r), ctypes.byref(w),
+                                      ctypes.byref(s)), "w4a16_plan_many_rows")
+    return dict(tile_rows=r.value, workgroups=w.value, shared=bool(s.value)) if r.value else None
 
 
 def w4a16_check(m, n, k, group_size, split_k) -> int:

@@ -2503,6 +2503,32 @@ static double plan_rows(int m, int n, int k, int ipg, int bits, bool share_ok, R
     return best;
 }
 
+// The many-row launch of a call that leaves every choice to the library, or row_blocks == 0 where the other launches
+// are taken.  Up to 64 rows, one launch of the streaming kernel stays the better one: 20.8 us against 27.2 at m = 64,
+// n = k = 8192, 16.1 against 27.1 at m = 48; level (within 5 %) only at m > 48 on matrices of 16384 x 8192 and more or
+// 22016 x 4096.  The kernel's 32-bit offsets span 128 rows of A, and 128 rows of C with room for a marker that lies
+// outside every tile: 256 n <= 2^31.
+// `share_ok` (may be null): workgroups may share tiles, through the device's scratch.  They do so only where the
+// other launches would split k and use scratch as well: what runs on two streams at once without it (the widest
+// matrices) goes on doing so, and is not refused for a stream's bound workspace of fewer columns.
+static int plan_many_rows(int m, int n, int k, int group_size, int bits, bool may_share, RowsPlan* plan, bool* share_ok)
+{
+    *plan = RowsPlan{0, 0, true};
+    const bool fine_groups = group_size < 128;
+    const int others_rows = fine_groups ? 16 : 16 * kStreamMaxRowTiles;
+    if (m <= others_rows || n > 1 << 23 || k >= 1 << 22) return W4A16_OK;
+    Plan others;
+    const int rc = make_plan(others_rows, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO, &others, bits);
+    if (rc != W4A16_OK) return rc;
+    const bool sharing = others.split_k > 1 && others.reduce != W4A16_REDUCE_ATOMIC_PK_F16;
+    RowsPlan best{};
+    if (plan_rows(m, n, k, fine_groups ? group_size / 32 : 4, bits, sharing && may_share, &best) <
+        row_tile_us(m, (double)n * k * 1e-6, fine_groups))
+        *plan = best;
+    if (share_ok) *share_ok = sharing;
+    return W4A16_OK;
+}
+
 static int run_rows(const RowsPlan& plan, const void* A, const void* qweight, const void* scales, const void* qzeros,
                     void* C, int m, int n, int k, int group_size, int bits, const ScratchView& view, hipStream_t stream)
 {
@@ -2569,24 +2595,14 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
     // cover (data-parallel kernel, group sizes below 128, the other tile widths and reductions)
     // runs as one launch per 16 rows.
     // Where the caller leaves every choice to the library, a call that would take several launches may be one of
-    // the many-row kernel (its 32-bit offsets span 128 rows of A).  Up to 64 rows, one launch of the streaming kernel stays
-    // the better one: 20.8 us against 27.2 at m = 64, n = k = 8192, 16.1 against 27.1 at m = 48; level (within 5 %) only at
-    // m > 48 on matrices of 16384 x 8192 and more or 22016 x 4096.
-    const bool fine_groups = group_size < 128;
-    if (m > (fine_groups ? 16 : 16 * kStreamMaxRowTiles) && !dp && split_k == 0 && tile_cols == 0 && waves == 0 &&
-        reduce == W4A16_REDUCE_AUTO && scratch_kind == kScratchLibrary && k < (1 << 22)) {
-        const double others_us = row_tile_us(m, (double)n * k * 1e-6, fine_groups);
-        const int ipg = fine_groups ? group_size / 32 : 4;
-        RowsPlan rows_plan{};
-        // Workgroups share tiles, through the device's scratch, only where the other launches would split k and use
-        // scratch as well: what runs on two streams at once without it (the widest matrices) goes on doing so, and
-        // is not refused for a stream's bound workspace of fewer columns.
-        Plan others;
-        rc = make_plan(fine_groups ? 16 : 16 * kStreamMaxRowTiles, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO,
-                       &others, bits);
+    // the many-row kernel.
+    if (!dp && split_k == 0 && tile_cols == 0 && waves == 0 && reduce == W4A16_REDUCE_AUTO &&
+        scratch_kind == kScratchLibrary) {
+        RowsPlan rows_plan;
+        bool share_ok = false;
+        rc = plan_many_rows(m, n, k, group_size, bits, true, &rows_plan, &share_ok);
         if (rc != W4A16_OK) return rc;
-        const bool share_ok = others.split_k > 1 && others.reduce != W4A16_REDUCE_ATOMIC_PK_F16;
-        if (plan_rows(m, n, k, ipg, bits, share_ok, &rows_plan) < others_us) {
+        if (rows_plan.row_blocks) {
             ScratchView view;
             if (share_ok) {
                 ScratchNeed need;
@@ -2595,7 +2611,11 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
                 rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);
                 if (rc != W4A16_OK) return rc;
             }
-            if (view.rows_partials || rows_plan.whole || plan_rows(m, n, k, ipg, bits, false, &rows_plan) < others_us)
+            if (!rows_plan.whole && !view.rows_partials) {
+                rc = plan_many_rows(m, n, k, group_size, bits, false, &rows_plan, nullptr);
+                if (rc != W4A16_OK) return rc;
+            }
+            if (rows_plan.row_blocks)
                 return run_rows(rows_plan, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, view,
                                 (hipStream_t)stream_v);
         }
@@ -2924,6 +2944,23 @@ int w4a16_plan_bits(int bits, int m, int n, int k, int group_size, int dp, int* 
     if (tile_cols) *tile_cols = plan.tile_cols;
     if (waves) *waves = plan.waves;
     if (reduce) *reduce = plan.reduce;
+    return W4A16_OK;
+}
+
+int w4a16_plan_many_rows(int bits, int m, int n, int k, int group_size, int may_share, int* tile_rows, int* workgroups,
+                         int* shared)
+{
+    if (bits != 2 && bits != 3 && bits != 4 && bits != 8) return W4A16_ERR_UNSUPPORTED;
+    int rc = w4a16::check_args(m, n, k, group_size, 0, true);
+    if (rc != W4A16_OK) return rc;
+    if ((bits == 2 && n % 16 != 0) || (bits == 3 && n % 32 != 0)) return W4A16_ERR_SHAPE;
+    if ((unsigned long long)k * (unsigned long long)n * (unsigned)bits / 8 >= (1ull << 31)) return W4A16_ERR_UNSUPPORTED;
+    w4a16::RowsPlan plan;
+    rc = w4a16::plan_many_rows(m, n, k, group_size, bits, may_share != 0, &plan, nullptr);
+    if (rc != W4A16_OK) return rc;
+    if (tile_rows) *tile_rows = 16 * plan.row_blocks;
+    if (workgroups) *workgroups = plan.workers;
+    if (shared) *shared = plan.whole ? 0 : 1;
     return W4A16_OK;
 }
 

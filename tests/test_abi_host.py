@@ -396,3 +396,23 @@ def test_plan_invariants_on_random_shapes():
         if S > 1:
             assert r in (b.REDUCE_ATOMIC_PK_F16, b.REDUCE_ATOMIC_FIXED, b.REDUCE_ATOMIC_PK_F16_PHASE), what
             assert r != b.REDUCE_ATOMIC_FIXED or m <= 4, what
+
+
+def test_many_row_route_ends_where_its_offsets_end():
+    """The many-row kernel addresses a tile's 128 rows of C in 32 bits, with everything from 2^31 on outside: wider
+    matrices go to the launches of 64 or 16 rows, refusals included."""
+    L = b.lib()
+    for g in (128, 32):
+        for m in (65, 100, 128, 4096):
+            assert b.w4a16_plan_many_rows(4, m, 1 << 23, 128, g) is not None, (m, g)
+            for n in ((1 << 23) + 8, 12000000, 16776960, 1 << 24):
+                assert b.w4a16_plan_many_rows(4, m, n, 128, g) is None, (m, n, g)
+    for may_share in (True, False):
+        assert b.w4a16_plan_many_rows(8, 128, (1 << 23) + 8, 128, 128, may_share) is None
+    assert b.w4a16_plan_many_rows(4, 64, 8192, 8192, 128) is None          # one launch of the streaming kernel
+    assert b.w4a16_plan_many_rows(4, 2048, 8192, 8192, 128) == dict(tile_rows=128, workgroups=512, shared=False)
+    assert b.w4a16_plan_many_rows(4, 333, 11008, 4096, 128)["shared"]
+    assert not b.w4a16_plan_many_rows(4, 333, 11008, 4096, 128, may_share=False)["shared"]
+    assert L.w4a16_plan_many_rows(5, 128, 1024, 1024, 128, 1, None, None, None) == b.ERR_UNSUPPORTED
+    assert L.w4a16_plan_many_rows(3, 128, 1040, 1024, 128, 1, None, None, None) == b.ERR_SHAPE
+    assert L.w4a16_plan_many_rows(8, 128, 1 << 17, 1 << 14, 128, 1, None, None, None) == b.ERR_UNSUPPORTED
