@@ -265,6 +265,13 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
                     zc[j] = nat_zero<BITS>(z);
                 }
                 sc[s] = par[s].s;
+                if constexpr (PG > 1) {
+                    // a group behind the end of k (a short last chunk) has products of zero; its parameters are the
+                    // last group's, whose scale may be infinite: a mask, not a product with 0
+                    const uint32_t real = g * PG + s < (int)cgroups ? 0xFFFFFFFFu : 0u;
+                    sc[s].r[0] &= real;
+                    sc[s].r[1] &= real;
+                }
                 asm volatile("" : "+v"(sc[s].r[0]), "+v"(sc[s].r[1]));
                 __builtin_amdgcn_sched_barrier(0);
                 load_params(g + 1, s);

@@ -1550,3 +1550,29 @@ def test_many_rows_unsplit_beside_a_narrow_workspace(oracle):
         b.w4a16_set_workspace(None, 0, 0, stream=stream)
     b.w4a16_gemm(*p.args(), 0)
     assert np.array_equal(got, p.result())
+
+
+@pytest.mark.parametrize("bits", [4, 8, 3, 2])
+@pytest.mark.parametrize("m,n,k,g", [(65, 288, 1056, 32), (97, 544, 1088, 64)])
+def test_many_rows_infinite_scale_in_the_last_group(oracle, bits, m, n, k, g):
+    """k ends inside a chunk: the groups that the last chunk lacks add nothing, also where the last real one has an
+    infinite scale.  Its columns are infinite with the sign of the group's product, the others as ever."""
+    assert b.w4a16_plan_many_rows(bits, m, n, k, g) is not None
+    A, qw, s, qz = random_case_3bit(m, n, k, g, 71) if bits == 3 else random_case_bits(m, n, k, g, bits, 71)
+    ref = (lambda t: oracle.gemm_3bit(A, qw, t, qz, g)[0]) if bits == 3 else (lambda t: oracle.gemm_bits(A, qw, t, qz, g, bits)[0])
+    huge = np.zeros(n, bool)
+    huge[[0, 5, 64, 255, 256, n - 1]] = True
+    only_last = np.zeros_like(s)
+    only_last[-1] = 1.0
+    sign = np.sign(ref(only_last))          # of the last group's product with scale 1
+    s = s.copy()
+    s[-1, huge] = np.inf
+    p = DeviceProblem(A, qw, s, qz, g)
+    call = {4: b.w4a16_gemm, 8: b.w8a16_gemm, 3: b.w3a16_gemm, 2: b.w2a16_gemm}[bits]
+    call(*p.args(), 0)
+    got = p.result().astype(np.float64)
+    product = sign[:, huge]
+    assert np.array_equal(got[:, huge][product != 0], (product * np.inf)[product != 0])
+    finite = s.copy()
+    finite[-1, huge] = 0.0
+    assert_parity(got[:, ~huge].astype(np.float16), ref(finite)[:, ~huge], f"bits={bits} g={g}")
