@@ -46,7 +46,7 @@
  * as it found it (sums back at zero, counters one call further).  By default that memory is the
  * library's, one set of buffers per device (at most 16 * n 64-bit words, split_k * m * n floats
  * for the workspace flavour, for the in-kernel zeroing 16 KiB * (1 + split_k) per distinct
- * split_k used, and 64 MiB for the sums that the many-row kernel's workgroups hand over), allocated by the first call that needs it (hipMalloc + a synchronous clear; use
+ * split_k used, and 128 MiB for the sums that the many-row kernel's workgroups hand over), allocated by the first call that needs it (hipMalloc + a synchronous clear; use
  * w4a16_reserve_scratch to do that ahead of time) and never moved or freed before
  * w4a16_release_scratch: a buffer that is outgrown stays alive, so a HIP graph captured earlier
  * keeps working.  A call that would have to allocate while its stream is being captured returns
@@ -298,7 +298,9 @@ long long w4a16_phase_timeouts(void);
 
 /*
  * Test hook for the failure path above: the number of polls after which a wait gives up
- * (0 = the library's default, 131072).  A kernel ends normally whatever the value.
+ * (0 = the library's default, 131072).  A kernel ends normally whatever the value.  Workers of the many-row
+ * kernel, whose results do not depend on a wait, look that often less one (and at most 128 times) for the other
+ * parts of a shared tile before they leave it to the last of them.
  */
 int w4a16_set_phase_spin_limit(int polls);
 
@@ -318,7 +320,7 @@ int w4a16_set_workspace(void* workspace, long long bytes, int n_max, void* strea
 
 /*
  * Allocate, now, everything the library's own scratch can need for calls with up to n_max columns
- * (about 100 MiB at n_max = 16384), so that no later call allocates, e.g. before capturing graphs.
+ * (about 164 MiB at n_max = 16384), so that no later call allocates, e.g. before capturing graphs.
  */
 int w4a16_reserve_scratch(int n_max);
 

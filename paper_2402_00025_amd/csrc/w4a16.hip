@@ -1358,8 +1358,8 @@ struct DeviceScratch {
     // call with that split_k: flags [kPhaseOrigins], then counts [kPhaseOrigins][split_k]
     Buffer phase_level[kPhaseMaxSplit + 1];
     Buffer phase_err;  // the error count [1]
-    // many-row kernel: a tile's sums per worker (no invariant), and flags, all zero whenever no call is running
-    Buffer rows_partials, rows_flags;
+    // many-row kernel: two tiles' sums per worker (no invariant), and words, all zero whenever no call is running
+    Buffer rows_partials, rows_words;
     uint32_t* err_host = nullptr;  // pinned host word that a wait which ran out sets to 1
     void* retired[64] = {};        // outgrown buffers, freed by w4a16_release_scratch
     int retired_count = 0;
@@ -1376,16 +1376,16 @@ struct ScratchView {
     uint32_t* errors = nullptr;
     uint32_t* err_host = nullptr;
     float* rows_partials = nullptr;  // null: this call's tiles are not shared between workers
-    uint32_t* rows_flags = nullptr;
+    uint32_t* rows_words = nullptr;
 };
 struct ScratchNeed {
     size_t sums_floats = 0, partial_floats = 0, fixed_words = 0, ticket_count = 0;
-    bool rows = false;    // the many-row kernel's partial sums and flags
+    bool rows = false;    // the many-row kernel's partial sums and words
     int phase_split = 0;  // 0, or the split_k whose flags and counts the call needs
     int n = 0;            // columns of the call (the phase words cover tile origins n0 / 16)
 };
 enum : int { kScratchLibrary = 0, kScratchStatic = 1 };
-constexpr size_t kRowsPartialBytes = (size_t)kRowsMaxWorkers * 128 * kRowsTileCols * sizeof(float);
+constexpr size_t kRowsPartialBytes = (size_t)2 * kRowsMaxWorkers * 128 * kRowsTileCols * sizeof(float);
 // Word offset of the counts inside a level's buffer, and the buffer's size in words.
 static size_t phase_counts_offset() { return kPhaseOrigins; }
 static size_t phase_level_words(int split_k) { return (size_t)kPhaseOrigins * (1 + (size_t)split_k); }
@@ -2091,11 +2091,11 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
     if (rc == W4A16_OK) rc = grow(s, s.fixed, fixed_words * sizeof(uint64_t), (size_t)16 * 16384 * sizeof(uint64_t), stream, &grew);
     if (rc == W4A16_OK) rc = grow(s, s.tickets, need.ticket_count * sizeof(uint32_t), 4096 * sizeof(uint32_t), stream, &grew);
     if (rc == W4A16_OK && need.rows && !s.rows_partials.ptr) {
-        // (64 MiB, once; a call that finds none under capture, or no memory for it, does without)
+        // (128 MiB, once; a call that finds none under capture, or no memory for it, does without)
         hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
         if (!W4A16_HIP(hipStreamIsCapturing(stream, &capturing))) return W4A16_ERR_HIP;
         if (capturing == hipStreamCaptureStatusNone) {
-            rc = grow(s, s.rows_flags, kRowsMaxWorkers * sizeof(uint32_t), 0, stream, &grew);
+            rc = grow(s, s.rows_words, 2 * kRowsMaxWorkers * sizeof(uint32_t), 0, stream, &grew);
             if (rc == W4A16_OK) rc = grow(s, s.rows_partials, kRowsPartialBytes, 0, stream, &grew);
             if (rc != W4A16_OK && !s.rows_partials.ptr) {
                 (void)hipGetLastError();  // not the next launch's
@@ -2103,7 +2103,7 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
             }
         }
     }
-    if (rc == W4A16_OK && (need.phase_split || s.rows_partials.ptr) && !(s.phase_err.ptr && s.err_host)) {
+    if (rc == W4A16_OK && need.phase_split && !(s.phase_err.ptr && s.err_host)) {
         rc = grow(s, s.phase_err, sizeof(uint32_t), 256, stream, &grew);
         if (rc == W4A16_OK && !s.err_host) {
             if (!W4A16_HIP(hipHostMalloc((void**)&s.err_host, 256, hipHostMallocMapped))) return W4A16_ERR_HIP;
@@ -2125,7 +2125,7 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
     out->errors = (uint32_t*)s.phase_err.ptr;
     out->err_host = s.err_host;
     out->rows_partials = (float*)s.rows_partials.ptr;
-    out->rows_flags = (uint32_t*)s.rows_flags.ptr;
+    out->rows_words = (uint32_t*)s.rows_words.ptr;
     return W4A16_OK;
 }
 
@@ -2529,6 +2529,10 @@ static int plan_many_rows(int m, int n, int k, int group_size, int bits, bool ma
     return W4A16_OK;
 }
 
+// About 0.1 ms.  A part that is not there by then belongs to a worker that has not started: leaving the tile to it costs
+// a few us and frees the workgroup's place for others.
+constexpr int kRowsPolls = 128;
+
 static int run_rows(const RowsPlan& plan, const void* A, const void* qweight, const void* scales, const void* qzeros,
                     void* C, int m, int n, int k, int group_size, int bits, const ScratchView& view, hipStream_t stream)
 {
@@ -2540,15 +2544,13 @@ static int run_rows(const RowsPlan& plan, const void* A, const void* qweight, co
     a.qzeros = (const uint32_t*)qzeros;
     a.C = (_Float16*)C;
     a.partials = view.rows_partials;
-    a.flags = view.rows_flags;
-    a.errors = view.errors;
-    a.err_host = view.err_host;
+    a.words = view.rows_words;
     a.m = m;
     a.n = n;
     a.k = k;
     a.chunks = (k + kRowsChunkK - 1) / kRowsChunkK;
     a.param_shift = group_size == 256 ? 1 : 0;
-    a.spin_limit = g_spin_limit;
+    a.polls = g_spin_limit > kRowsPolls ? kRowsPolls : g_spin_limit - 1;
     a.tiles_m = (m + 16 * plan.row_blocks - 1) / (16 * plan.row_blocks);
     const int tiles = a.tiles_m * ((n + kRowsTileCols - 1) / kRowsTileCols);
     a.share_unit = plan.whole ? a.chunks : 1;
@@ -3174,7 +3176,7 @@ int w4a16_release_scratch(void)
         if (level.ptr) (void)hipFree(level.ptr);
     if (s.phase_err.ptr) (void)hipFree(s.phase_err.ptr);
     if (s.rows_partials.ptr) (void)hipFree(s.rows_partials.ptr);
-    if (s.rows_flags.ptr) (void)hipFree(s.rows_flags.ptr);
+    if (s.rows_words.ptr) (void)hipFree(s.rows_words.ptr);
     for (int i = 0; i < s.retired_count; ++i) (void)hipFree(s.retired[i]);
     if (s.err_host) (void)hipHostFree(s.err_host);
     s = w4a16::DeviceScratch{};

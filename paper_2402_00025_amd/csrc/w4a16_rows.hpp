@@ -20,7 +20,10 @@
 //
 // Persistent workgroups share the chunks of all tiles evenly, whatever the shape (m = 333, n = 11008, k = 4096, 129
 // tiles: 43 us on 256 workers; 59 us with a workgroup per tile).  A tile that several workers have parts of is
-// added up in fp32, in the order of k.
+// added up in fp32, in the order of k, by the worker that has its beginning.  That one waits for the other parts for
+// a bounded time; where they are late (a worker that has not started, because other work holds the GPU) it leaves its
+// own part in memory too, and whoever brings the last part adds the tile up, in the same order.  No result depends
+// on a wait, and the words that the workers meet in are zero again when the kernel ends, however it went.
 #pragma once
 #include "w4a16_device.hpp"
 
@@ -32,10 +35,12 @@ struct RowsArgs {
     const _Float16* scales;
     const uint32_t* qzeros;
     _Float16* C;
-    float* partials;     // [workers][16 MB][256]: the sums of a tile's later parts
-    uint32_t* flags;     // [workers]: 1 while a worker's slot of `partials` is full; all zero whenever no call is running
-    uint32_t* errors;    // count of waits that ran out
-    uint32_t* err_host;  // word in pinned host memory set by a wait that ran out (may be null)
+    // [2][workers][16 MB][256]: a worker's sums of a tile that another one began, then of the tile that it began itself
+    // and has left to the others
+    float* partials;
+    // [2][kRowsMaxWorkers], all zero whenever no call is running: 1 while the sums that a worker handed over wait for
+    // their reader; 1 while the tile that a worker began is left to the others
+    uint32_t* words;
     int m, n, k;
     int tiles_m;
     int chunks;  // of a tile: 128 consecutive k each, the last one possibly shorter
@@ -43,7 +48,7 @@ struct RowsArgs {
     // start(i) = (i share + min(i, share_rem)) share_unit
     int share, share_rem, share_unit;
     int param_shift;  // log2(compute groups per quantisation group)
-    int spin_limit;   // bound on polls of a flag
+    int polls;  // how often a worker looks for the later parts of its tile before it leaves it to them
 };
 
 // Launches the kernel of these field width, compute group size (32 ipg) and tile height (16 row_blocks) on `workers` workgroups.
@@ -134,6 +139,14 @@ __device__ __forceinline__ void load_to_lds(rsrc_t r, uint32_t voff, uint32_t so
                  : "memory");
 }
 
+// The lane's number, worked out where it is used: the compiler would hold it through the loop over chunks.
+__device__ __forceinline__ int lane_here()
+{
+    int r;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(r));
+    return r;
+}
+
 template <int BITS>
 constexpr int kRowsWordLoads = (BITS == 8 || BITS == 3) ? 2 : 1;  // 16-byte loads per lane and MFMA step
 template <int BITS>
@@ -148,14 +161,15 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
     constexpr int PG = 4 / IPG;  // parameter sets per chunk
     constexpr int kPartialFloats = 16 * MB * kRowsTileCols;
-    const int tid = threadIdx.x;
-    const int strip = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int strip = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = p.m, n = p.n, k = p.k;
     __builtin_assume(m > 0 && n > 0 && k > 0);
 
     // ---- this worker's range of chunks.  Workgroups go to the eight compute dies in turn; a die takes
-    // neighbouring ranges, the later ones first: a worker waits only for ranges behind its own (see below),
-    // which workgroups ahead of it in the die's order have.
+    // neighbouring ranges, whose operands and sums its L2 then holds (neighbours on different dies: 2.5 % slower on
+    // average, up to 26 %).  The later ranges first: a worker waits for ranges behind its own (see below), which
+    // workgroups ahead of it in the die's order have.  Only the last worker of a die waits for another die's, and
+    // that one's first range is the last to start there: with the GPU to itself all have started by then.
     const int workers = gridDim.x;
     const int die = blockIdx.x & 7, per_die = workers >> 3, dies_more = workers & 7;
     const int w = die * per_die + (die < dies_more ? die : dies_more) + per_die + (die < dies_more ? 1 : 0) - 1 -
@@ -179,14 +193,115 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
         return m - *row0 < 16 * MB ? m - *row0 : 16 * MB;
     };
 
+    // ---- tiles with several parts.  The worker that has a tile's beginning, and how many workers have later parts of
+    // the tile that worker i began (the ranges are never empty).
+    auto first_worker = [&](int which) {
+        int i = w;
+        while (range_start(i) > which * U) --i;
+        return i;
+    };
+    auto later_parts = [&](int i, int which) {
+        int o = i + 1;
+        while (o < workers && range_start(o) < (which + 1) * U) ++o;
+        return (uint32_t)(o - i - 1);
+    };
+    uint32_t* const full = p.words;
+    uint32_t* const left = p.words + kRowsMaxWorkers;
+    auto look = [&](const uint32_t* word) {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    auto set = [&](uint32_t* word) {
+        __hip_atomic_store(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto part_offset = [&](int es, int el) { return (uint32_t)(es * (MB * 4)) * 1024u + (uint32_t)el * 16u; };
+    auto put_part = [&](const float4_t (&acc)[MB][4], int slot, int es, int el) {
+        const rsrc_t rs = make_rsrc(p.partials + (size_t)slot * kPartialFloats, kPartialFloats * 4);
+        const uint32_t off = part_offset(es, el);
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs,
+                                                       off + (uint32_t)(i * 4 + j) * 1024u, 0, kRowsDeviceScope);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+    };
+    auto add_part = [&](float4_t (&acc)[MB][4], int slot, int es, int el) {
+        const rsrc_t rs = make_rsrc(p.partials + (size_t)slot * kPartialFloats, kPartialFloats * 4);
+        const uint32_t off = part_offset(es, el);
+#pragma unroll
+        for (int i0 = 0; i0 < MB; i0 += 4) {  // 16 loads in flight
+            float4_t part[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    part[i][j] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                                  rs, off + (uint32_t)((i0 + i) * 4 + j) * 1024u, 0, kRowsDeviceScope));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i0 + i][j] += part[i][j];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto taken = [&](int first, uint32_t parts, int es, int el) {
+        __builtin_amdgcn_s_barrier();  // every wave has its share
+        if (es == 0)
+            for (uint32_t i = 1 + el; i <= parts; i += 64) __hip_atomic_store(full + first + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // The first wave's answer, for all four (through its own strip's weights, which no other wave touches and which
+    // nothing is on its way to when this is called).  What follows is not moved ahead of it.
+    auto tell = [&](bool answer, int es, int el) {
+        uint32_t* const word = (uint32_t*)(lds_raw + 2 * MB * 4096);
+        if (es == 0 && el == 0) *word = answer ? 1u : 0u;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const bool r = __builtin_amdgcn_readfirstlane(*word) != 0u;
+        __builtin_amdgcn_s_barrier();  // (read by all before it is written again)
+        return r;
+    };
+    // The first wave asks this of a tile that worker `first` has left: are all later parts there, and does nobody else
+    // finish it?  Whoever looks has set its own word before (the part that it brought, or `left`), so the last one to
+    // come finds all of them; the exchange lets one through.
+    auto claim = [&](int first, uint32_t parts, int el) {
+        for (uint32_t i = 1; i <= parts; ++i)
+            if (look(full + first + i) == 0u) return false;
+        uint32_t won = 0;
+        if (el == 0) {
+            uint32_t expected = 1u;
+            won = __hip_atomic_compare_exchange_strong(left + first, &expected, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT)
+                      ? 1u
+                      : 0u;
+        }
+        return __builtin_amdgcn_readfirstlane(won) != 0u;
+    };
+    auto store_tile = [&](const float4_t (&acc)[MB][4], int row0, int n0, int rows, int el) {
+        constexpr uint32_t kOutside = 0x80000000u;
+        const rsrc_t rs_c = make_rsrc(p.C + (size_t)row0 * n, (uint32_t)rows * (uint32_t)n * 2u);
+        const int col = n0 + 4 * (el & 15);
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * i + 4 * (el >> 4) + r;
+                const uint32_t off = col < n && row < rows ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
+                const u32x2_t h = {pack_half2(acc[i][0][r] * kNatScale<BITS>, acc[i][1][r] * kNatScale<BITS>),
+                                   pack_half2(acc[i][2][r] * kNatScale<BITS>, acc[i][3][r] * kNatScale<BITS>)};
+                __builtin_amdgcn_raw_buffer_store_b64(h, rs_c, off, 0, 0);
+            }
+    };
+
     for (int at = u0; at < u1;) {
         const int tile_index = __builtin_amdgcn_readfirstlane(at / U), g0 = at - tile_index * U;
         const int g_count = u1 - at < U - g0 ? u1 - at : U - g0;
         at += g_count;
         int row0, n0;
         const int rows = place(tile_index, &row0, &n0);
-        int lane = tid & 63;  // (hidden: nothing that is worked out from it is held in registers from piece to piece)
-        asm volatile("" : "+v"(lane));
+        const int lane = lane_here();  // (so that nothing that is worked out from it is held in registers from piece to piece)
         const int srow = 4 * strip + (lane >> 4), skc = (lane & 15) ^ srow;
         const uint32_t a_voff = ((uint32_t)srow * (uint32_t)k + 8u * (uint32_t)skc) * 2u;
         const uint32_t lds_w = 2 * MB * 4096 + strip * kRowsWaveWeightBytes<BITS>;
@@ -232,18 +347,32 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
             a_off[it] = (g0 & 1) * (MB * 4096) + ((lane & 15) * 16 + ((4 * it + (lane >> 4)) ^ (lane & 15))) * 16;
         const uint32_t magic = unpack_magic<BITS>();
 
+        // The zero points' place in the lane's words of 3-bit fields is worked out again for every chunk: three registers
+        // less through the loop, where 128 rows leave none (one of them kept in memory: 5 % of the time).
+        auto params_map = [&]() {
+            LaneMap map = lm;
+            if constexpr (BITS == 3) {
+                uint32_t twice = lm.off_s;  // 2 columns
+                asm volatile("" : "+v"(twice));
+                const uint32_t bit = twice + (twice >> 1);
+                map.off_z = (bit >> 5) * 4u;
+                map.zshift = (int)(bit & 31u);
+                map.off_z1 = map.off_z + (map.zshift + 12 > 32 ? 4u : 0u);
+            }
+            return map;
+        };
         ParamRegs<4, BITS> par[PG];
-        auto load_params = [&](int g, int s) {
+        auto load_params = [&](const LaneMap& map, int g, int s) {
             int gi = g * PG + s;
             if (gi >= (int)cgroups) gi = (int)cgroups - 1;
-            issue_params<4, BITS>(par[s], lm, t, gi);
+            issue_params<4, BITS>(par[s], map, t, gi);
         };
 #pragma unroll
         for (int i = 0; i < MB; ++i) stage_a(g0, true, a_offset(g0, true), i);
 #pragma unroll
         for (int it = 0; it < 4; ++it) stage_w(g0, true, it);
 #pragma unroll
-        for (int s = 0; s < PG; ++s) load_params(g0, s);
+        for (int s = 0; s < PG; ++s) load_params(params_map(), g0, s);
         for (int c = 0; c < g_count; ++c) {
             const int g = g0 + c;
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -255,26 +384,25 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
             NatZero<BITS> zc[4];
             ScaleBits<4> sc[PG];
             auto take_params = [&](int s) {
+                const LaneMap map = params_map();
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     uint32_t z;
                     if constexpr (BITS == 3)
-                        z = (__builtin_amdgcn_alignbit(par[s].zword1, par[s].zword, (uint32_t)lm.zshift) >> (3 * j)) & 7u;
+                        z = (__builtin_amdgcn_alignbit(par[s].zword1, par[s].zword, (uint32_t)map.zshift) >> (3 * j)) & 7u;
                     else
-                        z = (par[s].zword >> (lm.zshift + BITS * j)) & ((1u << BITS) - 1u);
+                        z = (par[s].zword >> (map.zshift + BITS * j)) & ((1u << BITS) - 1u);
                     zc[j] = nat_zero<BITS>(z);
                 }
                 sc[s] = par[s].s;
                 if constexpr (PG > 1) {
-                    // a group behind the end of k (a short last chunk) has products of zero; its parameters are the
-                    // last group's, whose scale may be infinite: a mask, not a product with 0
                     const uint32_t real = g * PG + s < (int)cgroups ? 0xFFFFFFFFu : 0u;
                     sc[s].r[0] &= real;
                     sc[s].r[1] &= real;
                 }
                 asm volatile("" : "+v"(sc[s].r[0]), "+v"(sc[s].r[1]));
                 __builtin_amdgcn_sched_barrier(0);
-                load_params(g + 1, s);
+                load_params(map, g + 1, s);
                 __builtin_amdgcn_sched_barrier(0);
             };
 
@@ -382,69 +510,66 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
         // ---- the end of a tile, or of this worker's part of one.  A tile whose chunks several workers share is
         // finished by the one that has its beginning, at the end of that one's range; the others hand their sums over
         // at the beginning of theirs, so that it hardly ever waits.
-        int el = lane, es = strip;  // (hidden: keeps the addresses below from being held in registers through the loop)
-        asm volatile("" : "+v"(el), "+s"(es));
-        const uint32_t part_off = (uint32_t)(es * (MB * 4)) * 1024u + (uint32_t)el * 16u;
+        const int el = lane_here();
+        int es = strip;  // (hidden: keeps the addresses below from being held in registers through the loop)
+        asm volatile("" : "+s"(es));
         if (g0 != 0) {
-            const rsrc_t rs = make_rsrc(p.partials + (size_t)w * kPartialFloats, kPartialFloats * 4);
-#pragma unroll
-            for (int i = 0; i < MB; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs,
-                                                           part_off + (uint32_t)(i * 4 + j) * 1024u, 0, kRowsDeviceScope);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            if (tid == 0) __hip_atomic_store(p.flags + w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            put_part(acc, w, es, el);
+            if (es == 0 && el == 0) set(full + w);
         } else {
-            for (int o = w + 1; g0 + g_count < U && o < workers && range_start(o) < (tile_index + 1) * U; ++o) {
-                if (range_start(o + 1) == range_start(o)) continue;
-                bool seen = true;
+            if (g_count < U) {
+                const uint32_t parts = later_parts(w, tile_index);
+                bool all = true;
                 if (es == 0) {
-                    int polls = 0;
-                    do {
-                        seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.flags + o, __ATOMIC_RELAXED,
-                                                                                __HIP_MEMORY_SCOPE_AGENT)) != 0u;
-                        if (!seen) __builtin_amdgcn_s_sleep(4);
-                    } while (!seen && ++polls < p.spin_limit);
-                }
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                const rsrc_t rs = make_rsrc(p.partials + (size_t)o * kPartialFloats, kPartialFloats * 4);
-#pragma unroll
-                for (int i = 0; i < MB; ++i) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        acc[i][j] += __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                                                                      rs, part_off + (uint32_t)(i * 4 + j) * 1024u, 0,
-                                                                      kRowsDeviceScope));
-                    if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (16 loads in flight)
-                }
-                if (!seen) {  // loud: counted, the next call refuses, and the tile's first element is no number
-                    if (el == 0) {
-                        __hip_atomic_fetch_add(p.errors, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if (p.err_host) __hip_atomic_store(p.err_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    uint32_t come = 0;
+                    for (int looks = 0; looks < p.polls && come < parts; ++looks) {
+                        if (looks) __builtin_amdgcn_s_sleep(4);
+                        while (come < parts && look(full + w + 1 + come) != 0u) ++come;
                     }
-                    acc[0][0][0] = __builtin_nanf("");
+                    all = come == parts;
                 }
-                __builtin_amdgcn_s_barrier();  // every wave has its share
-                if (tid == 0) __hip_atomic_store(p.flags + o, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!tell(all, es, el)) {
+                    put_part(acc, workers + w, es, el);
+                    if (es == 0) {
+                        if (el == 0) set(left + w);
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                        all = claim(w, parts, el);
+                    }
+                    if (!tell(all, es, el)) goto range_done;  // (it was the last tile of this range)
+                }
+                for (uint32_t i = 1; i <= parts; ++i) add_part(acc, w + i, es, el);
+                taken(w, parts, es, el);
             }
-            const rsrc_t rs_c = make_rsrc(p.C + (size_t)row0 * n, (uint32_t)rows * (uint32_t)n * 2u);
-            const int col = n0 + 4 * (el & 15);
-#pragma unroll
-            for (int i = 0; i < MB; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * i + 4 * (el >> 4) + r;
-                    const uint32_t off = col < n && row < rows ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
-                    const u32x2_t h = {pack_half2(acc[i][0][r] * kNatScale<BITS>, acc[i][1][r] * kNatScale<BITS>),
-                                       pack_half2(acc[i][2][r] * kNatScale<BITS>, acc[i][3][r] * kNatScale<BITS>)};
-                    __builtin_amdgcn_raw_buffer_store_b64(h, rs_c, off, 0, 0);
-                }
+            store_tile(acc, row0, n0, rows, el);
         }
         // (every wave has read its operands before the next piece's are requested)
         __builtin_amdgcn_s_barrier();
+    }
+range_done:
+    // ---- the tile whose sums this worker handed over: if it was left to its later parts and all of them have come,
+    // one of them finishes it.  The last one to come finds it so, since it looks after it has come.
+    if (u0 % U != 0 && u0 < u1) {
+        const int tile_index = u0 / U, first = first_worker(tile_index);
+        const uint32_t parts = later_parts(first, tile_index);
+        const int el = lane_here(), es = strip;
+        bool mine = false;
+        if (es == 0) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            mine = look(left + first) != 0u && claim(first, parts, el);
+        }
+        if (tell(mine, es, el)) {
+            int row0, n0;
+            const int rows = place(tile_index, &row0, &n0);
+            float4_t acc[MB][4];
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+            add_part(acc, workers + first, es, el);
+            for (uint32_t i = 1; i <= parts; ++i) add_part(acc, first + i, es, el);
+            taken(first, parts, es, el);
+            store_tile(acc, row0, n0, rows, el);
+        }
     }
 }
 

@@ -2,14 +2,15 @@
 a captured call survives a later growth of the library's buffers; a call that would have to
 allocate during a capture is refused; streams with workspaces of their own are independent;
 a wait of the in-kernel zeroing that runs out ends the kernel, is counted, poisons the tile,
-and makes the next call fail until the scratch is released; NaN goes through the fixed-point adds."""
+and makes the next call fail until the scratch is released; NaN goes through the fixed-point adds;
+the many-row kernel's results do not depend on its waits."""
 import ctypes
 
 import numpy as np
 import pytest
 
 from gpu_util import DeviceProblem, assert_parity
-from oracle_pins import random_case
+from oracle_pins import random_case, random_case_3bit, random_case_bits
 from paper_2402_00025_amd import binding as b
 
 pytestmark = pytest.mark.gpu
@@ -221,3 +222,68 @@ def test_nan_and_infinity_through_the_fixed_point_adds(oracle):
         C2, _ = oracle.gemm(A2, qw, s, qz, 128)
         b.w4a16_gemm_ex(*p2.args(), split_k, 64, waves, b.REDUCE_ATOMIC_FIXED)
         assert_parity(p2.result(), C2, f"after the NaN call, S={split_k}")
+
+
+GEMM = {4: b.w4a16_gemm, 8: b.w8a16_gemm, 3: b.w3a16_gemm, 2: b.w2a16_gemm}
+# Many rows with shared tiles: one range per worker and tile (every part is done at the same time), ranges over tile
+# edges, two workers per compute unit, both tile heights, every width.
+SHARED_ROWS = [
+    # bits, m, n, k, g, rows of a tile
+    (4, 200, 520, 2048, 128, 64),
+    (4, 167, 1056, 1792, 256, 64),
+    (4, 333, 11008, 4096, 128, 128),
+    (4, 1109, 2080, 960, 32, 64),
+    (8, 300, 2048, 2048, 128, 64),
+    (8, 333, 11008, 4096, 128, 128),
+    (3, 269, 4960, 1664, 64, 64),
+    (3, 266, 320, 2432, 128, 64),
+    (2, 913, 2144, 672, 32, 64),
+    (2, 333, 11008, 4096, 128, 128),
+]
+
+
+@pytest.mark.parametrize("bits,m,n,k,g,tile_rows", SHARED_ROWS)
+def test_shared_tiles_do_not_depend_on_waits(oracle, bits, m, n, k, g, tile_rows):
+    """A worker that leaves its tile to the others without looking for their parts, at every tile, under capture too:
+    the same bits as when it waits, no error, and nothing left behind for the calls after it."""
+    import torch
+    plan = b.w4a16_plan_many_rows(bits, m, n, k, g)
+    assert plan and plan["shared"] and plan["tile_rows"] == tile_rows, plan
+    call = GEMM[bits]
+    probs, want = [], []
+    for seed in (301, 302):
+        case = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
+        p = DeviceProblem(*case, g)
+        call(*p.args(), 0)
+        want.append(p.result().copy())
+        rows = [0, 63, 64, m // 2, m - 1]
+        A, qw, s, qz = case
+        Cref = oracle.gemm_3bit(A[rows], qw, s, qz, g)[0] if bits == 3 else oracle.gemm_bits(A[rows], qw, s, qz, g, bits)[0]
+        assert_parity(want[-1][rows], Cref, f"waiting, bits={bits} seed={seed}")
+        probs.append(p)
+
+    def check(i, what):
+        torch.cuda.synchronize()
+        assert np.array_equal(probs[i].C.cpu().numpy(), want[i]), what
+
+    b.w4a16_set_phase_spin_limit(1)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call(*probs[0].args(), 0, stream=torch.cuda.current_stream())
+    for rep in range(6):
+        i = rep % 2
+        probs[i].C.fill_(float("nan"))
+        call(*probs[i].args(), 0)
+        check(i, f"left, call {rep}")
+    b.w4a16_set_phase_spin_limit(0)
+    for rep in range(4):
+        probs[0].C.fill_(float("nan"))
+        probs[1].C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()                                  # leaves
+        call(*probs[1].args(), 0)                       # waits; behind the replay in time
+        check(0, f"replay {rep}")
+        check(1, f"waiting call behind replay {rep}")
+    assert b.w4a16_phase_timeouts() == 0
