@@ -2139,9 +2139,9 @@ static int launch_bound(const GemmArgs& a, int waves, size_t lds_bytes, hipStrea
             return W4A16_ERR_HIP;
     }
     const unsigned threads = (unsigned)(waves + (MODE == kAtomicPkF16Service ? 1 : 0)) * kWave;
-    // (the second grid dimension holds at most 65535)
-    if (a.m > 31 || a.param_shift > 3 || a.waves > 31 || a.groups_base >= (1 << 20) || a.groups_rem >= (1 << 15) ||
-        a.split_k < 1 || a.split_k >= (1 << 16))
+    // (the second grid dimension holds at most 65535; more tiles or parts with a group more than these were never taken)
+    if (a.m > 31 || a.param_shift > 3 || a.waves > 31 || a.groups_base >= (1 << 20) || a.groups_rem >= (1 << 11) ||
+        a.tiles >= (1 << 20) || a.split_k < 1 || a.split_k >= (1 << 16))
         return W4A16_ERR_UNSUPPORTED;
     const int packed = a.m | a.param_shift << 5 | a.waves << 7 | (int)((unsigned)a.groups_base << 12);
     const int split_rem = a.split_k | a.groups_rem << 16;

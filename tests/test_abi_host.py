@@ -121,6 +121,15 @@ def test_gemm_rejects_before_touching_hip():
     assert L.w4a16_set_phase_spin_limit(0) == b.OK
 
 
+def test_launches_of_more_than_a_million_tiles_are_refused():
+    """Refused before any HIP call: 2^20 and more column tiles of the per-wave kernel."""
+    L = b.lib()
+    p = ctypes.c_void_p(4096)       # never dereferenced
+    for n, cols in ((1 << 24, 16), (1 << 25, 32), ((1 << 24) + 8, 16)):
+        for waves in (1, 4):
+            assert L.w4a16_gemm_dp_ex(p, p, p, p, p, 1, n, 32 * waves, 32, cols, waves, None) == b.ERR_UNSUPPORTED, (n, cols)
+
+
 def test_reported_plans_can_be_passed_back():
     """Whatever launch w4a16_plan reports for a shape is accepted, unchanged, when it is given
     explicitly (a data-parallel shaped launch names a reduction it does not use)."""
