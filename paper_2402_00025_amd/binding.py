@@ -125,21 +125,32 @@ def _call_module():
             f"{_HERE / '_call.so'} cannot be loaded ({e}): build it with `python -m paper_2402_00025_amd.build`") from e
 
 
-def _gemm_entries():
-    """The per-layer calls, as the extension's own functions: nothing of Python lies between a call and
-    the library.  On a tree that has not been built yet they are stand-ins that look again when called."""
-    names = ("w4a16_gemm", "w4a16_gemm_static", "w4a16_gemm_dp", "w8a16_gemm", "w8a16_gemm_dp", "w3a16_gemm",
-             "w3a16_gemm_dp", "w2a16_gemm", "w2a16_gemm_dp", "w4a16_gemm_actorder")
+_GEMM_CALLS = ("w4a16_gemm", "w4a16_gemm_static", "w4a16_gemm_dp", "w8a16_gemm", "w8a16_gemm_dp", "w3a16_gemm",
+               "w3a16_gemm_dp", "w2a16_gemm", "w2a16_gemm_dp", "w4a16_gemm_actorder")
+
+
+def __getattr__(name):
+    """The per-layer calls, looked up when they are first asked for: the extension's own functions, so that nothing of
+    Python lies between a call and the library.  Where that cannot be loaded (a tree that has not been built yet), a
+    stand-in that looks again, and raises, when it is called."""
+    if name not in _GEMM_CALLS:
+        raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
     try:
         module = _call_module()
-    except FileNotFoundError:
-        def later(name):
-            return lambda *args, **kwargs: getattr(_call_module(), name)(*args, **kwargs)
-        return {name: later(name) for name in names}
-    return {name: getattr(module, name) for name in names}
+    except Exception:
+        def later(*args, **kwargs):
+            return getattr(_call_module(), name)(*args, **kwargs)
+        later.__name__ = later.__qualname__ = name
+        return later
+    for call in _GEMM_CALLS:
+        function = getattr(module, call)
+        function.__module__ = __name__
+        globals()[call] = function
+    return globals()[name]
 
 
-globals().update(_gemm_entries())
+def __dir__():
+    return sorted({*globals(), *_GEMM_CALLS})
 
 
 def _p(t):

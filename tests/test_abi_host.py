@@ -425,3 +425,47 @@ def test_many_row_route_ends_where_its_offsets_end():
     assert L.w4a16_plan_many_rows(5, 128, 1024, 1024, 128, 1, None, None, None) == b.ERR_UNSUPPORTED
     assert L.w4a16_plan_many_rows(3, 128, 1040, 1024, 128, 1, None, None, None) == b.ERR_SHAPE
     assert L.w4a16_plan_many_rows(8, 128, 1 << 17, 1 << 14, 128, 1, None, None, None) == b.ERR_UNSUPPORTED
+
+
+def _in_a_process_of_its_own(code):
+    import subprocess
+    import sys
+    return subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+
+
+def test_importing_the_binding_loads_nothing():
+    """The library, the extension module and torch are loaded when a call is first asked for; a library that cannot be
+    loaded raises when it is called."""
+    r = _in_a_process_of_its_own("""
+import pathlib, pickle, sys, tempfile
+from paper_2402_00025_amd import binding as b
+assert "torch" not in sys.modules and "paper_2402_00025_amd._call" not in sys.modules
+assert "w4a16_gemm" in dir(b)
+good = b.LIB_PATH
+with tempfile.TemporaryDirectory() as tmp:
+    for bad, error in ((pathlib.Path(tmp) / "none.so", FileNotFoundError), (pathlib.Path(tmp) / "text.so", OSError)):
+        if error is OSError:
+            bad.write_text("no library")
+        b.LIB_PATH = bad
+        call = b.w4a16_gemm
+        for f in (call, b.w8a16_gemm_dp):
+            try:
+                f(0, 0, 0, 0, 0, 1, 1024, 1024, 128, 0)
+            except error:
+                continue
+            raise SystemExit(f"{bad}: called")
+b.LIB_PATH = good
+try:
+    call(0, 0, 0, 0, 0, 1, 1024, 1024, 128, 0, 0)   # the stand-in looks again
+except b.W4A16Error as e:
+    assert e.code == b.ERR_NULL
+else:
+    raise SystemExit("null pointers were taken")
+assert b.w4a16_gemm is b.__dict__["w4a16_gemm"] and type(b.w4a16_gemm).__name__ == "builtin_function_or_method"
+assert pickle.loads(pickle.dumps(b.w4a16_gemm)) is b.w4a16_gemm
+try:
+    b.w4a16_gemmm
+except AttributeError:
+    print("fine")
+""")
+    assert r.stdout.strip().endswith("fine"), r.stdout + r.stderr
