@@ -12,6 +12,7 @@ There is no fallback: if the library has not been built, loading raises.
 from __future__ import annotations
 
 import ctypes
+import operator
 import pathlib
 
 _HERE = pathlib.Path(__file__).resolve().parent
@@ -151,6 +152,18 @@ def __getattr__(name):
 
 def __dir__():
     return sorted({*globals(), *_GEMM_CALLS})
+
+
+def _int(o, position: int) -> int:
+    """An integer argument that is no int: what ctypes makes of it as a c_int."""
+    if isinstance(o, ctypes.c_int):
+        return o.value
+    try:
+        return operator.index(o)
+    except Exception:
+        if hasattr(o, "_as_parameter_"):
+            return _int(o._as_parameter_, position)
+    raise ctypes.ArgumentError(f"argument {position}: TypeError: wrong type")
 
 
 def _p(t):

@@ -6,12 +6,17 @@
 // where the C entry point called in a loop gives 4.1 us), so the host set the pace.  Here a call reads
 // the tensors' addresses and the stream from torch's own C++ objects and goes straight into the
 // library; the argument rules (names, defaults, tensors or raw addresses, stream None = the current
-// stream) are those of the functions' signatures below.
+// stream) are those of the functions' signatures below, and of `_p`, `_stream` and ctypes' c_int for what
+// is no plain tensor, address or integer: such arguments take the slow way through their own methods.
 #include <Python.h>
 
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <c10/hip/HIPStream.h>
+
+#include <ATen/PythonTorchFunctionTLS.h>
+
+#include <pthread.h>
 
 #include "../../include/w4a16.h"
 
@@ -33,51 +38,82 @@ struct Values {
     void* stream;
 };
 
-// The address a pointer argument names: a tensor's data, a raw address, None, or anything with data_ptr().
-bool to_pointer(PyObject* o, void** out)
+// The address of an int (its low 64 bits, as a void* argument of ctypes takes it) or of None.
+bool to_address(PyObject* o, void** out)
 {
-    if (THPVariable_Check(o)) {
-        *out = THPVariable_Unpack(o).data_ptr();
-        return true;
-    }
     if (o == Py_None) {
         *out = nullptr;
         return true;
     }
-    if (PyLong_Check(o)) {
-        *out = PyLong_AsVoidPtr(o);
-        return *out || !PyErr_Occurred();
+    if (!PyLong_Check(o)) {
+        PyErr_SetString(PyExc_TypeError, "cannot be converted to pointer");
+        return false;
     }
-    PyObject* address = PyObject_CallMethod(o, "data_ptr", nullptr);
-    if (!address) return false;
-    *out = PyLong_AsVoidPtr(address);
-    Py_DECREF(address);
-    return *out || !PyErr_Occurred();
+    const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+    if (v == ~0ull && PyErr_Occurred()) return false;
+    *out = (void*)(uintptr_t)v;
+    return true;
 }
 
-bool to_int(PyObject* o, int* out)
+// The address a pointer argument names: a tensor's data, a raw address, None, or what data_ptr() says: also of a
+// tensor's subclass, which may have its own, and while a mode looks on at the calls of tensors' methods.
+bool to_pointer(PyObject* o, void** out)
 {
-    const unsigned long v = PyLong_AsUnsignedLongMask(o);
-    if (v == (unsigned long)-1 && PyErr_Occurred()) return false;
+    if (THPVariable_CheckExact(o) && !at::impl::torch_function_mode_enabled()) {
+        *out = THPVariable_Unpack(o).data_ptr();
+        return true;
+    }
+    if (o == Py_None || PyLong_Check(o)) return to_address(o, out);
+    PyObject* address = PyObject_CallMethod(o, "data_ptr", nullptr);
+    if (!address) return false;
+    const bool ok = to_address(address, out);
+    Py_DECREF(address);
+    return ok;
+}
+
+bool to_int(PyObject* o, int position, int* out)
+{
+    unsigned long v = PyLong_AsUnsignedLongMask(o);
+    if (v == (unsigned long)-1 && PyErr_Occurred()) {
+        PyErr_Clear();
+        PyObject* binding = PyImport_ImportModule("paper_2402_00025_amd.binding");
+        if (!binding) return false;
+        PyObject* i = PyObject_CallMethod(binding, "_int", "Oi", o, position);
+        Py_DECREF(binding);
+        if (!i) return false;
+        v = PyLong_AsUnsignedLongMask(i);
+        Py_DECREF(i);
+        if (v == (unsigned long)-1 && PyErr_Occurred()) return false;
+    }
     *out = (int)v;
     return true;
 }
 
+// Has torch set the GPU up in this process?  It does so when it is first asked for a stream, and refuses in a child
+// forked from a process that has used the GPU.
+bool torch_ready = false;
+
 bool to_stream(PyObject* o, void** out)
 {
     if (!o || o == Py_None) {
+        if (!torch_ready) {
+            PyObject* cuda = PyImport_ImportModule("torch.cuda");
+            if (!cuda) return false;
+            PyObject* current = PyObject_CallMethod(cuda, "current_stream", nullptr);
+            Py_DECREF(cuda);
+            if (!current) return false;
+            Py_DECREF(current);
+            torch_ready = true;
+        }
         *out = (void*)c10::hip::getCurrentHIPStream().stream();
         return true;
     }
-    if (PyLong_Check(o)) {
-        *out = PyLong_AsVoidPtr(o);
-        return *out || !PyErr_Occurred();
-    }
+    if (PyLong_Check(o)) return to_address(o, out);
     PyObject* handle = PyObject_GetAttrString(o, "cuda_stream");
     if (!handle) return false;
-    *out = PyLong_AsVoidPtr(handle);
+    const bool ok = to_address(handle, out);
     Py_DECREF(handle);
-    return *out || !PyErr_Occurred();
+    return ok;
 }
 
 bool parse(const Entry& e, PyObject* const* args, Py_ssize_t nargs, PyObject* kwnames, Values* v)
@@ -111,11 +147,12 @@ bool parse(const Entry& e, PyObject* const* args, Py_ssize_t nargs, PyObject* kw
         }
     for (int i = 0; i < e.ptrs; ++i)
         if (!to_pointer(slot[i], &v->p[i])) return false;
+    if (!to_stream(slot[total - 1], &v->stream)) return false;
     for (int i = 0; i < e.ints; ++i) {
         v->i[i] = 0;
-        if (slot[e.ptrs + i] && !to_int(slot[e.ptrs + i], &v->i[i])) return false;
+        if (slot[e.ptrs + i] && !to_int(slot[e.ptrs + i], e.ptrs + i + 1, &v->i[i])) return false;
     }
-    return to_stream(slot[total - 1], &v->stream);
+    return true;
 }
 
 // None, or the exception that binding._check raises for a negative return code.
@@ -215,4 +252,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", "The GEMM entry points of 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__call(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__call(void)
+{
+    pthread_atfork(nullptr, nullptr, [] { torch_ready = false; });
+    return PyModule_Create(&module);
+}

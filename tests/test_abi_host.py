@@ -469,3 +469,110 @@ except AttributeError:
     print("fine")
 """)
     assert r.stdout.strip().endswith("fine"), r.stdout + r.stderr
+
+
+class _Index:
+    def __init__(self, v):
+        self.v = v
+
+    def __index__(self):
+        return self.v
+
+
+class _AsParameter:
+    def __init__(self, v):
+        self._as_parameter_ = v
+
+
+class _Address:
+    def __init__(self, v):
+        self.data_ptr = lambda: v
+        self.cuda_stream = v
+
+
+# Every call below is refused for its shape (m = 0), its null pointer or an argument's type, before any HIP call.
+_HERE = 4096
+
+
+def _outcome(call, *args, **kwargs):
+    try:
+        call(*args, **kwargs)
+    except b.W4A16Error as e:
+        return e.code
+    except Exception as e:
+        return type(e)
+    return b.OK
+
+
+@pytest.mark.parametrize("value,outcome", [
+    (0, b.ERR_SHAPE), (False, b.ERR_SHAPE), (_Index(0), b.ERR_SHAPE), (1 << 32, b.ERR_SHAPE), (-1, b.ERR_SHAPE),
+    (1 << 70, b.ERR_SHAPE), (ctypes.c_int(0), b.ERR_SHAPE), (_AsParameter(0), b.ERR_SHAPE),
+    (_AsParameter(ctypes.c_int(0)), b.ERR_SHAPE), (_AsParameter(_AsParameter(_Index(0))), b.ERR_SHAPE),
+    (ctypes.c_long(0), ctypes.ArgumentError), (0.0, ctypes.ArgumentError), ("0", ctypes.ArgumentError),
+    (None, ctypes.ArgumentError), (_AsParameter("0"), ctypes.ArgumentError)])
+def test_gemm_call_integers(value, outcome):
+    """The GEMM calls take for an integer what ctypes takes for a c_int."""
+    assert _outcome(b.w4a16_gemm, *[_HERE] * 5, value, 1024, 1024, 128, 0, 0) == outcome
+    if outcome is ctypes.ArgumentError:
+        with pytest.raises(ctypes.ArgumentError, match="argument 10"):
+            b.w8a16_gemm(*[_HERE] * 5, 0, 1024, 1024, 128, value, stream=0)
+
+
+def test_gemm_call_addresses():
+    import numpy as np
+    import torch
+
+    class Elsewhere(torch.Tensor):
+        def data_ptr(self):
+            return 4100
+
+    def with_a(a, m=0):
+        return _outcome(b.w4a16_gemm, a, *[_HERE] * 4, m, 1024, 1024, 128, 0, 0)
+
+    storage = torch.zeros(64)
+    for a in (_HERE, True, -4096, (1 << 64) - 4096, (1 << 70) + 4096, _Address(_HERE), _Address((1 << 70) + 4096), storage,
+              torch.nn.Parameter(storage)):
+        assert with_a(a) == b.ERR_SHAPE, a
+    for a in (None, 0, _Address(None), torch.zeros(4, device="meta")):
+        assert with_a(a) == b.ERR_NULL, a
+    for a in (np.int64(_HERE), 1.0, "x", ctypes.c_void_p(_HERE)):
+        assert with_a(a) is AttributeError, a
+    for a in (_Address(4096.0), _Address(np.int64(_HERE)), _Address(_Index(_HERE))):
+        assert with_a(a) is TypeError, a
+    assert with_a(torch.zeros(4, 4).to_sparse()) is RuntimeError
+    assert with_a(storage.as_subclass(Elsewhere), m=1) == b.ERR_UNSUPPORTED      # its own, misaligned data_ptr
+
+    class Watching(torch.overrides.TorchFunctionMode):
+        seen = []
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.seen.append(func)
+            return func(*args, **(kwargs or {}))
+
+    with Watching() as mode:
+        assert with_a(storage) == b.ERR_SHAPE
+    assert torch.Tensor.data_ptr in mode.seen
+    # streams: an address, an object with one, None for torch's current stream
+    for st, outcome in ((0, b.ERR_SHAPE), (-1, b.ERR_SHAPE), (1 << 70, b.ERR_SHAPE), (_Address(5), b.ERR_SHAPE),
+                        (_Address(None), b.ERR_SHAPE), (1.0, AttributeError), (_Address(1.5), TypeError)):
+        assert _outcome(b.w4a16_gemm_dp, *[_HERE] * 5, 0, 1024, 1024, 128, st) == outcome, st
+    if not torch.cuda.is_available():
+        with pytest.raises(Exception) as torchs:
+            torch.cuda.current_stream()
+        with pytest.raises(type(torchs.value), match=re.escape(str(torchs.value))):
+            b.w4a16_gemm(*[_HERE] * 5, 0, 1024, 1024, 128, 0)
+
+
+def test_gemm_call_argument_lists():
+    p, sizes = [_HERE] * 5, (0, 1024, 1024, 128)
+    assert _outcome(b.w4a16_gemm, *p[:4], C=_HERE, m=0, n=1024, k=1024, group_size=128, split_k=0, stream=0) == b.ERR_SHAPE
+    for call in (b.w8a16_gemm, b.w3a16_gemm, b.w2a16_gemm):      # split_k has a default
+        assert _outcome(call, *p, *sizes, stream=0) == b.ERR_SHAPE
+    assert _outcome(b.w4a16_gemm_actorder, *p, *p[:2], *sizes, stream=0) == b.ERR_SHAPE
+    for call in (b.w4a16_gemm, b.w4a16_gemm_static):             # here it has none
+        assert _outcome(call, *p, *sizes, stream=0) is TypeError
+    assert _outcome(b.w4a16_gemm, *p, *sizes, 0, 0, 0) is TypeError                # one too many
+    assert _outcome(b.w4a16_gemm, *p, *sizes, 0, 0, A=_HERE) is TypeError          # twice
+    assert _outcome(b.w4a16_gemm, *p, *sizes, 0, 0, a=_HERE) is TypeError          # unknown
+    assert _outcome(b.w4a16_gemm_dp, *p, *sizes, split_k=0, stream=0) is TypeError
+    assert _outcome(b.w4a16_gemm) is TypeError
