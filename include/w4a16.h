@@ -51,7 +51,8 @@
  * w4a16_release_scratch: a buffer that is outgrown stays alive, so a HIP graph captured earlier
  * keeps working.  A call that would have to allocate while its stream is being captured returns
  * W4A16_ERR_STATE instead (the many-row kernel then shares no tile between workgroups and needs
- * none).  Split-k calls that overlap in time on one device share the library's
+ * none, as it does where there is no memory for its sums; that is asked for once, and again by
+ * w4a16_reserve_scratch or after w4a16_release_scratch).  Split-k calls that overlap in time on one device share the library's
  * buffers and must not be issued on different streams; a caller with several streams gives each
  * its own memory with w4a16_set_workspace, and calls on different streams are then independent.
  *
@@ -320,7 +321,8 @@ int w4a16_set_workspace(void* workspace, long long bytes, int n_max, void* strea
 
 /*
  * Allocate, now, everything the library's own scratch can need for calls with up to n_max columns
- * (about 164 MiB at n_max = 16384), so that no later call allocates, e.g. before capturing graphs.
+ * (about 164 MiB at n_max = 16384, 128 of them for the many-row kernel), so that no later call allocates, e.g. before
+ * capturing graphs.  W4A16_ERR_HIP where memory for any of it is missing (calls go on as without the reservation).
  */
 int w4a16_reserve_scratch(int n_max);
 

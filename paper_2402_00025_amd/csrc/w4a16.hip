@@ -1360,6 +1360,7 @@ struct DeviceScratch {
     Buffer phase_err;  // the error count [1]
     // many-row kernel: two tiles' sums per worker (no invariant), and words, all zero whenever no call is running
     Buffer rows_partials, rows_words;
+    bool rows_denied = false;  // there was no memory for them
     uint32_t* err_host = nullptr;  // pinned host word that a wait which ran out sets to 1
     void* retired[64] = {};        // outgrown buffers, freed by w4a16_release_scratch
     int retired_count = 0;
@@ -1381,6 +1382,7 @@ struct ScratchView {
 struct ScratchNeed {
     size_t sums_floats = 0, partial_floats = 0, fixed_words = 0, ticket_count = 0;
     bool rows = false;    // the many-row kernel's partial sums and words
+    bool reserve = false; // these as well, or an error: no later call may allocate them
     int phase_split = 0;  // 0, or the split_k whose flags and counts the call needs
     int n = 0;            // columns of the call (the phase words cover tile origins n0 / 16)
 };
@@ -2090,15 +2092,16 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
     if (rc == W4A16_OK) rc = grow(s, s.partials, need.partial_floats * sizeof(float), 0, stream, &grew);
     if (rc == W4A16_OK) rc = grow(s, s.fixed, fixed_words * sizeof(uint64_t), (size_t)16 * 16384 * sizeof(uint64_t), stream, &grew);
     if (rc == W4A16_OK) rc = grow(s, s.tickets, need.ticket_count * sizeof(uint32_t), 4096 * sizeof(uint32_t), stream, &grew);
-    if (rc == W4A16_OK && need.rows && !s.rows_partials.ptr) {
+    if (rc == W4A16_OK && need.rows && !s.rows_partials.ptr && (need.reserve || !s.rows_denied)) {
         // (128 MiB, once; a call that finds none under capture, or no memory for it, does without)
         hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
         if (!W4A16_HIP(hipStreamIsCapturing(stream, &capturing))) return W4A16_ERR_HIP;
-        if (capturing == hipStreamCaptureStatusNone) {
+        if (need.reserve || capturing == hipStreamCaptureStatusNone) {
             rc = grow(s, s.rows_words, 2 * kRowsMaxWorkers * sizeof(uint32_t), 0, stream, &grew);
             if (rc == W4A16_OK) rc = grow(s, s.rows_partials, kRowsPartialBytes, 0, stream, &grew);
-            if (rc != W4A16_OK && !s.rows_partials.ptr) {
+            if (rc != W4A16_OK && !need.reserve) {
                 (void)hipGetLastError();  // not the next launch's
+                s.rows_denied = true;     // until it is reserved or released: not one attempt per call
                 rc = W4A16_OK;
             }
         }
@@ -3152,6 +3155,7 @@ int w4a16_reserve_scratch(int n_max)
         need.n = n_max;
         need.fixed_words = (size_t)16 * n_max;
         need.rows = true;
+        need.reserve = true;
         need.phase_split = (size_t)n_max <= 16 * (size_t)w4a16::kPhaseOrigins ? split_k : 0;
         w4a16::ScratchView view;
         const int rc = w4a16::resolve_scratch(w4a16::kScratchLibrary, nullptr, need, &view);

@@ -1,0 +1,47 @@
+/* A stand-in for the HIP calls of libw4a16.so's host side, loaded ahead of the runtime (LD_PRELOAD) in a process that
+ * has no GPU: device memory is host memory, nothing is launched, and every launch is noted. */
+#include <stdint.h>
+#include <stdlib.h>
+
+typedef struct { uint32_t x, y, z; } dim3;
+
+size_t stand_in_largest = (size_t)1 << 40; /* the largest allocation that succeeds */
+int stand_in_capturing = 0, stand_in_mallocs = 0, stand_in_launches = 0;
+uint32_t stand_in_grid[3], stand_in_block[3];
+
+int hipGetDevice(int* dev) { return *dev = 0; }
+int hipDeviceSynchronize(void) { return 0; }
+int hipGetLastError(void) { return 0; }
+int hipStreamIsCapturing(void* stream, int* status) { (void)stream; *status = stand_in_capturing; return 0; }
+int hipMalloc(void** p, size_t bytes)
+{
+    ++stand_in_mallocs;
+    if (bytes > stand_in_largest) return 2; /* out of memory */
+    *p = calloc(1, bytes);
+    return 0;
+}
+int hipFree(void* p) { free(p); return 0; }
+int hipMemset(void* p, int value, size_t bytes) { (void)p; (void)value; (void)bytes; return 0; } /* calloc cleared it */
+int hipHostMalloc(void** p, size_t bytes, unsigned flags) { (void)flags; *p = calloc(1, bytes); return 0; }
+int hipHostFree(void* p) { free(p); return 0; }
+int hipFuncSetAttribute(const void* f, int attr, int value) { (void)f; (void)attr; (void)value; return 0; }
+int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, void* stream)
+{
+    (void)lds; (void)stream;
+    stand_in_grid[0] = grid.x; stand_in_grid[1] = grid.y; stand_in_grid[2] = grid.z;
+    stand_in_block[0] = block.x; stand_in_block[1] = block.y; stand_in_block[2] = block.z;
+    return 0;
+}
+int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** stream)
+{
+    grid->x = grid->y = grid->z = block->x = block->y = block->z = 1;
+    *lds = 0;
+    *stream = 0;
+    return 0;
+}
+int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, void* stream)
+{
+    (void)f; (void)grid; (void)block; (void)args; (void)lds; (void)stream;
+    ++stand_in_launches;
+    return 0;
+}

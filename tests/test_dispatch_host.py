@@ -1,0 +1,107 @@
+"""The library's host side without a GPU, on a stand-in for the HIP calls (hip_stand_in.c): which launches a call of many
+rows makes, with and without scratch, under capture, beside a bound workspace, and what it refuses."""
+import os
+import pathlib
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = pathlib.Path(__file__).resolve().parent.parent
+
+PRELUDE = """
+import ctypes, sys
+H = ctypes.CDLL(sys.argv[1])
+L = ctypes.CDLL(sys.argv[2])
+L.w4a16_workspace_bytes.restype = ctypes.c_longlong
+vp, OK, UNSUPPORTED, HIP, LIMIT = ctypes.c_void_p, 0, -4, -5, -7
+PTR = vp(4096)          # never dereferenced: nothing is launched
+largest = ctypes.c_size_t.in_dll(H, "stand_in_largest")
+capturing, mallocs, launches = (ctypes.c_int.in_dll(H, "stand_in_" + x) for x in ("capturing", "mallocs", "launches"))
+grid, block = ((ctypes.c_uint32 * 3).in_dll(H, "stand_in_" + x) for x in ("grid", "block"))
+
+def gemm(m, n, k, g, bits=4, stream=0):
+    before = launches.value
+    rc = getattr(L, f"w{bits}a16_gemm")(PTR, PTR, PTR, PTR, PTR, m, n, k, g, 0, vp(stream))
+    return rc, launches.value - before, tuple(grid)
+
+def plan(m, n, k, g, bits=4, may_share=1):
+    r, w, s = (ctypes.c_int() for _ in range(3))
+    assert L.w4a16_plan_many_rows(bits, m, n, k, g, may_share, *map(ctypes.byref, (r, w, s))) == OK
+    return r.value, w.value, s.value
+"""
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    lib = tmp_path_factory.mktemp("stand_in") / "libstand_in.so"
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(lib), str(ROOT / "tests" / "hip_stand_in.c")], check=True)
+
+    def run(code):
+        preload = " ".join(filter(None, (str(lib), os.environ.get("LD_PRELOAD"))))
+        r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(code) + "\nprint('fine')", str(lib),
+                            str(ROOT / "paper_2402_00025_amd" / "libw4a16.so")],
+                           env={**os.environ, "LD_PRELOAD": preload}, capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0 and r.stdout.strip().endswith("fine"), r.stdout + r.stderr
+    return run
+
+
+def test_reserve_reports_memory_it_could_not_get(stand_in):
+    """w4a16_reserve_scratch promises that no later call allocates: without memory for the many-row kernel's sums it
+    fails, and a call goes on without sharing tiles, asking for the memory once and not at every call."""
+    stand_in("""
+    shape = (333, 11008, 4096, 128)
+    shared, whole = plan(*shape), plan(*shape, may_share=0)
+    assert shared[2] == 1 and whole[0] and whole[2] == 0 and shared[1] != whole[1]
+    largest.value = 100 << 20
+    assert L.w4a16_reserve_scratch(4096) == HIP
+    assert L.w4a16_release_scratch() == OK
+    asked = []
+    for _ in range(3):
+        before = mallocs.value
+        assert gemm(*shape) == (OK, 1, (whole[1], 1, 1))
+        asked.append(mallocs.value - before)
+    assert asked[0] > 0 and asked[1:] == [0, 0], asked
+    largest.value = 1 << 40
+    assert gemm(*shape) == (OK, 1, (whole[1], 1, 1))
+    assert L.w4a16_reserve_scratch(4096) == OK      # asked for by name: tried again
+    before = mallocs.value
+    assert gemm(*shape) == (OK, 1, (shared[1], 1, 1))
+    for m, n, k, g in (shape, (16, 4096, 4096, 128), (4, 4096, 4096, 128), (64, 8192, 8192, 128)):
+        assert gemm(m, n, min(k, 4096), g)[0] == OK
+    assert mallocs.value == before
+    """)
+
+
+def test_route_of_many_rows(stand_in):
+    """Under capture without scratch, with scratch, and on a stream with a bound workspace."""
+    stand_in("""
+    shape = (333, 11008, 4096, 128)
+    shared, whole = plan(*shape), plan(*shape, may_share=0)
+    capturing.value = 1
+    assert gemm(*shape) == (OK, 1, (whole[1], 1, 1)) and mallocs.value == 0
+    capturing.value = 0
+    assert gemm(*shape) == (OK, 1, (shared[1], 1, 1))
+    capturing.value = 1
+    assert gemm(*shape) == (OK, 1, (shared[1], 1, 1))
+    capturing.value = 0
+    space = (ctypes.c_char * (L.w4a16_workspace_bytes(16384) + 256))()
+    base = (ctypes.addressof(space) + 255) // 256 * 256
+    assert L.w4a16_set_workspace(vp(base), ctypes.c_longlong(L.w4a16_workspace_bytes(16384)), 16384, vp(64)) == OK
+    assert gemm(*shape, stream=64) == (OK, 1, (whole[1], 1, 1))
+    assert gemm(333, 16392, 4096, 128, stream=64)[0] == LIMIT       # as the launches of 64 rows would
+    assert gemm(*shape) == (OK, 1, (shared[1], 1, 1))
+    assert L.w4a16_release_scratch() == OK
+    """)
+
+
+def test_many_rows_too_wide_for_the_kernel(stand_in):
+    """Beyond 2^23 columns: the launches of 64 rows, which refuse 2^24."""
+    stand_in("""
+    assert gemm(128, 1 << 23, 128, 128)[1] == 1
+    assert gemm(128, (1 << 23) + 8, 128, 128)[:2] == (OK, 2)
+    assert gemm(100, 16776960, 128, 128)[:2] == (OK, 2)
+    assert gemm(128, 1 << 24, 128, 128)[:2] == (UNSUPPORTED, 0)
+    assert gemm(33, (1 << 23) + 8, 128, 32)[:2] == (OK, 3)
+    """)
