@@ -2506,6 +2506,40 @@ static double plan_rows(int m, int n, int k, int ipg, int bits, bool share_ok, R
     return best;
 }
 
+// Both ways again, per field width, to keep out of the many-row kernel what it would slow down: the launches of 64 or 16
+// rows, and the many-row launch that plan_rows chose.  Fitted to 38,700 random shapes around the crossing (17 to 100
+// rows with fine groups, 65 to 400 otherwise, every width and group size, both ways timed; spread 8 and 7 %), checked on
+// 38,500 others: of 26,400 calls that the estimates above alone send to the kernel 201 were more than 2 % slower there
+// than before (107 more than 5 %, at worst 21 %); with these as well 79 (30, 14 %), and 115 that were more than 2 %
+// faster there (of 26,000) stay out.
+static double fitted_launches_us(int m, double mfields, int group_size, int bits)
+{
+    const int width = bits == 4 ? 0 : bits == 8 ? 1 : bits == 3 ? 2 : 3;
+    if (group_size < 128) {
+        constexpr double per_field[2][4] = {{0.126, 0.193, 0.141, 0.106}, {0.1445, 0.21, 0.157, 0.128}};  // groups of 64, 32
+        return ((m + 15) / 16) * (3.9 + per_field[group_size == 32][width] * mfields);
+    }
+    constexpr double rest_per_field[4] = {0.055, 0.13, 0.077, 0.067};
+    const int full = m / 64, rest = m % 64;
+    return full * (9.4 + 0.21 * mfields) + (rest ? 3.2 + 0.12 * rest + (rest_per_field[width] + 0.0019 * rest) * mfields : 0.0);
+}
+
+static double fitted_rows_us(const RowsPlan& plan, int m, int n, int k, int ipg, int bits)
+{
+    const long long chunks = (k + kRowsChunkK - 1) / kRowsChunkK;
+    const long long tiles = (long long)((m + 16 * plan.row_blocks - 1) / (16 * plan.row_blocks)) * ((n + kRowsTileCols - 1) / kRowsTileCols);
+    const long long each = plan.whole ? (tiles + plan.workers - 1) / plan.workers * chunks : (tiles * chunks + plan.workers - 1) / plan.workers;
+    const bool tall = plan.row_blocks == 8, pairs = plan.workers > 256;
+    const int groups = ipg == 4 ? 0 : ipg == 2 ? 1 : 2;
+    constexpr double single[3] = {1.4, 1.58, 1.81}, paired[3] = {2.05, 2.2, 2.72};
+    const double chunk = tall ? (pairs ? 3.2 : 1.86) * (bits == 8 ? 1.12 : bits == 3 ? 1.06 : 1.0)
+                              : (pairs ? paired : single)[groups] * (bits == 8 ? 1.19 : bits == 3 ? 1.06 : 1.0);
+    if (plan.whole) return 4.4 + (double)each * chunk;
+    const double around = tall ? (pairs ? 14.0 : 10.8) : !pairs ? 5.9 : ipg == 4 ? 9.0 : 11.0;
+    const double part = tall ? (pairs ? 2.6 : 1.4) : pairs ? 1.1 : 0.85;
+    return around + (double)each * chunk + (double)((chunks + each - 1) / each - 1) * part;
+}
+
 // The many-row launch of a call that leaves every choice to the library, or row_blocks == 0 where the other launches
 // are taken.  Up to 64 rows, one launch of the streaming kernel stays the better one: 20.8 us against 27.2 at m = 64,
 // n = k = 8192, 16.1 against 27.1 at m = 48; level (within 5 %) only at m > 48 on matrices of 16384 x 8192 and more or
@@ -2525,8 +2559,10 @@ static int plan_many_rows(int m, int n, int k, int group_size, int bits, bool ma
     if (rc != W4A16_OK) return rc;
     const bool sharing = others.split_k > 1 && others.reduce != W4A16_REDUCE_ATOMIC_PK_F16;
     RowsPlan best{};
-    if (plan_rows(m, n, k, fine_groups ? group_size / 32 : 4, bits, sharing && may_share, &best) <
-        row_tile_us(m, (double)n * k * 1e-6, fine_groups))
+    const int ipg = fine_groups ? group_size / 32 : 4;
+    const double mfields = (double)n * k * 1e-6;
+    if (plan_rows(m, n, k, ipg, bits, sharing && may_share, &best) < row_tile_us(m, mfields, fine_groups) &&
+        fitted_rows_us(best, m, n, k, ipg, bits) < 0.94 * fitted_launches_us(m, mfields, group_size, bits))
         *plan = best;
     if (share_ok) *share_ok = sharing;
     return W4A16_OK;

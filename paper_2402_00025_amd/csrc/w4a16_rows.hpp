@@ -131,8 +131,9 @@ __device__ __forceinline__ half8_t nat_unpack(uint32_t w0, uint32_t w1, const La
 }
 
 // 16 bytes per lane from memory straight into LDS: lane l's go to lds + 16 l.  (A transfer into LDS reads m0, and a
-// scalar write of m0 needs one wait state before it; the compiler adds none inside inline asm.  Nothing else in this
-// kernel uses m0.)
+// scalar write of m0 needs one wait state before it; the compiler adds none inside inline asm.  m0 is a register that
+// the compiler does not allocate: it takes no note of it as a clobber but for a warning, and writes it itself right
+// before an instruction that reads it, of which these kernels have none.)
 __device__ __forceinline__ void load_to_lds(rsrc_t r, uint32_t voff, uint32_t soff, uint32_t lds)
 {
     asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(r), "s"(soff), "s"(lds)
