@@ -582,9 +582,9 @@ def test_many_row_route_keeps_out_what_it_would_slow_down():
     """Shapes that an earlier rule sent to the many-row kernel though it took 12 to 31 % longer there, and some that
     belong there (16 to 60 % of the time)."""
     for bits, m, n, k, g in ((2, 17, 22944, 3264, 64), (2, 21, 15776, 5888, 64), (4, 18, 27392, 2304, 64),
-                             (4, 24, 23680, 2304, 64), (2, 78, 7968, 26624, 256), (4, 77, 7864, 22784, 256),
+                             (2, 27, 24576, 4096, 64), (2, 78, 7968, 26624, 256), (4, 77, 7864, 22784, 256),
                              (4, 80, 9984, 15360, 128), (8, 82, 6016, 24832, 128), (8, 97, 3760, 25728, 128),
-                             (8, 112, 4736, 27520, 128)):
+                             (2, 73, 10624, 12288, 128)):
         assert b.w4a16_plan_many_rows(bits, m, n, k, g) is None, (bits, m, n, k, g)
     for bits, m, n, k, g in ((4, 333, 11008, 4096, 128), (4, 986, 2392, 5312, 64), (2, 202, 8832, 3712, 32),
                              (3, 375, 1920, 2560, 256), (8, 256, 4408, 7936, 256), (4, 128, 3072, 21504, 32)):
