@@ -1346,6 +1346,7 @@ def test_extreme_shapes(oracle, m, n, k, g, split_k):
     (9, 72, 1024, 256, 2),
     (40, 264, 1024, 128, 0),      # more than 16 rows
     (16, 4096, 4096, 128, 0),     # the headline shape
+    (130, 1032, 2048, 128, 0),    # the many-row kernel
 ])
 def test_activation_ordering(oracle, m, n, k, g, split_k):
     import torch
@@ -1451,58 +1452,119 @@ def test_cfg5_split_sweep(oracle):
 
 
 # Many rows, the library's own launch: the kernel of 64- and 128-row tiles whose chunks of 128 k persistent
-# workgroups share (each case twice: the flags of a hand-over are reset by the call that used them).
+# workgroups share (each case twice: the words of a hand-over are reset by the call that used them).
 MANY_ROWS = [
-    # m, n, k, g
-    (200, 520, 2048, 128),    # ragged rows and columns, tiles in several parts
-    (333, 1032, 128, 128),    # one chunk: nothing to share
-    (129, 264, 4096, 256),    # one row in the last 128-row tile; a group of two chunks
-    (1030, 288, 384, 128),    # many row tiles
-    (40, 288, 1056, 32),      # fine groups, k not a multiple of a chunk
-    (100, 40, 2080, 32),      # fewer columns than one strip
-    (97, 520, 1088, 64),      # half a chunk at the end
-    (65, 288, 1056, 32),      # one row in the last tile, a quarter of a chunk at the end
-    (600, 2048, 2048, 64),
-    (700, 4096, 1152, 128),   # more tiles than workgroups that share them evenly
+    # m, n, k, g, rows of a tile, shared
+    (200, 520, 2048, 128, 64, True),     # ragged rows and columns, tiles in several parts
+    (333, 1032, 128, 128, 64, False),    # one chunk: nothing to share
+    (257, 2056, 4096, 256, 64, True),    # one row in the last tile; a group of two chunks
+    (1030, 288, 384, 128, 64, False),    # many row tiles
+    (50, 2072, 1056, 32, 64, True),      # fine groups, k not a multiple of a chunk, fewer rows than a tile
+    (100, 40, 2080, 32, 64, True),       # fewer columns than one strip
+    (97, 520, 1088, 64, 64, True),       # half a chunk at the end
+    (65, 288, 1056, 32, 64, True),       # one row in the last tile, a quarter of a chunk at the end
+    (600, 2048, 2048, 64, 64, True),
+    (700, 4096, 1152, 128, 64, False),   # 176 tiles, a workgroup each
+    (2875, 1312, 128, 128, 128, False),  # tiles of 128 rows, 59 in the last one; a strip of 32 columns
+    (2805, 1408, 1152, 128, 128, True),
+    (2668, 1568, 1024, 256, 128, True),  # a group of two chunks
+    (2970, 6272, 512, 128, 128, True),   # more tiles than workgroups: 512 for 4 and 2 bits, 256 for 8 and 3
+    (2956, 8320, 128, 128, 128, False),  # several whole tiles each
 ]
+MANY_ROWS_GEMM = {4: b.w4a16_gemm, 8: b.w8a16_gemm, 3: b.w3a16_gemm, 2: b.w2a16_gemm}
 
 
 @pytest.mark.parametrize("bits", [4, 8, 3, 2])
-@pytest.mark.parametrize("m,n,k,g", MANY_ROWS)
-def test_many_rows(oracle, bits, m, n, k, g):
+@pytest.mark.parametrize("m,n,k,g,tile_rows,shared", MANY_ROWS)
+def test_many_rows(oracle, bits, m, n, k, g, tile_rows, shared):
     n = n // 32 * 32 if bits in (2, 3) else n
+    plan = b.w4a16_plan_many_rows(bits, m, n, k, g)
+    assert plan and plan["tile_rows"] == tile_rows and plan["shared"] == shared, plan
     seed = 4000 + m + n
     A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
     rows = np.unique(np.concatenate([np.arange(0, m, max(1, m // 24)), [63 % m, 64 % m, 127 % m, 128 % m, m - 1]]))
     Cref, _ = oracle.gemm_3bit(A[rows], qw, s, qz, g) if bits == 3 else oracle.gemm_bits(A[rows], qw, s, qz, g, bits)
     p = DeviceProblem(A, qw, s, qz, g)
-    call = {4: b.w4a16_gemm, 8: b.w8a16_gemm, 3: b.w3a16_gemm, 2: b.w2a16_gemm}[bits]
+    first = None
     for rep in range(2):
         p.C.fill_(float("nan"))
-        call(*p.args(), 0)
+        MANY_ROWS_GEMM[bits](*p.args(), 0)
         got = p.result().copy()
         assert np.isfinite(got.astype(np.float32)).all()
         assert_parity(got[rows], Cref, f"bits={bits} m={m} n={n} k={k} g={g} call {rep}")
+        assert first is None or np.array_equal(got, first), "the sums do not depend on which part comes last"
+        first = got
     assert b.w4a16_phase_timeouts() == 0
 
 
-def test_many_rows_one_hot_bit_exact():
+@pytest.mark.parametrize("bits", [4, 8, 3, 2])
+@pytest.mark.parametrize("m,n,k,g,tile_rows", [(320, 288, 1280, 128, 64), (320, 288, 1312, 32, 64), (320, 288, 1344, 64, 64),
+                                               (2805, 1408, 1152, 128, 128)])
+def test_many_rows_one_hot_bit_exact(bits, m, n, k, g, tile_rows):
     """One non-zero term per row, swept over all k: every operand of the unpacking in the order of k lands where
     it belongs, at tile and chunk edges too."""
-    m, n, k, g = 320, 264, 1280, 128
-    rng = np.random.default_rng(11)
-    _, qw, s, qz = random_case(1, n, k, g, seed=12)
-    q = ((qw.view(np.uint32)[:, None, :] >> (4 * np.arange(8, dtype=np.uint32))[None, :, None]) & 15).reshape(k, n)
-    z = ((qz.view(np.uint32)[:, :, None] >> (4 * np.arange(8, dtype=np.uint32))[None, None, :]) & 15).reshape(k // g, n)
+    import torch
+    plan = b.w4a16_plan_many_rows(bits, m, n, k, g)
+    assert plan and plan["tile_rows"] == tile_rows, plan
+    if bits == 3:
+        _, qw, s, qz = random_case_3bit(1, n, k, g, seed=12)
+        W = np_dense_weight_3bit(qw, s, qz, g).astype(np.float16)
+    else:
+        _, qw, s, qz = random_case_bits(1, n, k, g, bits, seed=12)
+        W = np_dense_weight_bits(qw, s, qz, g, bits).astype(np.float16)
+    p = DeviceProblem(np.zeros((m, k), np.float16), qw, s, qz, g)
     for base in range(0, k, m):
+        rows = (base + np.arange(m)) % k
         A = np.zeros((m, k), np.float16)
-        A[np.arange(m), base + np.arange(m)] = 1.0
-        p = DeviceProblem(A, qw, s, qz, g)
+        A[np.arange(m), rows] = 1.0
+        p.A.copy_(torch.from_numpy(A))
+        MANY_ROWS_GEMM[bits](*p.args(), 0)
+        assert np.array_equal(p.result(), W[rows]), (bits, base)   # (zeros may differ in sign)
+
+
+def test_many_rows_under_capture_and_beside_a_workspace(oracle):
+    """A shape whose tiles are shared: captured before the scratch is there, and on a stream with a workspace of its
+    own, whole tiles; the replays and the eager calls between them give what they gave before."""
+    import torch
+    m, n, k, g = 300, 2048, 2048, 128
+    assert b.w4a16_plan_many_rows(4, m, n, k, g)["shared"]
+    assert not b.w4a16_plan_many_rows(4, m, n, k, g, may_share=False)["shared"]
+    A, qw, s, qz = random_case(m, n, k, g, seed=51)
+    Cref, _ = oracle.gemm(A[[0, 64, 299]], qw, s, qz, g)
+    p = DeviceProblem(A, qw, s, qz, g)
+    torch.cuda.synchronize()
+    b.w4a16_release_scratch()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        b.w4a16_gemm(*p.args(), 0, stream=torch.cuda.current_stream())
+    graph.replay()
+    whole = p.result().copy()
+    assert_parity(whole[[0, 64, 299]], Cref, "captured without scratch")
+    b.w4a16_gemm(*p.args(), 0)
+    shared = p.result().copy()
+    assert_parity(shared[[0, 64, 299]], Cref, "shared tiles")
+    for rep in range(3):
+        p.C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        assert np.array_equal(p.result(), whole), rep
+        p.C.fill_(float("nan"))
         b.w4a16_gemm(*p.args(), 0)
-        rows = base + np.arange(m)
-        want = ((q[rows].astype(np.float32) - z[rows // g].astype(np.float32)) * s[rows // g].astype(np.float32)).astype(np.float16)
-        got = p.result()
-        assert np.array_equal(got, want), base   # (zeros may differ in sign)
+        assert np.array_equal(p.result(), shared), rep
+    nbytes = b.w4a16_workspace_bytes(n)
+    ws = torch.zeros(nbytes // 4 + 64, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    b.w4a16_set_workspace(ws, nbytes, n, stream=stream)
+    try:
+        p.C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        b.w4a16_gemm(*p.args(), 0, stream=stream)
+        assert np.array_equal(p.result(), whole)
+    finally:
+        b.w4a16_set_workspace(None, 0, 0, stream=stream)
 
 
 def test_many_rows_unsplit_on_two_streams(oracle):
@@ -1568,8 +1630,7 @@ def test_many_rows_infinite_scale_in_the_last_group(oracle, bits, m, n, k, g):
     s = s.copy()
     s[-1, huge] = np.inf
     p = DeviceProblem(A, qw, s, qz, g)
-    call = {4: b.w4a16_gemm, 8: b.w8a16_gemm, 3: b.w3a16_gemm, 2: b.w2a16_gemm}[bits]
-    call(*p.args(), 0)
+    MANY_ROWS_GEMM[bits](*p.args(), 0)
     got = p.result().astype(np.float64)
     product = sign[:, huge]
     assert np.array_equal(got[:, huge][product != 0], (product * np.inf)[product != 0])
