@@ -27,7 +27,8 @@
  * SplitK entry points leave every choice to the library (split_k == 0) and more than one such
  * launch would be needed, it is one launch of a kernel for many rows instead, unless that takes longer: tiles
  * of 64 or 128 rows x 256 columns, their k ranges shared by persistent workgroups, the sums
- * added in fp32 in the order of k (bit-reproducible).  Ranges are shared, through scratch memory,
+ * added in fp32 in the order of k (bit-reproducible between calls that take the same launch: where a call finds no
+ * scratch for shared tiles, see below, the sums are grouped otherwise).  Ranges are shared, through scratch memory,
  * only where w4a16_plan reports a split_k above 1 for the call.  n is at most 2^23 for it.  w4a16_plan does not describe
  * it (it reports the launch per 64 or 16 rows); w4a16_plan_many_rows does.  n a multiple of 8;
  * g (group_size) one of 32, 64, 128, 256; k a multiple of g; k * n < 2^32.  A split_k requested from w4a16_gemm must cut k into equal

@@ -8,18 +8,18 @@
 // and an unpacked operand serves 8 (4) row blocks.  The activations of a chunk (128 k) come straight
 // from memory into LDS, one chunk ahead, as do the packed weights of each wave's own strip: neither
 // passes through registers, which the sums (128), the unpacked operands (64) and the products in flight
-// fill to the last ones that two waves per SIMD leave.  Their requests are spread over the unpacking: one
+// fill to the last ones that two waves per SIMD leave (none of them lies in memory).  Their requests are spread over the unpacking: one
 // 16-byte-per-lane request occupies the unit's memory pipe for 20 cycles, and four waves that issue theirs in
 // one burst stand still for it (m = 333, n = 11008, k = 4096 on whole tiles: 76 us with the burst, 59 without).
 // The scale of a group is applied in fp32 to its products, as in the other kernels.
 //
 // What bounds it: the issue of instructions.  A 16x16x32 MFMA takes 16 cycles of the matrix unit and about
 // 10 of the issue port, every other vector instruction 4; a chunk has 128 and about 340 of them per wave.
-// m = 2048, n = k = 8192: 217 us = 1270 TFLOP/s (664 us with row tiles), the matrix units 56 % busy; the clock is at
-// 1.73 GHz then, where their ceiling is 1.8 PFLOP/s.
+// m = 2048, n = k = 8192: 219-232 us by the run = 1185-1255 TFLOP/s (664 us with row tiles).  In a run of 232 us the
+// clock is at 1.79 GHz, where the matrix units' ceiling is 1.88 PFLOP/s, and they are busy 63 % of the time.
 //
 // Persistent workgroups share the chunks of all tiles evenly, whatever the shape (m = 333, n = 11008, k = 4096, 129
-// tiles: 43 us on 256 workers; 59 us with a workgroup per tile).  A tile that several workers have parts of is
+// tiles: 40.5 us on 256 workers; 59 us with a workgroup per tile).  A tile that several workers have parts of is
 // added up in fp32, in the order of k, by the worker that has its beginning.  That one waits for the other parts for
 // a bounded time; where they are late (a worker that has not started, because other work holds the GPU) it leaves its
 // own part in memory too, and whoever brings the last part adds the tile up, in the same order.  No result depends
