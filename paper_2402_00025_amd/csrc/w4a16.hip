@@ -2463,7 +2463,8 @@ struct RowsPlan {
 };
 
 // us of `n k` fields and m rows on the launches of up to 64 (group_size 128, 256) or 16 rows; fitted to square and
-// decoder-projection shapes from 2048 x 2048 to 28672 x 4096 (within 15 %).
+// decoder-projection shapes from 2048 x 2048 to 28672 x 4096 of 4-bit fields (within 15 %; on random shapes of every width it
+// says 0.70 to 1.10 of the measured time on average, so it errs on the side of these launches).
 static double row_tile_us(int m, double mfields, bool fine_groups)
 {
     if (fine_groups) return ((m + 15) / 16) * (3.8 + 0.125 * mfields);
