@@ -287,3 +287,28 @@ def test_shared_tiles_do_not_depend_on_waits(oracle, bits, m, n, k, g, tile_rows
         check(0, f"replay {rep}")
         check(1, f"waiting call behind replay {rep}")
     assert b.w4a16_phase_timeouts() == 0
+
+
+@pytest.mark.parametrize("bits,m,n,k,g", [(4, 333, 11008, 4096, 128), (8, 300, 2048, 2048, 128)])
+def test_shared_tiles_beside_other_work(bits, m, n, k, g):
+    """Workgroups of other streams' kernels hold a part of the GPU, so that those of a call start late and in any
+    order: the same bits, and no wait is counted."""
+    import torch
+    assert b.w4a16_plan_many_rows(bits, m, n, k, g)["shared"]
+    p = DeviceProblem(*random_case_bits(m, n, k, g, bits, 311), g)
+    GEMM[bits](*p.args(), 0)
+    want = p.result().copy()
+    outs = [torch.empty_like(p.C) for _ in range(12)]
+    x = torch.randn(4096, 4096, device="cuda").half()
+    y = [torch.empty_like(x) for _ in range(2)]
+    others = [torch.cuda.Stream() for _ in y]
+    torch.cuda.synchronize()
+    for out in outs:
+        for st, z in zip(others, y):
+            with torch.cuda.stream(st):
+                torch.mm(x, x, out=z)
+        GEMM[bits](p.A, p.qweight, p.scales, p.qzeros, out, m, n, k, g, 0)
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        assert np.array_equal(out.cpu().numpy(), want), i
+    assert b.w4a16_phase_timeouts() == 0
