@@ -24,8 +24,11 @@
  * 256, waves 0 or 4, reduce AUTO, ATOMIC_PK_F16 or ATOMIC_PK_F16_PHASE) take up to 64 rows per
  * launch as row tiles that share one pass over the weights; everything else, the data-parallel
  * kernel included, runs one launch per 16 rows, each streaming the weights again.  Where the
- * SplitK entry points leave every choice to the library (split_k == 0) and more than one such
- * launch would be needed, it is one launch of a kernel for many rows instead, unless that takes longer: tiles
+ * SplitK entry points leave every choice to the library (split_k == 0), 17 to 64 rows of n <= 65536 columns are one
+ * launch of a kernel for decode batches at every group size, unless the others take less time (w4a16_plan_batch reports
+ * it; w4a16_plan reports the others): 64 or 128 columns a workgroup, k split no further than by the other launches and
+ * with the same reduction and scratch (packed-fp16 adds into C that the kernel zeroes, or plain stores).  And where more than
+ * one launch would be needed, it is one launch of a kernel for many rows instead, unless that takes longer: tiles
  * of 64 or 128 rows x 256 columns, their k ranges shared by persistent workgroups, the sums
  * added in fp32 in the order of k (bit-reproducible between calls that take the same launch: where a call finds no
  * scratch for shared tiles, see below, the sums are grouped otherwise).  Ranges are shared, through scratch memory,
@@ -248,12 +251,19 @@ int w4a16_plan_bits(int bits, int m, int n, int k, int group_size, int dp, int* 
                     int* waves, int* reduce);
 /*
  * The many-row launch of a SplitK call of this field width with split_k == 0: the rows of a tile (64 or 128; 0 if the
- * call goes to the launches w4a16_plan reports instead), the workgroups, and whether these share tiles (1) or take
+ * call goes to the launches w4a16_plan reports instead; up to 64 rows w4a16_plan_batch comes first), the workgroups, and whether these share tiles (1) or take
  * whole ones (0).  may_share == 0: the launch of a call that finds no scratch for shared tiles (a stream with a bound
  * workspace; under capture before any such call).  Host only; no HIP call; the last three may be NULL.
  */
 int w4a16_plan_many_rows(int bits, int m, int n, int k, int group_size, int may_share, int* tile_rows,
                          int* workgroups, int* shared);
+
+/*
+ * The launch of the kernel for 17 to 64 rows of a SplitK call of this field width with split_k == 0: in how many parts
+ * it splits k (0 if the call goes to other launches) and the columns of a workgroup (64 or 128).  Host only; no HIP call;
+ * the last two may be NULL.
+ */
+int w4a16_plan_batch(int bits, int m, int n, int k, int group_size, int* split_k, int* tile_cols);
 
 /* Argument check alone (host only, no HIP call): what w4a16_gemm would return before launching
  * (equal shares required of a requested split_k). */

@@ -7,6 +7,7 @@
 #include "w4a16_device.hpp"
 #include "w4a16_stream.hpp"
 #include "w4a16_rows.hpp"
+#include "w4a16_batch.hpp"
 
 #include <cstdio>
 #include <cstdlib>
@@ -117,17 +118,6 @@ __device__ __forceinline__ void store_through(uint32_t* word, uint32_t value)
 // before it goes on.  On gfx9-family hardware the vector memory counter also covers stores and
 // atomics without return.  The "memory" clobber keeps the compiler from moving accesses across.
 __device__ __forceinline__ void wait_memory_ops() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// A wait of the phase protocol ran out (one lane calls this): count it, raise the sticky word the
-// host looks at before its next call, and add NaN to the first column pair of the tile, so that
-// the output cannot pass for a result.  `c_off` is a byte offset inside C.
-__device__ __forceinline__ void phase_wait_failed(uint32_t* errors, uint32_t* err_host, rsrc_t rs_c, uint32_t c_off)
-{
-    __hip_atomic_fetch_add(errors, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (err_host) __hip_atomic_store(err_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    const half2_t poison = {(_Float16)__builtin_nanf(""), (_Float16)__builtin_nanf("")};
-    __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(poison, rs_c, c_off, 0, 0);
-}
 
 // One workgroup = WAVES wavefronts that share one output tile [m, 16 V] and divide the
 // workgroup's k range between them; blockIdx = (tile, slice), dispatched as slice * tiles + tile.
@@ -2456,6 +2446,68 @@ static int run_streamk(const void* A, const void* qweight, const void* scales, c
     return W4A16_HIP(hipGetLastError()) ? W4A16_OK : W4A16_ERR_HIP;
 }
 
+// ---- 17 to 64 rows (see w4a16_batch.hpp): the library's own launch, or none where the other launches take less time.
+struct BatchPlan {
+    int split_k, strips;  // split_k == 0: no such launch
+};
+
+// us of a launch of the batch kernel: what surrounds its rounds (of 256 workgroups), the chunks that a wave goes through,
+// the weights' bytes and the adds into C.  Fitted to 18,900 random shapes (17 to 64 rows, n and k from 1024 to 28672, every
+// width and group size, five splits each; spread 8 and 9 %).
+static double batch_us(int strips, int split_k, int m, int n, int k, int ipg, int bits)
+{
+    const int mt = (m + 15) / 16, chunks = (k + 127) / 128, tiles = (n + 64 * strips - 1) / (64 * strips);
+    const int parts = split_k * kBatchWaves / strips;
+    const double rounds = (split_k * tiles + 255) / 256, walk = rounds * ((chunks + parts - 1) / parts);
+    const double megabytes = (double)n * k * bits / 8e6, adds = split_k > 1 ? (double)m * n * split_k * 1e-6 : 0.0;
+    if (strips == 1)
+        return 2.0 - 0.1 * mt + rounds * (1.02 + 0.32 * mt) +
+               walk * (0.28 + 0.33 * mt + (bits == 8 ? 0.08 : bits == 3 ? 0.25 : 0.0) + (ipg == 1 ? 0.47 : ipg == 2 ? 0.12 : 0.0)) +
+               0.12 * megabytes + (split_k > 1 ? 0.33 : 0.0) + 1.14 * adds;
+    return 6.4 - 1.18 * mt + rounds * (-3.08 + 1.57 * mt) +
+           walk * (1.06 + 0.07 * mt + (bits == 8 ? 0.18 : bits == 3 ? 0.39 : 0.0) + (ipg == 1 ? 0.72 : ipg == 2 ? 0.21 : 0.0)) +
+           0.08 * megabytes - (split_k > 1 ? rounds > 1 ? -2.0 : 0.55 : 0.0) + 1.09 * adds;
+}
+
+// us of the streaming kernel's launch `others` for 17 to 64 rows: fitted to the same shapes with groups of 128 and 256 (spread 8 %).
+static double stream_rows_us(const Plan& others, int m, int n, int k, int bits)
+{
+    const int mt = (m + 15) / 16, s = others.split_k, tiles = (n + kStreamTileCols - 1) / kStreamTileCols;
+    const double walk = (double)((k / 128 + s - 1) / s) * ((tiles * s + 255) / 256), mfields = (double)n * k * 1e-6;
+    return (s > 1 ? 4.4 + 15.5e-6 * mt * n * s : 2.2) + 0.24 * mt + 0.34 * mt * walk +
+           mfields * ((bits == 8 ? 0.051 : bits == 3 ? 0.035 : bits == 2 ? 0.008 : 0.011) - 0.004 * mt);
+}
+
+static int run_batch(const BatchPlan& plan, const void* A, const void* qweight, const void* scales, const void* qzeros,
+                     void* C, int m, int n, int k, int group_size, int bits, const ScratchView& view, hipStream_t stream)
+{
+    BatchArgs a;
+    a.A = (const _Float16*)A;
+    a.qweight = (const uint32_t*)qweight;
+    a.scales = (const _Float16*)scales;
+    a.qzeros = (const uint32_t*)qzeros;
+    a.C = (_Float16*)C;
+    a.m = m;
+    a.n = n;
+    a.k = k;
+    a.tiles = (n + 64 * plan.strips - 1) / (64 * plan.strips);
+    a.split_k = plan.split_k;
+    a.strips = plan.strips;
+    const int chunks = (k + 127) / 128, parts = plan.split_k * kBatchWaves / plan.strips;
+    a.chunks_base = chunks / parts;
+    a.chunks_rem = chunks % parts;
+    a.param_shift = group_size == 256 ? 1 : 0;
+    a.flags = view.flags;
+    a.counts = view.counts;
+    a.errors = view.errors;
+    a.err_host = view.err_host;
+    a.spin_limit = g_spin_limit;
+    a.probe_delay = g_probe_delay;
+    // (a wave without a chunk takes no part in the zeroing: only where k is not split)
+    if (a.split_k > 1 && a.chunks_base < 1) return W4A16_ERR_SPLIT;
+    return W4A16_HIP(launch_batch(a, bits, group_size >= 128 ? 4 : group_size / 32, stream)) ? W4A16_OK : W4A16_ERR_HIP;
+}
+
 // ---- Many rows (see w4a16_rows.hpp): the library's own launch, or none where other launches take less time.
 struct RowsPlan {
     int row_blocks, workers;
@@ -2569,6 +2621,47 @@ static int plan_many_rows(int m, int n, int k, int group_size, int bits, bool ma
     return W4A16_OK;
 }
 
+// The launch of a call that leaves every choice to the library.  It splits k no further than the launch that would
+// run otherwise, `others` (the parts of a sum are added in fp16 in both), and so needs no scratch where that needs none;
+// where the many-row kernel is that other launch, which adds in fp32, it does not split k at all.
+// With groups of 32 and 64 it stands against a launch per 16 rows and always wins (1.7 to 1.9 times as fast on average);
+// otherwise the estimates have to be 5 % apart, with two strips, which they tell less well, 10 %.  On 26,000 random calls
+// of 17 to 64 rows, 1.35 times as fast on average; of those that go here 10 are more than 5 % slower than before, at
+// worst 9 %.  The phase words cover n <= 65536.
+static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* plan, Plan* others)
+{
+    *plan = BatchPlan{0, 0};
+    if (m <= 16 || m > 64 || (size_t)n > 16 * (size_t)kPhaseOrigins || k >= 1 << 22) return W4A16_OK;
+    const bool fine_groups = group_size < 128;
+    const int rc = make_plan(fine_groups ? 16 : m, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO, others, bits);
+    if (rc != W4A16_OK) return rc;
+    const int chunks = (k + 127) / 128, ipg = fine_groups ? group_size / 32 : 4;
+    RowsPlan rows{0, 0, true};
+    if (fine_groups) {
+        const int rc_rows = plan_many_rows(m, n, k, group_size, bits, true, &rows, nullptr);
+        if (rc_rows != W4A16_OK) return rc_rows;
+    }
+    const bool may_split = others->split_k > 1 && others->reduce != W4A16_REDUCE_ATOMIC_PK_F16 && !rows.row_blocks;
+    double best = 1e30;
+    for (int strips = 1; strips <= 2; ++strips) {
+        const int tiles = (n + 64 * strips - 1) / (64 * strips);
+        int most = chunks * strips / kBatchWaves;  // every wave has a chunk
+        most = most < others->split_k ? most : others->split_k;
+        most = most < 1 || !may_split ? 1 : most < 32 ? most : 32;
+        for (int s : {1, 256 / tiles, 256 / tiles + 1, 512 / tiles, most}) {
+            s = s < 1 ? 1 : s < most ? s : most;
+            const double us = batch_us(strips, s, m, n, k, ipg, bits);
+            if (us < best) {
+                best = us;
+                *plan = BatchPlan{s, strips};
+            }
+        }
+    }
+    if (rows.row_blocks && best >= 0.85 * fitted_rows_us(rows, m, n, k, ipg, bits)) *plan = BatchPlan{0, 0};
+    if (!fine_groups && best >= (plan->strips == 2 ? 0.9 : 0.95) * stream_rows_us(*others, m, n, k, bits)) *plan = BatchPlan{0, 0};
+    return W4A16_OK;
+}
+
 // About 0.1 ms.  A part that is not there by then belongs to a worker that has not started: leaving the tile to it costs
 // a few us and frees the workgroup's place for others.
 constexpr int kRowsPolls = 128;
@@ -2638,8 +2731,26 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
     // runs as one launch per 16 rows.
     // Where the caller leaves every choice to the library, a call that would take several launches may be one of
     // the many-row kernel.
-    if (!dp && split_k == 0 && tile_cols == 0 && waves == 0 && reduce == W4A16_REDUCE_AUTO &&
-        scratch_kind == kScratchLibrary) {
+    const bool librarys_choice = !dp && split_k == 0 && tile_cols == 0 && waves == 0 && reduce == W4A16_REDUCE_AUTO &&
+                                 scratch_kind == kScratchLibrary;
+    if (librarys_choice && m > 16 && m <= 16 * kStreamMaxRowTiles) {
+        BatchPlan batch;
+        Plan others;
+        rc = plan_batch(m, n, k, group_size, bits, &batch, &others);
+        if (rc != W4A16_OK) return rc;
+        if (batch.split_k) {
+            ScratchView view;
+            if (others.split_k > 1 && others.reduce != W4A16_REDUCE_ATOMIC_PK_F16) {
+                ScratchNeed need;
+                need.phase_split = batch.split_k > 1 ? batch.split_k : 0;
+                need.n = n;
+                rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);
+                if (rc != W4A16_OK) return rc;
+            }
+            return run_batch(batch, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, view, (hipStream_t)stream_v);
+        }
+    }
+    if (librarys_choice) {
         RowsPlan rows_plan;
         bool share_ok = false;
         rc = plan_many_rows(m, n, k, group_size, bits, true, &rows_plan, &share_ok);
@@ -2662,7 +2773,14 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
                                 (hipStream_t)stream_v);
         }
     }
-    const int rows_per_launch = stream_rows_ok(group_size, dp, tile_cols, waves, reduce) ? 16 * kStreamMaxRowTiles : 16;
+    int rows_per_launch = stream_rows_ok(group_size, dp, tile_cols, waves, reduce) ? 16 * kStreamMaxRowTiles : 16;
+    if (librarys_choice && m > 16 * kStreamMaxRowTiles) {  // (64 rows of a longer call: as a call of 64)
+        BatchPlan batch;
+        Plan others;
+        rc = plan_batch(16 * kStreamMaxRowTiles, n, k, group_size, bits, &batch, &others);
+        if (rc != W4A16_OK) return rc;
+        if (batch.split_k) rows_per_launch = 16 * kStreamMaxRowTiles;
+    }
     if (m > rows_per_launch) {
         for (int r = 0; r < m; r += rows_per_launch) {
             const int mm = m - r < rows_per_launch ? m - r : rows_per_launch;
@@ -3003,6 +3121,22 @@ int w4a16_plan_many_rows(int bits, int m, int n, int k, int group_size, int may_
     if (tile_rows) *tile_rows = 16 * plan.row_blocks;
     if (workgroups) *workgroups = plan.workers;
     if (shared) *shared = plan.whole ? 0 : 1;
+    return W4A16_OK;
+}
+
+int w4a16_plan_batch(int bits, int m, int n, int k, int group_size, int* split_k, int* tile_cols)
+{
+    if (bits != 4 && bits != 8 && bits != 3 && bits != 2) return W4A16_ERR_UNSUPPORTED;
+    const int rc = w4a16::check_args(m, n, k, group_size, 0);
+    if (rc != W4A16_OK) return rc;
+    if ((bits == 2 && n % 16 != 0) || (bits == 3 && n % 32 != 0)) return W4A16_ERR_SHAPE;
+    if ((unsigned long long)k * (unsigned long long)n * (unsigned)bits / 8 >= (1ull << 31)) return W4A16_ERR_UNSUPPORTED;
+    w4a16::BatchPlan plan;
+    w4a16::Plan others;
+    const int rc_plan = w4a16::plan_batch(m, n, k, group_size, bits, &plan, &others);
+    if (rc_plan != W4A16_OK) return rc_plan;
+    if (split_k) *split_k = plan.split_k;
+    if (tile_cols) *tile_cols = plan.split_k ? 64 * plan.strips : 0;
     return W4A16_OK;
 }
 

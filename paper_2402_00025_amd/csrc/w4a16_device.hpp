@@ -254,6 +254,17 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes)
 // neighbouring tile's, which then has to fetch it again (n = 3480, k = 2176, m = 4, unsplit 16-column tiles: 4.2 -> 4.5).
 constexpr int kWeightLoadAux = 2;  // the builtin's aux bit 1: `nt` on gfx950
 
+// A wait of the phase protocol ran out (one lane calls this): count it, raise the sticky word the
+// host looks at before its next call, and add NaN to the first column pair of the tile, so that
+// the output cannot pass for a result.  `c_off` is a byte offset inside C.
+__device__ __forceinline__ void phase_wait_failed(uint32_t* errors, uint32_t* err_host, rsrc_t rs_c, uint32_t c_off)
+{
+    __hip_atomic_fetch_add(errors, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (err_host) __hip_atomic_store(err_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const half2_t poison = {(_Float16)__builtin_nanf(""), (_Float16)__builtin_nanf("")};
+    __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(poison, rs_c, c_off, 0, 0);
+}
+
 // V consecutive 32-bit words of the weight stream.
 template <int V> struct Words;
 template <> struct Words<1> {

@@ -105,3 +105,47 @@ def test_many_rows_too_wide_for_the_kernel(stand_in):
     assert gemm(128, 1 << 24, 128, 128)[:2] == (UNSUPPORTED, 0)
     assert gemm(33, (1 << 23) + 8, 128, 32)[:2] == (OK, 3)
     """)
+
+
+def test_route_of_batch_rows(stand_in):
+    """17 to 64 rows: one launch at every group size, split no further than the other launches, refused where those are."""
+    stand_in("""
+    def batch(m, n, k, g, bits=4):
+        s, t = ctypes.c_int(), ctypes.c_int()
+        assert L.w4a16_plan_batch(bits, m, n, k, g, ctypes.byref(s), ctypes.byref(t)) == OK
+        return s.value, t.value
+    def other(m, n, k, g, bits=4):
+        s = ctypes.c_int(0)
+        assert L.w4a16_plan_bits(bits, m if g >= 128 else min(m, 16), n, k, g, 0, ctypes.byref(s), None, None, None) == OK
+        return s.value
+    for bits in (4, 8, 3, 2):
+        for m in (17, 33, 48, 64):
+            for n, k in ((1024, 1024), (4096, 4096), (32, 28672), (28672, 1280), (65536, 512)):
+                for g in (32, 64, 128, 256):
+                    s, t = batch(m, n, k, g, bits)
+                    many = plan(m, n, k, g, bits)[0]
+                    assert g < 128 or m <= 48 or s, (bits, m, n, k, g)
+                    if not s: continue
+                    assert s <= (1 if many else max(1, other(m, n, k, g, bits))) and t in (64, 128), (bits, m, n, k, g, s, t)
+                    assert s == 1 or s * 8 * 64 // t <= -(-k // 128)
+                    assert gemm(m, n, k, g, bits) == (OK, 1, (s, -(-n // t), 1)), (bits, m, n, k, g)
+    assert batch(16, 4096, 4096, 128) == batch(65, 4096, 4096, 128) == batch(40, 65544, 4096, 128) == (0, 0)
+    assert L.w4a16_plan_batch(5, 40, 4096, 4096, 128, None, None) == UNSUPPORTED
+    assert L.w4a16_plan_batch(4, 40, 4096, 4096, 128, None, None) == OK
+    assert L.w4a16_release_scratch() == OK
+    s = batch(40, 4096, 4096, 128)[0]
+    assert s > 1
+    capturing.value = 1                              # (the other launches need the same words)
+    assert gemm(40, 4096, 4096, 128)[:2] == (-6, 0)
+    capturing.value = 0
+    assert gemm(40, 4096, 4096, 128)[:2] == (OK, 1)
+    capturing.value = 1
+    assert gemm(40, 4096, 4096, 128)[:2] == (OK, 1)
+    capturing.value = 0
+    space = (ctypes.c_char * (L.w4a16_workspace_bytes(1024) + 256))()
+    base = (ctypes.addressof(space) + 255) // 256 * 256
+    assert L.w4a16_set_workspace(vp(base), ctypes.c_longlong(L.w4a16_workspace_bytes(1024)), 1024, vp(64)) == OK
+    assert gemm(40, 4096, 4096, 128, stream=64)[0] == LIMIT
+    assert gemm(40, 1024, 4096, 128, stream=64)[:2] == (OK, 1)
+    assert L.w4a16_release_scratch() == OK
+    """)

@@ -1637,3 +1637,132 @@ def test_many_rows_infinite_scale_in_the_last_group(oracle, bits, m, n, k, g):
     finite = s.copy()
     finite[-1, huge] = 0.0
     assert_parity(got[:, ~huge].astype(np.float16), ref(finite)[:, ~huge], f"bits={bits} g={g}")
+
+
+# 17 to 64 rows, the library's own launch: one and two strips a workgroup, k split and not (four bits; the other widths' plans
+# may differ), every group size.
+BATCH = [
+    # m, n, k, g, (split_k, columns of a workgroup) with four bits
+    (17, 40, 32, 32, (1, 64)),        # one MFMA step, fewer columns than a strip, seven waves without a chunk
+    (31, 40, 384, 128, (1, 64)),      # fewer chunks than waves
+    (32, 288, 2048, 128, (2, 64)),    # one chunk a wave
+    (17, 40, 1536, 128, (3, 128)),    # two strips, the second without columns
+    (48, 520, 4736, 128, (4, 64)),    # shares of one and two chunks
+    (33, 40, 1536, 256, (3, 128)),    # a group of two chunks
+    (63, 2080, 2048, 256, (2, 64)),
+    (64, 40, 1152, 128, (2, 128)),    # shares of one and two chunks between barriers
+    (49, 16416, 160, 32, (1, 128)),   # a quarter of a chunk at the end
+    (32, 16416, 64, 64, (1, 128)),    # half a chunk is all
+    (47, 40, 1984, 64, (2, 64)),      # half a chunk at the end of a split range
+    (64, 40, 1984, 64, (4, 128)),
+    (64, 528, 1120, 32, (1, 64)),     # three quarters of a chunk at the end
+    (16 + 64, 40, 1984, 64, None),    # 64 rows as a call of their own, then 16
+]
+
+
+@pytest.mark.parametrize("bits", [4, 8, 3, 2])
+@pytest.mark.parametrize("m,n,k,g,plan4", BATCH)
+def test_batch_rows(oracle, bits, m, n, k, g, plan4):
+    n = -(-n // 32) * 32 if bits in (2, 3) else n
+    plan = b.w4a16_plan_batch(bits, m, n, k, g)
+    if bits == 4:
+        assert (plan and (plan["split_k"], plan["tile_cols"])) == plan4, plan
+    seed = 6000 + m + n + k
+    A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
+    Cref, _ = oracle.gemm_3bit(A, qw, s, qz, g) if bits == 3 else oracle.gemm_bits(A, qw, s, qz, g, bits)
+    p = DeviceProblem(A, qw, s, qz, g)
+    for rep in range(2):      # (the phase words count calls)
+        p.C.fill_(float("nan"))
+        MANY_ROWS_GEMM[bits](*p.args(), 0)
+        assert_parity(p.result(), Cref, f"bits={bits} m={m} n={n} k={k} g={g} call {rep}")
+    assert b.w4a16_phase_timeouts() == 0
+
+
+@pytest.mark.parametrize("bits", [4, 8, 3, 2])
+@pytest.mark.parametrize("m,n,k,g", [(64, 160, 1152, 128), (64, 160, 1120, 32), (48, 160, 1984, 64)])
+def test_batch_rows_one_hot_bit_exact(bits, m, n, k, g):
+    """One non-zero term per row, swept over all k: every operand lands where it belongs."""
+    import torch
+    assert b.w4a16_plan_batch(bits, m, n, k, g)
+    if bits == 3:
+        _, qw, s, qz = random_case_3bit(1, n, k, g, seed=13)
+        W = np_dense_weight_3bit(qw, s, qz, g).astype(np.float16)
+    else:
+        _, qw, s, qz = random_case_bits(1, n, k, g, bits, seed=13)
+        W = np_dense_weight_bits(qw, s, qz, g, bits).astype(np.float16)
+    p = DeviceProblem(np.zeros((m, k), np.float16), qw, s, qz, g)
+    for base in range(0, k, m):
+        rows = (base + np.arange(m)) % k
+        A = np.zeros((m, k), np.float16)
+        A[np.arange(m), rows] = 1.0
+        p.A.copy_(torch.from_numpy(A))
+        MANY_ROWS_GEMM[bits](*p.args(), 0)
+        assert np.array_equal(p.result(), W[rows]), (bits, base)   # (zeros may differ in sign)
+
+
+@pytest.mark.parametrize("bits", [4, 8, 3, 2])
+@pytest.mark.parametrize("m,n,k,g", [(33, 288, 1056, 32), (40, 160, 1984, 64), (20, 544, 192, 64)])
+def test_batch_rows_infinite_scale_in_the_last_group(oracle, bits, m, n, k, g):
+    """k ends inside a chunk: the groups that the last chunk lacks add nothing, also where the last real one has an
+    infinite scale."""
+    assert b.w4a16_plan_batch(bits, m, n, k, g)
+    A, qw, s, qz = random_case_3bit(m, n, k, g, 73) if bits == 3 else random_case_bits(m, n, k, g, bits, 73)
+    ref = (lambda t: oracle.gemm_3bit(A, qw, t, qz, g)[0]) if bits == 3 else (lambda t: oracle.gemm_bits(A, qw, t, qz, g, bits)[0])
+    huge = np.zeros(n, bool)
+    huge[[0, 5, 64, n - 1]] = True
+    only_last = np.zeros_like(s)
+    only_last[-1] = 1.0
+    sign = np.sign(ref(only_last))
+    s = s.copy()
+    s[-1, huge] = np.inf
+    p = DeviceProblem(A, qw, s, qz, g)
+    MANY_ROWS_GEMM[bits](*p.args(), 0)
+    got = p.result().astype(np.float64)
+    product = sign[:, huge]
+    assert np.array_equal(got[:, huge][product != 0], (product * np.inf)[product != 0])
+    finite = s.copy()
+    finite[-1, huge] = 0.0
+    assert_parity(got[:, ~huge].astype(np.float16), ref(finite)[:, ~huge], f"bits={bits} g={g}")
+
+
+def test_batch_rows_captured_and_with_a_workspace(oracle):
+    """A split call in a graph, replayed with eager calls between, and on a stream with a workspace of its own."""
+    import torch
+    m, n, k, g = 40, 520, 4096, 128
+    assert b.w4a16_plan_batch(4, m, n, k, g)["split_k"] > 1
+    probs = []
+    for seed in (61, 62):
+        A, qw, s, qz = random_case(m, n, k, g, seed=seed)
+        probs.append((DeviceProblem(A, qw, s, qz, g), oracle.gemm(A, qw, s, qz, g)[0]))
+    for p, Cref in probs:
+        b.w4a16_gemm(*p.args(), 0)
+        assert_parity(p.result(), Cref, "eager")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        b.w4a16_gemm(*probs[0][0].args(), 0, stream=torch.cuda.current_stream())
+    for rep in range(3):
+        for p, _ in probs:
+            p.C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        b.w4a16_gemm(*probs[1][0].args(), 0)
+        for p, Cref in probs:
+            assert_parity(p.result(), Cref, f"replay {rep}")
+    nbytes = b.w4a16_workspace_bytes(n)
+    ws = torch.zeros(nbytes // 4 + 64, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    b.w4a16_set_workspace(ws, nbytes, n, stream=stream)
+    try:
+        for p, _ in probs:
+            p.C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        b.w4a16_gemm(*probs[0][0].args(), 0, stream=stream)
+        b.w4a16_gemm(*probs[1][0].args(), 0)                      # beside it, on the library's scratch
+        for p, Cref in probs:
+            assert_parity(p.result(), Cref, "two streams")
+    finally:
+        b.w4a16_set_workspace(None, 0, 0, stream=stream)
+    assert b.w4a16_phase_timeouts() == 0
