@@ -124,7 +124,6 @@ def test_route_of_batch_rows(stand_in):
                 for g in (32, 64, 128, 256):
                     s, t = batch(m, n, k, g, bits)
                     many = plan(m, n, k, g, bits)[0]
-                    assert g < 128 or m <= 48 or s, (bits, m, n, k, g)
                     if not s: continue
                     assert s <= (1 if many else max(1, other(m, n, k, g, bits))) and t in (64, 128), (bits, m, n, k, g, s, t)
                     assert s == 1 or s * 8 * 64 // t <= -(-k // 128)

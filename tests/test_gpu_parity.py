@@ -1651,8 +1651,8 @@ BATCH = [
     (33, 40, 1536, 256, (3, 128)),    # a group of two chunks
     (63, 2080, 2048, 256, (2, 64)),
     (64, 40, 1152, 128, (2, 128)),    # shares of one and two chunks between barriers
-    (49, 16416, 160, 32, (1, 128)),   # a quarter of a chunk at the end
-    (32, 16416, 64, 64, (1, 128)),    # half a chunk is all
+    (47, 16416, 160, 32, (1, 128)),   # a quarter of a chunk at the end
+    (64, 16416, 320, 64, (1, 128)),   # half a chunk at the end, most waves without any
     (47, 40, 1984, 64, (2, 64)),      # half a chunk at the end of a split range
     (64, 40, 1984, 64, (4, 128)),
     (64, 528, 1120, 32, (1, 64)),     # three quarters of a chunk at the end
