@@ -29,7 +29,7 @@
  * it; w4a16_plan reports the others): 64 or 128 columns a workgroup, k split no further than by the other launches and
  * with the same reduction and scratch (packed-fp16 adds into C that the kernel zeroes, or plain stores).  And where more than
  * one launch would be needed, it is one launch of a kernel for many rows instead, unless that takes longer: tiles
- * of 64 or 128 rows x 256 columns, their k ranges shared by persistent workgroups, the sums
+ * of up to 64 or 128 rows x 256 columns, their k ranges shared by persistent workgroups, the sums
  * added in fp32 in the order of k (bit-reproducible between calls that take the same launch: where a call finds no
  * scratch for shared tiles, see below, the sums are grouped otherwise).  Ranges are shared, through scratch memory,
  * only where w4a16_plan reports a split_k above 1 for the call.  n is at most 2^23 for it.  w4a16_plan does not describe
@@ -250,9 +250,10 @@ int w4a16_plan(int m, int n, int k, int group_size, int dp, int* split_k, int* t
 int w4a16_plan_bits(int bits, int m, int n, int k, int group_size, int dp, int* split_k, int* tile_cols,
                     int* waves, int* reduce);
 /*
- * The many-row launch of a SplitK call of this field width with split_k == 0: the rows of a tile (64 or 128; 0 if the
- * call goes to the launches w4a16_plan reports instead; up to 64 rows w4a16_plan_batch comes first), the workgroups, and whether these share tiles (1) or take
- * whole ones (0).  may_share == 0: the launch of a call that finds no scratch for shared tiles (a stream with a bound
+ * The many-row launch of a SplitK call of this field width with split_k == 0: the most rows a tile may have (64 or 128:
+ * the tiles are evened out to as few row blocks of 16 as that many of them need, three at least; 0 if the call goes to
+ * the launches w4a16_plan reports instead; up to 64 rows w4a16_plan_batch comes first), the workgroups, and whether these
+ * share tiles (1) or take whole ones (0).  may_share == 0: the launch of a call that finds no scratch for shared tiles (a stream with a bound
  * workspace; under capture before any such call).  Host only; no HIP call; the last three may be NULL.
  */
 int w4a16_plan_many_rows(int bits, int m, int n, int k, int group_size, int may_share, int* tile_rows,

@@ -2685,12 +2685,14 @@ static int run_rows(const RowsPlan& plan, const void* A, const void* qweight, co
     a.param_shift = group_size == 256 ? 1 : 0;
     a.polls = g_spin_limit > kRowsPolls ? kRowsPolls : g_spin_limit - 1;
     a.tiles_m = (m + 16 * plan.row_blocks - 1) / (16 * plan.row_blocks);
+    // as many tiles, evened out: 333 rows are three of 112 and not 128, 128 and 77 in the place of 128 each
+    const int even = ((m + 15) / 16 + a.tiles_m - 1) / a.tiles_m, row_blocks = even < 3 ? 3 : even;
     const int tiles = a.tiles_m * ((n + kRowsTileCols - 1) / kRowsTileCols);
     a.share_unit = plan.whole ? a.chunks : 1;
     const int units = plan.whole ? tiles : tiles * a.chunks;
     a.share = units / plan.workers;
     a.share_rem = units % plan.workers;
-    return W4A16_HIP(launch_rows(a, bits, ipg, plan.row_blocks, plan.workers, stream)) ? W4A16_OK : W4A16_ERR_HIP;
+    return W4A16_HIP(launch_rows(a, bits, ipg, row_blocks, plan.workers, stream)) ? W4A16_OK : W4A16_ERR_HIP;
 }
 
 static void read_tuning_env()

@@ -19,12 +19,18 @@ static hipError_t launch_rows_one(const RowsArgs& a, int workers, hipStream_t st
 template <int BITS>
 static hipError_t launch_rows_width(const RowsArgs& a, int ipg, int row_blocks, int workers, hipStream_t stream)
 {
-    if (row_blocks == 8 && rows_tall_ok(ipg)) return launch_rows_one<8, BITS, 4>(a, workers, stream);
-    switch (ipg) {
-    case 1: return launch_rows_one<4, BITS, 1>(a, workers, stream);
-    case 2: return launch_rows_one<4, BITS, 2>(a, workers, stream);
-    default: return launch_rows_one<4, BITS, 4>(a, workers, stream);
+    if (ipg == 4) {
+        switch (row_blocks) {
+        case 3: return launch_rows_one<3, BITS, 4>(a, workers, stream);
+        case 5: return launch_rows_one<5, BITS, 4>(a, workers, stream);
+        case 6: return launch_rows_one<6, BITS, 4>(a, workers, stream);
+        case 7: return launch_rows_one<7, BITS, 4>(a, workers, stream);
+        case 8: return launch_rows_one<8, BITS, 4>(a, workers, stream);
+        default: return launch_rows_one<4, BITS, 4>(a, workers, stream);
+        }
     }
+    if (ipg == 2) return row_blocks == 3 ? launch_rows_one<3, BITS, 2>(a, workers, stream) : launch_rows_one<4, BITS, 2>(a, workers, stream);
+    return row_blocks == 3 ? launch_rows_one<3, BITS, 1>(a, workers, stream) : launch_rows_one<4, BITS, 1>(a, workers, stream);
 }
 
 hipError_t launch_rows(const RowsArgs& a, int bits, int ipg, int row_blocks, int workers, hipStream_t stream)

@@ -155,7 +155,9 @@ constexpr int kRowsWaveWeightBytes = 4 * kRowsWordLoads<BITS> * 1024;
 template <int MB, int BITS>
 constexpr int kRowsLdsBytes = 2 * MB * 4096 + kRowsStrips * kRowsWaveWeightBytes<BITS>;
 
-// MB: 16-row blocks per workgroup tile.  IPG: MFMA steps (32 k) per quantisation group in a chunk (4, 2, 1).
+// MB: 16-row blocks per workgroup tile: 8 or 4, or the fewer (down to 3) that as many tiles need when they are evened
+// out (m = 333, n = 11008, k = 4096: 46.5 -> 43.5 us with 7; m = 129, n = k = 4096: 18.5 -> 16.6 with 3; nothing gained where
+// one workgroup a unit waits for memory: m = 150, n = 28672, k = 4096: 53).  IPG: MFMA steps (32 k) per quantisation group in a chunk (4, 2, 1).
 template <int MB, int BITS, int IPG>
 __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const RowsArgs p)
 {
@@ -234,14 +236,14 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
         for (int i0 = 0; i0 < MB; i0 += 4) {  // 16 loads in flight
             float4_t part[4][4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4 && i0 + i < MB; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     part[i][j] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(
                                                                   rs, off + (uint32_t)((i0 + i) * 4 + j) * 1024u, 0, kRowsDeviceScope));
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4 && i0 + i < MB; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc[i0 + i][j] += part[i][j];
             __builtin_amdgcn_sched_barrier(0);
@@ -447,7 +449,7 @@ __global__ void __launch_bounds__(64 * kRowsStrips, 2) gemm_rows_kernel(const Ro
                 for (int j = 0; j < 4; ++j) {
                     bq[it][j] = nat_unpack<BITS>(raw[it & 1][0][j], raw[it & 1][1][j], lm, zc[j], magic);
                     mfma(it, j, it % IPG == 0);
-                    if ((it * 4 + j) % (16 / MB) == 0) {
+                    if ((it * 4 + j) % (16 / MB) == 0 && (it * 4 + j) / (16 / MB) < MB) {
                         __builtin_amdgcn_sched_barrier(0);
                         stage_a(g + 1, more, a_next, (it * 4 + j) / (16 / MB));
                         __builtin_amdgcn_sched_barrier(0);

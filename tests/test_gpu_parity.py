@@ -1471,11 +1471,25 @@ MANY_ROWS = [
     (2970, 6272, 512, 128, 128, True),   # more tiles than workgroups: 512 for 4 and 2 bits, 256 for 8 and 3
     (2956, 8320, 128, 128, 128, False),  # several whole tiles each
 ]
+# Tiles evened out to fewer than 64 or 128 rows: three row blocks of 16 at every group size, five to seven of 64 to 128.
+EVENED_ROWS = [
+    # m, n, k, g, rows of a tile at most, shared
+    (65, 40, 128, 128, 64, False),      # two tiles of 48
+    (129, 40, 1024, 128, 64, True),
+    (74, 96, 64, 64, 64, False),
+    (66, 40, 576, 64, 64, True),
+    (77, 40, 416, 32, 64, True),
+    (150, 22016, 256, 128, 128, False),  # two tiles of 80
+    (310, 16416, 128, 128, 128, False),  # 112
+    (198, 16416, 1152, 128, 128, True),
+    (259, 16416, 128, 128, 128, False),  # 96
+    (430, 28672, 256, 128, 128, False),
+]
 MANY_ROWS_GEMM = {4: b.w4a16_gemm, 8: b.w8a16_gemm, 3: b.w3a16_gemm, 2: b.w2a16_gemm}
 
 
 @pytest.mark.parametrize("bits", [4, 8, 3, 2])
-@pytest.mark.parametrize("m,n,k,g,tile_rows,shared", MANY_ROWS)
+@pytest.mark.parametrize("m,n,k,g,tile_rows,shared", MANY_ROWS + EVENED_ROWS)
 def test_many_rows(oracle, bits, m, n, k, g, tile_rows, shared):
     n = n // 32 * 32 if bits in (2, 3) else n
     plan = b.w4a16_plan_many_rows(bits, m, n, k, g)
