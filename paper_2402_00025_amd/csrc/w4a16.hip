@@ -8,6 +8,7 @@
 #include "w4a16_stream.hpp"
 #include "w4a16_rows.hpp"
 #include "w4a16_batch.hpp"
+#include "w4a16_order.hpp"
 
 #include <cstdio>
 #include <cstdlib>
@@ -1254,18 +1255,6 @@ __global__ void actorder_repack_kernel(const uint32_t* __restrict__ qweight, con
         word |= field(qweight[(size_t)(src >> 3) * n + j], src & 7) << (4 * i);
     }
     out[idx] = word;
-}
-
-// A_work[i][t] = A[i][perm[t]].
-__global__ void actorder_gather_kernel(const _Float16* __restrict__ A, const int32_t* __restrict__ perm,
-                                       _Float16* __restrict__ A_work, int m, int k)
-{
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)m * k) return;
-    const int i = (int)(idx / k), t = (int)(idx % k);
-    int src = perm[t];
-    src = src < 0 ? 0 : (src >= k ? k - 1 : src);
-    A_work[idx] = A[(size_t)i * k + src];
 }
 
 // ---- measurement probe: a plain coalesced read of a buffer (U 16-byte loads in flight per
@@ -3043,10 +3032,7 @@ int w4a16_gemm_actorder(const void* A, const void* qweight_sorted, const void* s
     int rc = w4a16::check_args(m, n, k, group_size, split_k);
     if (rc != W4A16_OK) return rc;
     if (!w4a16::aligned16(A_work) || A_work == A) return W4A16_ERR_UNSUPPORTED;
-    const size_t elems = (size_t)m * k;
-    hipLaunchKernelGGL(w4a16::actorder_gather_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)stream, (const _Float16*)A, (const int32_t*)perm, (_Float16*)A_work, m, k);
-    if (!w4a16::W4A16_HIP(hipGetLastError())) return W4A16_ERR_HIP;
+    if (!w4a16::W4A16_HIP(w4a16::launch_gather(A, perm, A_work, m, k, (hipStream_t)stream))) return W4A16_ERR_HIP;
     return w4a16::run_gemm(A_work, qweight_sorted, scales, qzeros, C, m, n, k, group_size, false, split_k, 0, 0,
                            W4A16_REDUCE_AUTO, true, stream);
 }

@@ -1375,6 +1375,35 @@ def test_activation_ordering(oracle, m, n, k, g, split_k):
         assert np.abs(p.result().astype(np.float64) - Cref).max() > 1e-2 * np.abs(Cref).max()
 
 
+@pytest.mark.parametrize("m,k,a_at,perm_at", [
+    (1, 32, 0, 0), (1, 32, 1, 1), (1, 288, 0, 0),   # one workgroup, mostly idle; a second one's first lanes
+    (47, 4096, 0, 0), (48, 4096, 0, 0), (49, 4096, 0, 0),   # around the line between the kernels; an odd last row
+    (48, 3392, 0, 0), (48, 3424, 0, 0),             # and at its other side, 160 K elements
+    (64, 4096, 1, 0), (64, 4096, 4, 0), (64, 4096, 0, 1), (64, 4096, 0, 2),   # pointers off their alignment
+    (160, 1056, 0, 0), (333, 2080, 0, 0), (600, 4128, 0, 0),   # three shares, two, one: remainders of a pass
+    (49, 16416, 0, 0), (48, 40960, 0, 0), (48, 40992, 0, 0),   # more than 64 KiB of LDS; all of it; too wide
+])
+def test_activation_gather(m, k, a_at, perm_at):
+    """A_work is A[:, perm], bit for bit, entries of perm outside the matrix clamped, whatever A holds."""
+    import torch
+    n, g = 64, 32
+    rng = np.random.default_rng(k + m)
+    bits_a = rng.integers(0, 1 << 16, m * k + a_at, dtype=np.uint16)   # NaN and infinities among them
+    order = rng.permutation(k).astype(np.int32)
+    order[[0, k // 2, k - 1]] = -7, k, 1 << 30
+    A = dev(bits_a.view(np.int16))[a_at:].view(m, k)
+    perm = dev(np.concatenate([np.zeros(perm_at, np.int32), order]))[perm_at:]
+    want = bits_a[a_at:].reshape(m, k)[:, np.clip(order, 0, k - 1)]
+    qw, qz = torch.zeros((k // 8, n), dtype=torch.int32, device="cuda"), torch.zeros((k // g, n // 8), dtype=torch.int32, device="cuda")
+    s, C = torch.ones((k // g, n), dtype=torch.float16, device="cuda"), torch.empty((m, n), dtype=torch.float16, device="cuda")
+    room = torch.full((m * k + 64,), 23, dtype=torch.int16, device="cuda")
+    A_work = room[:m * k].view(m, k)
+    b.w4a16_gemm_actorder(A.view(torch.float16), qw, s, qz, perm, A_work.view(torch.float16), C, m, n, k, g, 0)
+    torch.cuda.synchronize()
+    assert np.array_equal(A_work.cpu().numpy().view(np.uint16), want)
+    assert (room[m * k:] == 23).all()
+
+
 def test_activation_ordering_rejects_bad_group_map():
     import torch
     n, k, g = 64, 512, 128
