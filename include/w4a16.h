@@ -24,8 +24,8 @@
  * 256, waves 0 or 4, reduce AUTO, ATOMIC_PK_F16 or ATOMIC_PK_F16_PHASE) take up to 64 rows per
  * launch as row tiles that share one pass over the weights; everything else, the data-parallel
  * kernel included, runs one launch per 16 rows, each streaming the weights again.  Where the
- * SplitK entry points leave every choice to the library (split_k == 0), 17 to 64 rows of n <= 65536 columns are one
- * launch of a kernel for decode batches at every group size, unless the others take less time (w4a16_plan_batch reports
+ * SplitK entry points leave every choice to the library (split_k == 0), 17 to 64 rows (with groups of 32 and 64 also
+ * fewer) of n <= 65536 columns are one launch of a kernel for decode batches at every group size, unless the others take less time (w4a16_plan_batch reports
  * it; w4a16_plan reports the others): 64 or 128 columns a workgroup, k split no further than by the other launches and
  * with the same reduction and scratch (packed-fp16 adds into C that the kernel zeroes, or plain stores).  And where more than
  * one launch would be needed, it is one launch of a kernel for many rows instead, unless that takes longer: tiles
@@ -260,7 +260,7 @@ int w4a16_plan_many_rows(int bits, int m, int n, int k, int group_size, int may_
                          int* workgroups, int* shared);
 
 /*
- * The launch of the kernel for 17 to 64 rows of a SplitK call of this field width with split_k == 0: in how many parts
+ * The launch of the kernel for decode batches (17 to 64 rows, with groups of 32 and 64 also fewer) of a SplitK call of this field width with split_k == 0: in how many parts
  * it splits k (0 if the call goes to other launches) and the columns of a workgroup (64 or 128).  Host only; no HIP call;
  * the last two may be NULL.
  */

@@ -259,7 +259,8 @@ def w4a16_plan_many_rows(bits, m, n, k, group_size, may_share=True) -> dict | No
 
 
 def w4a16_plan_batch(bits, m, n, k, group_size) -> dict | None:
-    """The launch for 17 to 64 rows of a SplitK call with split_k = 0, or None where the call goes to other launches."""
+    """The launch for decode batches (17 to 64 rows, with groups of 32 and 64 also fewer) of a SplitK call with split_k = 0,
+    or None where the call goes to other launches."""
     s, t = (ctypes.c_int(0) for _ in range(2))
     _check(lib().w4a16_plan_batch(bits, m, n, k, group_size, ctypes.byref(s), ctypes.byref(t)), "w4a16_plan_batch")
     return dict(split_k=s.value, tile_cols=t.value) if s.value else None

@@ -10,6 +10,7 @@
 #include "w4a16_batch.hpp"
 #include "w4a16_order.hpp"
 
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <mutex>
@@ -2467,6 +2468,39 @@ static double stream_rows_us(const Plan& others, int m, int n, int k, int bits)
            mfields * ((bits == 8 ? 0.051 : bits == 3 ? 0.035 : bits == 2 ? 0.008 : 0.011) - 0.004 * mt);
 }
 
+// Up to 16 rows and groups of 32 and 64: us of the batch kernel and of the per-wave kernel's launch `others`, both fitted to
+// 3,500 random shapes (5 to 16 rows, n and k from 1024 to 28672, every width, ten splits each; spread 7, 6 and 6 %).
+static double batch_few_us(int strips, int split_k, int m, int n, int k, int ipg, int bits)
+{
+    const int chunks = (k + 127) / 128, tiles = (n + 64 * strips - 1) / (64 * strips), wgs = split_k * tiles;
+    const int parts = split_k * kBatchWaves / strips;
+    const double full = wgs / 256.0, per = (chunks + parts - 1) / parts, r1 = (wgs + 255) / 256, r2 = (wgs + 511) / 512, walk = r2 * per;
+    const double rows = m / 16.0, megabytes = (double)n * k * bits / 8e6, params = (double)(k / (32 * ipg)) * n * (2 + bits / 8.0) * 1e-6;
+    const double adds = split_k > 1 ? (double)m * n * split_k * 1e-6 : 0.0;
+    if (strips == 1)
+        return 1.5389 + 1.0392 * full + (0.3527 + 0.292 * (full > 1.0 ? full : 1.0) - 0.8909 * full - (wgs <= 256 ? 0.026 : 0.0)) * per +
+               (-0.4051 + (ipg == 1 ? 0.1529 : 0.0) + 0.1451 * rows + (bits == 8 ? 0.234 : bits == 3 ? 0.2504 : bits == 2 ? 0.1009 : 0.0)) * walk +
+               (-0.5912 + 1.0654 * per) * r1 + 1.2245 * r2 - 0.0606 * rows + 0.12 * megabytes + 0.3135 * params +
+               (split_k > 1 ? 0.7349 : 0.0) + 1.2728 * adds;
+    return 2.2795 + 1.13 * full + (-0.1828 + 0.3758 * (full > 1.0 ? full : 1.0) - 0.8519 * full + (wgs <= 256 ? 0.2507 : 0.0)) * per +
+           (0.857 + (ipg == 1 ? 0.15 : 0.0) + 0.0203 * rows + (bits == 8 ? -0.0205 : bits == 3 ? 0.2963 : bits == 2 ? 0.0737 : 0.0)) * walk +
+           (0.3792 + 0.6225 * per) * r1 - 0.786 * r2 + 0.0201 * rows + 0.103 * megabytes + 0.276 * params +
+           (split_k > 1 ? 0.5088 : 0.0) + 0.7096 * adds;
+}
+
+static double wave_few_us(const Plan& others, int m, int n, int k, int ipg, int bits)
+{
+    const int s = others.split_k, wgs = s * ((n + others.tile_cols - 1) / others.tile_cols), groups = k / (32 * ipg);
+    const double waves = (double)wgs * others.waves, full = waves / 1024.0, fuller = full > 1.0 ? full : 1.0;
+    const double per = (groups + s * others.waves - 1) / (s * others.waves), walk = per * ipg, rounds = (wgs + 255) / 256;
+    const double rows = m / 16.0, megabytes = (double)n * k * bits / 8e6, params = (double)groups * n * (2 + bits / 8.0) * 1e-6;
+    const double adds = s > 1 ? (double)m * n * s * 1e-6 : 0.0, activations = waves * walk * 1024e-6, root = std::sqrt(megabytes);
+    return 1.6925 + (0.0291 + 0.0855 * rows + (bits == 8 ? 0.0165 : 0.0)) * megabytes + 0.3028 * params + 0.168 * adds +
+           (s > 1 ? 0.7443 : 0.0) - 0.0673 * rounds + (-0.0343 + 0.1689 * rounds + 0.3314 * fuller) * walk - 0.7262 * fuller +
+           1.1368 * full + 0.7365 * rows + (-0.4173 + 0.0342 * rows) * activations + (0.4712 - 0.3903 * rows) * root + 0.0887 * per +
+           (bits == 8 ? 0.0078 : bits == 3 ? 0.0716 : bits == 2 ? 0.025 : 0.0) * walk * full;
+}
+
 static int run_batch(const BatchPlan& plan, const void* A, const void* qweight, const void* scales, const void* qzeros,
                      void* C, int m, int n, int k, int group_size, int bits, const ScratchView& view, hipStream_t stream)
 {
@@ -2610,6 +2644,36 @@ static int plan_many_rows(int m, int n, int k, int group_size, int bits, bool ma
     return W4A16_OK;
 }
 
+// The same for up to 16 rows, where groups of 32 and 64 cost the per-wave kernel its depth (a ring of two groups holds 64 or
+// 128 k on their way; here 128 and more) and every wave its own activations.  Only from 8 MB of weights on, where the
+// estimates are 10 % apart, and inside the shapes that they are fitted to: below, start and end of a launch are all there is, and the per-wave kernel's are shorter (m = 3,
+// n = k = 2048: 3.7 against 4.5 us).  The parts meet in fp16, so only where they do in the other launch, or not at all; k is split no
+// further than there.  us per call, cold weights, before -> now (m; n x k, groups of 64): 16; 14176 x 1792: 7.6 -> 5.7,
+// 11; 8256 x 21888: 27.8 -> 22.7, groups of 32, 5; 4512 x 21088: 16.4 -> 14.1, 8 bits, groups of 32, 12; 6784 x 11936:
+// 20.1 -> 18.4.  Of 1172 shapes that the fits have not seen it takes 312, 1.16 times as fast on average, two of them more than
+// 2 % slower, at worst 7 %.
+static void plan_batch_few(int m, int n, int k, int group_size, int bits, const Plan& others, BatchPlan* plan)
+{
+    const bool splits = others.split_k > 1;
+    if ((double)n * k * bits < 64e6 || n > 28672 || k < 1024 || k > 28672 || (splits && others.reduce != W4A16_REDUCE_ATOMIC_PK_F16_PHASE)) return;
+    const int chunks = (k + 127) / 128, ipg = group_size / 32;
+    double best = 0.9 * wave_few_us(others, m, n, k, ipg, bits);
+    for (int strips = 1; strips <= 2; ++strips) {
+        const int tiles = (n + 64 * strips - 1) / (64 * strips);
+        int most = chunks * strips / kBatchWaves;  // every wave has a chunk
+        most = most < others.split_k ? most : others.split_k;
+        most = most < 1 ? 1 : most < 32 ? most : 32;
+        for (int s : {1, 2, 3, 4, 256 / tiles, 512 / tiles}) {
+            s = s < 1 ? 1 : s < most ? s : most;
+            const double us = batch_few_us(strips, s, m, n, k, ipg, bits);
+            if (us < best) {
+                best = us;
+                *plan = BatchPlan{s, strips};
+            }
+        }
+    }
+}
+
 // The launch of a call that leaves every choice to the library.  It splits k no further than the launch that would
 // run otherwise, `others` (the parts of a sum are added in fp16 in both), and so needs no scratch where that needs none;
 // where the many-row kernel is that other launch, which adds in fp32, it does not split k at all.
@@ -2620,10 +2684,14 @@ static int plan_many_rows(int m, int n, int k, int group_size, int bits, bool ma
 static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* plan, Plan* others)
 {
     *plan = BatchPlan{0, 0};
-    if (m <= 16 || m > 64 || (size_t)n > 16 * (size_t)kPhaseOrigins || k >= 1 << 22) return W4A16_OK;
     const bool fine_groups = group_size < 128;
-    const int rc = make_plan(fine_groups ? 16 : m, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO, others, bits);
+    if ((m <= 16 && !fine_groups) || m > 64 || (size_t)n > 16 * (size_t)kPhaseOrigins || k >= 1 << 22) return W4A16_OK;
+    const int rc = make_plan(fine_groups && m > 16 ? 16 : m, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO, others, bits);
     if (rc != W4A16_OK) return rc;
+    if (m <= 16) {
+        plan_batch_few(m, n, k, group_size, bits, *others, plan);
+        return W4A16_OK;
+    }
     const int chunks = (k + 127) / 128, ipg = fine_groups ? group_size / 32 : 4;
     RowsPlan rows{0, 0, true};
     if (fine_groups) {
@@ -2724,7 +2792,7 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
     // the many-row kernel.
     const bool librarys_choice = !dp && split_k == 0 && tile_cols == 0 && waves == 0 && reduce == W4A16_REDUCE_AUTO &&
                                  scratch_kind == kScratchLibrary;
-    if (librarys_choice && m > 16 && m <= 16 * kStreamMaxRowTiles) {
+    if (librarys_choice && (m > 16 || group_size < 128) && m <= 16 * kStreamMaxRowTiles) {
         BatchPlan batch;
         Plan others;
         rc = plan_batch(m, n, k, group_size, bits, &batch, &others);
@@ -2736,9 +2804,10 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
                 need.phase_split = batch.split_k > 1 ? batch.split_k : 0;
                 need.n = n;
                 rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);
-                if (rc != W4A16_OK) return rc;
+                // (under capture there may be scratch for the other launch's split alone, which looks for itself)
+                if (rc != W4A16_OK && rc != W4A16_ERR_STATE) return rc;
             }
-            return run_batch(batch, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, view, (hipStream_t)stream_v);
+            if (rc == W4A16_OK) return run_batch(batch, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, view, (hipStream_t)stream_v);
         }
     }
     if (librarys_choice) {

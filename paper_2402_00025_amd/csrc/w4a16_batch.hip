@@ -1,4 +1,4 @@
-// Launches of the kernel for 17 to 64 rows (see w4a16_batch.hpp).
+// Launches of the kernel for up to 64 rows (see w4a16_batch.hpp).
 #include "w4a16_batch.hpp"
 
 namespace w4a16 {
@@ -26,6 +26,10 @@ template <int BITS, int IPG>
 static hipError_t launch_batch_rows(const BatchArgs& a, hipStream_t stream)
 {
     switch ((a.m + 15) / 16) {
+    case 1:
+        // (groups of 128: the per-wave and the streaming kernel are faster, by 5 to 15 % on average)
+        if constexpr (IPG < 4) return launch_batch_strips<1, BITS, IPG>(a, stream);
+        return hipErrorInvalidValue;
     case 2: return launch_batch_strips<2, BITS, IPG>(a, stream);
     case 3: return launch_batch_strips<3, BITS, IPG>(a, stream);
     case 4: return launch_batch_strips<4, BITS, IPG>(a, stream);

@@ -1,4 +1,4 @@
-// Kernel for 17 to 64 activation rows (a decode batch) on gfx950, wave64.
+// Kernel for 17 to 64 activation rows (a decode batch) on gfx950, wave64; with groups of 32 and 64 also for fewer rows.
 //
 // The streaming kernel's row tiles (four waves on 256 columns, one wave per SIMD) split k in many parts to fill the
 // chip, and the adds of 64 rows x 8 parts alone cost 6 us at the memory side; groups of 32 and 64 had no such kernel and

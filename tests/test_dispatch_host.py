@@ -128,6 +128,12 @@ def test_route_of_batch_rows(stand_in):
                     assert s <= (1 if many else max(1, other(m, n, k, g, bits))) and t in (64, 128), (bits, m, n, k, g, s, t)
                     assert s == 1 or s * 8 * 64 // t <= -(-k // 128)
                     assert gemm(m, n, k, g, bits) == (OK, 1, (s, -(-n // t), 1)), (bits, m, n, k, g)
+    for bits, m, n, k, g in ((4, 16, 5120, 13824, 32), (4, 8, 4128, 4160, 64), (8, 16, 8224, 4128, 32), (3, 5, 8192, 8192, 64)):
+        s, t = batch(m, n, k, g, bits)   # up to 16 rows, fine groups: the same
+        assert 1 <= s <= max(1, other(m, n, k, g, bits)) and gemm(m, n, k, g, bits) == (OK, 1, (s, -(-n // t), 1)), (bits, m, n, k, g)
+    for m in (1, 2, 3):                  # sums that do not meet in fp16
+        assert batch(m, 8192, 8192, 32) == batch(m, 5120, 13824, 64) == (0, 0)
+    assert batch(16, 2048, 2048, 32) == batch(16, 65536, 512, 32, 8) == (0, 0)
     assert batch(16, 4096, 4096, 128) == batch(65, 4096, 4096, 128) == batch(40, 65544, 4096, 128) == (0, 0)
     assert L.w4a16_plan_batch(5, 40, 4096, 4096, 128, None, None) == UNSUPPORTED
     assert L.w4a16_plan_batch(4, 40, 4096, 4096, 128, None, None) == OK

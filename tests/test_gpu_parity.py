@@ -1721,6 +1721,27 @@ def test_batch_rows(oracle, bits, m, n, k, g, plan4):
     assert b.w4a16_phase_timeouts() == 0
 
 
+# Up to 16 rows with fine groups: whole k and split k, one strip and two, overhanging strips, a quarter and half a chunk at
+# the end of k, shares of k of two lengths.
+@pytest.mark.parametrize("bits,m,n,k,g,plan", [
+    (4, 16, 12320, 2720, 32, (1, 64)), (4, 5, 12320, 2720, 32, (1, 64)), (4, 8, 4128, 4160, 64, (3, 64)),
+    (4, 16, 2080, 15936, 32, (7, 64)), (8, 16, 8224, 4128, 32, (3, 128)), (8, 16, 8224, 4160, 64, (3, 128)),
+    (3, 5, 8224, 4128, 32, (3, 64)), (2, 8, 8224, 4160, 64, (3, 64)), (2, 16, 9632, 3360, 32, (1, 64)),
+])
+def test_batch_few_rows(oracle, bits, m, n, k, g, plan):
+    got = b.w4a16_plan_batch(bits, m, n, k, g)
+    assert got and (got["split_k"], got["tile_cols"]) == plan, got
+    seed = 7000 + m + n + k
+    A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
+    Cref, _ = oracle.gemm_3bit(A, qw, s, qz, g) if bits == 3 else oracle.gemm_bits(A, qw, s, qz, g, bits)
+    p = DeviceProblem(A, qw, s, qz, g)
+    for rep in range(2):      # (the phase words count calls)
+        p.C.fill_(float("nan"))
+        MANY_ROWS_GEMM[bits](*p.args(), 0)
+        assert_parity(p.result(), Cref, f"bits={bits} m={m} n={n} k={k} g={g} call {rep}")
+    assert b.w4a16_phase_timeouts() == 0
+
+
 @pytest.mark.parametrize("bits", [4, 8, 3, 2])
 @pytest.mark.parametrize("m,n,k,g", [(64, 160, 1152, 128), (64, 160, 1120, 32), (48, 160, 1984, 64)])
 def test_batch_rows_one_hot_bit_exact(bits, m, n, k, g):

@@ -312,3 +312,30 @@ def test_shared_tiles_beside_other_work(bits, m, n, k, g):
     for i, out in enumerate(outs):
         assert np.array_equal(out.cpu().numpy(), want), i
     assert b.w4a16_phase_timeouts() == 0
+
+
+def test_decode_batch_captured_with_the_other_launchs_scratch_alone(oracle):
+    """A captured call finds scratch for the split of the launch that would run otherwise but not for the batch kernel's own:
+    it takes that other launch, and is not refused."""
+    import torch
+    m, n, k, g = 8, 4128, 4160, 64
+    A, qw, s, qz = random_case(m, n, k, g, seed=47)
+    Cref, _ = oracle.gemm(A, qw, s, qz, g)
+    p = DeviceProblem(A, qw, s, qz, g)
+    own, other = b.w4a16_plan_batch(4, m, n, k, g), b.w4a16_plan(m, n, k, g)
+    assert other["reduce"] == b.REDUCE_ATOMIC_PK_F16_PHASE and own["split_k"] not in (1, other["split_k"])
+    b.w4a16_gemm_ex(*p.args(), other["split_k"], other["tile_cols"], other["waves"], other["reduce"])
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        b.w4a16_gemm(*p.args(), 0, stream=torch.cuda.current_stream())
+    for rep in range(3):
+        p.C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        assert_parity(p.result(), Cref, f"replay {rep}")
+        p.C.fill_(float("nan"))
+        b.w4a16_gemm(*p.args(), 0)                                         # eager: allocates
+        assert_parity(p.result(), Cref, f"eager {rep}")
