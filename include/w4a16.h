@@ -25,9 +25,11 @@
  * launch as row tiles that share one pass over the weights; everything else, the data-parallel
  * kernel included, runs one launch per 16 rows, each streaming the weights again.  Where the
  * SplitK entry points leave every choice to the library (split_k == 0), 17 to 64 rows (with groups of 32 and 64 also
- * fewer) of n <= 65536 columns are one launch of a kernel for decode batches at every group size, unless the others take less time (w4a16_plan_batch reports
- * it; w4a16_plan reports the others): 64 or 128 columns a workgroup, k split no further than by the other launches and
- * with the same reduction and scratch (packed-fp16 adds into C that the kernel zeroes, or plain stores).  And where more than
+ * fewer) of n <= 65536 columns are one launch of a kernel for decode batches at every group size, unless the others
+ * take less time (w4a16_plan_batch reports it; w4a16_plan reports the others): 64 or 128 columns a workgroup, k split
+ * no further than by the other launches and with the same reductions (packed-fp16 adds into C that the kernel zeroes;
+ * with groups of 32 and 64 fixed-point adds for the last m % 16 rows if these are one to four; plain stores where k
+ * is not split).  And where more than
  * one launch would be needed, it is one launch of a kernel for many rows instead, unless that takes longer: tiles
  * of up to 64 or 128 rows x 256 columns, their k ranges shared by persistent workgroups, the sums
  * added in fp32 in the order of k (bit-reproducible between calls that take the same launch: where a call finds no

@@ -53,57 +53,6 @@ enum : int {
     kAtomicPkF16Service = 6  // the phase protocol run by one extra wavefront per workgroup (internal)
 };
 
-// kAtomicFixed: one 64-bit integer atomic add per output element and workgroup.
-//   bits 58..63  arrivals before this one (0..63: split_k <= 64; the last add may carry out of
-//                the word, which is then reset anyway)
-//   bits 52..57  how many of the contributions so far were NaN (they add nothing to the sum)
-//   bits  0..51  sum of (partial * 2^28 + 2^45): fixed point, biased so it never goes negative;
-//                every term is below 2^46 (|partial| is clamped below 2^17, beyond fp16's range),
-//                so 64 of them stay below 2^52.  2^-28 resolves every product of an fp16 value
-//                with a small integer exactly and is finer than the fp32 partial sums' own
-//                last place from 1/16 on.
-// The add returns the previous word, so the workgroup that sees split_k - 1 earlier arrivals
-// holds the complete sum (previous + its own) and finishes the element: one memory round trip,
-// no separate ticket, and a sum that does not depend on arrival order (integer addition).  A NaN
-// among the partial sums makes the result NaN, as with every other reduction; an infinite or
-// huge one is clamped and comes out as an fp16 infinity.
-constexpr int kFixedFracBits = 28;
-constexpr uint64_t kFixedBias = 1ull << 45;
-constexpr int kFixedNanShift = 52;
-constexpr int kFixedArrivalShift = 58;
-constexpr uint64_t kFixedArrival = 1ull << kFixedArrivalShift;
-constexpr uint64_t kFixedSumMask = (1ull << kFixedNanShift) - 1;
-constexpr uint64_t kFixedNanMask = (kFixedArrival - 1) & ~kFixedSumMask;
-constexpr float kFixedClamp = 131071.0f;  // |partial| < 2^17 keeps partial * 2^28 inside the bias
-
-__device__ __forceinline__ uint64_t fixed_contribution(float v)
-{
-    const bool nan = v != v;
-    v = nan ? 0.f : fminf(fmaxf(v, -kFixedClamp), kFixedClamp);
-    const long long q = __double2ll_rn((double)v * (double)(1ull << kFixedFracBits));
-    return (uint64_t)(q + (long long)kFixedBias) + kFixedArrival + (nan ? 1ull << kFixedNanShift : 0ull);
-}
-
-// The total of the word before the last add (`old`) and the last contribution (`mine`); the
-// fields are read from each on its own, so a NaN count of 64 cannot wrap to "none".
-__device__ __forceinline__ float fixed_total(uint64_t old, uint64_t mine, int split_k)
-{
-    const long long q =
-        (long long)((old & kFixedSumMask) + (mine & kFixedSumMask)) - (long long)split_k * (long long)kFixedBias;
-    const float sum = (float)((double)q * (1.0 / (double)(1ull << kFixedFracBits)));
-    return ((old | mine) & kFixedNanMask) ? __builtin_nanf("") : sum;
-}
-
-// After `old = fetch_add(word, mine)`: if this was the last of split_k arrivals, returns true
-// with the total in *total and resets the word to zero for the next call.
-__device__ __forceinline__ bool fixed_finish(uint64_t* word, uint64_t old, uint64_t mine, int split_k, float* total)
-{
-    if ((int)(old >> kFixedArrivalShift) != split_k - 1) return false;
-    *total = fixed_total(old, mine, split_k);
-    __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
-}
-
 // Results and protocol words are stored write-through (the sc1 bit of a buffer store, an
 // agent-scope atomic store elsewhere).  A plain store leaves a dirty line in the die's L2 that
 // the release at the end of the kernel has to find and write back: 0.16 us per launch on the
@@ -2502,7 +2451,8 @@ static double wave_few_us(const Plan& others, int m, int n, int k, int ipg, int 
 }
 
 static int run_batch(const BatchPlan& plan, const void* A, const void* qweight, const void* scales, const void* qzeros,
-                     void* C, int m, int n, int k, int group_size, int bits, const ScratchView& view, hipStream_t stream)
+                     void* C, int m, int n, int k, int group_size, int bits, const ScratchView& view, bool fixed_tail,
+                     hipStream_t stream)
 {
     BatchArgs a;
     a.A = (const _Float16*)A;
@@ -2524,6 +2474,7 @@ static int run_batch(const BatchPlan& plan, const void* A, const void* qweight, 
     a.counts = view.counts;
     a.errors = view.errors;
     a.err_host = view.err_host;
+    a.fixed = fixed_tail && plan.split_k > 1 ? view.fixed : nullptr;
     a.spin_limit = g_spin_limit;
     a.probe_delay = g_probe_delay;
     // (a wave without a chunk takes no part in the zeroing: only where k is not split)
@@ -2674,40 +2625,56 @@ static void plan_batch_few(int m, int n, int k, int group_size, int bits, const 
     }
 }
 
-// The launch of a call that leaves every choice to the library.  It splits k no further than the launch that would
-// run otherwise, `others` (the parts of a sum are added in fp16 in both), and so needs no scratch where that needs none;
-// where the many-row kernel is that other launch, which adds in fp32, it does not split k at all.
+// The launches that a call would make without the batch kernel.
+struct BatchOthers {
+    Plan rows{1, 0, 0, 0};  // of up to 64 rows; with fine groups of 16
+    Plan tail{1, 0, 0, 0};  // fine groups: of the last m % 16 rows behind those of 16
+    bool tail_fixed() const { return tail.split_k > 1 && tail.reduce == W4A16_REDUCE_ATOMIC_FIXED; }
+    bool scratch() const { return (rows.split_k > 1 && rows.reduce != W4A16_REDUCE_ATOMIC_PK_F16) || tail_fixed(); }
+};
+
+// The launch of a call that leaves every choice to the library.  It splits k no further than the launches that would
+// run otherwise, `others`, and adds the parts in fp16 only where they do: the last one to four rows of a call with fine
+// groups, whose launch of their own adds in fixed point, are added in fixed point here as well.  So it needs no scratch
+// where they need none; where the many-row kernel is that other launch, which adds in fp32, it does not split k at all.
+// The fixed-point adds, whose round trip to memory ends the launch, cost 1.3 us more than adds in fp16, two strips' 2.2 (377
+// shapes; m; n x k, groups of 64: 17; 4096 x 4096: 5.7 -> 6.9 us, a launch per 16 rows 9.9, k whole 9.1; 20; 6864 x 1472: 5.9 ->
+// 8.5 with k in three parts, 6.0 whole).
 // With groups of 32 and 64 it stands against a launch per 16 rows and always wins (1.7 to 1.9 times as fast on average);
 // otherwise the estimates have to be 5 % apart, with two strips, which they tell less well, 10 %.  On 26,000 random calls
 // of 17 to 64 rows, 1.35 times as fast on average; of those that go here 10 are more than 5 % slower than before, at
 // worst 9 %.  The phase words cover n <= 65536.
-static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* plan, Plan* others)
+static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* plan, BatchOthers* others)
 {
     *plan = BatchPlan{0, 0};
+    *others = BatchOthers{};
     const bool fine_groups = group_size < 128;
     if ((m <= 16 && !fine_groups) || m > 64 || (size_t)n > 16 * (size_t)kPhaseOrigins || k >= 1 << 22) return W4A16_OK;
-    const int rc = make_plan(fine_groups && m > 16 ? 16 : m, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO, others, bits);
+    int rc = make_plan(fine_groups && m > 16 ? 16 : m, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO, &others->rows, bits);
     if (rc != W4A16_OK) return rc;
     if (m <= 16) {
-        plan_batch_few(m, n, k, group_size, bits, *others, plan);
+        plan_batch_few(m, n, k, group_size, bits, others->rows, plan);
         return W4A16_OK;
     }
     const int chunks = (k + 127) / 128, ipg = fine_groups ? group_size / 32 : 4;
     RowsPlan rows{0, 0, true};
+    int split_most = others->rows.split_k;
     if (fine_groups) {
-        const int rc_rows = plan_many_rows(m, n, k, group_size, bits, true, &rows, nullptr);
-        if (rc_rows != W4A16_OK) return rc_rows;
+        rc = plan_many_rows(m, n, k, group_size, bits, true, &rows, nullptr);
+        if (rc == W4A16_OK && m % 16) rc = make_plan(m % 16, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO, &others->tail, bits);
+        if (rc != W4A16_OK) return rc;
+        if (m % 16 && !others->tail_fixed() && others->tail.split_k < split_most) split_most = others->tail.split_k;
     }
-    const bool may_split = others->split_k > 1 && others->reduce != W4A16_REDUCE_ATOMIC_PK_F16 && !rows.row_blocks;
+    const bool may_split = others->rows.split_k > 1 && others->rows.reduce != W4A16_REDUCE_ATOMIC_PK_F16 && !rows.row_blocks;
     double best = 1e30;
     for (int strips = 1; strips <= 2; ++strips) {
         const int tiles = (n + 64 * strips - 1) / (64 * strips);
         int most = chunks * strips / kBatchWaves;  // every wave has a chunk
-        most = most < others->split_k ? most : others->split_k;
+        most = most < split_most ? most : split_most;
         most = most < 1 || !may_split ? 1 : most < 32 ? most : 32;
         for (int s : {1, 256 / tiles, 256 / tiles + 1, 512 / tiles, most}) {
             s = s < 1 ? 1 : s < most ? s : most;
-            const double us = batch_us(strips, s, m, n, k, ipg, bits);
+            const double us = batch_us(strips, s, m, n, k, ipg, bits) + (s > 1 && others->tail_fixed() ? strips == 1 ? 1.3 : 2.2 : 0.0);
             if (us < best) {
                 best = us;
                 *plan = BatchPlan{s, strips};
@@ -2715,7 +2682,7 @@ static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* 
         }
     }
     if (rows.row_blocks && best >= 0.85 * fitted_rows_us(rows, m, n, k, ipg, bits)) *plan = BatchPlan{0, 0};
-    if (!fine_groups && best >= (plan->strips == 2 ? 0.9 : 0.95) * stream_rows_us(*others, m, n, k, bits)) *plan = BatchPlan{0, 0};
+    if (!fine_groups && best >= (plan->strips == 2 ? 0.9 : 0.95) * stream_rows_us(others->rows, m, n, k, bits)) *plan = BatchPlan{0, 0};
     return W4A16_OK;
 }
 
@@ -2794,20 +2761,22 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
                                  scratch_kind == kScratchLibrary;
     if (librarys_choice && (m > 16 || group_size < 128) && m <= 16 * kStreamMaxRowTiles) {
         BatchPlan batch;
-        Plan others;
+        BatchOthers others;
         rc = plan_batch(m, n, k, group_size, bits, &batch, &others);
         if (rc != W4A16_OK) return rc;
         if (batch.split_k) {
             ScratchView view;
-            if (others.split_k > 1 && others.reduce != W4A16_REDUCE_ATOMIC_PK_F16) {
+            if (others.scratch()) {
                 ScratchNeed need;
                 need.phase_split = batch.split_k > 1 ? batch.split_k : 0;
+                need.fixed_words = batch.split_k > 1 && others.tail_fixed() ? (size_t)(m % 16) * n : 0;
                 need.n = n;
                 rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);
                 // (under capture there may be scratch for the other launch's split alone, which looks for itself)
                 if (rc != W4A16_OK && rc != W4A16_ERR_STATE) return rc;
             }
-            if (rc == W4A16_OK) return run_batch(batch, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, view, (hipStream_t)stream_v);
+            if (rc == W4A16_OK)
+                return run_batch(batch, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, view, others.tail_fixed(), (hipStream_t)stream_v);
         }
     }
     if (librarys_choice) {
@@ -2836,7 +2805,7 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
     int rows_per_launch = stream_rows_ok(group_size, dp, tile_cols, waves, reduce) ? 16 * kStreamMaxRowTiles : 16;
     if (librarys_choice && m > 16 * kStreamMaxRowTiles) {  // (64 rows of a longer call: as a call of 64)
         BatchPlan batch;
-        Plan others;
+        BatchOthers others;
         rc = plan_batch(16 * kStreamMaxRowTiles, n, k, group_size, bits, &batch, &others);
         if (rc != W4A16_OK) return rc;
         if (batch.split_k) rows_per_launch = 16 * kStreamMaxRowTiles;
@@ -3189,7 +3158,7 @@ int w4a16_plan_batch(int bits, int m, int n, int k, int group_size, int* split_k
     if ((bits == 2 && n % 16 != 0) || (bits == 3 && n % 32 != 0)) return W4A16_ERR_SHAPE;
     if ((unsigned long long)k * (unsigned long long)n * (unsigned)bits / 8 >= (1ull << 31)) return W4A16_ERR_UNSUPPORTED;
     w4a16::BatchPlan plan;
-    w4a16::Plan others;
+    w4a16::BatchOthers others;
     const int rc_plan = w4a16::plan_batch(m, n, k, group_size, bits, &plan, &others);
     if (rc_plan != W4A16_OK) return rc_plan;
     if (split_k) *split_k = plan.split_k;

@@ -10,7 +10,7 @@ static hipError_t launch_batch_one(const BatchArgs& a, hipStream_t stream)
     const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kBatchLdsBytes<MT>);
     if (e != hipSuccess) return e;
     const int packed = a.m | a.param_shift << 7 | (int)((unsigned)a.chunks_base << 9);
-    const BatchRest rest{a.flags, a.counts, a.errors, a.err_host, a.spin_limit, a.probe_delay};
+    const BatchRest rest{a.flags, a.counts, a.errors, a.err_host, a.fixed, a.spin_limit, a.probe_delay};
     hipLaunchKernelGGL(kern, dim3((unsigned)a.split_k, (unsigned)a.tiles), dim3(64 * kBatchWaves), kBatchLdsBytes<MT>, stream, a.A,
                        a.qweight, a.scales, a.qzeros, a.C, packed, a.n, a.k, a.split_k | a.chunks_rem << 16, rest);
     return hipGetLastError();

@@ -19,7 +19,8 @@
 // us per call, cold weights, before -> now (m; n x k): 64; 8192 x 8192: 22.0 -> 15.1, 64; 4096 x 4096: 14.0 -> 7.5,
 // 32; 4096 x 4096: 9.1 -> 5.7, 64; 28672 x 8192: 55 -> 37, 33; 1024 x 1024: 6.7 -> 4.9; groups of 64, 29; 8192 x 8192: 21.9 -> 12.6.
 // Sums of the parts through fp32 scratch and a ticket instead of the packed-fp16 adds: 17.1 instead of 15.1 us, 10.0
-// instead of 7.5 (m = 64, n = k = 8192 and 4096).
+// instead of 7.5 (m = 64, n = k = 8192 and 4096).  One to four last rows of a call with fine groups, which the launch per 16 rows adds
+// in fixed point, are added so here too: 5.7 -> 6.9 us (m = 17, n = k = 4096, groups of 64).
 #pragma once
 #include "w4a16_rows.hpp"
 
@@ -42,6 +43,7 @@ struct BatchArgs {
     uint32_t* counts;
     uint32_t* errors;
     uint32_t* err_host;
+    uint64_t* fixed;              // not null: the rows from the last multiple of 16 on are added in fixed point, here [m % 16, n]
     int spin_limit, probe_delay;
 };
 // What a wave does not need before its first loads.
@@ -50,6 +52,7 @@ struct BatchRest {
     uint32_t* counts;
     uint32_t* errors;
     uint32_t* err_host;
+    uint64_t* fixed;
     int spin_limit, probe_delay;
 };
 
@@ -292,6 +295,9 @@ __global__ void __launch_bounds__(64 * kBatchWaves, 2) gemm_batch_kernel(const _
     // ---- split k, first part of the phase protocol: this workgroup's call count, and the zeros of slice 0, an eighth by
     // every wave.  They precede a wave's loads, so that its first wait for those covers them.
     const bool split = split_k > 1;
+    // the rows that are added in fp16; those behind them are added in fixed point
+    constexpr bool kFixedRows = MT > 1 && IPG < 4;
+    const int half_rows = kFixedRows && split && rest.fixed ? m & ~15 : m;
     const uint32_t origin = (uint32_t)tile * (4 * STRIPS);
     uint32_t count_word = 0;
     if (split) {
@@ -300,7 +306,7 @@ __global__ void __launch_bounds__(64 * kBatchWaves, 2) gemm_batch_kernel(const _
 #pragma unroll
             for (int u = tid; u < 16 * MT * 8 * STRIPS; u += 64 * kBatchWaves) {
                 const int row = u / (8 * STRIPS), col = tile * (64 * STRIPS) + 8 * (u % (8 * STRIPS));
-                const uint32_t off = row < m && col < n ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
+                const uint32_t off = row < half_rows && col < n ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
                 __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0u, 0u, 0u, 0u}, rs_c, off, 0, kRowsDeviceScope);
             }
         }
@@ -403,7 +409,21 @@ __global__ void __launch_bounds__(64 * kBatchWaves, 2) gemm_batch_kernel(const _
         v.x *= kNatScale<BITS>;
         v.y *= kNatScale<BITS>;
         const uint32_t off = row < m && col < n ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
-        if (split) {
+        if (kFixedRows && row >= half_rows) {
+            if (off != kOutside) {
+                uint64_t* const word = rest.fixed + (size_t)(row - half_rows) * n + col;
+                const uint64_t mine[2] = {fixed_contribution(v.x), fixed_contribution(v.y)};
+                uint64_t old[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) old[i] = __hip_atomic_fetch_add(word + i, mine[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    float total;
+                    if (fixed_finish(word + i, old[i], mine[i], split_k, &total))
+                        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, (_Float16)total), rs_c, off + 2u * i, 0, kRowsDeviceScope);
+                }
+            }
+        } else if (split) {
             const half2_t h = {(_Float16)v.x, (_Float16)v.y};
             __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(h, rs_c, off, 0, 0);
         } else {

@@ -254,6 +254,57 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes)
 // neighbouring tile's, which then has to fetch it again (n = 3480, k = 2176, m = 4, unsplit 16-column tiles: 4.2 -> 4.5).
 constexpr int kWeightLoadAux = 2;  // the builtin's aux bit 1: `nt` on gfx950
 
+// Fixed-point adds (kAtomicFixed, and the last rows of the batch kernel): one 64-bit integer atomic add per output element and workgroup.
+//   bits 58..63  arrivals before this one (0..63: split_k <= 64; the last add may carry out of
+//                the word, which is then reset anyway)
+//   bits 52..57  how many of the contributions so far were NaN (they add nothing to the sum)
+//   bits  0..51  sum of (partial * 2^28 + 2^45): fixed point, biased so it never goes negative;
+//                every term is below 2^46 (|partial| is clamped below 2^17, beyond fp16's range),
+//                so 64 of them stay below 2^52.  2^-28 resolves every product of an fp16 value
+//                with a small integer exactly and is finer than the fp32 partial sums' own
+//                last place from 1/16 on.
+// The add returns the previous word, so the workgroup that sees split_k - 1 earlier arrivals
+// holds the complete sum (previous + its own) and finishes the element: one memory round trip,
+// no separate ticket, and a sum that does not depend on arrival order (integer addition).  A NaN
+// among the partial sums makes the result NaN, as with every other reduction; an infinite or
+// huge one is clamped and comes out as an fp16 infinity.
+constexpr int kFixedFracBits = 28;
+constexpr uint64_t kFixedBias = 1ull << 45;
+constexpr int kFixedNanShift = 52;
+constexpr int kFixedArrivalShift = 58;
+constexpr uint64_t kFixedArrival = 1ull << kFixedArrivalShift;
+constexpr uint64_t kFixedSumMask = (1ull << kFixedNanShift) - 1;
+constexpr uint64_t kFixedNanMask = (kFixedArrival - 1) & ~kFixedSumMask;
+constexpr float kFixedClamp = 131071.0f;  // |partial| < 2^17 keeps partial * 2^28 inside the bias
+
+__device__ __forceinline__ uint64_t fixed_contribution(float v)
+{
+    const bool nan = v != v;
+    v = nan ? 0.f : fminf(fmaxf(v, -kFixedClamp), kFixedClamp);
+    const long long q = __double2ll_rn((double)v * (double)(1ull << kFixedFracBits));
+    return (uint64_t)(q + (long long)kFixedBias) + kFixedArrival + (nan ? 1ull << kFixedNanShift : 0ull);
+}
+
+// The total of the word before the last add (`old`) and the last contribution (`mine`); the
+// fields are read from each on its own, so a NaN count of 64 cannot wrap to "none".
+__device__ __forceinline__ float fixed_total(uint64_t old, uint64_t mine, int split_k)
+{
+    const long long q =
+        (long long)((old & kFixedSumMask) + (mine & kFixedSumMask)) - (long long)split_k * (long long)kFixedBias;
+    const float sum = (float)((double)q * (1.0 / (double)(1ull << kFixedFracBits)));
+    return ((old | mine) & kFixedNanMask) ? __builtin_nanf("") : sum;
+}
+
+// After `old = fetch_add(word, mine)`: if this was the last of split_k arrivals, returns true
+// with the total in *total and resets the word to zero for the next call.
+__device__ __forceinline__ bool fixed_finish(uint64_t* word, uint64_t old, uint64_t mine, int split_k, float* total)
+{
+    if ((int)(old >> kFixedArrivalShift) != split_k - 1) return false;
+    *total = fixed_total(old, mine, split_k);
+    __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
 // A wait of the phase protocol ran out (one lane calls this): count it, raise the sticky word the
 // host looks at before its next call, and add NaN to the first column pair of the tile, so that
 // the output cannot pass for a result.  `c_off` is a byte offset inside C.

@@ -1743,6 +1743,42 @@ def test_batch_few_rows(oracle, bits, m, n, k, g, plan):
 
 
 @pytest.mark.parametrize("bits", [4, 8, 3, 2])
+@pytest.mark.parametrize("m,n,k,g", [(17, 288, 4160, 64), (18, 2080, 5056, 64), (35, 288, 4160, 32), (36, 544, 3008, 32),
+                                     (49, 32, 4160, 32), (52, 96, 1984, 64), (35, 4128, 10048, 64)])  # (the last: two strips)
+def test_batch_rows_last_rows_add_in_fixed_point(oracle, bits, m, n, k, g):
+    """Fine groups: the last one to four rows of a split call keep the fixed-point sum of the launch that they would have
+    alone.  Their parts lie beyond fp16's range and cancel; every sum is a whole multiple of one power of two, below 2^24 of
+    them, so the result is exact.  The rows before them, and calls of such rows alone in between, are as ever."""
+    import torch
+    plan, tail = b.w4a16_plan_batch(bits, m, n, k, g), m % 16
+    alone = b.w4a16_plan_bits(bits, tail, n, k, g)
+    assert plan["split_k"] > 1 and alone["split_k"] > 1 and alone["reduce"] == b.REDUCE_ATOMIC_FIXED
+    A, qw, s, qz = random_case_3bit(m, n, k, g, 83) if bits == 3 else random_case_bits(m, n, k, g, bits, 83)
+    top = (1 << bits) - 1
+    qw[:, -1], qz[:, -1] = -1, 0                # the last columns: q = 2^bits - 1, z = 0
+    s[:, -1] = 1.0
+    per_slice = 8 * 64 // plan["tile_cols"]     # k parts of a workgroup, in chunks of 128; slice 0 has the longest of them
+    chunks, more = divmod(-(-k // 128), plan["split_k"] * per_slice)
+    longest = 128 * (chunks * per_slice + min(more, per_slice))
+    unit = 2.0 ** np.floor(np.log2(131008 / (top * longest)))               # its sum: between 65504 and 131008
+    A[m - tail:] = np.where(np.arange(k) < k // 2, unit, -unit)
+    for i in range(tail):
+        A[m - tail + i, k - 1 - i:] = 0.0       # (1 + i) units of the second half are missing
+    Cref, _ = oracle.gemm_3bit(A, qw, s, qz, g) if bits == 3 else oracle.gemm_bits(A, qw, s, qz, g, bits)
+    want = unit * top * (1 + np.arange(tail))
+    assert np.array_equal(Cref[m - tail:, -1], want)
+    p, few = DeviceProblem(A, qw, s, qz, g), DeviceProblem(A[m - tail:], qw, s, qz, g)
+    for rep in range(3):
+        for q in (p, few):
+            q.C.fill_(float("nan"))
+            MANY_ROWS_GEMM[bits](*q.args(), 0)
+        assert np.array_equal(p.result()[m - tail:, -1], want.astype(np.float16)), rep
+        assert np.array_equal(few.result()[:, -1], want.astype(np.float16)), rep
+        assert_parity(p.result()[:m - tail], Cref[:m - tail], f"bits={bits} m={m} n={n} k={k} g={g} call {rep}")
+    assert b.w4a16_phase_timeouts() == 0
+
+
+@pytest.mark.parametrize("bits", [4, 8, 3, 2])
 @pytest.mark.parametrize("m,n,k,g", [(64, 160, 1152, 128), (64, 160, 1120, 32), (48, 160, 1984, 64)])
 def test_batch_rows_one_hot_bit_exact(bits, m, n, k, g):
     """One non-zero term per row, swept over all k: every operand lands where it belongs."""
