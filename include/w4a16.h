@@ -52,8 +52,10 @@
  * as it found it (sums back at zero, counters one call further).  By default that memory is the
  * library's, one set of buffers per device (at most 16 * n 64-bit words, split_k * m * n floats
  * for the workspace flavour, for the in-kernel zeroing 16 KiB * (1 + split_k) per distinct
- * split_k used, and 128 MiB for the sums that the many-row kernel's workgroups hand over), allocated by the first call that needs it (hipMalloc + a synchronous clear; use
- * w4a16_reserve_scratch to do that ahead of time) and never moved or freed before
+ * split_k used, and 128 MiB for the sums that the many-row kernel's workgroups hand over), allocated by the first call
+ * that needs it (hipMalloc + a synchronous clear; use w4a16_reserve_scratch to do that ahead of time; a launch of the
+ * kernel for decode batches also allocates what the launches in whose place it runs would need, so that a captured call
+ * of other rows, which may be one of those, finds it) and never moved or freed before
  * w4a16_release_scratch: a buffer that is outgrown stays alive, so a HIP graph captured earlier
  * keeps working.  A call that would have to allocate while its stream is being captured returns
  * W4A16_ERR_STATE instead (the many-row kernel then shares no tile between workgroups and needs

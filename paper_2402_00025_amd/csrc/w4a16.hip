@@ -1313,6 +1313,10 @@ struct ScratchNeed {
     bool rows = false;    // the many-row kernel's partial sums and words
     bool reserve = false; // these as well, or an error: no later call may allocate them
     int phase_split = 0;  // 0, or the split_k whose flags and counts the call needs
+    // What the launches that this one runs in the place of would need, as above.  Allocated as well, but no call fails for want
+    // of it under capture: a later call of other rows may be one of those, be captured, and find what they would have left.
+    size_t others_fixed_words = 0;
+    int others_phase_split[2] = {0, 0};
     int n = 0;            // columns of the call (the phase words cover tile origins n0 / 16)
 };
 enum : int { kScratchLibrary = 0, kScratchStatic = 1 };
@@ -2035,16 +2039,25 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
             }
         }
     }
-    if (rc == W4A16_OK && need.phase_split && !(s.phase_err.ptr && s.err_host)) {
-        rc = grow(s, s.phase_err, sizeof(uint32_t), 256, stream, &grew);
-        if (rc == W4A16_OK && !s.err_host) {
-            if (!W4A16_HIP(hipHostMalloc((void**)&s.err_host, 256, hipHostMallocMapped))) return W4A16_ERR_HIP;
-            *s.err_host = 0u;
+    auto grow_phase = [&](int split_k) {
+        if (!(s.phase_err.ptr && s.err_host)) {
+            const int rce = grow(s, s.phase_err, sizeof(uint32_t), 256, stream, &grew);
+            if (rce != W4A16_OK) return rce;
+            if (!s.err_host) {
+                if (!W4A16_HIP(hipHostMalloc((void**)&s.err_host, 256, hipHostMallocMapped))) return (int)W4A16_ERR_HIP;
+                *s.err_host = 0u;
+            }
         }
-    }
-    if (rc == W4A16_OK && need.phase_split)
-        rc = grow(s, s.phase_level[need.phase_split], phase_level_words(need.phase_split) * sizeof(uint32_t), 0, stream, &grew);
+        return grow(s, s.phase_level[split_k], phase_level_words(split_k) * sizeof(uint32_t), 0, stream, &grew);
+    };
+    if (rc == W4A16_OK && need.phase_split) rc = grow_phase(need.phase_split);
     if (rc != W4A16_OK) return rc;
+    for (int split_k : need.others_phase_split)
+        if (rc == W4A16_OK && split_k) rc = grow_phase(split_k);
+    if (rc == W4A16_OK && need.others_fixed_words)
+        rc = grow(s, s.fixed, (need.others_fixed_words > rows16 ? need.others_fixed_words : rows16) * sizeof(uint64_t),
+                  (size_t)16 * 16384 * sizeof(uint64_t), stream, &grew);
+    if (rc != W4A16_OK && rc != W4A16_ERR_STATE) return rc;
     if (grew && !W4A16_HIP(hipDeviceSynchronize())) return W4A16_ERR_HIP;
     out->sums = (float*)s.sums.ptr;
     out->partials = (float*)s.partials.ptr;
@@ -2629,7 +2642,9 @@ static void plan_batch_few(int m, int n, int k, int group_size, int bits, const 
 struct BatchOthers {
     Plan rows{1, 0, 0, 0};  // of up to 64 rows; with fine groups of 16
     Plan tail{1, 0, 0, 0};  // fine groups: of the last m % 16 rows behind those of 16
+    static int phase_split(const Plan& p) { return p.split_k > 1 && p.reduce == W4A16_REDUCE_ATOMIC_PK_F16_PHASE ? p.split_k : 0; }
     bool tail_fixed() const { return tail.split_k > 1 && tail.reduce == W4A16_REDUCE_ATOMIC_FIXED; }
+    bool rows_shared = false;  // the many-row kernel's, with tiles shared between workgroups
     bool scratch() const { return (rows.split_k > 1 && rows.reduce != W4A16_REDUCE_ATOMIC_PK_F16) || tail_fixed(); }
 };
 
@@ -2661,6 +2676,7 @@ static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* 
     int split_most = others->rows.split_k;
     if (fine_groups) {
         rc = plan_many_rows(m, n, k, group_size, bits, true, &rows, nullptr);
+        others->rows_shared = rows.row_blocks && !rows.whole;
         if (rc == W4A16_OK && m % 16) rc = make_plan(m % 16, n, k, group_size, false, 0, 0, 0, W4A16_REDUCE_AUTO, &others->tail, bits);
         if (rc != W4A16_OK) return rc;
         if (m % 16 && !others->tail_fixed() && others->tail.split_k < split_most) split_most = others->tail.split_k;
@@ -2770,6 +2786,10 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
                 ScratchNeed need;
                 need.phase_split = batch.split_k > 1 ? batch.split_k : 0;
                 need.fixed_words = batch.split_k > 1 && others.tail_fixed() ? (size_t)(m % 16) * n : 0;
+                need.others_phase_split[0] = BatchOthers::phase_split(others.rows);
+                need.others_phase_split[1] = BatchOthers::phase_split(others.tail);
+                need.rows = others.rows_shared;
+                need.others_fixed_words = group_size < 128 ? (size_t)4 * n : 0;  // (of another call's last one to four rows)
                 need.n = n;
                 rc = resolve_scratch(scratch_kind, (hipStream_t)stream_v, need, &view);
                 // (under capture there may be scratch for the other launch's split alone, which looks for itself)
@@ -2875,6 +2895,7 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
             need.fixed_words = mode == kAtomicFixed ? (size_t)m * n : 0;
             need.ticket_count = mode == kAtomicF32 || mode == kWorkspace ? (size_t)a.tiles : 0;
             need.phase_split = mode == kAtomicPkF16Phase ? plan.split_k : 0;
+            need.others_fixed_words = need.phase_split && group_size < 128 && librarys_choice ? (size_t)4 * n : 0;  // (as above)
             ScratchView view;
             rc = resolve_scratch(scratch_kind, stream, need, &view);
             if (rc != W4A16_OK) return rc;

@@ -154,3 +154,25 @@ def test_route_of_batch_rows(stand_in):
     assert gemm(40, 1024, 4096, 128, stream=64)[:2] == (OK, 1)
     assert L.w4a16_release_scratch() == OK
     """)
+
+
+def test_scratch_of_a_batch_call_serves_captured_calls_of_other_rows(stand_in):
+    """What an eager call leaves is what the launches in whose place the batch kernel runs would have left: a call of
+    other rows that is captured after it is not refused."""
+    stand_in("""
+    many = (17, 20, 24, 32, 33, 40, 48, 50, 63, 64)
+    matrices = [(4096, 4096), (8192, 8192), (5120, 13824), (11008, 4096), (4096, 14336), (28672, 8192), (1024, 4096)]
+    for bits in (4, 8, 3, 2):
+        for eager, captured, groups in ((many, many, (128, 256)), ((5, 8, 12, 16), (5, 8, 12, 16), (32, 64)),
+                                        ((63, 64), (65, 100), (32, 64)), ((24, 32), (17, 20, 35), (32, 64))):
+            for n, k in matrices:
+                if eager == (24, 32) and n * k > 1 << 24: continue     # (there many rows come into it)
+                for g in groups:
+                    for m in eager:
+                        assert L.w4a16_release_scratch() == OK
+                        assert gemm(m, n, k, g, bits)[0] == OK
+                        capturing.value = 1
+                        for later in captured:
+                            assert gemm(later, n, k, g, bits)[0] == OK, (bits, n, k, g, m, later)
+                        capturing.value = 0
+    """)
