@@ -2656,7 +2656,9 @@ struct BatchOthers {
 // shapes; m; n x k, groups of 64: 17; 4096 x 4096: 5.7 -> 6.9 us, a launch per 16 rows 9.9, k whole 9.1; 20; 6864 x 1472: 5.9 ->
 // 8.5 with k in three parts, 6.0 whole).
 // With groups of 32 and 64 it stands against a launch per 16 rows and always wins (1.7 to 1.9 times as fast on average);
-// otherwise the estimates have to be 5 % apart, with two strips, which they tell less well, 10 %.  On 26,000 random calls
+// otherwise the estimates have to be 5 % apart, with two strips, which they tell less well, 10 %.  Beyond 28672 columns or k,
+// where nothing was fitted, they err by up to a quarter against the many-row kernel and, with 8-bit fields and two strips, against the
+// streaming kernel: there they have to be 23 % apart (m = 58, n = 35216, k = 6656, 8 bits, groups of 256: 66 us there, 76 here).  On 26,000 random calls
 // of 17 to 64 rows, 1.35 times as fast on average; of those that go here 10 are more than 5 % slower than before, at
 // worst 9 %.  The phase words cover n <= 65536.
 static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* plan, BatchOthers* others)
@@ -2697,8 +2699,10 @@ static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* 
             }
         }
     }
-    if (rows.row_blocks && best >= 0.85 * fitted_rows_us(rows, m, n, k, ipg, bits)) *plan = BatchPlan{0, 0};
-    if (!fine_groups && best >= (plan->strips == 2 ? 0.9 : 0.95) * stream_rows_us(others->rows, m, n, k, bits)) *plan = BatchPlan{0, 0};
+    const bool fitted = n <= 28672 && k <= 28672;
+    if (rows.row_blocks && best >= (fitted ? 0.85 : 0.77) * fitted_rows_us(rows, m, n, k, ipg, bits)) *plan = BatchPlan{0, 0};
+    const double margin = plan->strips == 1 ? 0.95 : fitted || bits != 8 ? 0.9 : 0.77;
+    if (!fine_groups && best >= margin * stream_rows_us(others->rows, m, n, k, bits)) *plan = BatchPlan{0, 0};
     return W4A16_OK;
 }
 

@@ -134,6 +134,8 @@ def test_route_of_batch_rows(stand_in):
     for m in (1, 2, 3):                  # sums that do not meet in fp16
         assert batch(m, 8192, 8192, 32) == batch(m, 5120, 13824, 64) == (0, 0)
     assert batch(16, 2048, 2048, 32) == batch(16, 65536, 512, 32, 8) == (0, 0)
+    # beyond the sizes that the estimates are fitted to: calls that the batch kernel was measured to slow down
+    assert batch(58, 35216, 6656, 256, 8) == batch(47, 1424, 179712, 256, 8) == batch(29, 42376, 320, 64) == (0, 0)
     assert batch(16, 4096, 4096, 128) == batch(65, 4096, 4096, 128) == batch(40, 65544, 4096, 128) == (0, 0)
     assert L.w4a16_plan_batch(5, 40, 4096, 4096, 128, None, None) == UNSUPPORTED
     assert L.w4a16_plan_batch(4, 40, 4096, 4096, 128, None, None) == OK
