@@ -196,6 +196,48 @@ def test_wait_that_runs_out_is_loud(oracle, tile_cols, waves, split_k, k):
     assert b.w4a16_phase_timeouts() == 0
 
 
+@pytest.mark.parametrize("m,k,g,plan", [(40, 4096, 64, (4, 64)), (64, 1536, 128, (3, 128)), (46, 2528, 32, (5, 128)),
+                                        (35, 4096, 32, (4, 64))])
+def test_wait_that_runs_out_is_loud_in_a_decode_batch(oracle, m, k, g, plan):
+    """The same for the decode-batch kernel, which the library alone chooses: one strip and two, and with last rows that are
+    added in fixed point."""
+    import torch
+    n, n_max = 512, 1024
+    nbytes = b.w4a16_workspace_bytes(n_max)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    b.w4a16_set_workspace(ws, nbytes, n_max, stream=torch.cuda.current_stream())
+    A, qw, s, qz = random_case(m, n, k, g, seed=96)
+    Cref, _ = oracle.gemm(A, qw, s, qz, g)
+    p = DeviceProblem(A, qw, s, qz, g)
+    split_k, cols = plan
+    assert b.w4a16_plan_batch(4, m, n, k, g) == dict(split_k=split_k, tile_cols=cols)
+    b.w4a16_gemm(*p.args(), 0)                                             # a good call first
+    assert_parity(p.result(), Cref, "before the corruption")
+    assert b.w4a16_phase_timeouts() == 0
+    level = 64 + n_max // 16 + 4096 * ((split_k - 2) + ((split_k - 1) * split_k // 2 - 1))
+    counts = ws.view(torch.int32)[level + 4096: level + 4096 * (1 + split_k)].view(4096, split_k)
+    used = (counts != 0).any(dim=1).nonzero().flatten().cpu().numpy()
+    assert np.array_equal(used, np.arange(0, n // 16, cols // 16))         # a set of words per tile
+    counts[:, 1:] += 5
+    torch.cuda.synchronize()
+    b.w4a16_set_phase_spin_limit(4)
+    p.C.fill_(0.0)
+    b.w4a16_gemm(*p.args(), 0)                                             # ends normally, wrong and loud
+    torch.cuda.synchronize()
+    assert b.w4a16_phase_timeouts() == (split_k - 1) * (n // cols)
+    poisoned = torch.isnan(p.C[0].float()).nonzero().flatten().cpu().numpy()
+    assert np.array_equal(poisoned, np.sort(np.concatenate([np.arange(0, n, cols), np.arange(1, n, cols)])))   # first pair of every tile
+    with pytest.raises(b.W4A16Error) as sticky:
+        b.w4a16_gemm(*p.args(), 0)
+    assert sticky.value.code == b.ERR_STATE
+    b.w4a16_set_phase_spin_limit(0)
+    b.w4a16_release_scratch()                                              # also forgets the binding
+    p.C.fill_(float("nan"))
+    b.w4a16_gemm(*p.args(), 0)
+    assert_parity(p.result(), Cref, "after the release")
+    assert b.w4a16_phase_timeouts() == 0
+
+
 def test_nan_and_infinity_through_the_fixed_point_adds(oracle):
     """Up to four rows with a split: a NaN activation makes its whole output row NaN (as the
     definition and every other reduction do), an infinite one gives NaN or infinities, and the
