@@ -178,3 +178,18 @@ def test_scratch_of_a_batch_call_serves_captured_calls_of_other_rows(stand_in):
                             assert gemm(later, n, k, g, bits)[0] == OK, (bits, n, k, g, m, later)
                         capturing.value = 0
     """)
+
+
+def test_parity_cases_reach_every_batch_kernel():
+    """Every instantiation of the batch kernel (row blocks, field width, groups, strips) runs in a parity case."""
+    from paper_2402_00025_amd import binding as b
+    from test_gpu_parity import BATCH, BATCH_FEW
+    reached = set()
+    for bits, m, n, k, g in ([(w, m, -(-n // 32) * 32 if w in (2, 3) else n, k, g) for m, n, k, g, _ in BATCH for w in (4, 8, 3, 2)] +
+                             [case[:5] for case in BATCH_FEW]):
+        plan = b.w4a16_plan_batch(bits, m, n, k, g)
+        if plan:
+            reached.add(((m + 15) // 16, bits, min(g, 128), plan["tile_cols"]))
+    every = {(blocks, bits, g, cols) for blocks in (1, 2, 3, 4) for bits in (4, 8, 3, 2) for g in (32, 64, 128)
+             for cols in (64, 128) if blocks > 1 or g < 128}
+    assert reached == every, every - reached

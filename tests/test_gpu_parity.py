@@ -271,7 +271,8 @@ ROW_TILES = [
     (64, 136, 1024, 128, 8, 0, 0, 0),      # one group per part: ring depth 1
     (64, 264, 1280, 256, 2, 0, 0, 0),      # group_size 256
     (65, 264, 1024, 128, 2, 0, 0, 0),      # 64 rows in one launch, one more in a second
-    (150, 200, 1024, 128, 0, 0, 0, 0),     # 64 + 64 + 22, the library's split
+    (150, 200, 1024, 128, 0, 0, 0, 0),     # the library's choice: the many-row kernel
+    (150, 200, 1024, 128, 4, 0, 0, 0),     # 64 + 64 + 22
     (40, 264, 1024, 64, 2, 0, 0, 0),       # group_size 64: one launch per 16 rows
     (40, 264, 1024, 128, 2, 64, 2, 1),     # 64-column tiles asked for: one launch per 16 rows
 ]
@@ -681,9 +682,9 @@ def _case_and_ref(oracle, bits, m, n, k, g, seed):
 
 @pytest.mark.parametrize("bits", [8, 3, 2])
 @pytest.mark.parametrize("m,n,k,g,split_k", [
-    (17, 288, 1024, 128, 0),      # two row tiles, the second with one row; ragged last column tile
+    (17, 288, 1024, 128, 4),      # two row tiles, the second with one row; ragged last column tile
     (40, 544, 2048, 128, 4),      # three row tiles
-    (64, 288, 1408, 128, 0),      # four row tiles, 11 groups (uneven shares)
+    (64, 288, 1408, 128, 11),     # four row tiles, one group per part
     (33, 320, 1024, 256, 2),      # group_size 256
     (150, 288, 1024, 128, 2),     # three launches of 64, 64 and 22 rows
     (48, 288, 512, 64, 2),        # group_size 64: one launch per 16 rows
@@ -700,6 +701,22 @@ def test_row_tiles_other_field_widths(oracle, bits, m, n, k, g, split_k):
         assert_parity(p.result(), Cref, f"{bits}-bit m={m} n={n} k={k} g={g} S={split_k} call {call}")
     pl = b.w4a16_plan_bits(bits, m, n, k, g, split_k=split_k)
     assert pl["tile_cols"] == (256 if g >= 128 else 64)     # the plan of one launch: row tiles where the streaming kernel takes them
+    assert b.w4a16_phase_timeouts() == 0
+
+
+@pytest.mark.parametrize("bits,m,n,k", [(8, 29, 16416, 640), (8, 47, 8224, 3200), (8, 61, 16608, 3712), (3, 23, 16512, 640),
+                                        (3, 48, 16448, 1664), (2, 18, 16544, 1664), (2, 41, 16640, 3712), (4, 20, 16608, 1280),
+                                        (4, 44, 16544, 2176)])
+def test_row_tiles_library_plan(oracle, bits, m, n, k):
+    """Calls of 17 to 64 rows that the library itself sends to the streaming kernel's row tiles: uneven shares of k."""
+    pl = b.w4a16_plan_bits(bits, m, n, k, 128)
+    assert b.w4a16_plan_batch(bits, m, n, k, 128) is None and pl["tile_cols"] == 256 and k // 128 % pl["split_k"], pl
+    A, qw, s, qz, Cref = _case_and_ref(oracle, bits, m, n, k, 128, seed=1400 + bits + m)
+    p = DeviceProblem(A, qw, s, qz, 128)
+    for call in range(2):
+        p.C.fill_(float("nan"))
+        MANY_ROWS_GEMM[bits](*p.args(), 0)
+        assert_parity(p.result(), Cref, f"{bits}-bit m={m} n={n} k={k} call {call}")
     assert b.w4a16_phase_timeouts() == 0
 
 
@@ -1488,7 +1505,10 @@ MANY_ROWS = [
     (333, 1032, 128, 128, 64, False),    # one chunk: nothing to share
     (257, 2056, 4096, 256, 64, True),    # one row in the last tile; a group of two chunks
     (1030, 288, 384, 128, 64, False),    # many row tiles
-    (50, 2072, 1056, 32, 64, True),      # fine groups, k not a multiple of a chunk, fewer rows than a tile
+    (50, 3904, 8256, 32, 64, True),      # fine groups, k not a multiple of a chunk, fewer rows than a tile
+    (40, 16448, 96, 32, 64, False),      # tiles of three row blocks
+    (37, 16448, 64, 64, 64, False),
+    (49, 264, 32, 32, 64, False),        # a quarter of a chunk in all
     (100, 40, 2080, 32, 64, True),       # fewer columns than one strip
     (97, 520, 1088, 64, 64, True),       # half a chunk at the end
     (65, 288, 1056, 32, 64, True),       # one row in the last tile, a quarter of a chunk at the end
@@ -1523,6 +1543,7 @@ def test_many_rows(oracle, bits, m, n, k, g, tile_rows, shared):
     n = n // 32 * 32 if bits in (2, 3) else n
     plan = b.w4a16_plan_many_rows(bits, m, n, k, g)
     assert plan and plan["tile_rows"] == tile_rows and plan["shared"] == shared, plan
+    assert m > 64 or b.w4a16_plan_batch(bits, m, n, k, g) is None
     seed = 4000 + m + n
     A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
     rows = np.unique(np.concatenate([np.arange(0, m, max(1, m // 24)), [63 % m, 64 % m, 127 % m, 128 % m, m - 1]]))
@@ -1682,34 +1703,41 @@ def test_many_rows_infinite_scale_in_the_last_group(oracle, bits, m, n, k, g):
     assert_parity(got[:, ~huge].astype(np.float16), ref(finite)[:, ~huge], f"bits={bits} g={g}")
 
 
-# 17 to 64 rows, the library's own launch: one and two strips a workgroup, k split and not (four bits; the other widths' plans
-# may differ), every group size.
+# 17 to 64 rows, the library's own launch: one and two strips a workgroup, k split and not, every group size and field width.
 BATCH = [
-    # m, n, k, g, (split_k, columns of a workgroup) with four bits
+    # m, n, k, g, (split_k, columns of a workgroup) of all widths, or by width
     (17, 40, 32, 32, (1, 64)),        # one MFMA step, fewer columns than a strip, seven waves without a chunk
-    (31, 40, 384, 128, (1, 64)),      # fewer chunks than waves
+    (31, 40, 384, 128, {4: (1, 64), 8: (1, 64), 3: None, 2: (1, 64)}),  # fewer chunks than waves
     (32, 288, 2048, 128, (2, 64)),    # one chunk a wave
     (17, 40, 1536, 128, (3, 128)),    # two strips, the second without columns
     (48, 520, 4736, 128, (4, 64)),    # shares of one and two chunks
     (33, 40, 1536, 256, (3, 128)),    # a group of two chunks
     (63, 2080, 2048, 256, (2, 64)),
-    (64, 40, 1152, 128, (2, 128)),    # shares of one and two chunks between barriers
+    (64, 40, 1152, 128, {4: (2, 128), 8: (1, 64), 3: (1, 64), 2: (2, 128)}),  # shares of one and two chunks between barriers
+    (61, 72, 1536, 256, (3, 128)),
     (47, 16416, 160, 32, (1, 128)),   # a quarter of a chunk at the end
     (64, 16416, 320, 64, (1, 128)),   # half a chunk at the end, most waves without any
     (47, 40, 1984, 64, (2, 64)),      # half a chunk at the end of a split range
-    (64, 40, 1984, 64, (4, 128)),
+    (64, 40, 1984, 64, {4: (4, 128), 8: (2, 64), 3: (2, 64), 2: (4, 128)}),
     (64, 528, 1120, 32, (1, 64)),     # three quarters of a chunk at the end
+    (22, 72, 2464, 32, (5, 128)),     # two strips, shares of less than a chunk between barriers
+    (29, 104, 1472, 64, (3, 128)),
+    (46, 72, 2528, 32, (5, 128)),
+    (62, 72, 2464, 32, (5, 128)),
+    (20, 552, 192, 64, (1, 64)),
+    (50, 296, 192, 64, (1, 64)),
+    (33, 296, 1056, 32, (1, 64)),
+    (46, 72, 1472, 64, (3, 128)),
     (16 + 64, 40, 1984, 64, None),    # 64 rows as a call of their own, then 16
 ]
 
 
 @pytest.mark.parametrize("bits", [4, 8, 3, 2])
-@pytest.mark.parametrize("m,n,k,g,plan4", BATCH)
-def test_batch_rows(oracle, bits, m, n, k, g, plan4):
+@pytest.mark.parametrize("m,n,k,g,plan", BATCH)
+def test_batch_rows(oracle, bits, m, n, k, g, plan):
     n = -(-n // 32) * 32 if bits in (2, 3) else n
-    plan = b.w4a16_plan_batch(bits, m, n, k, g)
-    if bits == 4:
-        assert (plan and (plan["split_k"], plan["tile_cols"])) == plan4, plan
+    got = b.w4a16_plan_batch(bits, m, n, k, g)
+    assert (got and (got["split_k"], got["tile_cols"])) == (plan[bits] if isinstance(plan, dict) else plan), got
     seed = 6000 + m + n + k
     A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
     Cref, _ = oracle.gemm_3bit(A, qw, s, qz, g) if bits == 3 else oracle.gemm_bits(A, qw, s, qz, g, bits)
@@ -1723,11 +1751,18 @@ def test_batch_rows(oracle, bits, m, n, k, g, plan4):
 
 # Up to 16 rows with fine groups: whole k and split k, one strip and two, overhanging strips, a quarter and half a chunk at
 # the end of k, shares of k of two lengths.
-@pytest.mark.parametrize("bits,m,n,k,g,plan", [
+BATCH_FEW = [
+    # bits, m, n, k, g, (split_k, columns of a workgroup)
     (4, 16, 12320, 2720, 32, (1, 64)), (4, 5, 12320, 2720, 32, (1, 64)), (4, 8, 4128, 4160, 64, (3, 64)),
-    (4, 16, 2080, 15936, 32, (7, 64)), (8, 16, 8224, 4128, 32, (3, 128)), (8, 16, 8224, 4160, 64, (3, 128)),
-    (3, 5, 8224, 4128, 32, (3, 64)), (2, 8, 8224, 4160, 64, (3, 64)), (2, 16, 9632, 3360, 32, (1, 64)),
-])
+    (4, 16, 2080, 15936, 32, (7, 64)), (4, 15, 6304, 4160, 32, (5, 128)), (4, 10, 4136, 6208, 64, (7, 128)),
+    (8, 16, 8224, 4128, 32, (3, 128)), (8, 16, 8224, 4160, 64, (3, 128)), (8, 8, 12296, 1056, 32, (1, 64)),
+    (8, 6, 14184, 1088, 64, (1, 64)), (3, 5, 8224, 4128, 32, (3, 64)), (3, 6, 3296, 8640, 32, (9, 128)),
+    (3, 5, 3744, 6592, 64, (4, 64)), (3, 7, 4256, 6784, 64, (7, 128)), (2, 8, 8224, 4160, 64, (3, 64)),
+    (2, 16, 9632, 3360, 32, (1, 64)), (2, 16, 4512, 10304, 32, (7, 128)), (2, 16, 6528, 6208, 64, (5, 128)),
+]
+
+
+@pytest.mark.parametrize("bits,m,n,k,g,plan", BATCH_FEW)
 def test_batch_few_rows(oracle, bits, m, n, k, g, plan):
     got = b.w4a16_plan_batch(bits, m, n, k, g)
     assert got and (got["split_k"], got["tile_cols"]) == plan, got
