@@ -11,6 +11,9 @@ With --bits 8, 3 or 2 the candidates are the launches the entry points of that w
 per-wave kernel with every split_k that divides k into whole groups (an explicit split_k never
 selects the two-strip or the streaming kernel there), so the table bounds the plan from one side only.
 
+Where `split_k = 0` goes to the kernel for decode batches or for many rows, which no explicit launch
+selects, that call is what is timed as the plan ("batch:..." and "rows:..." in the table).
+
 Timing protocol: calls captured in a HIP graph over a rotation of weight sets (at least 512 MiB, so
 the weights come from HBM), replayed 12 times, median of the HIP-event time per call.  The
 output is a text table: one line per shape with the plan's launch, its time, the best candidate
@@ -76,6 +79,17 @@ def candidates_bits(binding, bits, m, n, k, g=128):
     return out
 
 
+def library_launch(binding, bits, m, n, k, g):
+    """What a call with split_k = 0 launches, as a dict; `ask`: timed as that call, not as an explicit launch."""
+    batch = binding.w4a16_plan_batch(bits, m, n, k, g)
+    if batch:
+        return dict(batch, kernel="batch", ask=0)
+    rows = binding.w4a16_plan_many_rows(bits, m, n, k, g)
+    if rows:
+        return dict(rows, kernel="rows", ask=0)
+    return binding.w4a16_plan(m, n, k, g) if bits == 4 else dict(binding.w4a16_plan_bits(bits, m, n, k, g), ask=0)
+
+
 class Problem:
     def __init__(self, torch, m, n, k, g=128, seed=0, bits=4):
         per = n * k * bits // 8
@@ -101,11 +115,11 @@ def time_launch(torch, binding, p: Problem, pl, replays=12):
     ptrs = [tuple(vp(t.data_ptr()) for t in s) for s in p.sets]
     count = max(len(ptrs), 32)
 
-    gemm_bits = {4: None, 8: L.w8a16_gemm, 3: L.w3a16_gemm, 2: L.w2a16_gemm}[p.bits]
+    gemm_bits = {4: L.w4a16_gemm, 8: L.w8a16_gemm, 3: L.w3a16_gemm, 2: L.w2a16_gemm}[p.bits]
 
     def call(i, stream):
         qw, sc, qz = ptrs[i % len(ptrs)]
-        if gemm_bits is not None:  # `ask`: the split_k argument (0 = the library's plan)
+        if "ask" in pl:  # the split_k argument (0 = the library's choice)
             return gemm_bits(A, qw, sc, qz, C, p.m, p.n, p.k, p.g, pl["ask"], vp(stream.cuda_stream))
         return L.w4a16_gemm_ex(A, qw, sc, qz, C, p.m, p.n, p.k, p.g, pl["split_k"], pl["tile_cols"], pl["waves"],
                                pl["reduce"], vp(stream.cuda_stream))
@@ -155,6 +169,10 @@ STRUCTURED = [(m, nk, nk) for nk in (4096, 8192) for m in (1, 4, 16)] + [(8, 163
 
 
 def fmt(pl):
+    if pl.get("kernel") == "batch":
+        return f"batch:S{pl['split_k']}/t{pl['tile_cols']}"
+    if pl.get("kernel") == "rows":
+        return f"rows:r{pl['tile_rows']}/g{pl['workgroups']}" + ("/shared" if pl["shared"] else "")
     return f"S{pl['split_k']}/t{pl['tile_cols']}/w{pl['waves']}/r{pl['reduce']}"
 
 
@@ -193,12 +211,8 @@ def main(argv=None):
         if m < 1 or n < 8 or n % 8 or k < 128 or k % 128:
             raise SystemExit(f"shape {m},{n},{k}: need m >= 1, n a multiple of 8, k a multiple of 128")
         p = Problem(torch, m, n, k, g=g, bits=bits)
-        if bits == 4:
-            plan = binding.w4a16_plan(m, n, k, g)
-            cands = candidates(binding, m, n, k, g)
-        else:
-            plan = dict(binding.w4a16_plan_bits(bits, m, n, k, g), ask=0)
-            cands = candidates_bits(binding, bits, m, n, k, g)
+        plan = library_launch(binding, bits, m, n, k, g)
+        cands = candidates(binding, m, n, k, g) if bits == 4 else candidates_bits(binding, bits, m, n, k, g)
         if all(fmt(c) != fmt(plan) for c in cands):
             cands.append(plan)
         res = []

@@ -39,3 +39,16 @@ def test_candidates_of_the_other_field_widths(bits):
     assert asks == sorted(set(asks)) and set(asks) <= {1, 2, 4, 8, 16, 32}   # 32 groups: the divisors only
     for c in cands:
         assert c["split_k"] == c["ask"] and c["tile_cols"] == 64            # an explicit split: the per-wave kernel
+
+
+@pytest.mark.parametrize("bits,m,n,k,g,label", [
+    (4, 16, 4096, 4096, 128, None), (4, 1, 5120, 13824, 32, None), (8, 16, 8192, 8192, 128, None),   # the plan's launch
+    (4, 16, 5120, 13824, 32, "batch:"), (8, 16, 8224, 4128, 32, "batch:"), (4, 64, 8192, 8192, 128, "batch:"),
+    (4, 333, 11008, 4096, 128, "rows:"),
+])
+def test_the_audited_launch_is_the_one_that_runs(bits, m, n, k, g, label):
+    launch = plan_audit.library_launch(b, bits, m, n, k, g)
+    if label:
+        assert plan_audit.fmt(launch).startswith(label) and launch["ask"] == 0
+    else:
+        assert plan_audit.fmt(launch) == plan_audit.fmt(b.w4a16_plan_bits(bits, m, n, k, g))
