@@ -7,8 +7,10 @@ template <int MT, int BITS, int IPG, int STRIPS>
 static hipError_t launch_batch_one(const BatchArgs& a, hipStream_t stream)
 {
     auto kern = gemm_batch_kernel<MT, BITS, IPG, STRIPS>;
-    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kBatchLdsBytes<MT>);
-    if (e != hipSuccess) return e;
+    if constexpr (kBatchLdsBytes<MT> > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kBatchLdsBytes<MT>);
+        if (e != hipSuccess) return e;
+    }
     const int packed = a.m | a.param_shift << 7 | (int)((unsigned)a.chunks_base << 9);
     const BatchRest rest{a.flags, a.counts, a.errors, a.err_host, a.fixed, a.spin_limit, a.probe_delay};
     hipLaunchKernelGGL(kern, dim3((unsigned)a.split_k, (unsigned)a.tiles), dim3(64 * kBatchWaves), kBatchLdsBytes<MT>, stream, a.A,
