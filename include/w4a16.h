@@ -36,8 +36,8 @@
  * scratch for shared tiles, see below, the sums are grouped otherwise).  Ranges are shared, through scratch memory,
  * only where w4a16_plan reports a split_k above 1 for the call.  n is at most 2^23 for it.  w4a16_plan does not describe
  * it (it reports the launch per 64 or 16 rows); w4a16_plan_many_rows does.  n a multiple of 8;
- * g (group_size) one of 32, 64, 128, 256; k a multiple of g; k * n < 2^32.  A split_k requested from w4a16_gemm must cut k into equal
- * shares of whole groups (k / split_k a multiple of g), as Algorithm 1 has it.  The library's own
+ * g (group_size) one of 32, 64, 128, 256; k a multiple of g; k * n < 2^32.  A split_k requested from
+ * w4a16_gemm must cut k into equal shares of whole groups (k / split_k a multiple of g), as Algorithm 1 has it.  The library's own
  * choice (split_k == 0) and w4a16_gemm_ex are not bound by that: they deal out k in compute
  * groups (min(g, 128) consecutive k) to the k parts in order, the first ones getting one group
  * more when the count does not divide, so that any k (llama's 11008 = 86 groups) gets a
@@ -60,8 +60,8 @@
  * keeps working.  A call that would have to allocate while its stream is being captured returns
  * W4A16_ERR_STATE instead (the many-row kernel then shares no tile between workgroups and needs
  * none, as it does where there is no memory for its sums; that is asked for once, and again by
- * w4a16_reserve_scratch or after w4a16_release_scratch).  Split-k calls that overlap in time on one device share the library's
- * buffers and must not be issued on different streams; a caller with several streams gives each
+ * w4a16_reserve_scratch or after w4a16_release_scratch).  Split-k calls that overlap in time on one
+ * device share the library's buffers and must not be issued on different streams; a caller with several streams gives each
  * its own memory with w4a16_set_workspace, and calls on different streams are then independent.
  *
  * Failure of the in-kernel zeroing (W4A16_REDUCE_ATOMIC_PK_F16_PHASE): its waits are bounded, so
@@ -160,8 +160,7 @@ int w4a16_gemm_streamk_bits(int bits, const void* A, const void* qweight, const 
  *     qzeros   int32  [k / g, n / 4]     field i of word (gi, c) is z[gi][4c + i]
  * The launch is the library's (per-wave kernel, two strips per wave or streaming kernel for SplitK;
  * 16- to 64-column tiles for the data-parallel kernel; w4a16_plan_bits reports it); more than 16
- * rows as described above (row tiles of the streaming kernel for SplitK).  w8a16_algorithmic_bytes: qweight + scales + qzeros + A + C for
- * this layout.
+ * rows as described above.  w8a16_algorithmic_bytes: qweight + scales + qzeros + A + C for this layout.
  */
 int w8a16_gemm(const void* A, const void* qweight, const void* scales, const void* qzeros, void* C,
                int m, int n, int k, int group_size, int split_k, void* stream);
@@ -256,17 +255,18 @@ int w4a16_plan_bits(int bits, int m, int n, int k, int group_size, int dp, int* 
 /*
  * The many-row launch of a SplitK call of this field width with split_k == 0: the most rows a tile may have (64 or 128:
  * the tiles are evened out to as few row blocks of 16 as that many of them need, three at least; 0 if the call goes to
- * the launches w4a16_plan reports instead; up to 64 rows w4a16_plan_batch comes first), the workgroups, and whether these
- * share tiles (1) or take whole ones (0).  may_share == 0: the launch of a call that finds no scratch for shared tiles (a stream with a bound
- * workspace; under capture before any such call).  Host only; no HIP call; the last three may be NULL.
+ * the launches w4a16_plan reports instead; up to 64 rows w4a16_plan_batch comes first), the workgroups, and
+ * whether these share tiles (1) or take whole ones (0).  may_share == 0: the launch of a call that finds no
+ * scratch for shared tiles (a stream with a bound workspace; under capture before any such call).  Host only; no
+ * HIP call; the last three may be NULL.
  */
 int w4a16_plan_many_rows(int bits, int m, int n, int k, int group_size, int may_share, int* tile_rows,
                          int* workgroups, int* shared);
 
 /*
- * The launch of the kernel for decode batches (17 to 64 rows, with groups of 32 and 64 also fewer) of a SplitK call of this field width with split_k == 0: in how many parts
- * it splits k (0 if the call goes to other launches) and the columns of a workgroup (64 or 128).  Host only; no HIP call;
- * the last two may be NULL.
+ * The launch of the kernel for decode batches (17 to 64 rows, with groups of 32 and 64 also fewer) of a SplitK call
+ * of this field width with split_k == 0: in how many parts it splits k (0 if the call goes to other launches) and the
+ * columns of a workgroup (64 or 128).  Host only; no HIP call; the last two may be NULL.
  */
 int w4a16_plan_batch(int bits, int m, int n, int k, int group_size, int* split_k, int* tile_cols);
 

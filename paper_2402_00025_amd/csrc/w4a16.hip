@@ -2501,6 +2501,10 @@ struct RowsPlan {
     bool whole;  // a worker takes whole tiles: nothing is handed over
 };
 
+// What follows prices the many-row kernel against launches of 64 row tiles (groups of 128 and 256) and of 16 rows (fine groups),
+// with tiles of 64 and 128 rows.  Since it was fitted, calls that stay out run as launches of the batch kernel of 64 rows each where that
+// is the faster one, and tiles are evened out to 48 to 112 rows where as many do: both are faster than these estimates say,
+// so near the crossing a call may go to the slower of two launches that are both faster than what the fits compare.
 // us of `n k` fields and m rows on the launches of up to 64 (group_size 128, 256) or 16 rows; fitted to square and
 // decoder-projection shapes from 2048 x 2048 to 28672 x 4096 of 4-bit fields (within 15 %; on random shapes of every width it
 // says 0.70 to 1.10 of the measured time on average, so it errs on the side of these launches).
@@ -2581,9 +2585,8 @@ static double fitted_rows_us(const RowsPlan& plan, int m, int n, int k, int ipg,
 }
 
 // The many-row launch of a call that leaves every choice to the library, or row_blocks == 0 where the other launches
-// are taken.  Up to 64 rows, one launch of the streaming kernel stays the better one: 20.8 us against 27.2 at m = 64,
-// n = k = 8192, 16.1 against 27.1 at m = 48; level (within 5 %) only at m > 48 on matrices of 16384 x 8192 and more or
-// 22016 x 4096.  The kernel's 32-bit offsets span 128 rows of A, and 128 rows of C with room for a marker that lies
+// are taken.  Groups of 128 and 256, up to 64 rows: one launch of the batch or the streaming kernel stays the better one
+// (15.1 and 20.8 us against 27.2 at m = 64, n = k = 8192).  The kernel's 32-bit offsets span 128 rows of A, and 128 rows of C with room for a marker that lies
 // outside every tile: 256 n <= 2^31.
 // `share_ok` (may be null): workgroups may share tiles, through the device's scratch.  They do so only where the
 // other launches would split k and use scratch as well: what runs on two streams at once without it (the widest
@@ -2610,12 +2613,14 @@ static int plan_many_rows(int m, int n, int k, int group_size, int bits, bool ma
 
 // The same for up to 16 rows, where groups of 32 and 64 cost the per-wave kernel its depth (a ring of two groups holds 64 or
 // 128 k on their way; here 128 and more) and every wave its own activations.  Only from 8 MB of weights on, where the
-// estimates are 10 % apart, and inside the shapes that they are fitted to: below, start and end of a launch are all there is, and the per-wave kernel's are shorter (m = 3,
-// n = k = 2048: 3.7 against 4.5 us).  The parts meet in fp16, so only where they do in the other launch, or not at all; k is split no
-// further than there.  us per call, cold weights, before -> now (m; n x k, groups of 64): 16; 14176 x 1792: 7.6 -> 5.7,
+// estimates are 10 % apart, and up to the 28672 columns and k that they are fitted to: below, start and end of a launch are all
+// there is, and the per-wave kernel's are shorter (m = 3, n = k = 2048: 3.7 against 4.5 us).  The parts meet in fp16, so only where
+// they do in the other launch, or not at all; k is split no further than there.  So one to four rows, whose parts the other launch
+// adds in fixed point, come here only with k whole on wide matrices (220 random ones: 1.05 times as fast on average, 7 more
+// than 2 % slower, at worst 6 %).  us per call, cold weights, before -> now (m; n x k, groups of 64): 16; 14176 x 1792: 7.6 -> 5.7,
 // 11; 8256 x 21888: 27.8 -> 22.7, groups of 32, 5; 4512 x 21088: 16.4 -> 14.1, 8 bits, groups of 32, 12; 6784 x 11936:
-// 20.1 -> 18.4.  Of 1172 shapes that the fits have not seen it takes 312, 1.16 times as fast on average, two of them more than
-// 2 % slower, at worst 7 %.
+// 20.1 -> 18.4.  Of 12,000 shapes of 5 to 16 rows that the fits have not seen it takes 3281, 1.15 times as fast on average, 86
+// of them more than 2 % slower, at worst 9 %.
 static void plan_batch_few(int m, int n, int k, int group_size, int bits, const Plan& others, BatchPlan* plan)
 {
     const bool splits = others.split_k > 1;
@@ -2655,12 +2660,12 @@ struct BatchOthers {
 // The fixed-point adds, whose round trip to memory ends the launch, cost 1.3 us more than adds in fp16, two strips' 2.2 (377
 // shapes; m; n x k, groups of 64: 17; 4096 x 4096: 5.7 -> 6.9 us, a launch per 16 rows 9.9, k whole 9.1; 20; 6864 x 1472: 5.9 ->
 // 8.5 with k in three parts, 6.0 whole).
-// With groups of 32 and 64 it stands against a launch per 16 rows and always wins (1.7 to 1.9 times as fast on average);
+// With groups of 32 and 64 it stands against a launch per 16 rows, or the many-row kernel, and wins all but always;
 // otherwise the estimates have to be 5 % apart, with two strips, which they tell less well, 10 %.  Beyond 28672 columns or k,
 // where nothing was fitted, they err by up to a quarter against the many-row kernel and, with 8-bit fields and two strips, against the
-// streaming kernel: there they have to be 23 % apart (m = 58, n = 35216, k = 6656, 8 bits, groups of 256: 66 us there, 76 here).  On 26,000 random calls
-// of 17 to 64 rows, 1.35 times as fast on average; of those that go here 10 are more than 5 % slower than before, at
-// worst 9 %.  The phase words cover n <= 65536.
+// streaming kernel: there they have to be 23 % apart (m = 58, n = 35216, k = 6656, 8 bits, groups of 256: 66 us there, 76 here).  Of 8000 random
+// calls of 17 to 64 rows, sizes that the fits cover, 6885 go here: 1.33 times as fast as before on average with groups of 128 and 256,
+// 1.69 times with 32 and 64; 14 of them take more than 5 % longer, at worst 19 %.  The phase words cover n <= 65536.
 static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* plan, BatchOthers* others)
 {
     *plan = BatchPlan{0, 0};

@@ -131,8 +131,9 @@ def test_route_of_batch_rows(stand_in):
     for bits, m, n, k, g in ((4, 16, 5120, 13824, 32), (4, 8, 4128, 4160, 64), (8, 16, 8224, 4128, 32), (3, 5, 8192, 8192, 64)):
         s, t = batch(m, n, k, g, bits)   # up to 16 rows, fine groups: the same
         assert 1 <= s <= max(1, other(m, n, k, g, bits)) and gemm(m, n, k, g, bits) == (OK, 1, (s, -(-n // t), 1)), (bits, m, n, k, g)
-    for m in (1, 2, 3):                  # sums that do not meet in fp16
-        assert batch(m, 8192, 8192, 32) == batch(m, 5120, 13824, 64) == (0, 0)
+    for m in (1, 2, 3, 4):               # sums that do not meet in fp16; with k whole, wide matrices
+        assert batch(m, 8192, 8192, 32) == batch(m, 5120, 13824, 64) == batch(m, 12288, 4096, 32, 8) == (0, 0)
+    assert batch(1, 28672, 9408, 32, 3) == batch(2, 16832, 1984, 64, 2) == batch(3, 28672, 4416, 32, 3) == (1, 64)
     assert batch(16, 2048, 2048, 32) == batch(16, 65536, 512, 32, 8) == (0, 0)
     # beyond the sizes that the estimates are fitted to: calls that the batch kernel was measured to slow down
     assert batch(58, 35216, 6656, 256, 8) == batch(47, 1424, 179712, 256, 8) == batch(29, 42376, 320, 64) == (0, 0)
