@@ -266,6 +266,28 @@ def test_nan_and_infinity_through_the_fixed_point_adds(oracle):
         assert_parity(p2.result(), C2, f"after the NaN call, S={split_k}")
 
 
+def test_nan_and_infinity_in_the_last_rows_of_a_decode_batch(oracle):
+    """The same for the last rows of a call with fine groups, which the decode-batch kernel adds in fixed point."""
+    m, n, k, g = 19, 520, 4160, 32
+    assert b.w4a16_plan_batch(4, m, n, k, g)["split_k"] > 1
+    A, qw, s, qz = random_case(m, n, k, g, seed=98)
+    C2, _ = oracle.gemm(A, qw, s, qz, g)
+    p2 = DeviceProblem(A, qw, s, qz, g)
+    bad = A.copy()
+    bad[16, 700] = np.float16(np.nan)
+    bad[18, 5] = np.float16(np.inf)
+    p = DeviceProblem(bad, qw, s, qz, g)
+    for rep in range(2):
+        p.C.fill_(0.0)
+        b.w4a16_gemm(*p.args(), 0)
+        got = p.result().astype(np.float64)
+        assert np.isnan(got[16]).all() and not np.isfinite(got[18]).any()
+        rest = np.delete(np.arange(m), [16, 18])
+        assert_parity(got[rest].astype(np.float16), C2[rest], f"finite rows, call {rep}")
+        b.w4a16_gemm(*p2.args(), 0)            # into the same words: nothing of it is left behind
+        assert_parity(p2.result(), C2, f"after call {rep}")
+
+
 GEMM = {4: b.w4a16_gemm, 8: b.w8a16_gemm, 3: b.w3a16_gemm, 2: b.w2a16_gemm}
 # Many rows with shared tiles: one range per worker and tile (every part is done at the same time), ranges over tile
 # edges, two workers per compute unit, both tile heights, every width.
