@@ -2657,8 +2657,8 @@ struct BatchOthers {
 // run otherwise, `others`, and adds the parts in fp16 only where they do: the last one to four rows of a call with fine
 // groups, whose launch of their own adds in fixed point, are added in fixed point here as well.  So it needs no scratch
 // where they need none; where the many-row kernel is that other launch, which adds in fp32, it does not split k at all.
-// The fixed-point adds, whose round trip to memory ends the launch, cost 1.3 us more than adds in fp16, two strips' 2.2 (377
-// shapes; m; n x k, groups of 64: 17; 4096 x 4096: 5.7 -> 6.9 us, a launch per 16 rows 9.9, k whole 9.1; 20; 6864 x 1472: 5.9 ->
+// The fixed-point adds, whose round trip to memory ends the launch, cost 1.1 us more than adds in fp16, two strips' 2.1 (377
+// shapes; m; n x k, groups of 64: 17; 4096 x 4096: 5.7 -> 6.8 us, a launch per 16 rows 9.9, k whole 9.1; 20; 6864 x 1472: 5.9 ->
 // 8.5 with k in three parts, 6.0 whole).
 // With groups of 32 and 64 it stands against a launch per 16 rows, or the many-row kernel, and wins all but always;
 // otherwise the estimates have to be 5 % apart, with two strips, which they tell less well, 10 %.  Beyond 28672 columns or k,
@@ -2697,7 +2697,7 @@ static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* 
         most = most < 1 || !may_split ? 1 : most < 32 ? most : 32;
         for (int s : {1, 256 / tiles, 256 / tiles + 1, 512 / tiles, most}) {
             s = s < 1 ? 1 : s < most ? s : most;
-            const double us = batch_us(strips, s, m, n, k, ipg, bits) + (s > 1 && others->tail_fixed() ? strips == 1 ? 1.3 : 2.2 : 0.0);
+            const double us = batch_us(strips, s, m, n, k, ipg, bits) + (s > 1 && others->tail_fixed() ? strips == 1 ? 1.1 : 2.1 : 0.0);
             if (us < best) {
                 best = us;
                 *plan = BatchPlan{s, strips};

@@ -20,7 +20,7 @@
 // 32; 4096 x 4096: 9.1 -> 5.7, 64; 28672 x 8192: 55 -> 37, 33; 1024 x 1024: 6.7 -> 4.9; groups of 64, 29; 8192 x 8192: 21.9 -> 12.6.
 // Sums of the parts through fp32 scratch and a ticket instead of the packed-fp16 adds: 17.1 instead of 15.1 us, 10.0
 // instead of 7.5 (m = 64, n = k = 8192 and 4096).  One to four last rows of a call with fine groups, which the launch per 16 rows adds
-// in fixed point, are added so here too: 5.7 -> 6.9 us (m = 17, n = k = 4096, groups of 64).
+// in fixed point, are added so here too: 5.7 -> 6.8 us (m = 17, n = k = 4096, groups of 64).
 #pragma once
 #include "w4a16_rows.hpp"
 
@@ -394,10 +394,7 @@ __global__ void __launch_bounds__(64 * kBatchWaves, 2) gemm_batch_kernel(const _
     __syncthreads();
     // Thread t adds up the column pairs t, t + 512, ... of the tile (strip, row, pair): consecutive lanes on consecutive
     // pairs, so that an instruction touches the fewest cache lines.
-#pragma unroll
-    for (int u = tid; u < STRIPS * MT * 512; u += 64 * kBatchWaves) {
-        const int st = u / (MT * 512), e = u - st * (MT * 512);
-        const int row = e >> 5, col = (tile * STRIPS + st) * 64 + 2 * (e & 31);
+    auto sum = [&](int st, int e) {
         const float2* src = (const float2*)lds_raw + st * (MT * 512) + e;
         float2 v = src[0];
 #pragma unroll
@@ -408,26 +405,55 @@ __global__ void __launch_bounds__(64 * kBatchWaves, 2) gemm_batch_kernel(const _
         }
         v.x *= kNatScale<BITS>;
         v.y *= kNatScale<BITS>;
-        const uint32_t off = row < m && col < n ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
-        if (kFixedRows && row >= half_rows) {
+        return v;
+    };
+    auto offset = [&](int st, int e) {
+        const int row = e >> 5, col = (tile * STRIPS + st) * 64 + 2 * (e & 31);
+        return row < m && col < n ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
+    };
+    // The fixed-point adds first, all strips': their round trip passes beside the others.
+    const bool fixed = kFixedRows && half_rows < m;
+    const int last = (MT - 1) * 512 + tid;  // this thread's pair of the last row block, which the fixed rows are in
+    uint64_t mine[STRIPS][2], old[STRIPS][2];
+    if (fixed) {
+#pragma unroll
+        for (int st = 0; st < STRIPS; ++st) {
+            const uint32_t off = offset(st, last);
             if (off != kOutside) {
-                uint64_t* const word = rest.fixed + (size_t)(row - half_rows) * n + col;
-                const uint64_t mine[2] = {fixed_contribution(v.x), fixed_contribution(v.y)};
-                uint64_t old[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) old[i] = __hip_atomic_fetch_add(word + i, mine[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    float total;
-                    if (fixed_finish(word + i, old[i], mine[i], split_k, &total))
-                        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, (_Float16)total), rs_c, off + 2u * i, 0, kRowsDeviceScope);
-                }
+                const float2 v = sum(st, last);
+                uint64_t* const word = rest.fixed + off / 2 - (size_t)half_rows * n;
+                mine[st][0] = fixed_contribution(v.x);
+                mine[st][1] = fixed_contribution(v.y);
+                old[st][0] = __hip_atomic_fetch_add(word, mine[st][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                old[st][1] = __hip_atomic_fetch_add(word + 1, mine[st][1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-        } else if (split) {
+        }
+    }
+#pragma unroll
+    for (int u = tid; u < STRIPS * MT * 512; u += 64 * kBatchWaves) {
+        const int st = u / (MT * 512), e = u - st * (MT * 512);
+        if (kFixedRows && fixed && e >= (MT - 1) * 512) continue;
+        const float2 v = sum(st, e);
+        const uint32_t off = offset(st, e);
+        if (split) {
             const half2_t h = {(_Float16)v.x, (_Float16)v.y};
             __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(h, rs_c, off, 0, 0);
         } else {
             __builtin_amdgcn_raw_buffer_store_b32(pack_half2(v.x, v.y), rs_c, off, 0, kRowsDeviceScope);
+        }
+    }
+    if (fixed) {
+#pragma unroll
+        for (int st = 0; st < STRIPS; ++st) {
+            const uint32_t off = offset(st, last);
+            if (off == kOutside) continue;
+            uint64_t* const word = rest.fixed + off / 2 - (size_t)half_rows * n;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                float total;
+                if (fixed_finish(word + i, old[st][i], mine[st][i], split_k, &total))
+                    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, (_Float16)total), rs_c, off + 2u * i, 0, kRowsDeviceScope);
+            }
         }
     }
 }
