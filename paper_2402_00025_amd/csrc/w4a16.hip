@@ -2616,11 +2616,11 @@ static int plan_many_rows(int m, int n, int k, int group_size, int bits, bool ma
 // estimates are 10 % apart, and up to the 28672 columns and k that they are fitted to: below, start and end of a launch are all
 // there is, and the per-wave kernel's are shorter (m = 3, n = k = 2048: 3.7 against 4.5 us).  The parts meet in fp16, so only where
 // they do in the other launch, or not at all; k is split no further than there.  So one to four rows, whose parts the other launch
-// adds in fixed point, come here only with k whole on wide matrices (220 random ones: 1.05 times as fast on average, 7 more
+// adds in fixed point, come here only with k whole on wide matrices (220 random ones: 1.05 times as fast on average, 8 more
 // than 2 % slower, at worst 6 %).  us per call, cold weights, before -> now (m; n x k, groups of 64): 16; 14176 x 1792: 7.6 -> 5.7,
 // 11; 8256 x 21888: 27.8 -> 22.7, groups of 32, 5; 4512 x 21088: 16.4 -> 14.1, 8 bits, groups of 32, 12; 6784 x 11936:
-// 20.1 -> 18.4.  Of 12,000 shapes of 5 to 16 rows that the fits have not seen it takes 3281, 1.15 times as fast on average, 86
-// of them more than 2 % slower, at worst 9 %.
+// 20.1 -> 18.4.  Of 12,000 shapes of 5 to 16 rows that the fits have not seen it takes 3281, 1.15 times as fast on average, 80
+// of them more than 2 % slower, at worst 10 %.
 static void plan_batch_few(int m, int n, int k, int group_size, int bits, const Plan& others, BatchPlan* plan)
 {
     const bool splits = others.split_k > 1;
@@ -2664,8 +2664,8 @@ struct BatchOthers {
 // otherwise the estimates have to be 5 % apart, with two strips, which they tell less well, 10 %.  Beyond 28672 columns or k,
 // where nothing was fitted, they err by up to a quarter against the many-row kernel and, with 8-bit fields and two strips, against the
 // streaming kernel: there they have to be 23 % apart (m = 58, n = 35216, k = 6656, 8 bits, groups of 256: 66 us there, 76 here).  Of 8000 random
-// calls of 17 to 64 rows, sizes that the fits cover, 6885 go here: 1.33 times as fast as before on average with groups of 128 and 256,
-// 1.69 times with 32 and 64; 14 of them take more than 5 % longer, at worst 19 %.  The phase words cover n <= 65536.
+// calls of 17 to 64 rows, sizes that the fits cover, 6885 go here: 1.34 times as fast as before on average with groups of 128 and 256,
+// 1.71 times with 32 and 64; 12 of them take more than 5 % longer, at worst 18 %.  The phase words cover n <= 65536.
 static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* plan, BatchOthers* others)
 {
     *plan = BatchPlan{0, 0};
@@ -2704,7 +2704,8 @@ static int plan_batch(int m, int n, int k, int group_size, int bits, BatchPlan* 
             }
         }
     }
-    const bool fitted = n <= 28672 && k <= 28672;
+    // (k whole here and split there: a captured call that finds no scratch runs here alone)
+    const bool fitted = (n <= 28672 && k <= 28672) || (plan->split_k == 1 && others->scratch());
     if (rows.row_blocks && best >= (fitted ? 0.85 : 0.77) * fitted_rows_us(rows, m, n, k, ipg, bits)) *plan = BatchPlan{0, 0};
     const double margin = plan->strips == 1 ? 0.95 : fitted || bits != 8 ? 0.9 : 0.77;
     if (!fine_groups && best >= margin * stream_rows_us(others->rows, m, n, k, bits)) *plan = BatchPlan{0, 0};

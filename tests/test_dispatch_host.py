@@ -136,6 +136,8 @@ def test_route_of_batch_rows(stand_in):
     assert batch(1, 28672, 9408, 32, 3) == batch(2, 16832, 1984, 64, 2) == batch(3, 28672, 4416, 32, 3) == (1, 64)
     assert batch(16, 2048, 2048, 32) == batch(16, 65536, 512, 32, 8) == (0, 0)
     # beyond the sizes that the estimates are fitted to: calls that the batch kernel was measured to slow down
+    # (where the other launches need no scratch that this one does without: those calls can be captured before any eager one)
+    assert batch(50, 32512, 5632, 256, 8) == (1, 128) and other(50, 32512, 5632, 256, 8) > 1
     assert batch(58, 35216, 6656, 256, 8) == batch(47, 1424, 179712, 256, 8) == batch(29, 42376, 320, 64) == (0, 0)
     assert batch(16, 4096, 4096, 128) == batch(65, 4096, 4096, 128) == batch(40, 65544, 4096, 128) == (0, 0)
     assert L.w4a16_plan_batch(5, 40, 4096, 4096, 128, None, None) == UNSUPPORTED
