@@ -1,0 +1,630 @@
+// Per-wave kernel of the fused W4A16 skinny GEMM on gfx950: a wave walks its own k range of a column tile (see
+// w4a16_device.hpp for its loop), the waves of a workgroup meet in LDS, the workgroups of a tile by one of several reductions.
+//
+// Paper: "Accelerating a Triton Fused Kernel for W4A16 Quantized Inference with SplitK work decomposition", Algorithm 1
+// (SplitK), Section 3, first paragraph (data-parallel) and Section 2.1 (the atomic reduction).
+#pragma once
+#include "w4a16_device.hpp"
+
+namespace w4a16 {
+
+struct GemmArgs {
+    // what every wave needs before its first load, packed at the front so that it arrives with
+    // one batch of scalar loads
+    const _Float16* A;
+    const uint32_t* qweight;
+    const _Float16* scales;
+    const uint32_t* qzeros;
+    _Float16* C;
+    float* scratch;     // split-k: fp32 sums [16, n] (atomic) or partial tiles [split_k, m, n] (workspace)
+    int m, n, k;
+    int tiles;            // column tiles = ceil(n / (16 V))
+    int split_k;
+    // The compute groups (32 * IPG consecutive k each) are dealt to the split_k * waves k parts
+    // in order: part i = slice * waves + wave gets groups_base of them, the first groups_rem
+    // parts one more (k need not divide evenly; every part stays a whole number of groups).
+    int groups_base;
+    int groups_rem;
+    int param_shift;      // log2(compute groups per quantisation group)
+    int waves;            // working waves per workgroup (the launch has one more in service mode)
+    int spin_limit;     // phase mode: bound on polls of a flag
+    int probe_delay;    // phase mode: 64-cycle sleeps before the early sample of the flag
+    uint32_t* tickets;  // split-k: one arrival counter per column tile
+    uint32_t* flags;    // phase mode: zeroings so far, per tile origin
+    uint32_t* counts;   // phase mode: calls so far, per (tile origin, slice)
+    uint32_t* errors;   // phase mode: count of waits that ran out
+    uint32_t* err_host; // phase mode: word in pinned host memory set to 1 by a wait that ran out (may be null)
+};
+
+enum : int {
+    kDirect = 0, kAtomicF32 = 1, kAtomicPkF16 = 2, kWorkspace = 3, kAtomicFixed = 4, kAtomicPkF16Phase = 5,
+    kAtomicPkF16Service = 6  // the phase protocol run by one extra wavefront per workgroup (internal)
+};
+
+// Results and protocol words are stored write-through (the sc1 bit of a buffer store, an
+// agent-scope atomic store elsewhere).  A plain store leaves a dirty line in the die's L2 that
+// the release at the end of the kernel has to find and write back: 0.16 us per launch on the
+// headline shape for a single dirty word per workgroup, which is as much as the whole sum over
+// the waves costs.  Written through, nothing is dirty when the kernel ends.
+constexpr int kWriteThrough = 16;  // aux bits of a buffer store: sc1
+
+__device__ __forceinline__ void store_through(uint32_t* word, uint32_t value)
+{
+    __hip_atomic_store(word, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Everything this thread has sent to memory (atomics, write-through stores) has been performed
+// before it goes on.  On gfx9-family hardware the vector memory counter also covers stores and
+// atomics without return.  The "memory" clobber keeps the compiler from moving accesses across.
+__device__ __forceinline__ void wait_memory_ops() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// One workgroup = WAVES wavefronts that share one output tile [m, 16 V] and divide the
+// workgroup's k range between them; blockIdx = (tile, slice), dispatched as slice * tiles + tile.
+//
+// MODE kDirect       the workgroup owns the tile alone (data-parallel kernel, or split_k == 1):
+//                    its sum is rounded once to fp16 and stored.
+// MODE kAtomicF32    Algorithm 1's final step with fp32 atomic adds into scratch; the workgroup
+//                    that arrives last at the tile's ticket swaps the sums out (leaving zeros
+//                    for the next call), rounds once and stores C.
+// MODE kAtomicPkF16  packed-fp16 atomic adds straight into a C that a fill kernel zeroed.
+// MODE kWorkspace    partial tiles are written through to memory; the last workgroup adds them
+//                    in slice order (bit-reproducible).
+// MODE kAtomicFixed  64-bit fixed-point atomic adds that also count arrivals (see above);
+//                    bit-reproducible, one round trip.
+// MODE kAtomicPkF16Phase  packed-fp16 atomic adds straight into C with no launch before this one:
+//                    the slice-0 workgroup of a tile zeroes the tile as its first action and
+//                    publishes that in the tile's flag; the others add once they have seen it.
+//
+// Synchronisation of the ticketed modes.  Every access that one workgroup makes and another
+// reads is a device-scope atomic operation (add, exchange, write-through store, cache-bypassing
+// load), so it is performed at the level where all compute dies see it; none of it sits dirty
+// in a die-local L2.  What is left to order is time: a workgroup waits until its own
+// contributions have been performed (wait_memory_ops + barrier) before one of its threads takes
+// the ticket, and the last workgroup reads only after its ticket came back.  A device-scope
+// release fence would do the same but also write back the whole L2 of the die, which costs
+// more than the GEMM itself.
+//
+// The phase protocol (kAtomicPkF16Phase) uses no atomic operation besides the adds into C
+// (atomics of several workgroups on one word are served one after the other, at about a
+// memory round trip each).  State, per split_k and per tile origin e = n0 / 16:
+//   counts[e][slice]  how many calls this (tile, slice) workgroup has run; only it writes it
+//   flags[e]          how many times the tile has been zeroed; only the slice-0 workgroup writes it
+// Every call that touches a tile runs all split_k of its workgroups, so before a call these
+// words are all equal (= c) and after it all are c + 1.  Wave 0 of the slice-0 workgroup stores
+// zeros (write-through) to the tile before it issues any load.  Then wave 0 of every workgroup
+// loads its own count c.  Vector memory operations of a wave complete in issue order, so when c
+// has arrived the zeros are in memory: the slice-0 workgroup stores c + 1 into flags[e] (and every
+// workgroup stores c + 1 into its own count).  Every wave samples flags[e] during its last
+// compute group and, after the workgroup's barrier, adds only when it has seen c + 1; otherwise
+// it polls (bounded by spin_limit; a wait that runs out is counted in `errors` and the wave goes
+// on).  The slice-0 workgroup never waits for anyone and has the lowest block index of the
+// tile's workgroups, so the wait ends.
+// MODE kAtomicPkF16Service is the same protocol with the roles moved out of the working waves:
+// the workgroup has one wavefront more, which stores the zeros (slice 0), loads the count,
+// publishes, samples the flag until it has seen this call's value, and only then joins the
+// workgroup's barrier.  The working waves neither issue the protocol's memory operations (whose
+// in-order completion would hold back their weight data) nor look at the flag: passing the
+// barrier means the zeros are in memory.  Used where a wave needs few registers (one compute
+// group per wave), so that the extra wave costs no occupancy.
+// WMAX (4 or 16) is the largest number of working waves the instantiation may be launched with;
+// the small one lets the compiler use more than 128 registers per lane.
+constexpr int kPhaseMaxSplit = 64;          // largest split_k of the phase protocol
+constexpr uint32_t kPhaseOrigins = 1u << 12;  // tile origins n0 / 16 it covers: n <= 65536
+
+// LDS region of one wave: its [m][BN] fp32 tile.  Two strips per wave: whole 16-row tiles whatever m
+// is, which the four-wave epilogue indexes with constants.
+__host__ __device__ constexpr int gemm_lds_wave_bytes(int BN, int m)
+{
+    return BN == 128 ? 16 * 128 * 4 : (m * BN * 4 + 15) & ~15;
+}
+
+// GC: 1 = every wave has exactly one compute group, 2 = at least two, 0 = decided at run time.
+// BITS: width of the packed fields, 4 (the paper's), 2, 3 or 8 (Section 2: the method carries
+// over to other n-bit schemes; qweight is then int32 [k BITS / 32, n] and qzeros int32
+// [k / g, n BITS / 32]; 3-bit fields: 32 of them in a stream of three words).
+// NS: strips of 16 V columns per wave.  2 (only with GC = 1): the wave multiplies the same
+// activations with the weights of two adjacent strips, which halves the activation traffic per
+// weight byte and the number of waves.
+template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1>
+__device__ __forceinline__ void gemm_body(const GemmArgs& p)
+{
+    static_assert(NS == 1 || (NS == 2 && GC == 1), "two strips per wave: one compute group per wave");
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    constexpr int BN = 16 * V * NS;
+    const int lds_wave_bytes = gemm_lds_wave_bytes(BN, p.m);
+    constexpr bool kService = MODE == kAtomicPkF16Service;
+
+    const int tid = threadIdx.x;
+    const int nthreads = p.waves * kWave;  // threads of the working waves (not read from the launch: an argument arrives with the others)
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // uniform: keeps offsets scalar
+    const int waves = nthreads / kWave;
+    // grid = (tiles, split_k): the same dispatch order as slice * tiles + tile, without a division
+    // at the head of every wave
+    const int tile = blockIdx.x;
+    const int slice = blockIdx.y;
+    const int n0 = tile * BN;
+    const int m = p.m, n = p.n, k = p.k;
+    // (the host has checked the shape: divisions by constants become single shifts)
+    __builtin_assume(m > 0 && n > 0 && k > 0);
+
+    if constexpr (kService) {
+        if (wave == waves) {
+            // ---- the service wave (see the protocol above)
+            constexpr uint32_t kOutside = 0xFFFFFF00u;
+            const uint32_t origin_s = (uint32_t)n0 / 16u;
+            const rsrc_t rs_c = make_rsrc(p.C, (uint32_t)m * (uint32_t)n * 2u);
+#pragma unroll
+            for (int i = 0; i < 2 * NS; ++i) {
+                const int u = lane + kWave * i;
+                const int row = u / (BN / 8), col = n0 + 8 * (u % (BN / 8));
+                const bool inside = slice == 0 && row < m && col < n;
+                const uint32_t off = inside ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0u, 0u, 0u, 0u}, rs_c, off, 0, 16);
+            }
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t* my_count = p.counts + origin_s * (uint32_t)p.split_k + (uint32_t)slice;
+            uint32_t count_s = *(volatile uint32_t*)my_count;  // issued after the stores: its arrival means they are done
+            asm volatile("" : "+v"(count_s)::"memory");
+            const uint32_t now = __builtin_amdgcn_readfirstlane(count_s) + 1u;
+            if (lane == 0) {
+                store_through(my_count, now);
+                if (slice == 0)
+                    __hip_atomic_store(p.flags + origin_s, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            uint32_t seen = now - 1u;
+            int polls = 0;
+            do {
+                for (int i = 0; i < p.probe_delay; ++i) __builtin_amdgcn_s_sleep(1);
+                seen = __builtin_amdgcn_readfirstlane(
+                    __hip_atomic_load(p.flags + origin_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                ++polls;
+            } while (seen != now && polls < p.spin_limit);
+            if (seen != now && lane == 0) phase_wait_failed(p.errors, p.err_host, rs_c, (uint32_t)n0 * 2u);
+            __syncthreads();  // the working waves' one barrier
+            return;
+        }
+    }
+
+    // ---- phase protocol, first part (wave 0): the zeros of slice 0, then this workgroup's call
+    // count.  Buffer instructions whose offset lies outside the buffer are dropped by the
+    // hardware, so the lanes and waves that take no part get such an offset instead of a branch:
+    // the count stays an ordinary value that is waited for only where it is used.
+    uint32_t count = 0, early = 0;
+    const uint32_t origin = (uint32_t)n0 / 16u;
+    if constexpr (MODE == kAtomicPkF16Phase) {
+        constexpr uint32_t kOutside = 0xFFFFFF00u;
+        // 16-byte units of the tile: unit u = (row, 8 columns); n % 8 == 0 keeps a unit either
+        // inside or outside the matrix.  m * BN / 8 <= 128 units: two per lane of wave 0.
+        const rsrc_t rs_c = make_rsrc(p.C, (uint32_t)m * (uint32_t)n * 2u);
+        const bool zeroer = slice == 0 && wave == 0;
+#pragma unroll
+        for (int i = 0; i < 2 * NS; ++i) {
+            const int u = lane + kWave * i;
+            const int row = u / (BN / 8), col = n0 + 8 * (u % (BN / 8));
+            const bool inside = zeroer && row < m && col < n;
+            const uint32_t off = inside ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
+            // aux 16 = sc1: written through to memory, where every compute die sees it
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0u, 0u, 0u, 0u}, rs_c, off, 0, 16);
+        }
+        // the count is the first load after the zero stores, and no load is issued ahead of it
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        const rsrc_t rs_counts = make_rsrc(p.counts, kPhaseOrigins * (uint32_t)p.split_k * 4u);
+        count = __builtin_amdgcn_raw_buffer_load_b32(
+            rs_counts, wave == 0 ? (origin * (uint32_t)p.split_k + (uint32_t)slice) * 4u : kOutside, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    const LaneMap lm = make_lane_map<V, BITS>(lane, n0, m, n, k);
+    const uint32_t qgroups = (uint32_t)(k / (32 * IPG)) >> p.param_shift;
+    Tensors tensors;
+    tensors.A = make_rsrc(p.A, (uint32_t)m * (uint32_t)k * 2u);
+    // (k and n times BITS / 32, written per width so that each keeps its shortest form; 3-bit: k, n % 32 == 0)
+    constexpr int kFields = BITS == 3 ? 1 : 32 / BITS;
+    tensors.qweight = make_rsrc(p.qweight, (uint32_t)(BITS == 3 ? k / 32 * 3 : k / kFields) * (uint32_t)n * 4u);
+    tensors.scales = make_rsrc(p.scales, qgroups * (uint32_t)n * 2u);
+    tensors.qzeros = make_rsrc(p.qzeros, qgroups * (uint32_t)(BITS == 3 ? n / 32 * 3 : n / kFields) * 4u);
+    tensors.m = m;
+    tensors.n = n;
+    tensors.k = k;
+    tensors.param_shift = p.param_shift;
+
+    float4_t acc[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) acc[j] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+    const int part = slice * p.waves + wave;
+    const int g_begin = part * p.groups_base + (part < p.groups_rem ? part : p.groups_rem);
+    const int g_count = p.groups_base + (part < p.groups_rem ? 1 : 0);
+    // LDS: [0] the flag value this call waits for, [1] wave 0's early sample of the flag; from byte 16 on one [m][BN] fp32 tile per wave
+    uint32_t* lds_phase = (uint32_t*)lds_raw;
+    char* lds_tiles = lds_raw + 16;
+    FlagProbe probe;
+    probe.addr = p.flags + origin;
+    probe.value = 0;
+    Ring<V, IPG, BITS> ring;
+    wave_prime<V, IPG, GC, BITS>(ring, tensors, lm, g_begin, g_count, [&]() {
+        if constexpr (MODE == kAtomicPkF16Phase) {
+            if (wave == 0) {
+                // wait for the count (the asm makes it a used value here)
+                asm volatile("" : "+v"(count)::"memory");
+                const uint32_t now = __builtin_amdgcn_readfirstlane(count) + 1u;
+                if (lane == 0) {
+                    lds_phase[0] = now;
+                    store_through(p.counts + origin * (uint32_t)p.split_k + (uint32_t)slice, now);
+                    if (slice == 0)
+                        __hip_atomic_store(p.flags + origin, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                // Early sample of the flag for the whole workgroup.  The slice-0 workgroup of
+                // the tile publishes at about this moment, so the sample is taken a little
+                // later; this wave has nothing to do but wait for its weights anyway.  A sample
+                // that comes too early only means that the late sample below is used instead.
+                for (int i = 0; i < p.probe_delay; ++i) __builtin_amdgcn_s_sleep(1);
+                early = __hip_atomic_load(p.flags + origin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    });
+    // second strip: its parameters and weights are requested behind the first strip's, so they
+    // arrive while the first strip is being computed; the activations are the first strip's
+    Ring<V, IPG, BITS> ring1;
+    float4_t acc1[V];
+    if constexpr (NS == 2) {
+        const LaneMap lm1 = make_lane_map<V, BITS>(lane, n0 + 16 * V, m, n, k);
+        issue_params<V, BITS>(ring1.par[0], lm1, tensors, g_begin);
+#pragma unroll
+        for (int it = 0; it < IPG; ++it)
+        {
+            if constexpr (BITS == 4)
+                ring1.step[0][it].w.load(tensors.qweight, lm1.off_w, ((uint32_t)g_begin * IPG + it) * 16u * (uint32_t)n);
+            else
+                issue_step_weights<V, BITS>(ring1.step[0][it], lm1, tensors, (uint32_t)g_begin * IPG + it);
+        }
+#pragma unroll
+        for (int j = 0; j < V; ++j) acc1[j] = float4_t{0.f, 0.f, 0.f, 0.f};
+        wave_run<V, IPG, MODE == kAtomicPkF16Phase, GC, BITS>(ring, tensors, lm, g_begin, g_count, acc, probe);
+#pragma unroll
+        for (int it = 0; it < IPG; ++it) ring1.step[0][it].a = ring.step[0][it].a;
+        FlagProbe none{nullptr, 0};
+        if constexpr (BITS == 8)
+            compute_group<V, IPG, 0, false, false, BITS>(ring1, lm1, tensors, magic_64x4(), 0, acc1, none);
+        else
+            compute_group<V, IPG, 0, false, false, BITS>(ring1, lm1, tensors, magic_1024x2(), 0, acc1, none);
+    } else {
+        wave_run<V, IPG, MODE == kAtomicPkF16Phase, GC, BITS>(ring, tensors, lm, g_begin, g_count, acc, probe);
+    }
+
+    if constexpr (MODE == kAtomicPkF16Phase) {
+        if (wave == 0 && lane == 0) lds_phase[1] = early;
+    }
+
+    // ---- two strips per wave, four waves (the launch the plan uses): the sum over the waves and
+    // the adds into C in as few instructions as possible behind the barrier, because one wave per
+    // SIMD runs them with nothing to overlap them with.  Every wave writes its whole [16][128]
+    // tile (rows >= m hold copies of row m - 1 and are never added); thread t then owns the column
+    // pair 2 (t % 64) of rows t / 64 + 4 i, i = 0..3: eight bytes at 8 t + 2048 i of every wave's
+    // tile, so all sixteen reads share one address register, and consecutive lanes add to
+    // consecutive words of one row of C.  The offsets into C are worked out before the barrier
+    // (the asm pins them there); rows >= m and columns >= n get an offset outside the buffer.
+    if constexpr (NS == 2 && kService) {
+        if (waves == 4) {
+            constexpr int kTileBytes = 16 * BN * 4;
+            constexpr uint32_t kOutside = 0xFFFFFF00u;
+            char* mine = lds_tiles + wave * kTileBytes + ((4 * (lane >> 4)) * BN + V * (lane & 15)) * 4;
+            uint32_t their_offset = 8u * (uint32_t)tid;
+            const rsrc_t rs_c = make_rsrc(p.C, (uint32_t)m * (uint32_t)n * 2u);
+            const int col = n0 + 2 * (tid & 63);
+            uint32_t off[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = (tid >> 6) + 4 * i;
+                off[i] = (row < m && col < n) ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
+            }
+            asm volatile("" : "+v"(off[0]), "+v"(off[1]), "+v"(off[2]), "+v"(off[3]), "+v"(their_offset));
+            const char* theirs = lds_tiles + their_offset;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                *(float4_t*)(mine + r * BN * 4) = float4_t{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+                *(float4_t*)(mine + r * BN * 4 + 16 * V * 4) = float4_t{acc1[0][r], acc1[1][r], acc1[2][r], acc1[3][r]};
+            }
+            __syncthreads();
+            float2 part[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) part[i][q] = *(const float2*)(theirs + q * kTileBytes + i * 2048);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float sx = (part[i][0].x + part[i][1].x) + (part[i][2].x + part[i][3].x);
+                const float sy = (part[i][0].y + part[i][1].y) + (part[i][2].y + part[i][3].y);
+                const half2_t h = {(_Float16)sx, (_Float16)sy};
+                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(h, rs_c, off[i], 0, 0);
+            }
+            return;
+        }
+    }
+
+    // ---- sum the waves' tiles through LDS.  acc[j][r] is row 4*(lane/16)+r, column V*(lane%16)+j.
+    float* red = (float*)(lds_tiles + wave * lds_wave_bytes);  // [m][BN]
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = 4 * (lane >> 4) + r;
+        if (row < m) {
+            float* dst = red + row * BN + V * (lane & 15);
+            if constexpr (NS == 2) {
+                static_assert(NS == 1 || V == 4, "two strips per wave: 128-bit loads");
+                *(float4_t*)(dst + 16 * V) = float4_t{acc1[0][r], acc1[1][r], acc1[2][r], acc1[3][r]};
+            }
+            if constexpr (V == 4) {
+                *(float4_t*)dst = float4_t{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+            } else if constexpr (V == 2) {
+                *(float2*)dst = float2{acc[0][r], acc[1][r]};
+            } else {
+                *dst = acc[0][r];
+            }
+        }
+    }
+
+    // A unit is one element (modes whose atomics are per element) or two adjacent columns.
+    // Consecutive threads take consecutive units, so an atomic instruction of a wave touches the
+    // fewest cache lines (the L2 charges atomics per line).  A thread's first two units are
+    // handled in straight-line code whose addresses are worked out before the barrier and whose
+    // LDS reads (two units x up to four waves) are in flight together; the modes that write C
+    // itself use buffer instructions, which drop lanes whose offset lies outside the buffer, so
+    // there is no branch between the barrier and the adds.  Further units (few threads, many
+    // rows) go through the loop behind.
+    constexpr int EPU = (MODE == kAtomicF32 || MODE == kAtomicFixed) ? 1 : 2;
+    constexpr bool kBufferOut =
+        MODE == kDirect || MODE == kAtomicPkF16 || MODE == kAtomicPkF16Phase || MODE == kAtomicPkF16Service;
+    constexpr uint32_t kOutsideC = 0xFFFFFF00u;
+    const int units = m * BN / EPU;
+    const int wave_floats = lds_wave_bytes / 4;
+    const float* red0 = (const float*)lds_tiles;
+    const rsrc_t rs_out = make_rsrc(p.C, (uint32_t)m * (uint32_t)n * 2u);
+
+    struct Unit {
+        bool ok;        // inside the tile and the matrix
+        int lds;        // float index inside a wave's tile
+        int row, col;
+        uint32_t off;   // byte offset into C, or kOutsideC
+    };
+    auto make_unit = [&](int u) {
+        Unit x;
+        const int uc = u < units ? u : 0;
+        const int e = uc * EPU;
+        x.lds = e;
+        x.row = e / BN;
+        x.col = n0 + e % BN;
+        x.ok = u < units && x.col < n;
+        x.off = x.ok ? ((uint32_t)x.row * (uint32_t)n + (uint32_t)x.col) * 2u : kOutsideC;
+        return x;
+    };
+    // `base` = wave index of the first of four tiles to read; tiles past the last wave are read
+    // from the last wave (a valid address) and left out of the sum
+    auto read_unit = [&](const Unit& x, int base, float (&v)[4][EPU]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int wq = base + q < waves ? base + q : waves - 1;
+            const float* src = red0 + wq * wave_floats + x.lds;
+            if constexpr (EPU == 2) {
+                const float2 t2 = *(const float2*)src;
+                v[q][0] = t2.x;
+                v[q][1] = t2.y;
+            } else {
+                v[q][0] = *src;
+            }
+        }
+    };
+    auto add_unit = [&](int base, const float (&v)[4][EPU], float (&sum)[EPU]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float keep = base + q < waves ? 1.f : 0.f;
+#pragma unroll
+            for (int e = 0; e < EPU; ++e) sum[e] = q == 0 ? sum[e] + v[q][e] : sum[e] + keep * v[q][e];
+        }
+    };
+    auto emit_pair = [&](const Unit& xa, const float (&sa)[EPU], const Unit& xb, const float (&sb)[EPU]) {
+        if constexpr (MODE == kDirect) {
+            __builtin_amdgcn_raw_buffer_store_b32(pack_half2(sa[0], sa[1]), rs_out, xa.off, 0, kWriteThrough);
+            __builtin_amdgcn_raw_buffer_store_b32(pack_half2(sb[0], sb[1]), rs_out, xb.off, 0, kWriteThrough);
+        } else if constexpr (MODE == kAtomicPkF16 || MODE == kAtomicPkF16Phase || MODE == kAtomicPkF16Service) {
+            const half2_t ha = {(_Float16)sa[0], (_Float16)sa[1]};
+            const half2_t hb = {(_Float16)sb[0], (_Float16)sb[1]};
+            __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(ha, rs_out, xa.off, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_v2f16(hb, rs_out, xb.off, 0, 0);
+        } else if constexpr (MODE == kAtomicFixed) {
+            const Unit* xs[2] = {&xa, &xb};
+            const float vs[2] = {sa[0], sb[0]};
+            uint64_t mine[2], old[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                mine[i] = fixed_contribution(vs[i]);
+                old[i] = 0;
+                if (xs[i]->ok)
+                    old[i] = __hip_atomic_fetch_add((uint64_t*)p.scratch + (size_t)xs[i]->row * n + xs[i]->col, mine[i],
+                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                float total = 0.f;
+                const size_t idx = (size_t)xs[i]->row * n + xs[i]->col;
+                if (xs[i]->ok && fixed_finish((uint64_t*)p.scratch + idx, old[i], mine[i], p.split_k, &total)) {
+                    const _Float16 h = (_Float16)total;
+                    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, h), rs_out, xs[i]->off, 0, kWriteThrough);
+                }
+            }
+        } else if constexpr (MODE == kAtomicF32) {
+            if (xa.ok)
+                __hip_atomic_fetch_add(p.scratch + (size_t)xa.row * n + xa.col, sa[0], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            if (xb.ok)
+                __hip_atomic_fetch_add(p.scratch + (size_t)xb.row * n + xb.col, sb[0], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        } else {  // kWorkspace
+            const Unit* xs[2] = {&xa, &xb};
+            const float* ss[2] = {sa, sb};
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (!xs[i]->ok) continue;
+                const uint64_t bits = (uint64_t)__builtin_bit_cast(uint32_t, ss[i][0]) |
+                                      ((uint64_t)__builtin_bit_cast(uint32_t, ss[i][EPU - 1]) << 32);
+                __hip_atomic_store((uint64_t*)(p.scratch + ((size_t)slice * m + xs[i]->row) * n + xs[i]->col), bits,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    };
+    (void)kBufferOut;
+
+    const Unit first_a = make_unit(tid), first_b = make_unit(tid + nthreads);
+    const bool has_units = tid < units;  // a workgroup of many waves on a narrow tile has idle threads
+    __syncthreads();
+    float va[4][EPU], vb[4][EPU];
+    if (has_units) {
+        read_unit(first_a, 0, va);
+        read_unit(first_b, 0, vb);
+    }
+
+    if constexpr (MODE == kAtomicPkF16Phase) {
+        // wait until this call's zeros of the tile are in memory (normally already seen)
+        const uint32_t expect = lds_phase[0];
+        uint32_t seen = lds_phase[1];
+        if (seen != expect) seen = __builtin_amdgcn_readfirstlane(probe.value);
+        int polls = 0;
+        while (seen != expect && polls < p.spin_limit) {
+            __builtin_amdgcn_s_sleep(4);
+            seen = __builtin_amdgcn_readfirstlane(
+                __hip_atomic_load(p.flags + origin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            ++polls;
+        }
+        if (seen != expect && lane == 0) phase_wait_failed(p.errors, p.err_host, rs_out, (uint32_t)n0 * 2u);
+    }
+
+    if (has_units) {
+        float sa[EPU], sb[EPU];
+#pragma unroll
+        for (int e = 0; e < EPU; ++e) sa[e] = sb[e] = 0.f;
+        add_unit(0, va, sa);
+        add_unit(0, vb, sb);
+        for (int base = 4; base < waves; base += 4) {
+            read_unit(first_a, base, va);
+            read_unit(first_b, base, vb);
+            add_unit(base, va, sa);
+            add_unit(base, vb, sb);
+        }
+        emit_pair(first_a, sa, first_b, sb);
+    }
+    for (int u0 = tid + 2 * nthreads; u0 < units; u0 += 2 * nthreads) {
+        const Unit xa = make_unit(u0), xb = make_unit(u0 + nthreads);
+        float sa[EPU], sb[EPU];
+#pragma unroll
+        for (int e = 0; e < EPU; ++e) sa[e] = sb[e] = 0.f;
+        for (int base = 0; base < waves; base += 4) {
+            read_unit(xa, base, va);
+            read_unit(xb, base, vb);
+            add_unit(base, va, sa);
+            add_unit(base, vb, sb);
+        }
+        emit_pair(xa, sa, xb, sb);
+    }
+
+    if constexpr (MODE == kAtomicF32 || MODE == kWorkspace) {
+        // ticket: the workgroup that arrives last at this tile finishes it
+        __shared__ uint32_t last_flag;
+        wait_memory_ops();
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const uint32_t old = __hip_atomic_fetch_add(p.tickets + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last_flag = (old == (uint32_t)(p.split_k - 1));
+        }
+        __syncthreads();
+        if (last_flag) {
+            const int pairs = m * (BN / 2);
+            if constexpr (MODE == kAtomicF32) {
+                const int elems = m * BN;
+                for (int e = threadIdx.x; e < elems; e += blockDim.x) {
+                    const int row = e / BN;
+                    const int col = n0 + e % BN;
+                    if (col >= n) continue;
+                    const size_t idx = (size_t)row * n + col;
+                    const float v = __hip_atomic_exchange(p.scratch + idx, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    p.C[idx] = (_Float16)v;
+                }
+            } else {
+                for (int e = threadIdx.x; e < pairs; e += blockDim.x) {
+                    const int row = e / (BN / 2);
+                    const int col = n0 + 2 * (e % (BN / 2));
+                    if (col >= n) continue;
+                    float v0 = 0.f, v1 = 0.f;
+                    for (int s = 0; s < p.split_k; ++s) {
+                        const uint64_t bits = __hip_atomic_load(
+                            (const uint64_t*)(p.scratch + ((size_t)s * m + row) * n + col), __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT);
+                        v0 += __builtin_bit_cast(float, (uint32_t)bits);
+                        v1 += __builtin_bit_cast(float, (uint32_t)(bits >> 32));
+                    }
+                    *(uint32_t*)(p.C + (size_t)row * n + col) = pack_half2(v0, v1);
+                }
+            }
+            if (threadIdx.x == 0)
+                __hip_atomic_store(p.tickets + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
+// Kernel entry.  The first 14 dwords of the argument list (five pointers, four integers) are
+// what a wave needs before it can issue its first load; the build asks the compiler to have
+// them preloaded into scalar registers at wave launch (kernarg preload), so that no round trip
+// to the kernarg segment (about 0.3 us) precedes the loads.  Everything else comes in `rest`
+// and is fetched by one batch of scalar loads while the first vector loads are in flight.
+//   packed = m | param_shift << 5 | waves << 7 | groups_base << 12
+//   split_rem = split_k | groups_rem << 16
+// The whole list is 96 bytes: the host's share of a launch is up to 0.7 us longer from 120 bytes on
+// (2.9 us against 3.6 us on a core far from the GPU; 112 bytes and less cost the same as 56).
+struct GemmRest {
+    union {
+        float* scratch;   // fp32 sums, partial tiles, fixed-point words
+        uint32_t* flags;  // phase protocol
+    };
+    union {
+        uint32_t* tickets;
+        uint32_t* counts;  // phase protocol
+    };
+    uint32_t* errors;
+    uint32_t* err_host;
+    int spin_limit;
+    int probe_delay;
+};
+
+template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1>
+__global__ void __launch_bounds__(kWave * (WMAX + (MODE == kAtomicPkF16Service ? 1 : 0)))
+gemm_kernel(const _Float16* A, const uint32_t* qweight, const _Float16* scales, const uint32_t* qzeros, _Float16* C,
+            int packed, int n, int k, int split_rem, const GemmRest rest)
+{
+    GemmArgs p;
+    p.A = A;
+    p.qweight = qweight;
+    p.scales = scales;
+    p.qzeros = qzeros;
+    p.C = C;
+    p.m = packed & 31;
+    p.param_shift = (packed >> 5) & 3;
+    p.waves = (packed >> 7) & 31;
+    p.groups_base = (int)((unsigned)packed >> 12);
+    p.groups_rem = (int)((unsigned)split_rem >> 16);
+    p.n = n;
+    p.k = k;
+    p.tiles = 0;  // only the launch needs it
+    p.split_k = split_rem & 0xFFFF;
+    p.scratch = rest.scratch;
+    p.tickets = rest.tickets;
+    p.flags = rest.flags;
+    p.counts = rest.counts;
+    p.errors = rest.errors;
+    p.err_host = rest.err_host;
+    p.spin_limit = rest.spin_limit;
+    p.probe_delay = rest.probe_delay;
+    gemm_body<V, IPG, MODE, WMAX, GC, BITS, NS>(p);
+}
+
+}  // namespace w4a16
