@@ -38,7 +38,7 @@ def kernel_source_id():
     h = hashlib.sha256()
     pkg = os.path.join(ROOT, "paper_2402_00025_amd")
     for rel in ("csrc/w4a16.hip", "csrc/w4a16_device.hpp", "csrc/w4a16_wave.hpp", "csrc/w4a16_stream.hpp",
-                "csrc/w4a16_rows.hpp", "csrc/w4a16_rows.hip", "build.py"):
+                "csrc/w4a16_rows.hpp", "csrc/w4a16_rows.hip", "csrc/w4a16_fine.hip", "build.py"):
         with open(os.path.join(pkg, rel), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -32,7 +32,7 @@ EXPORTS = (
     "w2a16_gemm", "w2a16_gemm_dp", "w2a16_algorithmic_bytes", "w3a16_gemm", "w3a16_gemm_dp", "w3a16_algorithmic_bytes", "w4a16_actorder_prepare", "w4a16_gemm_actorder",
     "w4a16_read_probe", "w4a16_gemm_static", "w4a16_set_phase_spin_limit", "w4a16_workspace_bytes",
     "w4a16_set_workspace", "w4a16_reserve_scratch", "w4a16_gemm_streamk_bits",
-    "w4a16_plan_many_rows", "w4a16_plan_batch",
+    "w4a16_plan_many_rows", "w4a16_plan_batch", "w4a16_plan_fine",
 )
 
 _lib = None
@@ -95,6 +95,7 @@ def lib() -> ctypes.CDLL:
     L.w4a16_plan_bits.argtypes = [ci] * 6 + [ip] * 4
     L.w4a16_plan_many_rows.argtypes = [ci] * 6 + [ip] * 3
     L.w4a16_plan_batch.argtypes = [ci] * 5 + [ip] * 2
+    L.w4a16_plan_fine.argtypes = [ci] * 5 + [ip] * 3
     L.w4a16_check.argtypes = [ci] * 5
     L.w4a16_unpack.argtypes = [vp] * 4 + [ci] * 3 + [vp]
     L.w4a16_dequant.argtypes = [vp] * 4 + [ci] * 3 + [vp]
@@ -264,6 +265,14 @@ def w4a16_plan_batch(bits, m, n, k, group_size) -> dict | None:
     s, t = (ctypes.c_int(0) for _ in range(2))
     _check(lib().w4a16_plan_batch(bits, m, n, k, group_size, ctypes.byref(s), ctypes.byref(t)), "w4a16_plan_batch")
     return dict(split_k=s.value, tile_cols=t.value) if s.value else None
+
+
+def w4a16_plan_fine(bits, m, n, k, group_size) -> dict | None:
+    """The per-wave launch in steps of 128 k (groups of 32 and 64, up to 16 rows) of a SplitK call with split_k = 0, or None
+    where the call goes to other launches."""
+    s, t, w = (ctypes.c_int(0) for _ in range(3))
+    _check(lib().w4a16_plan_fine(bits, m, n, k, group_size, ctypes.byref(s), ctypes.byref(t), ctypes.byref(w)), "w4a16_plan_fine")
+    return dict(split_k=s.value, tile_cols=t.value, waves=w.value) if s.value else None
 
 
 def w4a16_check(m, n, k, group_size, split_k) -> int:

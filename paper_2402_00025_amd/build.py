@@ -9,7 +9,8 @@ import sysconfig
 import tempfile
 
 HERE = pathlib.Path(__file__).resolve().parent
-SOURCES = [HERE / "csrc" / "w4a16.hip", HERE / "csrc" / "w4a16_rows.hip", HERE / "csrc" / "w4a16_batch.hip"]
+SOURCES = [HERE / "csrc" / "w4a16.hip", HERE / "csrc" / "w4a16_rows.hip", HERE / "csrc" / "w4a16_batch.hip",
+           HERE / "csrc" / "w4a16_fine.hip"]
 LIB = HERE / "libw4a16.so"
 CALL_SRC = HERE / "csrc" / "py_call.cpp"
 CALL_LIB = HERE / "_call.so"

@@ -1458,35 +1458,8 @@ static int resolve_scratch(int kind, hipStream_t stream, const ScratchNeed& need
 template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1>
 static int launch_bound(const GemmArgs& a, int waves, size_t lds_bytes, hipStream_t stream)
 {
-    auto kern = gemm_kernel<V, IPG, MODE, WMAX, GC, BITS, NS>;
-    if (lds_bytes > 64 * 1024) {
-        if (!W4A16_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds_bytes)))
-            return W4A16_ERR_HIP;
-    }
-    const unsigned threads = (unsigned)(waves + (MODE == kAtomicPkF16Service ? 1 : 0)) * kWave;
-    // (the second grid dimension holds at most 65535; more tiles or parts with a group more than these were never taken)
-    if (a.m > 31 || a.param_shift > 3 || a.waves > 31 || a.groups_base >= (1 << 20) || a.groups_rem >= (1 << 11) ||
-        a.tiles >= (1 << 20) || a.split_k < 1 || a.split_k >= (1 << 16))
-        return W4A16_ERR_UNSUPPORTED;
-    const int packed = a.m | a.param_shift << 5 | a.waves << 7 | (int)((unsigned)a.groups_base << 12);
-    const int split_rem = a.split_k | a.groups_rem << 16;
-    constexpr bool kPhase = MODE == kAtomicPkF16Phase || MODE == kAtomicPkF16Service;
-    GemmRest rest;
-    if constexpr (kPhase) {
-        rest.flags = a.flags;
-        rest.counts = a.counts;
-    } else {
-        rest.scratch = a.scratch;
-        rest.tickets = a.tickets;
-    }
-    rest.errors = a.errors;
-    rest.err_host = a.err_host;
-    rest.spin_limit = a.spin_limit;
-    rest.probe_delay = a.probe_delay;
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.tiles, (unsigned)a.split_k), dim3(threads), lds_bytes, stream, a.A,
-                       a.qweight, a.scales, a.qzeros, a.C, packed, a.n, a.k, split_rem, rest);
-    return W4A16_HIP(hipGetLastError()) ? W4A16_OK : W4A16_ERR_HIP;
+    if (!wave_args_ok(a)) return W4A16_ERR_UNSUPPORTED;
+    return W4A16_HIP((launch_wave<V, IPG, MODE, WMAX, GC, BITS, NS>(a, waves, lds_bytes, stream))) ? W4A16_OK : W4A16_ERR_HIP;
 }
 
 template <int V, int IPG, int MODE>
@@ -2024,6 +1997,101 @@ static void plan_batch_few(int m, int n, int k, int group_size, int bits, const 
     }
 }
 
+// ---- Up to 16 rows, groups of 32 and 64, k a multiple of 128: the per-wave kernel with compute groups of 128 k, that is with
+// two groups of 128 k on their way where the ring of single groups holds 64 or 128 k in all, and one request in the place of
+// two or four for their parameters (see Ring).
+struct FineShape {
+    double megabytes, params, adds, full, fuller, per, walk, rounds;
+    bool uneven, single, splits;
+    FineShape(int tile_cols, int waves, int split_k, int m, int n, int k, int group_k, int group_size, int bits)
+    {
+        const int groups = k / group_k, parts = split_k * waves, wgs = split_k * ((n + tile_cols - 1) / tile_cols);
+        megabytes = (double)n * k * bits / 8e6;
+        params = (double)(k / group_size) * n * (2 + bits / 8.0) * 1e-6;
+        splits = split_k > 1;
+        adds = splits ? (double)m * n * split_k * 1e-6 : 0.0;
+        full = (double)wgs * waves / 1024.0;
+        fuller = full > 1.0 ? full : 1.0;
+        rounds = (wgs + 255) / 256;
+        const int longest = (groups + parts - 1) / parts;
+        per = longest * (group_k / 128.0);
+        walk = per * fuller;
+        uneven = groups % parts != 0 && longest <= 2;
+        single = groups == parts;
+    }
+};
+
+// us of such a launch, and of the launch `others` of the ring of single groups: fitted to 13,500 random shapes (n and k from 1024 to
+// 28672, every width, seven launches each; spread 7, 9, 5, 6 % and 6, 6 %; those 35 % behind the best of a shape left out).
+static double fine_us(int tile_cols, int waves, int split_k, int m, int n, int k, int group_size, int bits)
+{
+    const FineShape x(tile_cols, waves, split_k, m, n, k, 128, group_size, bits);
+    const double rows = m / 16.0, w8 = bits == 8, w3 = bits == 3, w2 = bits == 2, g32 = group_size == 32;
+    const double activations = x.full * 1.024 * x.per;
+    if (m <= 4)
+        return 2.7548 + 0.1381 * x.megabytes + 3.4937 * x.adds + 0.509 * x.splits + 0.3988 * x.per * x.rounds - 0.4874
+               * x.single - 0.2238 * activations + 0.2291 * w3 * x.walk + 0.1752 * w2 * x.walk + 0.1133 * g32 * x.walk;
+    if (tile_cols == 128)
+        return 2.4274 - 1.1648 * x.megabytes + 10.4644 * x.full + 1.0423 * x.per * x.rounds + 0.4557 * rows + 0.6642 *
+               w8 * x.megabytes - 0.3848 * w3 * x.megabytes - 1.2334 * w2 * x.megabytes + 0.6675 * w3 * x.walk +
+               0.2817 * g32 * x.walk;
+    if (waves == 2)
+        return 2.8756 + 0.0676 * x.megabytes + 0.3087 * std::sqrt(x.megabytes) - 1.3795 * x.fuller + 0.3148 * x.rounds
+               - 0.8904 * x.per + 1.3613 * x.walk + 0.9859 * rows + 0.199 * w3 * x.walk + 0.1316 * w2 * x.walk +
+               0.1626 * g32 * x.walk;
+    return 1.7213 + 0.2534 * std::sqrt(x.megabytes) + 0.741 * x.fuller - 0.144 * x.per + 0.7186 * x.per * x.rounds
+               + 0.3157 * x.uneven + 0.2274 * activations * rows + 0.0531 * w8 * x.megabytes + 0.1481 * w3 * x.walk +
+               0.1559 * g32 * x.walk;
+}
+
+static double single_groups_us(const Plan& others, int m, int n, int k, int group_size, int bits)
+{
+    const FineShape x(others.tile_cols, others.waves, others.split_k, m, n, k, group_size, group_size, bits);
+    const double rows = m / 16.0, w8 = bits == 8, w3 = bits == 3, g32 = group_size == 32;
+    const double activations = x.full * 1.024 * x.per;
+    if (m <= 4)
+        return 2.9591 + 0.9246 * x.params + 0.4616 * x.per * x.rounds + 0.0427 * w8 * x.megabytes + 0.1845 * w3 *
+               x.walk - 0.0217 * g32 * x.megabytes + 0.6308 * std::sqrt(x.megabytes) * rows;
+    return 2.982 + 0.0343 * x.megabytes + 0.5852 * x.params + 0.4122 * x.full + 0.7144 * x.per * x.rounds - 0.3931
+               * activations + 0.294 * activations * rows + 0.2981 * w8 * x.walk + 0.23 * w3 * x.walk;
+}
+
+// The launch, if the estimates put it 5 % ahead of `others`, 10 % ahead of `batch` where that is the call's launch.  It splits k only
+// where the other does, and no further where the parts meet in fp16 (up to four rows they meet in fixed point both ways).
+// us per call, cold weights, before -> now (m; n x k): groups of 32, 1; 5120 x 13824: 11.9 -> 9.9, 1; 8192 x 8192: 11.2 -> 9.3,
+// 8; 4096 x 4096: 5.8 -> 4.7; groups of 64, 8; 1536 x 16384: 8.2 -> 5.9.  Of 5681 shapes that the fits have not seen 2703 go here,
+// 0.89 times the time on average, 68 of them more than 2 % slower, at worst 13 %.  Narrower than 1024 columns, k below that
+// and beyond 28672, where nothing was fitted, the calls stay where they were.
+static bool plan_fine(int m, int n, int k, int group_size, int bits, const Plan& others, const BatchPlan& batch, Plan* plan)
+{
+    if (m > 16 || group_size >= 128 || k % 128 != 0 || n < 1024 || n > 28672 || k < 1024 || k > 28672) return false;
+    const int groups = k / 128, tiles = (n + 63) / 64;
+    const int reduce = m <= 4 ? W4A16_REDUCE_ATOMIC_FIXED : W4A16_REDUCE_ATOMIC_PK_F16_PHASE;
+    const int most = others.split_k == 1 || others.reduce != reduce ? 1 : m <= 4 ? 64 : others.split_k;
+    double best = 0.95 * single_groups_us(others, m, n, k, group_size, bits);
+    if (batch.split_k) {
+        const double us = 0.9 * batch_few_us(batch.strips, batch.split_k, m, n, k, group_size / 32, bits);
+        best = us < best ? us : best;
+    }
+    bool found = false;
+    auto consider = [&](int tile_cols, int waves, int split_k) {
+        if (split_k < 1 || split_k > most || split_k * waves > groups) return;
+        const double us = fine_us(tile_cols, waves, split_k, m, n, k, group_size, bits);
+        if (us < best) {
+            best = us;
+            *plan = Plan{split_k, tile_cols, waves, reduce};
+            found = true;
+        }
+    };
+    for (int split_k : {1, 2, 3, 4, 6, 8, 256 / tiles, 512 / tiles, 768 / tiles, 1024 / tiles, groups / 4}) consider(64, 4, split_k);
+    if (m > 4) {
+        consider(64, 2, groups / 2);
+        consider(64, 2, 256 / tiles);
+        if (groups % 4 == 0 && groups >= 8) consider(128, 4, groups / 4);
+    }
+    return found;
+}
+
 // The launches that a call would make without the batch kernel.
 struct BatchOthers {
     Plan rows{1, 0, 0, 0};  // of up to 64 rows; with fine groups of 16
@@ -2126,6 +2194,69 @@ static int run_rows(const RowsPlan& plan, const void* A, const void* qweight, co
     return W4A16_HIP(launch_rows(a, bits, ipg, row_blocks, plan.workers, stream)) ? W4A16_OK : W4A16_ERR_HIP;
 }
 
+// What the launch `plan` of the per-wave kernel is told, but for its scratch.
+static GemmArgs wave_args(const Plan& plan, const void* A, const void* qweight, const void* scales, const void* qzeros, void* C,
+                          int m, int n, int k, int ipg, int param_shift)
+{
+    GemmArgs a;
+    a.A = (const _Float16*)A;
+    a.qweight = (const uint32_t*)qweight;
+    a.scales = (const _Float16*)scales;
+    a.qzeros = (const uint32_t*)qzeros;
+    a.C = (_Float16*)C;
+    a.scratch = nullptr;
+    a.tickets = nullptr;
+    a.m = m;
+    a.n = n;
+    a.k = k;
+    a.tiles = (n + plan.tile_cols - 1) / plan.tile_cols;
+    a.split_k = plan.split_k;
+    const int cgroups = k / (32 * ipg), kparts = plan.split_k * plan.waves;
+    a.groups_base = cgroups / kparts;
+    a.groups_rem = cgroups % kparts;
+    a.waves = plan.waves;
+    a.param_shift = param_shift;
+    a.flags = nullptr;
+    a.counts = nullptr;
+    a.errors = nullptr;
+    a.err_host = nullptr;
+    a.spin_limit = g_spin_limit;
+    a.probe_delay = g_probe_delay;
+    return a;
+}
+
+// LDS: 16 bytes for the phase word, then one [m, tile_cols] fp32 tile per wave, for the sum over the workgroup's waves
+static size_t wave_lds_bytes(const Plan& plan, int m) { return 16 + (size_t)gemm_lds_wave_bytes(plan.tile_cols, m) * plan.waves; }
+
+// The launch of plan_fine.  W4A16_ERR_STATE: there is no scratch for it (under capture).
+static int run_fine(const Plan& plan, const BatchOthers& others, const void* A, const void* qweight, const void* scales, const void* qzeros,
+                    void* C, int m, int n, int k, int group_size, int bits, hipStream_t stream)
+{
+    GemmArgs a = wave_args(plan, A, qweight, scales, qzeros, C, m, n, k, 4, 0);
+    const int mode = plan.split_k > 1 ? plan.reduce : (int)kDirect;
+    if (others.scratch()) {  // (what the other launches would leave is left, whether k is split here or not)
+        ScratchNeed need;
+        need.n = n;
+        need.fixed_words = mode == kAtomicFixed ? (size_t)m * n : 0;
+        need.phase_split = mode == kAtomicPkF16Phase ? plan.split_k : 0;
+        need.others_phase_split[0] = BatchOthers::phase_split(others.rows);
+        need.others_fixed_words = (size_t)4 * n;
+        ScratchView view;
+        const int rc = resolve_scratch(kScratchLibrary, stream, need, &view);
+        if (rc != W4A16_OK) return rc;
+        a.scratch = (float*)view.fixed;
+        if (mode == kAtomicPkF16Phase) {
+            a.flags = view.flags;
+            a.counts = view.counts;
+            a.errors = view.errors;
+            a.err_host = view.err_host;
+        }
+    }
+    if (!wave_args_ok(a)) return W4A16_ERR_UNSUPPORTED;
+    return W4A16_HIP(launch_fine(a, bits, 128 / group_size, plan.tile_cols, plan.waves, wave_lds_bytes(plan, m), mode, stream)) ? W4A16_OK
+                                                                                                                                : W4A16_ERR_HIP;
+}
+
 static void read_tuning_env()
 {
     static bool done = false;
@@ -2171,6 +2302,13 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
         BatchOthers others;
         rc = plan_batch(m, n, k, group_size, bits, &batch, &others);
         if (rc != W4A16_OK) return rc;
+        Plan fine;
+        if (plan_fine(m, n, k, group_size, bits, others.rows, batch, &fine)) {
+            rc = run_fine(fine, others, A, qweight, scales, qzeros, C, m, n, k, group_size, bits, (hipStream_t)stream_v);
+            // (under capture there may be scratch for the other launches alone)
+            if (rc != W4A16_ERR_STATE) return rc;
+            rc = W4A16_OK;
+        }
         if (batch.split_k) {
             ScratchView view;
             if (others.scratch()) {
@@ -2242,36 +2380,10 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
 
     hipStream_t stream = (hipStream_t)stream_v;
     const int ipg = group_size >= 128 ? 4 : group_size / 32;  // MFMA steps (32 k each) per compute group
-    const int param_shift = group_size == 256 ? 1 : 0;
     const bool two_strips = plan.tile_cols == 128;
     const int V = two_strips ? 4 : plan.tile_cols / 16;
-    GemmArgs a;
-    a.A = (const _Float16*)A;
-    a.qweight = (const uint32_t*)qweight;
-    a.scales = (const _Float16*)scales;
-    a.qzeros = (const uint32_t*)qzeros;
-    a.C = (_Float16*)C;
-    a.scratch = nullptr;
-    a.tickets = nullptr;
-    a.m = m;
-    a.n = n;
-    a.k = k;
-    a.tiles = (n + plan.tile_cols - 1) / plan.tile_cols;
-    a.split_k = plan.split_k;
-    const int cgroups = k / (32 * ipg), kparts = plan.split_k * plan.waves;
-    a.groups_base = cgroups / kparts;
-    a.groups_rem = cgroups % kparts;
-    a.waves = plan.waves;
-    a.param_shift = param_shift;
-    // LDS: 16 bytes for the phase word, then one [m, tile_cols] fp32 tile per wave, for the sum
-    // over the workgroup's waves
-    const size_t lds_bytes = 16 + (size_t)gemm_lds_wave_bytes(plan.tile_cols, m) * plan.waves;
-    a.flags = nullptr;
-    a.counts = nullptr;
-    a.errors = nullptr;
-    a.err_host = nullptr;
-    a.spin_limit = g_spin_limit;
-    a.probe_delay = g_probe_delay;
+    GemmArgs a = wave_args(plan, A, qweight, scales, qzeros, C, m, n, k, ipg, group_size == 256 ? 1 : 0);
+    const size_t lds_bytes = wave_lds_bytes(plan, m);
     if (lds_bytes > 160 * 1024) return W4A16_ERR_UNSUPPORTED;
 
     int mode = kDirect;
@@ -2304,6 +2416,13 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
                                (uint32_t*)C, words);
             if (!W4A16_HIP(hipGetLastError())) return W4A16_ERR_HIP;
         }
+    }
+    // Up to four rows: with QUAD, which asks for a compute group's activations once and folds a quarter of the products in.  us per call,
+    // cold weights, before -> now (m; n x k): 4 bits, 1; 4096 x 4096: 3.96 -> 3.88, 3 bits, 2; 4096 x 4096: 4.52 -> 4.12, 2 bits, 1;
+    // 8192 x 8192: 8.83 -> 7.71, 8 bits, 1; 11008 x 4096: 10.85 -> 10.18.  160 random calls: 0.97 times the time, at worst 1.013.
+    if (m <= 4 && V == 4 && ipg == 4 && plan.waves <= 4 && (mode == kDirect || mode == kAtomicFixed || mode == kAtomicPkF16Phase)) {
+        if (!wave_args_ok(a)) return W4A16_ERR_UNSUPPORTED;
+        return W4A16_HIP(launch_fine(a, bits, 1, plan.tile_cols, plan.waves, lds_bytes, mode, stream)) ? W4A16_OK : W4A16_ERR_HIP;
     }
     if (two_strips) {
         if (ipg != 4 || mode != kAtomicPkF16Phase || a.groups_base != 1 || a.groups_rem != 0 || plan.waves > 4)
@@ -2573,8 +2692,29 @@ int w4a16_plan_batch(int bits, int m, int n, int k, int group_size, int* split_k
     w4a16::BatchOthers others;
     const int rc_plan = w4a16::plan_batch(m, n, k, group_size, bits, &plan, &others);
     if (rc_plan != W4A16_OK) return rc_plan;
+    w4a16::Plan fine;
+    if (w4a16::plan_fine(m, n, k, group_size, bits, others.rows, plan, &fine)) plan = w4a16::BatchPlan{0, 0};
     if (split_k) *split_k = plan.split_k;
     if (tile_cols) *tile_cols = plan.split_k ? 64 * plan.strips : 0;
+    return W4A16_OK;
+}
+
+int w4a16_plan_fine(int bits, int m, int n, int k, int group_size, int* split_k, int* tile_cols, int* waves)
+{
+    if (bits != 4 && bits != 8 && bits != 3 && bits != 2) return W4A16_ERR_UNSUPPORTED;
+    int rc = w4a16::check_args(m, n, k, group_size, 0);
+    if (rc != W4A16_OK) return rc;
+    if ((bits == 2 && n % 16 != 0) || (bits == 3 && n % 32 != 0)) return W4A16_ERR_SHAPE;
+    if ((unsigned long long)k * (unsigned long long)n * (unsigned)bits / 8 >= (1ull << 31)) return W4A16_ERR_UNSUPPORTED;
+    w4a16::BatchPlan batch;
+    w4a16::BatchOthers others;
+    w4a16::Plan fine{0, 0, 0, 0};
+    rc = w4a16::plan_batch(m, n, k, group_size, bits, &batch, &others);
+    if (rc != W4A16_OK) return rc;
+    (void)w4a16::plan_fine(m, n, k, group_size, bits, others.rows, batch, &fine);
+    if (split_k) *split_k = fine.split_k;
+    if (tile_cols) *tile_cols = fine.tile_cols;
+    if (waves) *waves = fine.waves;
     return W4A16_OK;
 }
 

@@ -451,11 +451,11 @@ __device__ __forceinline__ void issue_step_weights(StepRegs<V, BITS>& r, const L
     }
 }
 
-template <int V, int IPG, int BITS = 4>
+template <int V, int IPG, int BITS = 4, bool QUAD = false>
 __device__ __forceinline__ void issue_step(StepRegs<V, BITS>& r, const LaneMap& lm, const Tensors& t, int gi, int it)
 {
     const uint32_t step = (uint32_t)gi * IPG + it;  // MFMA step index along k: k = 32 * step
-    r.a = __builtin_amdgcn_raw_buffer_load_b128(t.A, lm.off_a, step * 64u, 0);
+    if (!QUAD || it == 0) r.a = __builtin_amdgcn_raw_buffer_load_b128(t.A, lm.off_a, step * 64u, 0);
     issue_step_weights<V, BITS>(r, lm, t, step);
 }
 
@@ -522,19 +522,75 @@ __device__ __forceinline__ half8_t order_activations(u32x4_t d)
     else return __builtin_bit_cast(half8_t, d);
 }
 
-// Ring of two compute groups: half h holds the IPG steps and the parameters of one group.
+// Ring of two compute groups: half h holds the IPG steps and the parameters of one group.  PG: quantisation groups per
+// compute group (2 or 4 where they are shorter than 128 k: 64, 32).  One request fetches the parameters of all of them, lane
+// group l / 16 those of group l / 16 (PG = 4) or l / 32; they are handed round when the compute group's turn has come.
+// QUAD: up to four activation rows.  One request fetches a compute group's activations too: lane l those of row l % 16 / 4,
+// step l % 4.  Each row then stands four times in the operand, and its sums in all four registers of lane group `row`.
 template <int V, int IPG, int BITS = 4>
 struct Ring {
     StepRegs<V, BITS> step[2][IPG];
     ParamRegs<V, BITS> par[2];
 };
 
-template <int V, int IPG, int H, int BITS = 4>
+template <int V, int IPG, int H, int BITS = 4, int PG = 1, bool QUAD = false>
 __device__ __forceinline__ void issue_group(Ring<V, IPG, BITS>& ring, const LaneMap& lm, const Tensors& t, int gi)
 {
-    issue_params<V, BITS>(ring.par[H], lm, t, gi);
+    issue_params<V, BITS>(ring.par[H], lm, t, gi * PG);
 #pragma unroll
-    for (int it = 0; it < IPG; ++it) issue_step<V, IPG, BITS>(ring.step[H][it], lm, t, gi, it);
+    for (int it = 0; it < IPG; ++it) issue_step<V, IPG, BITS, QUAD>(ring.step[H][it], lm, t, gi, it);
+}
+
+// What lane group s (of four, or of two halves) of the wave holds, in all of them.
+template <int PG>
+__device__ __forceinline__ void hand_round(uint32_t x, uint32_t (&out)[PG])
+{
+    if constexpr (PG == 1) {
+        out[0] = x;
+    } else {
+        const auto halves = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        if constexpr (PG == 2) {
+            out[0] = halves[0];
+            out[1] = halves[1];
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const auto rows = __builtin_amdgcn_permlane16_swap(halves[h], halves[h], false, false);
+                out[2 * h] = rows[0];
+                out[2 * h + 1] = rows[1];
+            }
+        }
+    }
+}
+
+// The lane map of PG > 1: the parameters' rows of this lane's group.
+template <int V, int BITS, int PG>
+__device__ __forceinline__ void spread_params(LaneMap& lm, int lane, int n)
+{
+    if constexpr (PG > 1) {
+        const uint32_t group = (uint32_t)(PG == 4 ? lane >> 4 : lane >> 5);
+        const uint32_t zrow = (uint32_t)(BITS == 3 ? n / 32 * 3 : n / (32 / (BITS == 3 ? 4 : BITS))) * 4u;
+        lm.off_z += group * zrow;
+        lm.off_z1 += group * zrow;
+        lm.off_s += group * (uint32_t)n * 2u;
+    }
+}
+
+// The lane map of QUAD.
+__device__ __forceinline__ void quad_activations(LaneMap& lm, int lane, int m, int k)
+{
+    const int row = (lane & 15) >> 2, arow = row < m ? row : m - 1;
+    lm.off_a = ((uint32_t)arow * (uint32_t)k + 32u * (uint32_t)(lane & 3) + 8u * (uint32_t)(lane >> 4)) * 2u;
+}
+
+// The four lanes of every four get what the S-th of them holds.
+template <int S>
+__device__ __forceinline__ half8_t quad_step(half8_t a)
+{
+    u32x4_t x = __builtin_bit_cast(u32x4_t, a);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[i], 0x55 * S, 0xF, 0xF, true);
+    return __builtin_bit_cast(half8_t, x);
 }
 
 // A word in memory that the last compute group of a wave samples while it still has work to
@@ -549,62 +605,74 @@ struct FlagProbe {
 // set, then acc += scale * tile in fp32.  Each step's registers are refilled with the same
 // step of group `refill` (two groups ahead) as soon as they have been consumed.  With PROBE the
 // flag is sampled once the second step's weights have arrived.
-template <int V, int IPG, int H, bool REFILL, bool PROBE, int BITS = 4>
+template <int V, int IPG, int H, bool REFILL, bool PROBE, int BITS = 4, int PG = 1, bool QUAD = false>
 __device__ __forceinline__ void compute_group(Ring<V, IPG, BITS>& ring, const LaneMap& lm, const Tensors& t,
                                               uint32_t magic, int refill, float4_t (&acc)[V], FlagProbe& probe)
 {
-    ZeroConst zc[V];
-    ZeroConst8 zc8[V];
-    ZeroConst2 zc2[V];
-    ZeroConst3 zc3[V];
-    float sc[V];
-    uint32_t zbits3 = 0;
-    if constexpr (BITS == 3)
-        zbits3 = __builtin_amdgcn_alignbit(ring.par[H].zword1, ring.par[H].zword, (uint32_t)lm.zshift);
+    static_assert(!QUAD || IPG == 4, "four steps");
+    constexpr int SPG = IPG / PG;  // steps per quantisation group
+    ParamRegs<V, BITS> par[PG];
+    {
+        uint32_t word[PG];
+        hand_round<PG>(ring.par[H].zword, word);
 #pragma unroll
-    for (int j = 0; j < V; ++j) {
-        if constexpr (BITS == 8) zc8[j] = zero_const8((ring.par[H].zword >> (lm.zshift + 8 * j)) & 0xFFu);
-        else if constexpr (BITS == 2) zc2[j] = zero_const2((ring.par[H].zword >> (lm.zshift + 2 * j)) & 0x3u);
-        else if constexpr (BITS == 3) zc3[j] = zero_const3((zbits3 >> (3 * j)) & 0x7u);
-        else zc[j] = zero_const((ring.par[H].zword >> (lm.zshift + 4 * j)) & 0xFu);
-        sc[j] = scale_of<V>(ring.par[H].s, j);
+        for (int s = 0; s < PG; ++s) par[s].zword = word[s];
+        if constexpr (BITS == 3) {
+            hand_round<PG>(ring.par[H].zword1, word);
+#pragma unroll
+            for (int s = 0; s < PG; ++s) par[s].zword1 = word[s];
+        }
+#pragma unroll
+        for (int i = 0; i < (V + 1) / 2; ++i) {
+            hand_round<PG>(ring.par[H].s.r[i], word);
+#pragma unroll
+            for (int s = 0; s < PG; ++s) par[s].s.r[i] = word[s];
+        }
     }
+    typename ZeroOf<BITS>::type zc[V];
+    float sc[V];
+    float4_t tile[V];
+    const half8_t quad = order_activations<BITS>(ring.step[H][0].a);
+    auto take = [&](int s) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            zc[j] = zero_of_column<V, BITS>(par[s], lm, j);
+            sc[j] = scale_of<V>(par[s].s, j);
+        }
+    };
+    take(0);
     if constexpr (REFILL) {
         // sched_barrier: keep the instruction scheduler from sinking the refill loads to the
         // end of the loop body (it would serialise load latency and compute)
         __builtin_amdgcn_sched_barrier(0);
-        issue_params<V, BITS>(ring.par[H], lm, t, refill);
+        issue_params<V, BITS>(ring.par[H], lm, t, refill * PG);
         __builtin_amdgcn_sched_barrier(0);
     }
-    float4_t tile[V];
-#pragma unroll
-    for (int j = 0; j < V; ++j) tile[j] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int it = 0; it < IPG; ++it) {
+        if (it % SPG == 0) {
+            if (it > 0) take(it / SPG);
+#pragma unroll
+            for (int j = 0; j < V; ++j) tile[j] = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+        // `magic` is the register of 0x64 bytes at 8 bits
         half8_t a8, b8[V];
-        if constexpr (BITS == 8) {
-            // `magic` is the register of 0x64 bytes here; the fields come out in the order of k
-            a8 = __builtin_bit_cast(half8_t, ring.step[H][it].a);
+        if constexpr (QUAD) a8 = it == 0 ? quad_step<0>(quad) : it == 1 ? quad_step<1>(quad) : it == 2 ? quad_step<2>(quad) : quad_step<3>(quad);
+        else a8 = order_activations<BITS>(ring.step[H][it].a);
 #pragma unroll
-            for (int j = 0; j < V; ++j)
-                b8[j] = unpack_shift8(ring.step[H][it].w.v[j], ring.step[H][it].w1.v[j], zc8[j], magic);
-        } else if constexpr (BITS == 2) {
-            a8 = __builtin_bit_cast(half8_t, ring.step[H][it].a);
+        for (int j = 0; j < V; ++j) b8[j] = unpack_column<V, BITS>(ring.step[H][it], j, lm, zc[j], magic);
+        if constexpr (REFILL && (QUAD || PG > 1)) {
+            // (the compiler otherwise puts most of the unpacking of both halves of the ring behind the requests, or all of it ahead of them)
 #pragma unroll
-            for (int j = 0; j < V; ++j) b8[j] = unpack_shift2(ring.step[H][it].w.v[j], lm.half_shift, zc2[j], magic);
-        } else if constexpr (BITS == 3) {
-            a8 = permute_activations(ring.step[H][it].a);
-#pragma unroll
-            for (int j = 0; j < V; ++j)
-                b8[j] = unpack_shift3(ring.step[H][it].w.v[j], ring.step[H][it].w1.v[j], lm.half_shift, zc3[j], magic);
-        } else {
-            a8 = permute_activations(ring.step[H][it].a);
-#pragma unroll
-            for (int j = 0; j < V; ++j) b8[j] = unpack_shift(ring.step[H][it].w.v[j], zc[j], magic);
+            for (int j = 0; j < V; ++j) {
+                u32x4_t b = __builtin_bit_cast(u32x4_t, b8[j]);
+                asm volatile("" : "+v"(b));
+                b8[j] = __builtin_bit_cast(half8_t, b);
+            }
         }
         if constexpr (REFILL) {
             __builtin_amdgcn_sched_barrier(0);
-            issue_step<V, IPG, BITS>(ring.step[H][it], lm, t, refill, it);
+            issue_step<V, IPG, BITS, QUAD>(ring.step[H][it], lm, t, refill, it);
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (PROBE) {
@@ -616,9 +684,14 @@ __device__ __forceinline__ void compute_group(Ring<V, IPG, BITS>& ring, const La
         }
 #pragma unroll
         for (int j = 0; j < V; ++j) tile[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, b8[j], tile[j], 0, 0, 0);
-    }
+        if (it % SPG == SPG - 1) {
 #pragma unroll
-    for (int j = 0; j < V; ++j) acc[j] += sc[j] * tile[j];
+            for (int j = 0; j < V; ++j) {
+                if constexpr (QUAD) acc[j][0] += sc[j] * tile[j][0];
+                else acc[j] += sc[j] * tile[j];
+            }
+        }
+    }
 }
 
 // The loop of Algorithm 1 for one wave: compute groups [g_begin, g_begin + g_count) of its
@@ -628,19 +701,19 @@ __device__ __forceinline__ void compute_group(Ring<V, IPG, BITS>& ring, const La
 // `primed()` runs once, after the loads have been issued, inside the branch that issued them:
 // a wait it contains then counts exactly the loads of that branch.  GC is what is known about
 // g_count at compile time: 1 = exactly one group, 2 = at least two, 0 = nothing.
-template <int V, int IPG, int GC, int BITS = 4, class F>
+template <int V, int IPG, int GC, int BITS = 4, int PG = 1, bool QUAD = false, class F>
 __device__ __forceinline__ void wave_prime(Ring<V, IPG, BITS>& ring, const Tensors& t, const LaneMap& lm, int g_begin,
                                            int g_count, F&& primed)
 {
-    issue_group<V, IPG, 0, BITS>(ring, lm, t, g_begin);
+    issue_group<V, IPG, 0, BITS, PG, QUAD>(ring, lm, t, g_begin);
     if constexpr (GC == 1) {
         primed();
     } else if constexpr (GC == 2) {
-        issue_group<V, IPG, 1, BITS>(ring, lm, t, g_begin + 1);
+        issue_group<V, IPG, 1, BITS, PG, QUAD>(ring, lm, t, g_begin + 1);
         primed();
     } else {
         if (g_count > 1) {
-            issue_group<V, IPG, 1, BITS>(ring, lm, t, g_begin + 1);
+            issue_group<V, IPG, 1, BITS, PG, QUAD>(ring, lm, t, g_begin + 1);
             primed();
         } else {
             primed();
@@ -648,7 +721,7 @@ __device__ __forceinline__ void wave_prime(Ring<V, IPG, BITS>& ring, const Tenso
     }
 }
 
-template <int V, int IPG, bool PROBE, int GC, int BITS = 4>
+template <int V, int IPG, bool PROBE, int GC, int BITS = 4, int PG = 1, bool QUAD = false>
 __device__ __forceinline__ void wave_run(Ring<V, IPG, BITS>& ring, const Tensors& t, const LaneMap& lm, int g_begin,
                                          int g_count, float4_t (&acc)[V], FlagProbe& probe)
 {
@@ -656,24 +729,24 @@ __device__ __forceinline__ void wave_run(Ring<V, IPG, BITS>& ring, const Tensors
     if constexpr (BITS == 8) magic = magic_64x4();
     else magic = magic_1024x2();
     if constexpr (GC == 1) {
-        compute_group<V, IPG, 0, false, PROBE, BITS>(ring, lm, t, magic, 0, acc, probe);
+        compute_group<V, IPG, 0, false, PROBE, BITS, PG, QUAD>(ring, lm, t, magic, 0, acc, probe);
         return;
     }
     int i = 0;
     for (; i + 3 < g_count; i += 2) {
-        compute_group<V, IPG, 0, true, false, BITS>(ring, lm, t, magic, g_begin + i + 2, acc, probe);
-        compute_group<V, IPG, 1, true, false, BITS>(ring, lm, t, magic, g_begin + i + 3, acc, probe);
+        compute_group<V, IPG, 0, true, false, BITS, PG, QUAD>(ring, lm, t, magic, g_begin + i + 2, acc, probe);
+        compute_group<V, IPG, 1, true, false, BITS, PG, QUAD>(ring, lm, t, magic, g_begin + i + 3, acc, probe);
     }
     const int left = g_count - i;  // 1, 2 or 3 groups; half 0 holds group i, half 1 group i + 1
     if (left == 3) {
-        compute_group<V, IPG, 0, true, false, BITS>(ring, lm, t, magic, g_begin + i + 2, acc, probe);
-        compute_group<V, IPG, 1, false, false, BITS>(ring, lm, t, magic, 0, acc, probe);
-        compute_group<V, IPG, 0, false, PROBE, BITS>(ring, lm, t, magic, 0, acc, probe);
+        compute_group<V, IPG, 0, true, false, BITS, PG, QUAD>(ring, lm, t, magic, g_begin + i + 2, acc, probe);
+        compute_group<V, IPG, 1, false, false, BITS, PG, QUAD>(ring, lm, t, magic, 0, acc, probe);
+        compute_group<V, IPG, 0, false, PROBE, BITS, PG, QUAD>(ring, lm, t, magic, 0, acc, probe);
     } else if (left == 2) {
-        compute_group<V, IPG, 0, false, false, BITS>(ring, lm, t, magic, 0, acc, probe);
-        compute_group<V, IPG, 1, false, PROBE, BITS>(ring, lm, t, magic, 0, acc, probe);
+        compute_group<V, IPG, 0, false, false, BITS, PG, QUAD>(ring, lm, t, magic, 0, acc, probe);
+        compute_group<V, IPG, 1, false, PROBE, BITS, PG, QUAD>(ring, lm, t, magic, 0, acc, probe);
     } else if (left == 1) {
-        compute_group<V, IPG, 0, false, PROBE, BITS>(ring, lm, t, magic, 0, acc, probe);
+        compute_group<V, IPG, 0, false, PROBE, BITS, PG, QUAD>(ring, lm, t, magic, 0, acc, probe);
     }
 }
 

@@ -1,0 +1,52 @@
+// Launches of the per-wave kernel for groups of 32 and 64 in compute groups of 128 k (see w4a16_wave.hpp).
+#include "w4a16_wave.hpp"
+
+namespace w4a16 {
+
+template <int BITS, int PG, int MODE, bool QUAD>
+static hipError_t launch_fine_mode(const GemmArgs& a, int waves, size_t lds_bytes, hipStream_t stream)
+{
+    if (a.groups_base == 1 && a.groups_rem == 0) return launch_wave<4, 4, MODE, 4, 1, BITS, 1, PG, QUAD>(a, waves, lds_bytes, stream);
+    if (a.groups_base >= 2) return launch_wave<4, 4, MODE, 4, 2, BITS, 1, PG, QUAD>(a, waves, lds_bytes, stream);
+    return launch_wave<4, 4, MODE, 4, 0, BITS, 1, PG, QUAD>(a, waves, lds_bytes, stream);
+}
+
+template <int BITS, int PG, bool QUAD>
+static hipError_t launch_fine_groups(const GemmArgs& a, int tile_cols, int waves, size_t lds_bytes, int mode, hipStream_t stream)
+{
+    if (waves > 4) return hipErrorInvalidConfiguration;
+    if (tile_cols == 128) {
+        if (a.groups_base != 1 || a.groups_rem != 0 || mode != kAtomicPkF16Phase) return hipErrorInvalidConfiguration;
+        return launch_wave<4, 4, kAtomicPkF16Service, 4, 1, BITS, 2, PG, QUAD>(a, waves, lds_bytes, stream);
+    }
+    if (mode == kDirect) return launch_fine_mode<BITS, PG, kDirect, QUAD>(a, waves, lds_bytes, stream);
+    if constexpr (QUAD) {
+        if (mode == kAtomicFixed) return launch_fine_mode<BITS, PG, kAtomicFixed, QUAD>(a, waves, lds_bytes, stream);
+    }
+    return mode == kAtomicPkF16Phase ? launch_fine_mode<BITS, PG, kAtomicPkF16Service, QUAD>(a, waves, lds_bytes, stream)
+                                     : hipErrorInvalidConfiguration;
+}
+
+template <int BITS>
+static hipError_t launch_fine_width(const GemmArgs& a, int pg, int tile_cols, int waves, size_t lds_bytes, int mode, hipStream_t stream)
+{
+    if (a.m <= 4) {
+        if (pg == 1) return launch_fine_groups<BITS, 1, true>(a, tile_cols, waves, lds_bytes, mode, stream);
+        if (pg == 2) return launch_fine_groups<BITS, 2, true>(a, tile_cols, waves, lds_bytes, mode, stream);
+        return launch_fine_groups<BITS, 4, true>(a, tile_cols, waves, lds_bytes, mode, stream);
+    }
+    if (pg == 2) return launch_fine_groups<BITS, 2, false>(a, tile_cols, waves, lds_bytes, mode, stream);
+    return launch_fine_groups<BITS, 4, false>(a, tile_cols, waves, lds_bytes, mode, stream);
+}
+
+hipError_t launch_fine(const GemmArgs& a, int bits, int pg, int tile_cols, int waves, size_t lds_bytes, int mode, hipStream_t stream)
+{
+    switch (bits) {
+    case 8: return launch_fine_width<8>(a, pg, tile_cols, waves, lds_bytes, mode, stream);
+    case 3: return launch_fine_width<3>(a, pg, tile_cols, waves, lds_bytes, mode, stream);
+    case 2: return launch_fine_width<2>(a, pg, tile_cols, waves, lds_bytes, mode, stream);
+    default: return launch_fine_width<4>(a, pg, tile_cols, waves, lds_bytes, mode, stream);
+    }
+}
+
+}  // namespace w4a16

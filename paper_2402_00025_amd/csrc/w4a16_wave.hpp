@@ -125,7 +125,9 @@ __host__ __device__ constexpr int gemm_lds_wave_bytes(int BN, int m)
 // NS: strips of 16 V columns per wave.  2 (only with GC = 1): the wave multiplies the same
 // activations with the weights of two adjacent strips, which halves the activation traffic per
 // weight byte and the number of waves.
-template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1>
+// PG: quantisation groups per compute group (IPG = 4: 2 or 4 for groups of 64 or 32 where k is a multiple of 128).
+// QUAD: up to four activation rows (IPG = 4; see Ring).
+template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1, int PG = 1, bool QUAD = false>
 __device__ __forceinline__ void gemm_body(const GemmArgs& p)
 {
     static_assert(NS == 1 || (NS == 2 && GC == 1), "two strips per wave: one compute group per wave");
@@ -217,8 +219,10 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
         __builtin_amdgcn_sched_barrier(0);
     }
 
-    const LaneMap lm = make_lane_map<V, BITS>(lane, n0, m, n, k);
-    const uint32_t qgroups = (uint32_t)(k / (32 * IPG)) >> p.param_shift;
+    LaneMap lm = make_lane_map<V, BITS>(lane, n0, m, n, k);
+    spread_params<V, BITS, PG>(lm, lane, n);
+    if constexpr (QUAD) quad_activations(lm, lane, m, k);
+    const uint32_t qgroups = (uint32_t)(k / (32 * IPG) * PG) >> p.param_shift;
     Tensors tensors;
     tensors.A = make_rsrc(p.A, (uint32_t)m * (uint32_t)k * 2u);
     // (k and n times BITS / 32, written per width so that each keeps its shortest form; 3-bit: k, n % 32 == 0)
@@ -245,7 +249,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
     probe.addr = p.flags + origin;
     probe.value = 0;
     Ring<V, IPG, BITS> ring;
-    wave_prime<V, IPG, GC, BITS>(ring, tensors, lm, g_begin, g_count, [&]() {
+    wave_prime<V, IPG, GC, BITS, PG, QUAD>(ring, tensors, lm, g_begin, g_count, [&]() {
         if constexpr (MODE == kAtomicPkF16Phase) {
             if (wave == 0) {
                 // wait for the count (the asm makes it a used value here)
@@ -271,8 +275,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
     Ring<V, IPG, BITS> ring1;
     float4_t acc1[V];
     if constexpr (NS == 2) {
-        const LaneMap lm1 = make_lane_map<V, BITS>(lane, n0 + 16 * V, m, n, k);
-        issue_params<V, BITS>(ring1.par[0], lm1, tensors, g_begin);
+        LaneMap lm1 = make_lane_map<V, BITS>(lane, n0 + 16 * V, m, n, k);
+        spread_params<V, BITS, PG>(lm1, lane, n);
+        issue_params<V, BITS>(ring1.par[0], lm1, tensors, g_begin * PG);
 #pragma unroll
         for (int it = 0; it < IPG; ++it)
         {
@@ -283,16 +288,13 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
         }
 #pragma unroll
         for (int j = 0; j < V; ++j) acc1[j] = float4_t{0.f, 0.f, 0.f, 0.f};
-        wave_run<V, IPG, MODE == kAtomicPkF16Phase, GC, BITS>(ring, tensors, lm, g_begin, g_count, acc, probe);
+        wave_run<V, IPG, MODE == kAtomicPkF16Phase, GC, BITS, PG, QUAD>(ring, tensors, lm, g_begin, g_count, acc, probe);
 #pragma unroll
         for (int it = 0; it < IPG; ++it) ring1.step[0][it].a = ring.step[0][it].a;
         FlagProbe none{nullptr, 0};
-        if constexpr (BITS == 8)
-            compute_group<V, IPG, 0, false, false, BITS>(ring1, lm1, tensors, magic_64x4(), 0, acc1, none);
-        else
-            compute_group<V, IPG, 0, false, false, BITS>(ring1, lm1, tensors, magic_1024x2(), 0, acc1, none);
+        compute_group<V, IPG, 0, false, false, BITS, PG, QUAD>(ring1, lm1, tensors, unpack_magic<BITS>(), 0, acc1, none);
     } else {
-        wave_run<V, IPG, MODE == kAtomicPkF16Phase, GC, BITS>(ring, tensors, lm, g_begin, g_count, acc, probe);
+        wave_run<V, IPG, MODE == kAtomicPkF16Phase, GC, BITS, PG, QUAD>(ring, tensors, lm, g_begin, g_count, acc, probe);
     }
 
     if constexpr (MODE == kAtomicPkF16Phase) {
@@ -311,31 +313,32 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
         if (waves == 4) {
             constexpr int kTileBytes = 16 * BN * 4;
             constexpr uint32_t kOutside = 0xFFFFFF00u;
-            char* mine = lds_tiles + wave * kTileBytes + ((4 * (lane >> 4)) * BN + V * (lane & 15)) * 4;
+            constexpr int kRows = QUAD ? 1 : 4;  // of a lane, and of a thread below
+            char* mine = lds_tiles + wave * kTileBytes + ((kRows * (lane >> 4)) * BN + V * (lane & 15)) * 4;
             uint32_t their_offset = 8u * (uint32_t)tid;
             const rsrc_t rs_c = make_rsrc(p.C, (uint32_t)m * (uint32_t)n * 2u);
             const int col = n0 + 2 * (tid & 63);
-            uint32_t off[4];
+            uint32_t off[4] = {};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < kRows; ++i) {
                 const int row = (tid >> 6) + 4 * i;
                 off[i] = (row < m && col < n) ? ((uint32_t)row * (uint32_t)n + (uint32_t)col) * 2u : kOutside;
             }
             asm volatile("" : "+v"(off[0]), "+v"(off[1]), "+v"(off[2]), "+v"(off[3]), "+v"(their_offset));
             const char* theirs = lds_tiles + their_offset;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < kRows; ++r) {
                 *(float4_t*)(mine + r * BN * 4) = float4_t{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
                 *(float4_t*)(mine + r * BN * 4 + 16 * V * 4) = float4_t{acc1[0][r], acc1[1][r], acc1[2][r], acc1[3][r]};
             }
             __syncthreads();
             float2 part[4][4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < kRows; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) part[i][q] = *(const float2*)(theirs + q * kTileBytes + i * 2048);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < kRows; ++i) {
                 const float sx = (part[i][0].x + part[i][1].x) + (part[i][2].x + part[i][3].x);
                 const float sy = (part[i][0].y + part[i][1].y) + (part[i][2].y + part[i][3].y);
                 const half2_t h = {(_Float16)sx, (_Float16)sy};
@@ -348,8 +351,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
     // ---- sum the waves' tiles through LDS.  acc[j][r] is row 4*(lane/16)+r, column V*(lane%16)+j.
     float* red = (float*)(lds_tiles + wave * lds_wave_bytes);  // [m][BN]
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = 4 * (lane >> 4) + r;
+    for (int r = 0; r < (QUAD ? 1 : 4); ++r) {
+        const int row = QUAD ? lane >> 4 : 4 * (lane >> 4) + r;
         if (row < m) {
             float* dst = red + row * BN + V * (lane & 15);
             if constexpr (NS == 2) {
@@ -596,7 +599,7 @@ struct GemmRest {
     int probe_delay;
 };
 
-template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1>
+template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1, int PG = 1, bool QUAD = false>
 __global__ void __launch_bounds__(kWave * (WMAX + (MODE == kAtomicPkF16Service ? 1 : 0)))
 gemm_kernel(const _Float16* A, const uint32_t* qweight, const _Float16* scales, const uint32_t* qzeros, _Float16* C,
             int packed, int n, int k, int split_rem, const GemmRest rest)
@@ -624,7 +627,46 @@ gemm_kernel(const _Float16* A, const uint32_t* qweight, const _Float16* scales, 
     p.err_host = rest.err_host;
     p.spin_limit = rest.spin_limit;
     p.probe_delay = rest.probe_delay;
-    gemm_body<V, IPG, MODE, WMAX, GC, BITS, NS>(p);
+    gemm_body<V, IPG, MODE, WMAX, GC, BITS, NS, PG, QUAD>(p);
+}
+
+// Launches the kernel of this field width for groups of 64 or 32 (`pg` = 2, 4 of them in a compute group of 128 k).
+hipError_t launch_fine(const GemmArgs& a, int bits, int pg, int tile_cols, int waves, size_t lds_bytes, int mode, hipStream_t stream);
+
+// The second grid dimension holds at most 65535; more tiles or parts with a group more than these were never taken.
+static inline bool wave_args_ok(const GemmArgs& a)
+{
+    return a.m <= 31 && a.param_shift <= 3 && a.waves <= 31 && a.groups_base < (1 << 20) && a.groups_rem < (1 << 11) &&
+           a.tiles < (1 << 20) && a.split_k >= 1 && a.split_k < (1 << 16);
+}
+
+template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1, int PG = 1, bool QUAD = false>
+static hipError_t launch_wave(const GemmArgs& a, int waves, size_t lds_bytes, hipStream_t stream)
+{
+    auto kern = gemm_kernel<V, IPG, MODE, WMAX, GC, BITS, NS, PG, QUAD>;
+    if (lds_bytes > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        if (e != hipSuccess) return e;
+    }
+    const unsigned threads = (unsigned)(waves + (MODE == kAtomicPkF16Service ? 1 : 0)) * kWave;
+    const int packed = a.m | a.param_shift << 5 | a.waves << 7 | (int)((unsigned)a.groups_base << 12);
+    const int split_rem = a.split_k | a.groups_rem << 16;
+    constexpr bool kPhase = MODE == kAtomicPkF16Phase || MODE == kAtomicPkF16Service;
+    GemmRest rest;
+    if constexpr (kPhase) {
+        rest.flags = a.flags;
+        rest.counts = a.counts;
+    } else {
+        rest.scratch = a.scratch;
+        rest.tickets = a.tickets;
+    }
+    rest.errors = a.errors;
+    rest.err_host = a.err_host;
+    rest.spin_limit = a.spin_limit;
+    rest.probe_delay = a.probe_delay;
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.tiles, (unsigned)a.split_k), dim3(threads), lds_bytes, stream, a.A,
+                       a.qweight, a.scales, a.qzeros, a.C, packed, a.n, a.k, split_rem, rest);
+    return hipGetLastError();
 }
 
 }  // namespace w4a16

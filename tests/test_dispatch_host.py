@@ -196,3 +196,63 @@ def test_parity_cases_reach_every_batch_kernel():
     every = {(blocks, bits, g, cols) for blocks in (1, 2, 3, 4) for bits in (4, 8, 3, 2) for g in (32, 64, 128)
              for cols in (64, 128) if blocks > 1 or g < 128}
     assert reached == every, every - reached
+
+
+def test_route_of_fine_groups(stand_in):
+    """Up to 16 rows, groups of 32 and 64: the launch in steps of 128 k splits k only where the other launch does, no further where
+    the parts meet in fp16, and gives way to the others under capture where there is scratch for those alone."""
+    stand_in("""
+    def fine(m, n, k, g, bits=4):
+        v = [ctypes.c_int() for _ in range(3)]
+        assert L.w4a16_plan_fine(bits, m, n, k, g, *map(ctypes.byref, v)) == OK
+        return tuple(x.value for x in v)
+    def other(m, n, k, g, bits=4):
+        v = [ctypes.c_int(0) for _ in range(4)]
+        assert L.w4a16_plan_bits(bits, m, n, k, g, 0, *map(ctypes.byref, v)) == OK
+        return tuple(x.value for x in v)
+    taken = 0
+    for bits in (4, 8, 3, 2):
+        for m in (1, 4, 5, 16):
+            for n, k in ((1024, 1024), (2048, 2048), (4096, 4096), (5120, 13824), (1536, 16384), (28672, 4096), (8192, 8192), (1024, 28672)):
+                for g in (32, 64):
+                    s, t, w = fine(m, n, k, g, bits)
+                    if not s: continue
+                    taken += 1
+                    o = other(m, n, k, g, bits)
+                    assert s == 1 or o[0] > 1 and (m <= 4 and s <= 64 or s <= o[0]), (bits, m, n, k, g, s, o)
+                    assert s * w <= k // 128 and (t, w) in ((64, 4), (64, 2), (128, 4)) and (t == 64 or s * 4 == k // 128)
+                    assert gemm(m, n, k, g, bits) == (OK, 1, (-(-n // t), s, 1)), (bits, m, n, k, g)
+    assert taken > 100
+    # k no multiple of 128; groups of 128; more rows; beyond the sizes that were measured
+    assert fine(8, 4096, 4160, 64) == fine(8, 4096, 4096, 128) == fine(17, 4096, 4096, 32) == (0, 0, 0)
+    assert fine(8, 1016, 4096, 32) == fine(8, 4096, 896, 32) == fine(8, 28680, 4096, 32) == fine(8, 4096, 28800, 32) == (0, 0, 0)
+    assert L.w4a16_plan_fine(5, 8, 4096, 4096, 32, None, None, None) == UNSUPPORTED
+    assert L.w4a16_plan_fine(4, 8, 4096, 4096, 32, None, None, None) == OK
+    # scratch: 12 rows split k otherwise than 5; an eager call of either serves a captured one of the other
+    matrices = [(n, k) for n in (1024, 2048, 4096, 5120, 11008) for k in (2048, 4096, 13824)]
+    for g in (32, 64):
+        for n, k in matrices:
+            for eager, captured in (((5, 8, 16), (5, 8, 12, 16)), ((1, 2, 4), (1, 2, 3, 4)), ((5, 16), (1, 4))):
+                for m in eager:
+                    assert L.w4a16_release_scratch() == OK
+                    assert gemm(m, n, k, g)[0] == OK
+                    capturing.value = 1
+                    for later in captured:
+                        # (sums of one to four rows meet in words that only an eager call leaves)
+                        assert gemm(later, n, k, g)[0] == OK, (n, k, g, m, later)
+                    capturing.value = 0
+    # only the other launch's words are there: that launch
+    assert L.w4a16_release_scratch() == OK
+    s, t, w = fine(8, 4096, 4096, 32)
+    o = other(8, 4096, 4096, 32)
+    assert s > 1 and (s, t, w) != o[:3]
+    capturing.value = 1
+    assert gemm(8, 4096, 4096, 32)[:2] == (-6, 0)
+    capturing.value = 0
+    space = (ctypes.c_char * (L.w4a16_workspace_bytes(1024) + 256))()
+    base = (ctypes.addressof(space) + 255) // 256 * 256
+    assert L.w4a16_set_workspace(vp(base), ctypes.c_longlong(L.w4a16_workspace_bytes(1024)), 1024, vp(64)) == OK
+    assert gemm(8, 4096, 4096, 32, stream=64)[0] == LIMIT
+    assert gemm(8, 1024, 4096, 32, stream=64)[:2] == (OK, 1)
+    assert L.w4a16_release_scratch() == OK
+    """)

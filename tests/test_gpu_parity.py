@@ -1902,3 +1902,93 @@ def test_batch_rows_captured_and_with_a_workspace(oracle, m, n, k, g):
     finally:
         b.w4a16_set_workspace(None, 0, 0, stream=stream)
     assert b.w4a16_phase_timeouts() == 0
+
+
+# Up to 16 rows, groups of 32 and 64, k a multiple of 128, in steps of 128 k: k whole and split, one group per wave, two and more,
+# even and uneven; one strip and two, overhanging strips; fixed-point and fp16 sums; two waves a workgroup.
+FINE = [
+    # bits, m, n, k, g, (split_k, columns of a workgroup, waves)
+    (2, 1, 2704, 1536, 32, (3, 64, 4)), (2, 2, 2064, 5248, 32, (7, 64, 4)), (2, 4, 4576, 3200, 32, (3, 64, 4)),
+    (2, 5, 1056, 1024, 32, (4, 64, 2)), (2, 5, 1680, 2432, 32, (9, 64, 2)), (2, 16, 1168, 1536, 32, (3, 64, 4)),
+    (2, 16, 1056, 6272, 32, (8, 64, 4)), (2, 16, 4112, 2048, 32, (2, 64, 4)), (2, 16, 4112, 3200, 32, (3, 64, 4)),
+    (2, 5, 1248, 6656, 32, (13, 128, 4)), (2, 4, 4112, 3200, 64, (3, 64, 4)), (2, 11, 2704, 3072, 64, (3, 64, 4)),
+    (2, 8, 5488, 2176, 64, (2, 64, 4)), (2, 8, 1232, 6656, 64, (13, 128, 4)), (3, 3, 2336, 6272, 32, (6, 64, 4)),
+    (3, 8, 2336, 4096, 32, (4, 64, 4)), (3, 16, 4128, 3200, 32, (3, 64, 4)), (3, 11, 3424, 3584, 32, (7, 128, 4)),
+    (3, 3, 1632, 2560, 64, (5, 64, 4)), (3, 1, 2080, 4224, 64, (7, 64, 4)), (3, 3, 4128, 3200, 64, (3, 64, 4)),
+    (3, 8, 1120, 1024, 64, (4, 64, 2)), (3, 5, 1120, 1152, 64, (4, 64, 2)), (3, 16, 1056, 1024, 64, (2, 64, 4)),
+    (3, 16, 5536, 1152, 64, (2, 64, 4)), (3, 8, 2720, 3072, 64, (3, 64, 4)), (3, 5, 5472, 2176, 64, (2, 64, 4)),
+    (3, 5, 3168, 3584, 64, (7, 128, 4)), (4, 2, 1608, 2560, 32, (5, 64, 4)), (4, 3, 1032, 8320, 32, (15, 64, 4)),
+    (4, 4, 4104, 3200, 32, (3, 64, 4)), (4, 5, 1040, 1024, 32, (4, 64, 2)), (4, 5, 2440, 1408, 32, (5, 64, 2)),
+    (4, 11, 1352, 1536, 32, (3, 64, 4)), (4, 16, 2512, 3200, 32, (4, 64, 4)), (4, 5, 2056, 4096, 32, (4, 64, 4)),
+    (4, 5, 4104, 3200, 32, (3, 64, 4)), (4, 8, 1240, 6656, 32, (13, 128, 4)), (4, 4, 5000, 1152, 64, (1, 64, 4)),
+    (4, 3, 1608, 2560, 64, (5, 64, 4)), (4, 3, 1032, 8320, 64, (15, 64, 4)), (4, 3, 4104, 3200, 64, (3, 64, 4)),
+    (4, 8, 1032, 1024, 64, (4, 64, 2)), (4, 8, 1096, 1152, 64, (4, 64, 2)), (4, 5, 4104, 2304, 64, (3, 64, 2)),
+    (4, 5, 4240, 1664, 64, (3, 64, 2)), (4, 16, 1056, 1024, 64, (2, 64, 4)), (4, 16, 5560, 1152, 64, (2, 64, 4)),
+    (4, 8, 2704, 3072, 64, (3, 64, 4)), (4, 8, 5448, 2176, 64, (2, 64, 4)), (4, 8, 1224, 6656, 64, (13, 128, 4)),
+    (8, 4, 1608, 2560, 32, (5, 64, 4)), (8, 4, 1544, 8320, 32, (10, 64, 4)), (8, 4, 2072, 8320, 32, (7, 64, 4)),
+    (8, 5, 1048, 1024, 32, (4, 64, 2)), (8, 5, 1352, 2944, 32, (11, 64, 2)), (8, 5, 4112, 2304, 32, (3, 64, 2)),
+    (8, 5, 1240, 6784, 32, (12, 64, 2)), (8, 16, 1360, 1536, 32, (3, 64, 4)), (8, 8, 1688, 4992, 32, (6, 64, 4)),
+    (8, 16, 2072, 4096, 32, (4, 64, 4)), (8, 11, 5448, 2176, 32, (2, 64, 4)), (8, 5, 1240, 6656, 32, (13, 128, 4)),
+    (8, 4, 3288, 4224, 64, (4, 64, 4)), (8, 5, 4144, 2304, 64, (3, 64, 2)), (8, 8, 4128, 1664, 64, (3, 64, 2)),
+    (8, 16, 2696, 3072, 64, (3, 64, 4)), (8, 16, 5456, 2176, 64, (2, 64, 4)), (8, 11, 1224, 6656, 64, (13, 128, 4)),
+    (2, 4, 8816, 1024, 32, (1, 64, 4)), (2, 5, 8208, 1408, 32, (1, 64, 4)), (2, 3, 8288, 1024, 64, (1, 64, 4)),
+    (2, 11, 8272, 1152, 64, (1, 64, 4)), (3, 4, 9632, 1024, 32, (1, 64, 4)), (3, 11, 9440, 1024, 32, (1, 64, 4)),
+    (3, 4, 8224, 1024, 64, (1, 64, 4)), (3, 16, 8416, 1024, 64, (1, 64, 4)), (4, 4, 8208, 1024, 32, (1, 64, 4)),
+    (4, 16, 8200, 1408, 32, (1, 64, 4)), (4, 11, 8224, 1152, 64, (1, 64, 4)), (8, 4, 8648, 1024, 32, (1, 64, 4)),
+    (8, 16, 8968, 1152, 32, (1, 64, 4)), (8, 4, 7008, 1152, 64, (1, 64, 4)), (8, 11, 8528, 1152, 64, (1, 64, 4)),
+]
+
+
+@pytest.mark.parametrize("bits,m,n,k,g,plan", FINE)
+def test_fine_groups_in_steps_of_128(oracle, bits, m, n, k, g, plan):
+    got = b.w4a16_plan_fine(bits, m, n, k, g)
+    assert got and (got["split_k"], got["tile_cols"], got["waves"]) == plan, got
+    assert b.w4a16_plan_batch(bits, m, n, k, g) is None
+    seed = 9000 + m + n + k
+    A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
+    Cref, _ = oracle.gemm_3bit(A, qw, s, qz, g) if bits == 3 else oracle.gemm_bits(A, qw, s, qz, g, bits)
+    p = DeviceProblem(A, qw, s, qz, g)
+    for rep in range(2):      # (the phase words count calls)
+        p.C.fill_(float("nan"))
+        MANY_ROWS_GEMM[bits](*p.args(), 0)
+        assert_parity(p.result(), Cref, f"bits={bits} m={m} n={n} k={k} g={g} call {rep}")
+    assert b.w4a16_phase_timeouts() == 0
+
+
+# Up to four rows: every row of the operand four times.  Rows that there are not, overhanging strips, groups of 256, and the
+# three ways in which the parts of k meet (k / 128 = 1, 2, 3 groups a wave and more).
+@pytest.mark.parametrize("bits", [4, 8, 3, 2])
+@pytest.mark.parametrize("m", [1, 2, 3, 4])
+@pytest.mark.parametrize("n,k,g,split_k", [(1056, 4096, 128, 0), (4128, 4096, 256, 0), (96, 1536, 128, 4), (2080, 5120, 256, 0), (14112, 1536, 128, 0),
+                                           (288, 2816, 128, 2), (160, 512, 128, 1)])
+def test_up_to_four_rows(oracle, bits, m, n, k, g, split_k):
+    seed = 9500 + m + n + k
+    A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
+    Cref, _ = oracle.gemm_3bit(A, qw, s, qz, g) if bits == 3 else oracle.gemm_bits(A, qw, s, qz, g, bits)
+    p = DeviceProblem(A, qw, s, qz, g)
+    for rep in range(2):
+        p.C.fill_(float("nan"))
+        MANY_ROWS_GEMM[bits](*p.args(), split_k)
+        assert_parity(p.result(), Cref, f"bits={bits} m={m} n={n} k={k} g={g} split_k={split_k} call {rep}")
+    assert b.w4a16_phase_timeouts() == 0
+
+
+@pytest.mark.parametrize("g", [32, 128])
+def test_up_to_four_rows_keep_apart(g):
+    """NaN and infinities in one row stay in it, and every other row keeps its bits."""
+    import torch
+    m, n, k = 4, 2048, 2048
+    A, qw, s, qz = random_case(m, n, k, g, seed=9700)
+    p = DeviceProblem(A, qw, s, qz, g)
+    b.w4a16_gemm(*p.args(), 0)
+    before = p.result().copy()
+    for bad in (np.nan, np.inf):
+        for row in range(m):
+            A2 = A.copy()
+            A2[row, 5::97] = bad
+            p.A.copy_(torch.from_numpy(A2))
+            b.w4a16_gemm(*p.args(), 0)
+            after = p.result()
+            rest = [i for i in range(m) if i != row]
+            assert not np.isfinite(after[row].astype(np.float32)).all()
+            assert np.array_equal(after[rest].view(np.uint16), before[rest].view(np.uint16)), (bad, row)
