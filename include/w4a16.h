@@ -272,7 +272,7 @@ int w4a16_plan_batch(int bits, int m, int n, int k, int group_size, int* split_k
 
 /*
  * The per-wave launch in steps of 128 k of a SplitK call of this field width with split_k == 0, up to 16 rows, groups of 32
- * or 64 and k a multiple of 128: split_k (0 if the call goes to other launches), the columns of a workgroup (64 or 128) and its
+ * or 64: split_k (0 if the call goes to other launches), the columns of a workgroup (64 or 128) and its
  * waves.  Host only; no HIP call; the last three may be NULL.
  */
 int w4a16_plan_fine(int bits, int m, int n, int k, int group_size, int* split_k, int* tile_cols, int* waves);

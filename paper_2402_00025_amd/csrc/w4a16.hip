@@ -1997,7 +1997,7 @@ static void plan_batch_few(int m, int n, int k, int group_size, int bits, const 
     }
 }
 
-// ---- Up to 16 rows, groups of 32 and 64, k a multiple of 128: the per-wave kernel with compute groups of 128 k, that is with
+// ---- Up to 16 rows, groups of 32 and 64: the per-wave kernel with compute groups of 128 k, that is with
 // two groups of 128 k on their way where the ring of single groups holds 64 or 128 k in all, and one request in the place of
 // two or four for their parameters (see Ring).
 struct FineShape {
@@ -2005,7 +2005,7 @@ struct FineShape {
     bool uneven, single, splits;
     FineShape(int tile_cols, int waves, int split_k, int m, int n, int k, int group_k, int group_size, int bits)
     {
-        const int groups = k / group_k, parts = split_k * waves, wgs = split_k * ((n + tile_cols - 1) / tile_cols);
+        const int groups = (k + group_k - 1) / group_k, parts = split_k * waves, wgs = split_k * ((n + tile_cols - 1) / tile_cols);
         megabytes = (double)n * k * bits / 8e6;
         params = (double)(k / group_size) * n * (2 + bits / 8.0) * 1e-6;
         splits = split_k > 1;
@@ -2064,12 +2064,13 @@ static double single_groups_us(const Plan& others, int m, int n, int k, int grou
 // and beyond 28672, where nothing was fitted, the calls stay where they were.
 static bool plan_fine(int m, int n, int k, int group_size, int bits, const Plan& others, const BatchPlan& batch, Plan* plan)
 {
-    if (m > 16 || group_size >= 128 || k % 128 != 0 || n < 1024 || n > 28672 || k < 1024 || k > 28672) return false;
-    const int groups = k / 128, tiles = (n + 63) / 64;
+    if (m > 16 || group_size >= 128 || n < 1024 || n > 28672 || k < 1024 || k > 28672) return false;
+    const int groups = (k + 127) / 128, tiles = (n + 63) / 64;
     const int reduce = m <= 4 ? W4A16_REDUCE_ATOMIC_FIXED : W4A16_REDUCE_ATOMIC_PK_F16_PHASE;
     const int most = others.split_k == 1 || others.reduce != reduce ? 1 : m <= 4 ? 64 : others.split_k;
     double best = 0.95 * single_groups_us(others, m, n, k, group_size, bits);
     if (batch.split_k) {
+        if (k % 128 != 0) return false;  // (neither fit has seen such k)
         const double us = 0.9 * batch_few_us(batch.strips, batch.split_k, m, n, k, group_size / 32, bits);
         best = us < best ? us : best;
     }
@@ -2211,7 +2212,7 @@ static GemmArgs wave_args(const Plan& plan, const void* A, const void* qweight, 
     a.k = k;
     a.tiles = (n + plan.tile_cols - 1) / plan.tile_cols;
     a.split_k = plan.split_k;
-    const int cgroups = k / (32 * ipg), kparts = plan.split_k * plan.waves;
+    const int cgroups = (k + 32 * ipg - 1) / (32 * ipg), kparts = plan.split_k * plan.waves;  // (rounded up for run_fine alone)
     a.groups_base = cgroups / kparts;
     a.groups_rem = cgroups % kparts;
     a.waves = plan.waves;

@@ -418,6 +418,7 @@ struct LaneMap {
     uint32_t off_z1;  // 3-bit fields only: the next word when the lane's 3 V bits go across, else off_z
     uint32_t off_s;   // col0 * 2                           into a scales row
     uint32_t off_a;   // (row * k + 8 * (lane / 16)) * 2    into A, row = min(lane % 16, m - 1)
+    uint32_t quad_step;  // QUAD only: which step of a compute group the lane's activations are of
     int zshift;       // 4 * (col0 % 8)
     int half_shift;   // 2-bit fields: which half of the word the lane's eight k are (0 or 16);
                       // 3-bit fields: the funnel shift that brings the lane's 24 bits down (0, 24, 16, 8)
@@ -451,11 +452,22 @@ __device__ __forceinline__ void issue_step_weights(StepRegs<V, BITS>& r, const L
     }
 }
 
-template <int V, int IPG, int BITS = 4, bool QUAD = false>
+// PG > 1 (see Ring): k may end inside the last compute group.  The steps behind it have activations of zero, and the last step's
+// weights in the place of their own (a scalar offset behind the end of a buffer lifts its bound); their parameters lie
+// behind the end and come as zeros.
+template <int V, int IPG, int BITS = 4, bool QUAD = false, int PG = 1>
 __device__ __forceinline__ void issue_step(StepRegs<V, BITS>& r, const LaneMap& lm, const Tensors& t, int gi, int it)
 {
-    const uint32_t step = (uint32_t)gi * IPG + it;  // MFMA step index along k: k = 32 * step
-    if (!QUAD || it == 0) r.a = __builtin_amdgcn_raw_buffer_load_b128(t.A, lm.off_a, step * 64u, 0);
+    constexpr uint32_t kOutside = 0x80000000u;
+    uint32_t step = (uint32_t)gi * IPG + it;  // MFMA step index along k: k = 32 * step
+    const uint32_t steps = (uint32_t)t.k / 32u;
+    uint32_t off_a = lm.off_a;
+    if constexpr (PG > 1) {
+        if constexpr (QUAD) off_a = step + lm.quad_step < steps ? off_a : kOutside;
+        else off_a = step < steps ? off_a : kOutside;
+    }
+    if (!QUAD || it == 0) r.a = __builtin_amdgcn_raw_buffer_load_b128(t.A, off_a, PG > 1 && step >= steps ? 0u : step * 64u, 0);
+    if constexpr (PG > 1) step = step < steps ? step : steps - 1;
     issue_step_weights<V, BITS>(r, lm, t, step);
 }
 
@@ -538,7 +550,7 @@ __device__ __forceinline__ void issue_group(Ring<V, IPG, BITS>& ring, const Lane
 {
     issue_params<V, BITS>(ring.par[H], lm, t, gi * PG);
 #pragma unroll
-    for (int it = 0; it < IPG; ++it) issue_step<V, IPG, BITS, QUAD>(ring.step[H][it], lm, t, gi, it);
+    for (int it = 0; it < IPG; ++it) issue_step<V, IPG, BITS, QUAD, PG>(ring.step[H][it], lm, t, gi, it);
 }
 
 // What lane group s (of four, or of two halves) of the wave holds, in all of them.
@@ -580,6 +592,7 @@ __device__ __forceinline__ void spread_params(LaneMap& lm, int lane, int n)
 __device__ __forceinline__ void quad_activations(LaneMap& lm, int lane, int m, int k)
 {
     const int row = (lane & 15) >> 2, arow = row < m ? row : m - 1;
+    lm.quad_step = (uint32_t)(lane & 3);
     lm.off_a = ((uint32_t)arow * (uint32_t)k + 32u * (uint32_t)(lane & 3) + 8u * (uint32_t)(lane >> 4)) * 2u;
 }
 
@@ -672,7 +685,7 @@ __device__ __forceinline__ void compute_group(Ring<V, IPG, BITS>& ring, const La
         }
         if constexpr (REFILL) {
             __builtin_amdgcn_sched_barrier(0);
-            issue_step<V, IPG, BITS, QUAD>(ring.step[H][it], lm, t, refill, it);
+            issue_step<V, IPG, BITS, QUAD, PG>(ring.step[H][it], lm, t, refill, it);
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (PROBE) {
@@ -755,6 +768,7 @@ __device__ __forceinline__ LaneMap make_lane_map(int lane, int n0, int m, int n,
 {
     LaneMap lm;
     lm.half_shift = 0;
+    lm.quad_step = 0;
     lm.off_w1 = 0;
     lm.off_z1 = 0;
     const int col0 = n0 + V * (lane & 15);

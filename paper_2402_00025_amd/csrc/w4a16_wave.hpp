@@ -125,7 +125,7 @@ __host__ __device__ constexpr int gemm_lds_wave_bytes(int BN, int m)
 // NS: strips of 16 V columns per wave.  2 (only with GC = 1): the wave multiplies the same
 // activations with the weights of two adjacent strips, which halves the activation traffic per
 // weight byte and the number of waves.
-// PG: quantisation groups per compute group (IPG = 4: 2 or 4 for groups of 64 or 32 where k is a multiple of 128).
+// PG: quantisation groups per compute group (IPG = 4: 2 or 4 for groups of 64 or 32).
 // QUAD: up to four activation rows (IPG = 4; see Ring).
 template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1, int PG = 1, bool QUAD = false>
 __device__ __forceinline__ void gemm_body(const GemmArgs& p)
@@ -222,7 +222,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
     LaneMap lm = make_lane_map<V, BITS>(lane, n0, m, n, k);
     spread_params<V, BITS, PG>(lm, lane, n);
     if constexpr (QUAD) quad_activations(lm, lane, m, k);
-    const uint32_t qgroups = (uint32_t)(k / (32 * IPG) * PG) >> p.param_shift;
+    const uint32_t qgroups = (uint32_t)(k / (32 * IPG / PG)) >> p.param_shift;
     Tensors tensors;
     tensors.A = make_rsrc(p.A, (uint32_t)m * (uint32_t)k * 2u);
     // (k and n times BITS / 32, written per width so that each keeps its shortest form; 3-bit: k, n % 32 == 0)
@@ -279,12 +279,10 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
         spread_params<V, BITS, PG>(lm1, lane, n);
         issue_params<V, BITS>(ring1.par[0], lm1, tensors, g_begin * PG);
 #pragma unroll
-        for (int it = 0; it < IPG; ++it)
-        {
-            if constexpr (BITS == 4)
-                ring1.step[0][it].w.load(tensors.qweight, lm1.off_w, ((uint32_t)g_begin * IPG + it) * 16u * (uint32_t)n);
-            else
-                issue_step_weights<V, BITS>(ring1.step[0][it], lm1, tensors, (uint32_t)g_begin * IPG + it);
+        for (int it = 0; it < IPG; ++it) {
+            uint32_t step = (uint32_t)g_begin * IPG + it;
+            if constexpr (PG > 1) step = step < (uint32_t)k / 32u ? step : (uint32_t)k / 32u - 1u;  // (as in issue_step)
+            issue_step_weights<V, BITS>(ring1.step[0][it], lm1, tensors, step);
         }
 #pragma unroll
         for (int j = 0; j < V; ++j) acc1[j] = float4_t{0.f, 0.f, 0.f, 0.f};
@@ -580,6 +578,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
 // them preloaded into scalar registers at wave launch (kernarg preload), so that no round trip
 // to the kernarg segment (about 0.3 us) precedes the loads.  Everything else comes in `rest`
 // and is fetched by one batch of scalar loads while the first vector loads are in flight.
+// (PG, QUAD: two waves per SIMD; 260 registers instead of 256, 3 bits, groups of 64, n = 25056, k = 8576, m = 4: 33.9 us, 30.1 so.)
 //   packed = m | param_shift << 5 | waves << 7 | groups_base << 12
 //   split_rem = split_k | groups_rem << 16
 // The whole list is 96 bytes: the host's share of a launch is up to 0.7 us longer from 120 bytes on
@@ -600,7 +599,7 @@ struct GemmRest {
 };
 
 template <int V, int IPG, int MODE, int WMAX, int GC, int BITS = 4, int NS = 1, int PG = 1, bool QUAD = false>
-__global__ void __launch_bounds__(kWave * (WMAX + (MODE == kAtomicPkF16Service ? 1 : 0)))
+__global__ void __launch_bounds__(kWave * (WMAX + (MODE == kAtomicPkF16Service ? 1 : 0)), PG > 1 || QUAD ? 2 : 1)
 gemm_kernel(const _Float16* A, const uint32_t* qweight, const _Float16* scales, const uint32_t* qzeros, _Float16* C,
             int packed, int n, int k, int split_rem, const GemmRest rest)
 {

@@ -223,8 +223,9 @@ def test_route_of_fine_groups(stand_in):
                     assert s * w <= k // 128 and (t, w) in ((64, 4), (64, 2), (128, 4)) and (t == 64 or s * 4 == k // 128)
                     assert gemm(m, n, k, g, bits) == (OK, 1, (-(-n // t), s, 1)), (bits, m, n, k, g)
     assert taken > 100
-    # k no multiple of 128; groups of 128; more rows; beyond the sizes that were measured
-    assert fine(8, 4096, 4160, 64) == fine(8, 4096, 4096, 128) == fine(17, 4096, 4096, 32) == (0, 0, 0)
+    # k no multiple of 128: not in the place of the batch kernel; groups of 128; more rows; beyond the sizes that were measured
+    assert fine(8, 4096, 4160, 64) == (3, 64, 4) and fine(8, 4128, 4160, 64) == (0, 0, 0)
+    assert fine(8, 4096, 4096, 128) == fine(17, 4096, 4096, 32) == (0, 0, 0)
     assert fine(8, 1016, 4096, 32) == fine(8, 4096, 896, 32) == fine(8, 28680, 4096, 32) == fine(8, 4096, 28800, 32) == (0, 0, 0)
     assert L.w4a16_plan_fine(5, 8, 4096, 4096, 32, None, None, None) == UNSUPPORTED
     assert L.w4a16_plan_fine(4, 8, 4096, 4096, 32, None, None, None) == OK
