@@ -282,7 +282,10 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& p)
         for (int it = 0; it < IPG; ++it) {
             uint32_t step = (uint32_t)g_begin * IPG + it;
             if constexpr (PG > 1) step = step < (uint32_t)k / 32u ? step : (uint32_t)k / 32u - 1u;  // (as in issue_step)
-            issue_step_weights<V, BITS>(ring1.step[0][it], lm1, tensors, step);
+            if constexpr (BITS == 4)  // (in place: through the function m = 10, n = 3840, k = 6656 takes 5.69 us in the place of 5.44)
+                ring1.step[0][it].w.load(tensors.qweight, lm1.off_w, step * 16u * (uint32_t)n);
+            else
+                issue_step_weights<V, BITS>(ring1.step[0][it], lm1, tensors, step);
         }
 #pragma unroll
         for (int j = 0; j < V; ++j) acc1[j] = float4_t{0.f, 0.f, 0.f, 0.f};
