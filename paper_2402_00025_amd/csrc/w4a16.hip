@@ -2424,7 +2424,10 @@ static int run_gemm(const void* A, const void* qweight, const void* scales, cons
     // Up to four rows: with QUAD, which asks for a compute group's activations once and folds a quarter of the products in.  us per call,
     // cold weights, before -> now (m; n x k): 4 bits, 1; 4096 x 4096: 3.96 -> 3.88, 3 bits, 2; 4096 x 4096: 4.52 -> 4.12, 2 bits, 1;
     // 8192 x 8192: 8.83 -> 7.71, 8 bits, 1; 11008 x 4096: 10.85 -> 10.18.  160 random calls: 0.97 times the time, at worst 1.013.
-    if (m <= 4 && V == 4 && ipg == 4 && plan.waves <= 4 && (mode == kDirect || mode == kAtomicFixed || mode == kAtomicPkF16Phase)) {
+    // Narrow tiles, eight waves: 4; 1784 x 1024: 2.89 -> 2.63, 3 bits, 4; 7584 x 1024: 3.55 -> 3.17; 90 random ones 0.91 to 0.97 by width,
+    // one 1.018 (65 to 121 registers: two workgroups of eight waves fit a unit as before).
+    if (m <= 4 && ipg == 4 && plan.waves <= (V == 4 ? 4 : 8) &&
+        (mode == kDirect || (V == 4 && (mode == kAtomicFixed || mode == kAtomicPkF16Phase)))) {
         if (!wave_args_ok(a)) return W4A16_ERR_UNSUPPORTED;
         return W4A16_HIP(launch_fine(a, bits, 1, plan.tile_cols, plan.waves, lds_bytes, mode, stream)) ? W4A16_OK : W4A16_ERR_HIP;
     }

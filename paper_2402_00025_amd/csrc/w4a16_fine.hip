@@ -27,10 +27,23 @@ static hipError_t launch_fine_groups(const GemmArgs& a, int tile_cols, int waves
                                      : hipErrorInvalidConfiguration;
 }
 
+// Up to four rows, k whole, narrow tiles
+template <int BITS>
+static hipError_t launch_few_narrow(const GemmArgs& a, int tile_cols, int waves, size_t lds_bytes, hipStream_t stream)
+{
+    if (waves > 8) return hipErrorInvalidConfiguration;
+    if (waves > 4)
+        return tile_cols == 16 ? launch_wave<1, 4, kDirect, 8, 0, BITS, 1, 1, true>(a, waves, lds_bytes, stream)
+                               : launch_wave<2, 4, kDirect, 8, 0, BITS, 1, 1, true>(a, waves, lds_bytes, stream);
+    return tile_cols == 16 ? launch_wave<1, 4, kDirect, 4, 0, BITS, 1, 1, true>(a, waves, lds_bytes, stream)
+                           : launch_wave<2, 4, kDirect, 4, 0, BITS, 1, 1, true>(a, waves, lds_bytes, stream);
+}
+
 template <int BITS>
 static hipError_t launch_fine_width(const GemmArgs& a, int pg, int tile_cols, int waves, size_t lds_bytes, int mode, hipStream_t stream)
 {
     if (a.m <= 4) {
+        if (tile_cols < 64) return pg == 1 && mode == kDirect ? launch_few_narrow<BITS>(a, tile_cols, waves, lds_bytes, stream) : hipErrorInvalidConfiguration;
         if (pg == 1) return launch_fine_groups<BITS, 1, true>(a, tile_cols, waves, lds_bytes, mode, stream);
         if (pg == 2) return launch_fine_groups<BITS, 2, true>(a, tile_cols, waves, lds_bytes, mode, stream);
         return launch_fine_groups<BITS, 4, true>(a, tile_cols, waves, lds_bytes, mode, stream);

@@ -1971,11 +1971,11 @@ def test_fine_groups_in_steps_of_128(oracle, bits, m, n, k, g, plan):
 
 
 # Up to four rows: every row of the operand four times.  Rows that there are not, overhanging strips, groups of 256, and the
-# three ways in which the parts of k meet (k / 128 = 1, 2, 3 groups a wave and more).
+# three ways in which the parts of k meet (k / 128 = 1, 2, 3 groups a wave and more); tiles of 16 and 32 columns.
 @pytest.mark.parametrize("bits", [4, 8, 3, 2])
 @pytest.mark.parametrize("m", [1, 2, 3, 4])
 @pytest.mark.parametrize("n,k,g,split_k", [(1056, 4096, 128, 0), (4128, 4096, 256, 0), (96, 1536, 128, 4), (2080, 5120, 256, 0), (14112, 1536, 128, 0),
-                                           (288, 2816, 128, 2), (160, 512, 128, 1)])
+                                           (288, 2816, 128, 2), (160, 512, 128, 1), (1056, 1024, 128, 0), (1056, 512, 256, 0), (4640, 1152, 128, 0)])
 def test_up_to_four_rows(oracle, bits, m, n, k, g, split_k):
     seed = 9500 + m + n + k
     A, qw, s, qz = random_case_3bit(m, n, k, g, seed) if bits == 3 else random_case_bits(m, n, k, g, bits, seed)
